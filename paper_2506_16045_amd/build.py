@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libsgn.so")
-SOURCES = ["sgn_lib.hip", "sgn_server.hip"]
+SOURCES = ["sgn_lib.hip", "sgn_line_solve.hip", "sgn_line_rk4.hip", "sgn_line_rk4_mixed.hip", "sgn_server.hip"]
 ARCH = os.environ.get("SGN_OFFLOAD_ARCH", "gfx950")
 
 
@@ -42,14 +42,18 @@ def flags():
 
 
 def build(verbose: bool = True) -> str:
-    objs = []
-    for src in SOURCES:
+    objs, running = [], []
+    for src in SOURCES:   # side by side: one compiler process per source
         obj = os.path.join(CSRC, os.path.splitext(src)[0] + ".o")
         cmd = [hipcc(), *flags(), "-c", os.path.join(CSRC, src), "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
+        running.append((cmd, subprocess.Popen(cmd)))
         objs.append(obj)
+    codes = [(cmd, p.wait()) for cmd, p in running]
+    for cmd, rc in codes:
+        if rc:
+            raise subprocess.CalledProcessError(rc, cmd)
     tmp = LIB + ".tmp"
     cmd = [hipcc(), f"--offload-arch={ARCH}", "-shared", "-fPIC", *objs, "-o", tmp]
     if verbose:

@@ -1,36 +1,23 @@
-// Batched independent 1D constraint solves in one launch: each workgroup takes
-// whole systems G_{eta,h} u = b (Def:G in 1D) of its own size and runs the
-// preconditioned CG of section 3.2 on them to completion, every vector in the
-// half spectrum (modes 0..N/2) and every transform in LDS.  MODE_FP64 iterates
-// in FP64; MODE_MIXED runs FP32 inner PCG solves of G d = r inside an FP64
-// iterative refinement (outer residual r = b - G x, the stop test and x in
-// FP64).  Per-system convergence: a workgroup moves to its next system as soon
-// as the current one is done.
+// Batched independent 1D constraint solves and RK4 runs in one launch: each
+// workgroup takes whole systems G_{eta,h} u = b (Def:G in 1D) of its own size and
+// runs the preconditioned CG of section 3.2 on them to completion, every vector in
+// the half spectrum (modes 0..N/2) and every transform in the workgroup.
+// MODE_FP64 iterates in FP64; MODE_MIXED runs FP32 inner PCG solves of G d = r
+// inside an FP64 iterative refinement (outer residual r = b - G x, the stop test
+// and x in FP64).  Per-system convergence: a workgroup moves to its next system as
+// soon as the current one is done.  Lines of 128 points and more run on the
+// register engine of sgn_line.h; the blk_ functions here take the shorter ones, whose
+// transforms (M <= 32, one entry per thread) that engine's eight entries per
+// thread do not divide into.
 #pragma once
 
-#include "sgn_kernels.h"
+#include <type_traits>
+#include "sgn_device.h"
 
 namespace sgn {
 
-constexpr int BATCH_MMAX = 4096;                 // largest half length M = N/2
-constexpr int BATCH_NMAX = 2 * BATCH_MMAX;       // 8192 points
-// Size classes: a system of n <= 2048 points runs on 256 threads whose
-// per-mode registers and transform tiling cover M <= 1024; a larger one on 512
-// threads covering M <= 4096.  The class is a function of n alone, so a
-// system's reductions, and its results, do not depend on what shares a launch.
-__host__ __device__ constexpr int batch_threads_for(int n) { return n <= 2048 ? 256 : 512; }
-template <int NT>
-constexpr int batch_mmax() { return NT <= 256 ? 1024 : BATCH_MMAX; }
-// Complex points per thread of one transform pass for a workgroup of NT threads.
-template <int NT>
-constexpr int batch_epc() { return batch_mmax<NT>() / NT; }
-#ifndef SGN_BATCH_WAVES_SMALL
-#define SGN_BATCH_WAVES_SMALL 2
-#endif
-// Waves per SIMD the compiler must leave room for (register budget): the small
-// class keeps several workgroups resident per CU.
-template <int NT>
-constexpr int batch_waves() { return NT <= 256 ? SGN_BATCH_WAVES_SMALL : 1; }
+constexpr int BATCH_NMAX = 8192;                 // points of the largest system
+constexpr int SMALL_MMAX = 32;                   // largest half length of the blk_ functions
 
 enum { BATCH_FP64 = 0, BATCH_MIXED = 1 };
 
@@ -125,10 +112,10 @@ __device__ __forceinline__ void blk_allmax(double (&v)[NACC], double* red) {
 // Forward real transforms of N = 2M points, NF fields at buf + f fstride held
 // as pairs buf[j] = (x_2j, x_2j+1), j < M: on return buf[k] = X_k =
 // sum_n x_n W_N^{kn} for k = 0..M.  Whole block; the fields in lockstep.
-template <typename T, int NT, int NF>
+template <typename T, int NF>
 __device__ __forceinline__ void blk_rfft_fwd_n(cpx<T>* buf, int fstride, int M, const cpx<T>* __restrict__ tw_all) {
     __syncthreads();
-    lds_fft<T, batch_epc<NT>(), NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), false);
+    lds_fft<T, 1, NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), false);
     const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
     const T half = (T)0.5;
     for (int p = threadIdx.x; p <= M / 2; p += blockDim.x) {
@@ -154,7 +141,7 @@ __device__ __forceinline__ void blk_rfft_fwd_n(cpx<T>* buf, int fstride, int M, 
 
 // Inverse of blk_rfft_fwd_n up to the factor N: buf[k] = X_k (k = 0..M; the
 // imaginary parts of X_0 and X_M are ignored) -> buf[j] = N (x_2j, x_2j+1).
-template <typename T, int NT, int NF>
+template <typename T, int NF>
 __device__ __forceinline__ void blk_rfft_inv_n(cpx<T>* buf, int fstride, int M, const cpx<T>* __restrict__ tw_all) {
     __syncthreads();
     const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
@@ -178,17 +165,17 @@ __device__ __forceinline__ void blk_rfft_inv_n(cpx<T>* buf, int fstride, int M, 
         }
     }
     __syncthreads();
-    lds_fft<T, batch_epc<NT>(), NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), true);
+    lds_fft<T, 1, NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), true);
 }
 
-template <typename T, int NT>
+template <typename T>
 __device__ __forceinline__ void blk_rfft_fwd(cpx<T>* buf, int M, const cpx<T>* __restrict__ tw_all) {
-    blk_rfft_fwd_n<T, NT, 1>(buf, 0, M, tw_all);
+    blk_rfft_fwd_n<T, 1>(buf, 0, M, tw_all);
 }
 
-template <typename T, int NT>
+template <typename T>
 __device__ __forceinline__ void blk_rfft_inv(cpx<T>* buf, int M, const cpx<T>* __restrict__ tw_all) {
-    blk_rfft_inv_n<T, NT, 1>(buf, 0, M, tw_all);
+    blk_rfft_inv_n<T, 1>(buf, 0, M, tw_all);
 }
 
 // One system's view for G applies in precision T.
@@ -209,14 +196,14 @@ struct BatchOp {
 // curvature is known (pq, every thread) before q_hat is formed; `fin(k, kk,
 // q_k, pq)` then consumes q_hat mode by mode (kk the wavenumber) with the same
 // thread mapping as every other mode loop of the system.
-template <typename T, int NT, typename Fin>
+template <typename T, typename Fin>
 __device__ __forceinline__ void blk_apply(const BatchOp<T>& A, const cpx<T>* vh, cpx<T>* lds, double* red,
                                           Fin&& fin) {
     const int M = A.M, N = A.N;
     const T invN = (T)1 / (T)N;
     // D v into the physical scratch
     for (int k = threadIdx.x; k <= M; k += blockDim.x) lds[k] = invN * ik(wavenumber<T>(k, N, A.tp), vh[k]);
-    blk_rfft_inv<T, NT>(lds, M, A.tw);
+    blk_rfft_inv<T>(lds, M, A.tw);
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
         A.scr[2 * j] = lds[j].re;
         A.scr[2 * j + 1] = lds[j].im;
@@ -224,7 +211,7 @@ __device__ __forceinline__ void blk_apply(const BatchOp<T>& A, const cpx<T>* vh,
     __syncthreads();
     // v, then the pointwise products (a into LDS, w into the scratch)
     for (int k = threadIdx.x; k <= M; k += blockDim.x) lds[k] = invN * vh[k];
-    blk_rfft_inv<T, NT>(lds, M, A.tw);
+    blk_rfft_inv<T>(lds, M, A.tw);
     const T third = (T)1 / (T)3, half = (T)0.5;
     double acc[1] = {0.0};
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
@@ -247,11 +234,11 @@ __device__ __forceinline__ void blk_apply(const BatchOp<T>& A, const cpx<T>* vh,
     blk_allsum<1>(acc, red);
     const double pq = acc[0];
     // a_hat to the spectral scratch, then w_hat; q = a_hat - i k w_hat
-    blk_rfft_fwd<T, NT>(lds, M, A.tw);
+    blk_rfft_fwd<T>(lds, M, A.tw);
     for (int k = threadIdx.x; k <= M; k += blockDim.x) A.ah[k] = lds[k];
     __syncthreads();
     for (int j = threadIdx.x; j < M; j += blockDim.x) lds[j] = C<T>(A.scr[2 * j], A.scr[2 * j + 1]);
-    blk_rfft_fwd<T, NT>(lds, M, A.tw);
+    blk_rfft_fwd<T>(lds, M, A.tw);
     for (int k = threadIdx.x; k <= M; k += blockDim.x) {
         const T kk = wavenumber<T>(k, N, A.tp);
         fin(k, kk, A.ah[k] - ik(kk, lds[k]), pq);
@@ -279,11 +266,12 @@ __device__ __forceinline__ cpx<T> cvt(cpx<U> v) {
 // r0 is read from r0h; on return xh += d (xh may hold a wider type).  Stops
 // when r.r <= tol2 * bbref or after max_iter iterations; returns the
 // iterations, rr the last r.r.
-template <typename T, int NT, bool REGCOEF, typename TX>
+template <typename T, bool REGCOEF, typename TX>
 __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h, T sig, T alp, double tol2,
                            double bbref, int max_iter, double& rr, cpx<T>* lds, double* red) {
-    constexpr int KPT = batch_mmax<NT>() / NT + 1;
-    constexpr int JPT = batch_mmax<NT>() / NT;
+    constexpr int NT = 64;    // lines of at most SMALL_MMAX entries: one slot per thread
+    constexpr int KPT = SMALL_MMAX / NT + 1;
+    constexpr int JPT = 1;
     constexpr int JC = REGCOEF ? JPT : 1;
     const int M = A.M, N = A.N, t = threadIdx.x;
     const int fs = M + 1;
@@ -347,7 +335,7 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
                 lb[k] = invN * ik(kk, p[e]);
             }
         }
-        blk_rfft_inv_n<T, NT, 2>(lds, fs, M, A.tw);
+        blk_rfft_inv_n<T, 2>(lds, fs, M, A.tw);
         // pointwise: a into buffer a, w into buffer b; curvature p.Gp
         double pqa[1] = {0.0};
         constexpr int PU = REGCOEF ? JPT : 1;   // the FP64 loop reads eta, h_x from memory
@@ -387,9 +375,9 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
             for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
             if ((threadIdx.x & 63) == 0) red[RED_PQ + (threadIdx.x >> 6)] = x;
         }
-        blk_rfft_fwd_n<T, NT, 2>(lds, fs, M, A.tw);
+        blk_rfft_fwd_n<T, 2>(lds, fs, M, A.tw);
         double pq = 0.0;
-        for (int w = 0; w < NT / 64; ++w) pq += red[RED_PQ + w];
+        for (unsigned w = 0; w < blockDim.x / 64; ++w) pq += red[RED_PQ + w];
         pq = uniform_d(pq);
         const double rho = rz;
         const T alpha = (T)(rho / pq);
@@ -429,13 +417,12 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
 }
 
 // r_hat = b_hat - G x_hat in FP64, with its (r.z, r.r).
-template <int NT>
 __device__ __forceinline__ void blk_residual(const BatchOp<double>& A, const cpx<double>* bh, const cpx<double>* xh,
                                              cpx<double>* rh, double sig, double alp, double& rz, double& rr,
                                              cpx<double>* lds, double* red) {
     const double invN = 1.0 / (double)A.N;
     double acc[2] = {0.0, 0.0};
-    blk_apply<double, NT>(A, xh, lds, red, [&](int k, double kk, cpx<double> q, double) {
+    blk_apply<double>(A, xh, lds, red, [&](int k, double kk, cpx<double> q, double) {
         const cpx<double> r = bh[k] - q;
         rh[k] = r;
         const cpx<double> z = batch_precond<double>(kk, sig, alp, r);
@@ -449,12 +436,11 @@ __device__ __forceinline__ void blk_residual(const BatchOp<double>& A, const cpx
 }
 
 // Transform N physical FP64 points into modes 0..M (dst), returning sum x^2.
-template <int NT>
 __device__ __forceinline__ void blk_to_spectral(const double* x, int N, cpx<double>* dst,
                                                 const cpx<double>* tw, cpx<double>* lds) {
     const int M = N / 2;
     for (int j = threadIdx.x; j < M; j += blockDim.x) lds[j] = C<double>(x[2 * j], x[2 * j + 1]);
-    blk_rfft_fwd<double, NT>(lds, M, tw);
+    blk_rfft_fwd<double>(lds, M, tw);
     for (int k = threadIdx.x; k <= M; k += blockDim.x) dst[k] = lds[k];
     __syncthreads();
 }
@@ -477,7 +463,7 @@ __device__ __forceinline__ int batch_next(int* queue, int cur, int* slot) {
 // (from u when `guess`, else from 0), PCG (FP64) or FP32 inner PCG inside FP64
 // refinement (MIXED), and u (physical) on return; w is the system's workspace
 // (batch_item_doubles).  Every thread of the block calls it.
-template <int MODE, int NT>
+template <int MODE>
 __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, const double* __restrict__ eta,
                                         const double* __restrict__ hx, const double* __restrict__ b, double* u,
                                         bool guess, double* w, const cpx<double>* __restrict__ tw64,
@@ -533,7 +519,7 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
     out.kap = kap;
     out.flat = fl;
     // b_hat, ||b||^2, and the initial x_hat, r_hat
-    blk_to_spectral<NT>(b, N, bh, tw64, lds64);
+    blk_to_spectral(b, N, bh, tw64, lds64);
     double bb = 0.0, rz = 0.0, rr = 0.0;
     {
         double acc[2] = {0.0, 0.0};
@@ -552,8 +538,8 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
     }
     const double tol2 = prm.tol * prm.tol;
     if (guess && bb > 0.0) {
-        blk_to_spectral<NT>(u, N, xh, tw64, lds64);
-        blk_residual<NT>(A64, bh, xh, rh, sig, alp, rz, rr, lds64, red);
+        blk_to_spectral(u, N, xh, tw64, lds64);
+        blk_residual(A64, bh, xh, rh, sig, alp, rz, rr, lds64, red);
     } else {
         for (int k = threadIdx.x; k <= M; k += blockDim.x) {
             xh[k] = C<double>(0, 0);
@@ -562,7 +548,7 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
         __syncthreads();
     }
     if (MODE == BATCH_FP64) {
-        out.iters = blk_pcg_reg<double, NT, false>(A64, xh, rh, sig, alp, tol2, bb, prm.max_iter, rr, lds64, red);
+        out.iters = blk_pcg_reg<double, false>(A64, xh, rh, sig, alp, tol2, bb, prm.max_iter, rr, lds64, red);
     } else {
         // FP32 view of the same system: coefficient fields rounded once
         float* e32 = reinterpret_cast<float*>(A64.scr + N);
@@ -590,9 +576,9 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
             double t2 = 0.25 * tol2 * (bb / rr);
             t2 = t2 < itol2 ? itol2 : (t2 > 0.25 ? 0.25 : t2);
             double irr = 0.0;
-            out.iters += blk_pcg_reg<float, NT, true>(A32, xh, rh, sig32, alp32, t2, rr, prm.max_iter, irr,
+            out.iters += blk_pcg_reg<float, true>(A32, xh, rh, sig32, alp32, t2, rr, prm.max_iter, irr,
                                                       lds32, red);
-            blk_residual<NT>(A64, bh, xh, rh, sig, alp, rz, rr, lds64, red);
+            blk_residual(A64, bh, xh, rh, sig, alp, rz, rr, lds64, red);
             out.outer += 1;
         }
     }
@@ -602,7 +588,7 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
     // u = x (physical)
     const double invN = 1.0 / (double)N;
     for (int k = threadIdx.x; k <= M; k += blockDim.x) lds64[k] = invN * xh[k];
-    blk_rfft_inv<double, NT>(lds64, M, tw64);
+    blk_rfft_inv<double>(lds64, M, tw64);
     for (int j = threadIdx.x; j < M; j += blockDim.x) {
         u[2 * j] = lds64[j].re;
         u[2 * j + 1] = lds64[j].im;
@@ -611,8 +597,44 @@ __device__ __forceinline__ BatchResult blk_solve_system(const BatchItem& it, con
     return out;
 }
 
-template <int MODE, int NT>
-__global__ void __launch_bounds__(NT, batch_waves<NT>()) k_batch_solve(const BatchItem* __restrict__ items, int nitems,
+}  // namespace sgn
+
+#include "sgn_line.h"
+
+namespace sgn {
+
+constexpr int BATCH_THREADS = 512;   // largest workgroup of the kernels below
+
+// Threads and LDS of a workgroup that takes systems of up to n points.
+__host__ __device__ constexpr int batch_threads_for(int n) { return n < 2 * LINE_MMIN ? 64 : line_threads_for(n); }
+__host__ __device__ constexpr size_t batch_lds_bytes(int n) {
+    return n < 2 * LINE_MMIN ? (size_t)2 * (SMALL_MMAX + 1) * 16 : line_lds_bytes(n);
+}
+
+// One system by the whole workgroup, on the engine of its size.
+template <int MODE>
+__device__ __forceinline__ BatchResult batch_solve_system(const BatchItem& it, const double* __restrict__ eta,
+                                                          const double* __restrict__ hx, const double* __restrict__ b,
+                                                          double* u, bool guess, double* w,
+                                                          const cpx<double>* __restrict__ tw64,
+                                                          const cpx<float>* __restrict__ tw32, const BatchParams& prm,
+                                                          void* lds, double* red) {
+    BatchResult out{};
+    const bool line = line_dispatch(it.n, [&](auto m) __attribute__((always_inline)) {
+        constexpr int M = decltype(m)::value;
+        // a system that fits one wave runs on the first, the others wait at the
+        // caller's barrier
+        if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
+        out = line_solve<MODE, M>(it.L, eta, hx, b, u, guess, w, tw64, tw32, prm, lds, red);
+    });
+    if (!line)
+        out = blk_solve_system<MODE>(it, eta, hx, b, u, guess, w, tw64, tw32, prm,
+                                     reinterpret_cast<cpx<double>*>(lds), reinterpret_cast<cpx<float>*>(lds), red);
+    return out;
+}
+
+template <int MODE>
+__global__ void __launch_bounds__(BATCH_THREADS) k_batch_solve(const BatchItem* __restrict__ items, int nitems,
                                                                const double* __restrict__ eta_all,
                                                                const double* __restrict__ hx_all,
                                                                const double* __restrict__ b_all,
@@ -621,23 +643,17 @@ __global__ void __launch_bounds__(NT, batch_waves<NT>()) k_batch_solve(const Bat
                                                                const cpx<float>* __restrict__ tw32, BatchParams prm,
                                                                BatchResult* __restrict__ res, int* queue) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    cpx<double>* lds64 = reinterpret_cast<cpx<double>*>(smem_raw);
-    cpx<float>* lds32 = reinterpret_cast<cpx<float>*>(smem_raw);
     __shared__ double red[RED_DOUBLES];
     __shared__ int next_slot;
     for (int s = blockIdx.x; s < nitems; s = batch_next(queue, s, &next_slot)) {
-        const BatchItem it = items[s];
+        const BatchItem& it = items[__builtin_amdgcn_readfirstlane(s)];   // uniform: scalar loads
         const BatchResult out =
-            blk_solve_system<MODE, NT>(it, eta_all + it.off, hx_all + it.off, b_all + it.off, u_all + it.off,
-                                       prm.x0_is_guess != 0, ws + it.wso, tw64, tw32, prm, lds64, lds32, red);
+            batch_solve_system<MODE>(it, eta_all + it.off, hx_all + it.off, b_all + it.off, u_all + it.off,
+                                     prm.x0_is_guess != 0, ws + it.wso, tw64, tw32, prm, smem_raw, red);
         if (threadIdx.x == 0) res[it.index] = out;
         __syncthreads();
     }
 }
-
-}  // namespace sgn
-
-namespace sgn {
 
 // Right-hand side f(w, p) of a 1D system (Eq:DSWEcf, Def:bigF, Eq:DAE_DSWE) by
 // the whole workgroup: eta_t = -(eta u)_x, U_t = -eta (eta - h)_x - (eta u u)_x + F
@@ -645,7 +661,6 @@ namespace sgn {
 // All thirteen real transforms run in LDS; spec (5 (N/2+1) modes) and st (5 N
 // points) are global scratch the workgroup owns.  Each thread always handles the
 // same points and modes, so the scratch needs no barriers of its own.
-template <int NT>
 __device__ void blk_rhs_1d(int N, double L, const double* __restrict__ eta, const double* __restrict__ hx,
                            const double* __restrict__ u, double* __restrict__ eta_t, double* __restrict__ U_t,
                            cpx<double>* __restrict__ spec, double* __restrict__ st,
@@ -660,7 +675,7 @@ __device__ void blk_rhs_1d(int N, double L, const double* __restrict__ eta, cons
     double* s_Q = st + 4 * N;
     // forward transforms of u, eta u, eta, eta u u, beta = h_x u
     for (int f = 0; f < 5; ++f) {
-        for (int j = threadIdx.x; j < M; j += NT) {
+        for (int j = threadIdx.x; j < M; j += blockDim.x) {
             double v[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -670,21 +685,21 @@ __device__ void blk_rhs_1d(int N, double L, const double* __restrict__ eta, cons
             }
             lds[j] = C<double>(v[0], v[1]);
         }
-        blk_rfft_fwd<double, NT>(lds, M, tw);
-        for (int k = threadIdx.x; k <= M; k += NT) spec[f * M1 + k] = lds[k];
+        blk_rfft_fwd<double>(lds, M, tw);
+        for (int k = threadIdx.x; k <= M; k += blockDim.x) spec[f * M1 + k] = lds[k];
         __syncthreads();
     }
     // the derivative fields, consumed pointwise as they arrive:
     // delta = u_x, delta_x = u_xx, m = (eta u)_x, eta_x, (eta u u)_x, beta_x
     for (int q = 0; q < 6; ++q) {
         const int src = q <= 1 ? 0 : q - 1;
-        for (int k = threadIdx.x; k <= M; k += NT) {
+        for (int k = threadIdx.x; k <= M; k += blockDim.x) {
             const double kk = wavenumber<double>(k, N, tp);
             const cpx<double> X = spec[src * M1 + k];
             lds[k] = invN * (q == 1 ? (-kk * kk) * X : ik(kk, X));
         }
-        blk_rfft_inv<double, NT>(lds, M, tw);
-        for (int j = threadIdx.x; j < M; j += NT) {
+        blk_rfft_inv<double>(lds, M, tw);
+        for (int j = threadIdx.x; j < M; j += blockDim.x) {
             const cpx<double> z = lds[j];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -709,7 +724,7 @@ __device__ void blk_rhs_1d(int N, double L, const double* __restrict__ eta, cons
         __syncthreads();
     }
     // S, T, eta_t and U_t without S_x; then U_t += S_x
-    for (int j = threadIdx.x; j < M; j += NT) {
+    for (int j = threadIdx.x; j < M; j += blockDim.x) {
         double sv[2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
@@ -724,24 +739,28 @@ __device__ void blk_rhs_1d(int N, double L, const double* __restrict__ eta, cons
         }
         lds[j] = C<double>(sv[0], sv[1]);
     }
-    blk_rfft_fwd<double, NT>(lds, M, tw);
-    for (int k = threadIdx.x; k <= M; k += NT) lds[k] = invN * ik(wavenumber<double>(k, N, tp), lds[k]);
-    blk_rfft_inv<double, NT>(lds, M, tw);
-    for (int j = threadIdx.x; j < M; j += NT) {
+    blk_rfft_fwd<double>(lds, M, tw);
+    for (int k = threadIdx.x; k <= M; k += blockDim.x) lds[k] = invN * ik(wavenumber<double>(k, N, tp), lds[k]);
+    blk_rfft_inv<double>(lds, M, tw);
+    for (int j = threadIdx.x; j < M; j += blockDim.x) {
         const cpx<double> z = lds[j];
         U_t[2 * j] = z.re + U_t[2 * j];
         U_t[2 * j + 1] = z.im + U_t[2 * j + 1];
     }
 }
 
-template <int NT>
-__global__ void __launch_bounds__(NT) k_rhs_1d(int N, double L, const double* __restrict__ eta,
-                                               const double* __restrict__ hx, const double* __restrict__ u,
-                                               double* __restrict__ eta_t, double* __restrict__ U_t,
-                                               cpx<double>* __restrict__ spec, double* __restrict__ st,
-                                               const cpx<double>* __restrict__ tw) {
+template <int KIND>   // one kind; a template so that only the launching source compiles it
+__global__ void __launch_bounds__(BATCH_THREADS) k_rhs_1d(int N, double L, const double* __restrict__ eta,
+                                                          const double* __restrict__ hx, const double* __restrict__ u,
+                                                          double* __restrict__ eta_t, double* __restrict__ U_t,
+                                                          cpx<double>* __restrict__ spec, double* __restrict__ st,
+                                                          const cpx<double>* __restrict__ tw) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    blk_rhs_1d<NT>(N, L, eta, hx, u, eta_t, U_t, spec, st, tw, reinterpret_cast<cpx<double>*>(smem_raw));
+    __shared__ double red[RED_DOUBLES];
+    const bool line = line_dispatch(N, [&](auto m) __attribute__((always_inline)) {
+        line_rhs<decltype(m)::value>(L, eta, hx, u, eta_t, U_t, tw, smem_raw, red);
+    });
+    if (!line) blk_rhs_1d(N, L, eta, hx, u, eta_t, U_t, spec, st, tw, reinterpret_cast<cpx<double>*>(smem_raw));
 }
 
 // ---- batched RK4 stepping --------------------------------------------------
@@ -786,13 +805,12 @@ __host__ __device__ inline long long step_scratch_doubles(int n, int mode) {
 
 // h_x = D h (zero when h is constant: the flat formulas apply) and U = G_{eta,h} u
 // for a state given by eta, h and u.  False for non-finite h.
-template <int NT>
 __device__ bool blk_step_prepare(const StepItem& it, int& flat, const cpx<double>* __restrict__ tw,
                                  cpx<double>* lds, double* red) {
     const int N = it.n, M = N / 2;
     const double invN = 1.0 / (double)N, tp = 6.283185307179586476925286766559 / it.L;
     double ex[3] = {-1.0e308, -1.0e308, 0.0};
-    for (int i = threadIdx.x; i < N; i += NT) {
+    for (int i = threadIdx.x; i < N; i += blockDim.x) {
         const double v = it.h[i];
         if (!isfinite(v)) ex[2] = 1.0;
         ex[0] = fmax(ex[0], -v);
@@ -802,13 +820,13 @@ __device__ bool blk_step_prepare(const StepItem& it, int& flat, const cpx<double
     if (ex[2] != 0.0) return false;
     flat = (-ex[0] == ex[1]) ? 1 : 0;
     if (flat) {
-        for (int i = threadIdx.x; i < N; i += NT) it.hx[i] = 0.0;
+        for (int i = threadIdx.x; i < N; i += blockDim.x) it.hx[i] = 0.0;
     } else {
-        for (int j = threadIdx.x; j < M; j += NT) lds[j] = C<double>(it.h[2 * j], it.h[2 * j + 1]);
-        blk_rfft_fwd<double, NT>(lds, M, tw);
-        for (int k = threadIdx.x; k <= M; k += NT) lds[k] = invN * ik(wavenumber<double>(k, N, tp), lds[k]);
-        blk_rfft_inv<double, NT>(lds, M, tw);
-        for (int j = threadIdx.x; j < M; j += NT) {
+        for (int j = threadIdx.x; j < M; j += blockDim.x) lds[j] = C<double>(it.h[2 * j], it.h[2 * j + 1]);
+        blk_rfft_fwd<double>(lds, M, tw);
+        for (int k = threadIdx.x; k <= M; k += blockDim.x) lds[k] = invN * ik(wavenumber<double>(k, N, tp), lds[k]);
+        blk_rfft_inv<double>(lds, M, tw);
+        for (int j = threadIdx.x; j < M; j += blockDim.x) {
             it.hx[2 * j] = lds[j].re;
             it.hx[2 * j + 1] = lds[j].im;
         }
@@ -825,11 +843,11 @@ __device__ bool blk_step_prepare(const StepItem& it, int& flat, const cpx<double
     A.ah = uh + (M + 1);
     A.scr = reinterpret_cast<double*>(A.ah + (M + 1));
     A.tw = tw;
-    blk_to_spectral<NT>(it.u, N, uh, tw, lds);
-    blk_apply<double, NT>(A, uh, lds, red, [&](int k, double, cpx<double> q, double) { uh[k] = invN * q; });
-    for (int k = threadIdx.x; k <= M; k += NT) lds[k] = uh[k];
-    blk_rfft_inv<double, NT>(lds, M, tw);
-    for (int j = threadIdx.x; j < M; j += NT) {
+    blk_to_spectral(it.u, N, uh, tw, lds);
+    blk_apply<double>(A, uh, lds, red, [&](int k, double, cpx<double> q, double) { uh[k] = invN * q; });
+    for (int k = threadIdx.x; k <= M; k += blockDim.x) lds[k] = uh[k];
+    blk_rfft_inv<double>(lds, M, tw);
+    for (int j = threadIdx.x; j < M; j += blockDim.x) {
         it.U[2 * j] = lds[j].re;
         it.U[2 * j + 1] = lds[j].im;
     }
@@ -837,14 +855,91 @@ __device__ bool blk_step_prepare(const StepItem& it, int& flat, const cpx<double
     return true;
 }
 
+// What a run needs of the engine of its size: the threads that share it, a barrier
+// that orders their global memory, and the three operations.
+template <int MODE>
+struct SmallEngine {
+    static __device__ __forceinline__ int threads() { return blockDim.x; }
+    static __device__ __forceinline__ void sync() { __syncthreads(); }
+    static __device__ __forceinline__ bool prepare(const StepItem& it, int& flat, const cpx<double>* tw, void* lds,
+                                                   double* red) {
+        return blk_step_prepare(it, flat, tw, reinterpret_cast<cpx<double>*>(lds), red);
+    }
+    static __device__ __forceinline__ BatchResult solve(const StepItem& it, const double* eta, const double* U,
+                                                        double* u, const cpx<double>* tw64, const cpx<float>* tw32,
+                                                        const BatchParams& prm, void* lds, double* red) {
+        BatchItem bi;
+        bi.n = it.n;
+        bi.index = it.index;
+        bi.L = it.L;
+        bi.off = 0;
+        bi.wso = 0;
+        return blk_solve_system<MODE>(bi, eta, it.hx, U, u, true, it.scr, tw64, tw32, prm,
+                                      reinterpret_cast<cpx<double>*>(lds), reinterpret_cast<cpx<float>*>(lds), red);
+    }
+    static __device__ __forceinline__ void rhs(const StepItem& it, const double* eta, const double* u, double* eta_t,
+                                               double* U_t, const cpx<double>* tw, void* lds, double*) {
+        blk_rhs_1d(it.n, it.L, eta, it.hx, u, eta_t, U_t, reinterpret_cast<cpx<double>*>(it.scr),
+                   it.scr + 10LL * (it.n / 2 + 1), tw, reinterpret_cast<cpx<double>*>(lds));
+    }
+};
+
+template <int MODE, int M>
+struct LineEngine {
+    static constexpr bool ONE = LineGeo<double, M>::ONE;
+    static __device__ __forceinline__ int threads() { return ONE ? 64 : blockDim.x; }
+    static __device__ __forceinline__ void sync() {
+        if (ONE) {   // one wave: its own memory operations done, no barrier
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            __builtin_amdgcn_wave_barrier();
+        } else {
+            __syncthreads();
+        }
+    }
+    static __device__ __forceinline__ bool prepare(const StepItem& it, int& flat, const cpx<double>* tw, void* lds,
+                                                   double* red) {
+        const Line<double, M> L(lds, red, tw);
+        double ex[3] = {-1.0e308, -1.0e308, 0.0};
+        if (L.act) {
+            for (int i = threadIdx.x; i < 2 * M; i += LineGeo<double, M>::TH) {
+                const double v = it.h[i];
+                if (!isfinite(v)) ex[2] = 1.0;
+                ex[0] = fmax(ex[0], -v);
+                ex[1] = fmax(ex[1], v);
+            }
+        }
+        line_max<double, M, 3>(L, ex);
+        if (ex[2] != 0.0) return false;
+        flat = (-ex[0] == ex[1]) ? 1 : 0;
+        if (flat) {
+            for (int i = threadIdx.x; i < 2 * M; i += threads()) it.hx[i] = 0.0;
+        } else {
+            line_slope<M>(it.L, it.h, it.hx, tw, lds, red);
+        }
+        sync();
+        line_momentum<M>(it.L, it.eta, it.hx, it.u, it.U, tw, lds, red);
+        sync();
+        return true;
+    }
+    static __device__ __forceinline__ BatchResult solve(const StepItem& it, const double* eta, const double* U,
+                                                        double* u, const cpx<double>* tw64, const cpx<float>* tw32,
+                                                        const BatchParams& prm, void* lds, double* red) {
+        return line_solve<MODE, M>(it.L, eta, it.hx, U, u, true, it.scr, tw64, tw32, prm, lds, red);
+    }
+    static __device__ __forceinline__ void rhs(const StepItem& it, const double* eta, const double* u, double* eta_t,
+                                               double* U_t, const cpx<double>* tw, void* lds, double* red) {
+        line_rhs<M>(it.L, eta, it.hx, u, eta_t, U_t, tw, lds, red);
+    }
+};
+
 // G_{eta,h} u = U for stepper slot `slot`, u holding the base velocity on entry.
 // With extrapolation the solve starts from base + o_1 (one recorded offset) or
 // base + (2 o_1 - o_2) (two), and records u - base afterwards.  0, -2 or -3.
-template <int MODE, int NT>
-__device__ int blk_step_solve(const StepItem& it, StepResult& out, int slot, bool extrapolate, const double* eta,
+template <typename Eng>
+__device__ __forceinline__ int step_solve(const StepItem& it, StepResult& out, int slot, bool extrapolate, const double* eta,
                               const double* U, double* u, const cpx<double>* __restrict__ tw64,
-                              const cpx<float>* __restrict__ tw32, const BatchParams& prm, cpx<double>* lds64,
-                              cpx<float>* lds32, double* red) {
+                              const cpx<float>* __restrict__ tw32, const BatchParams& prm, void* lds,
+                                          double* red) {
     const int N = it.n;
     int& cnt = out.cnt[slot];
     int& head = out.head[slot];
@@ -852,7 +947,7 @@ __device__ int blk_step_solve(const StepItem& it, StepResult& out, int slot, boo
     if (extrapolate) {
         const double* o1 = it.off[slot][head];
         const double* o2 = it.off[slot][head ^ 1];
-        for (int i = threadIdx.x; i < N; i += NT) {
+        for (int i = threadIdx.x; i < N; i += Eng::threads()) {
             const double b = u[i];
             it.base[i] = b;
             if (cnt == 1) {
@@ -866,16 +961,10 @@ __device__ int blk_step_solve(const StepItem& it, StepResult& out, int slot, boo
                 u[i] = b + 1.0 * s;
             }
         }
-        __syncthreads();
+        Eng::sync();
     }
-    BatchItem bi;
-    bi.n = N;
-    bi.index = it.index;
-    bi.L = it.L;
-    bi.off = 0;
-    bi.wso = 0;
-    const BatchResult r = blk_solve_system<MODE, NT>(bi, eta, it.hx, U, u, true, it.scr, tw64, tw32, prm, lds64,
-                                                     lds32, red);
+    const BatchResult r = Eng::solve(it, eta, U, u, tw64, tw32, prm, lds, red);
+    Eng::sync();
     out.solves += 1;
     out.iters += r.iters;
     if (r.iters > out.max_iters) out.max_iters = r.iters;
@@ -884,12 +973,12 @@ __device__ int blk_step_solve(const StepItem& it, StepResult& out, int slot, boo
     if (!r.converged) return -3;
     if (extrapolate) {
         double* o = it.off[slot][nh];
-        for (int i = threadIdx.x; i < N; i += NT) {
+        for (int i = threadIdx.x; i < N; i += Eng::threads()) {
             double s = 0.0;
             s += -1.0 * it.base[i];
             o[i] = u[i] + 1.0 * s;
         }
-        __syncthreads();
+        Eng::sync();
         head = nh;
         if (cnt < 2) cnt += 1;
     }
@@ -900,10 +989,9 @@ __device__ int blk_step_solve(const StepItem& it, StepResult& out, int slot, boo
 // eta_n + dt a_i f^(i-1) and U_n + dt a_i f^(i-1) and solves G u^(i) = U^(i) from
 // u^(i-1); the weighted sum advances eta and U, and u_{n+1} is solved from u^(4).
 // A step counts once eta and U have advanced, even if its last solve fails.
-template <int MODE, int NT>
-__device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cpx<double>* __restrict__ tw64,
-                                  const cpx<float>* __restrict__ tw32, BatchParams prm, cpx<double>* lds64,
-                                  cpx<float>* lds32, double* red) {
+template <typename Eng>
+__device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapolate, const cpx<double>* __restrict__ tw64,
+                                  const cpx<float>* __restrict__ tw32, BatchParams prm, void* lds, double* red) {
     StepResult out{};
     out.converged = 1;
 #pragma unroll
@@ -913,7 +1001,7 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
     }
     const int N = it.n;
     int flat = it.flat;
-    if (it.h && !blk_step_prepare<NT>(it, flat, tw64, lds64, red)) {
+    if (it.h && !Eng::prepare(it, flat, tw64, lds, red)) {
         out.status = -2;
         return out;
     }
@@ -921,8 +1009,6 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
     prm.flat = flat ? 1 : 0;
     prm.have_coeffs = 0;
     prm.x0_is_guess = 1;
-    cpx<double>* spec = reinterpret_cast<cpx<double>*>(it.scr);
-    double* st = it.scr + 10LL * (N / 2 + 1);
     const double a[3] = {0.5, 0.5, 1.0};
     const double w[4] = {1.0 / 6.0, 1.0 / 3.0, 1.0 / 3.0, 1.0 / 6.0};
     const double dt = it.dt;
@@ -934,7 +1020,7 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
         for (int k = 0; k <= 4; ++k) {
             if (k > 0) {
                 const bool last = k == 4;
-                for (int i = threadIdx.x; i < N; i += NT) {
+                for (int i = threadIdx.x; i < N; i += Eng::threads()) {
                     if (!last) {
                         double s = 0.0;
                         s += a[k - 1] * it.fe[k - 1][i];
@@ -954,10 +1040,9 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
                         it.u[i] = it.u_s[i];
                     }
                 }
-                __syncthreads();
-                const int rc = blk_step_solve<MODE, NT>(it, out, k - 1, extrapolate, last ? it.eta : it.eta_s,
-                                                        last ? it.U : it.U_s, last ? it.u : it.u_s, tw64, tw32, prm,
-                                                        lds64, lds32, red);
+                Eng::sync();
+                const int rc = step_solve<Eng>(it, out, k - 1, extrapolate, last ? it.eta : it.eta_s,
+                                               last ? it.U : it.U_s, last ? it.u : it.u_s, tw64, tw32, prm, lds, red);
                 if (last) out.steps += 1;
                 if (rc != 0) {
                     out.status = rc;
@@ -965,12 +1050,11 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
                 }
             }
             if (k < 4) {
-                blk_rhs_1d<NT>(N, it.L, k ? it.eta_s : it.eta, it.hx, k ? it.u_s : it.u, it.fe[k], it.fU[k], spec,
-                               st, tw64, lds64);
-                __syncthreads();
+                Eng::rhs(it, k ? it.eta_s : it.eta, k ? it.u_s : it.u, it.fe[k], it.fU[k], tw64, lds, red);
+                Eng::sync();
                 if (k == 0) {
-                    for (int i = threadIdx.x; i < N; i += NT) it.u_s[i] = it.u[i];
-                    __syncthreads();
+                    for (int i = threadIdx.x; i < N; i += Eng::threads()) it.u_s[i] = it.u[i];
+                    Eng::sync();
                 }
             }
         }
@@ -979,25 +1063,62 @@ __device__ StepResult blk_rk4_run(const StepItem& it, bool extrapolate, const cp
 }
 
 // Batched RK4 runs: workgroups take states from the table (a work queue when
-// queue is set, its counter zero at launch) until none is left.  LDS: two FP64
-// transform buffers of the largest state's N/2 + 1 modes.
-template <int MODE, int NT>
-__global__ void __launch_bounds__(NT, batch_waves<NT>()) k_batch_rk4(const StepItem* __restrict__ items, int nitems,
-                                                  const cpx<double>* __restrict__ tw64,
-                                                  const cpx<float>* __restrict__ tw32, BatchParams prm,
-                                                  int extrapolate, StepResult* __restrict__ res, int* queue) {
+// queue is set, its counter zero at launch) until none is left.
+template <int MODE>
+__global__ void __launch_bounds__(BATCH_THREADS) k_batch_rk4(const StepItem* __restrict__ items, int nitems,
+                                                             const cpx<double>* __restrict__ tw64,
+                                                             const cpx<float>* __restrict__ tw32, BatchParams prm,
+                                                             int extrapolate, StepResult* __restrict__ res,
+                                                             int* queue) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    cpx<double>* lds64 = reinterpret_cast<cpx<double>*>(smem_raw);
-    cpx<float>* lds32 = reinterpret_cast<cpx<float>*>(smem_raw);
     __shared__ double red[RED_DOUBLES];
     __shared__ int next_slot;
     for (int s = blockIdx.x; s < nitems; s = batch_next(queue, s, &next_slot)) {
         // the table entry stays in memory and is read where used (uniform loads)
         const StepItem& it = items[__builtin_amdgcn_readfirstlane(s)];
-        const StepResult out = blk_rk4_run<MODE, NT>(it, extrapolate != 0, tw64, tw32, prm, lds64, lds32, red);
+        StepResult out{};
+        const bool line = line_dispatch(it.n, [&](auto m) __attribute__((always_inline)) {
+            constexpr int M = decltype(m)::value;
+            if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
+            out = rk4_run<LineEngine<MODE, M>>(it, extrapolate != 0, tw64, tw32, prm, smem_raw, red);
+        });
+        if (!line) out = rk4_run<SmallEngine<MODE>>(it, extrapolate != 0, tw64, tw32, prm, smem_raw, red);
         if (threadIdx.x == 0) res[it.index] = out;
         __syncthreads();
     }
+}
+
+// Launches of the kernels above, one source file per kernel (the sizes make them
+// the long part of the build).  grid = 0: as many workgroups as fit the device's
+// `cus` compute units (at most nitems).  n: points of the largest system, which
+// fixes the workgroup and its LDS.
+hipError_t launch_batch_solve_kernel(int mode, int n, int grid, int cus, hipStream_t stream, const BatchItem* items,
+                                     int nitems, const double* eta, const double* hx, const double* b, double* u,
+                                     double* ws, const cpx<double>* tw64, const cpx<float>* tw32,
+                                     const BatchParams& prm, BatchResult* res, int* queue);
+hipError_t launch_rhs_1d_kernel(int n, hipStream_t stream, double L, const double* eta, const double* hx,
+                                const double* u, double* eta_t, double* U_t, cpx<double>* spec, double* st,
+                                const cpx<double>* tw);
+template <int MODE>   // defined for the two modes by their source files
+hipError_t launch_batch_rk4_kernel(int n, int grid, int cus, hipStream_t stream, const StepItem* items, int nitems,
+                                   const cpx<double>* tw64, const cpx<float>* tw32, const BatchParams& prm,
+                                   int extrapolate, StepResult* res, int* queue);
+
+// Grid of a batched launch of `kernel` and its LDS allowance.
+template <typename K>
+hipError_t batch_grid(K kernel, int nt, size_t lds, int cus, int nitems, int& grid) {
+    if (lds > 65536) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    if (grid <= 0) {
+        int per_cu = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, nt, lds) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        grid = nitems < per_cu * cus ? nitems : per_cu * cus;
+    }
+    return hipSuccess;
 }
 
 }  // namespace sgn

@@ -722,4 +722,35 @@ __device__ __forceinline__ void final_max(const double* __restrict__ partials, u
     __syncthreads();
 }
 
+// Mode weight of the half spectrum for Parseval sums: kx = 0 and kx = nx/2 appear
+// once in the full spectrum, every other kx twice (with its conjugate).
+__device__ __forceinline__ double half_weight(int kx, int nx) {
+    return (kx == 0 || 2 * kx == nx) ? 1.0 : 2.0;
+}
+
+// (sigma*, alpha*, kappa_ub) of Eq:FlatbathCoeff (flat), Eq:Optcoeff and
+// Eq:Optcoeffb (kind 0) or Remark 4.2 (kind 1) from min eta, max eta,
+// max(eta + lambda_+ eta |grad h|^2) and max |grad h|^2.  flat < 0 selects the
+// flat formulas iff |grad h|_max = 0; the choice is returned in fl.
+__host__ __device__ inline void coeffs_formula(double emin, double emax, double smx, double g2m, int flat, int kind,
+                                               double& sig, double& alp, double& kap, int& fl) {
+    const double lp = (4.0 + sqrt(13.0)) / 6.0;
+    const double lm = (4.0 - sqrt(13.0)) / 6.0;
+    const double ratio3 = (emax / emin) * (emax / emin) * (emax / emin);
+    fl = flat < 0 ? (g2m == 0.0 ? 1 : 0) : (flat != 0 ? 1 : 0);
+    if (fl) {
+        sig = emax;
+        alp = emax * emax * emax / 3.0;
+        kap = ratio3;
+    } else if (kind == 0) {
+        sig = smx;
+        alp = lp * emax * emax * emax;
+        kap = fmax(smx / emin, (lp / lm) * ratio3);
+    } else {
+        sig = emax * (1.0 + lp * g2m);
+        alp = lp * emax * emax * emax;
+        kap = fmax((emax / emin) * (1.0 + lp * g2m), (lp / lm) * ratio3);
+    }
+}
+
 }  // namespace sgn

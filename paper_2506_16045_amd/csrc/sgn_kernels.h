@@ -39,12 +39,6 @@ struct PtrList {
 };
 constexpr int MAXF = 12;
 
-// Mode weight of the half spectrum for Parseval sums: kx = 0 and kx = nx/2 appear
-// once in the full spectrum, every other kx twice (with its conjugate).
-__device__ __forceinline__ double half_weight(int kx, int nx) {
-    return (kx == 0 || 2 * kx == nx) ? 1.0 : 2.0;
-}
-
 // z = A^{-1} r in Fourier space (Def:A, section 6.1): the symbol of A is
 //   1D: sig + alp k^2;   2D: sig I + alp k k^T.
 // In 2D the inverse splits r into its parts along k and across k,
@@ -1583,31 +1577,6 @@ __global__ void __launch_bounds__(256) k_coeffs(size_t npts, const double* __res
             for (int w = 1; w < nw; ++w) s = fmax(s, red[a * 16 + w]);
             part[PART_GEN + 5 * blockIdx.x + a] = s;
         }
-    }
-}
-
-// (sigma*, alpha*, kappa_ub) of Eq:FlatbathCoeff (flat), Eq:Optcoeff and
-// Eq:Optcoeffb (kind 0) or Remark 4.2 (kind 1) from min eta, max eta,
-// max(eta + lambda_+ eta |grad h|^2) and max |grad h|^2.  flat < 0 selects the
-// flat formulas iff |grad h|_max = 0; the choice is returned in fl.
-__host__ __device__ inline void coeffs_formula(double emin, double emax, double smx, double g2m, int flat, int kind,
-                                               double& sig, double& alp, double& kap, int& fl) {
-    const double lp = (4.0 + sqrt(13.0)) / 6.0;
-    const double lm = (4.0 - sqrt(13.0)) / 6.0;
-    const double ratio3 = (emax / emin) * (emax / emin) * (emax / emin);
-    fl = flat < 0 ? (g2m == 0.0 ? 1 : 0) : (flat != 0 ? 1 : 0);
-    if (fl) {
-        sig = emax;
-        alp = emax * emax * emax / 3.0;
-        kap = ratio3;
-    } else if (kind == 0) {
-        sig = smx;
-        alp = lp * emax * emax * emax;
-        kap = fmax(smx / emin, (lp / lm) * ratio3);
-    } else {
-        sig = emax * (1.0 + lp * g2m);
-        alp = lp * emax * emax * emax;
-        kap = fmax((emax / emin) * (1.0 + lp * g2m), (lp / lm) * ratio3);
     }
 }
 

@@ -1885,22 +1885,10 @@ sgn_status solve_1d_block(sgn_ctx* ctx, const Dims& d, double L, const double* e
         prm.kap = coeffs->kappa_ub;
         prm.flat = coeffs->flat ? 1 : 0;
     }
-    const size_t lds = (size_t)(d.nx / 2 + 1) * sizeof(cpx<double>) * (mode == BATCH_FP64 ? 2 : 1);
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH);
-        auto launch = [&](auto k, int nt) -> sgn_status {
-            HIPCHK(ctx, allow_lds(k, lds));
-            hipLaunchKernelGGL(k, dim3(1), dim3(nt), lds, ctx->stream, (const BatchItem*)d_item, 1, eta, gh, rhs, u,
-                               d_data, ctx->tw64, ctx->tw32, prm, d_res, (int*)nullptr);
-            CHECK_LAUNCH(ctx);
-            return SGN_OK;
-        };
-        const bool mx = mode == BATCH_MIXED;
-        if (d.nx <= 2048)
-            s = mx ? launch(k_batch_solve<BATCH_MIXED, 256>, 256) : launch(k_batch_solve<BATCH_FP64, 256>, 256);
-        else
-            s = mx ? launch(k_batch_solve<BATCH_MIXED, 512>, 512) : launch(k_batch_solve<BATCH_FP64, 512>, 512);
-        if (s != SGN_OK) return s;
+        HIPCHK(ctx, launch_batch_solve_kernel(mode, d.nx, 1, ctx->cus, ctx->stream, d_item, 1, eta, gh, rhs, u, d_data,
+                                              ctx->tw64, ctx->tw32, prm, d_res, nullptr));
     }
     BatchResult* hres = static_cast<BatchResult*>(ctx->hbatch);
     HIPCHK(ctx, hipMemcpyAsync(hres, d_res, sizeof(BatchResult), hipMemcpyDeviceToHost, ctx->stream));
@@ -2201,16 +2189,9 @@ sgn_status rhs_1d_block(sgn_ctx* ctx, const Dims& d, const double* eta, const do
     const int M1 = d.nx / 2 + 1;
     cpx<double>* spec = cv.take<cpx<double>>((size_t)5 * M1);
     double* st = cv.take<double>((size_t)5 * d.nx);
-    const size_t lds = (size_t)M1 * sizeof(cpx<double>);
     ProfScope ps(ctx, SGN_KERNEL_ROWS);
-    auto launch = [&](auto k, int nt) -> sgn_status {
-        HIPCHK(ctx, allow_lds(k, lds));
-        hipLaunchKernelGGL(k, dim3(1), dim3(nt), lds, ctx->stream, d.nx, d.Lx, eta, gh, u, eta_t, U_t, spec, st,
-                           ctx->tw64);
-        CHECK_LAUNCH(ctx);
-        return SGN_OK;
-    };
-    return d.nx <= 2048 ? launch(k_rhs_1d<256>, 256) : launch(k_rhs_1d<512>, 512);
+    HIPCHK(ctx, launch_rhs_1d_kernel(d.nx, ctx->stream, d.Lx, eta, gh, u, eta_t, U_t, spec, st, ctx->tw64));
+    return SGN_OK;
 }
 
 sgn_status rhs_dispatch(sgn_ctx* ctx, const Dims& d, const double* eta, const double* gh, const double* u,
@@ -3405,38 +3386,6 @@ BatchLayout batch_layout(int nitems, const int32_t* n, int mode) {
 
 bool batch_size_ok(int n) { return n >= 2 && n <= BATCH_NMAX && (n & (n - 1)) == 0; }
 
-// Workgroup size of every system of a batched call (sgn_batch_solve,
-// sgn_batch_step_rk4); the one-system paths take the size class of their n.
-constexpr int BATCH_CALL_THREADS = 512;
-
-// k_batch_solve over nitems table entries (workgroups of nt threads) on
-// `stream`.  LDS: two transform buffers of the largest system's M + 1 modes (FP64
-// ones in FP64 mode; in mixed mode the FP32 pair or one FP64 buffer, the
-// refinement residual, whichever is larger).  grid = 0: as many workgroups as fit
-// the device (at most nitems), sharing the work queue d_queue.
-sgn_status launch_batch_solve(sgn_ctx* ctx, hipStream_t stream, int nt, const BatchItem* d_items, int nitems,
-                              int nmax, int mode, int grid, const double* eta, const double* gh, const double* rhs,
-                              double* u, double* d_data, const BatchParams& prm, BatchResult* d_res, int* d_queue) {
-    const size_t lds = (size_t)(nmax / 2 + 1) * sizeof(cpx<double>) * (mode == BATCH_FP64 ? 2 : 1);
-    auto launch = [&](auto k) -> sgn_status {
-        HIPCHK(ctx, allow_lds(k, lds));
-        int g = grid;
-        if (g <= 0) {
-            int per_cu = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, nt, lds) != hipSuccess || per_cu < 1)
-                per_cu = 1;
-            g = std::min(nitems, per_cu * ctx->cus);
-        }
-        hipLaunchKernelGGL(k, dim3(g), dim3(nt), lds, stream, d_items, nitems, eta, gh, rhs, u, d_data, ctx->tw64,
-                           ctx->tw32, prm, d_res, d_queue);
-        CHECK_LAUNCH(ctx);
-        return SGN_OK;
-    };
-    const bool mx = mode == BATCH_MIXED;
-    if (nt == 256) return mx ? launch(k_batch_solve<BATCH_MIXED, 256>) : launch(k_batch_solve<BATCH_FP64, 256>);
-    return mx ? launch(k_batch_solve<BATCH_MIXED, 512>) : launch(k_batch_solve<BATCH_FP64, 512>);
-}
-
 // ---- batched RK4 runs (k_batch_rk4) ----------------------------------------
 
 // One state's arrays in a batched run, each 256-byte aligned: h_x, U, the four
@@ -3477,34 +3426,17 @@ BatchParams step_params(const sgn_solve_opts& o, int nitems) {
     return prm;
 }
 
-// Workgroup size of a state's runs: fixed by its own size, so that its
-// reductions (and with them its results) do not depend on what shares a launch.
-int step_threads(int n) { return batch_threads_for(n); }
-
-// k_batch_rk4 over nitems table entries (workgroups of nt
-// threads) on `stream`; grid = 0: as many workgroups as fit the device (at most
-// nitems), which then share the work queue d_queue (zero at launch).
-sgn_status launch_batch_rk4(sgn_ctx* ctx, hipStream_t stream, int nt, const StepItem* d_items, int nitems, int nmax,
-                            int mode, int grid, const BatchParams& prm, bool extrapolate, StepResult* d_res,
-                            int* d_queue) {
-    const size_t lds = (size_t)(nmax / 2 + 1) * sizeof(cpx<double>) * (mode == BATCH_FP64 ? 2 : 1);
-    auto launch = [&](auto k) -> sgn_status {
-        HIPCHK(ctx, allow_lds(k, lds));
-        int g = grid;
-        if (g <= 0) {
-            int per_cu = 0;
-            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k, nt, lds) != hipSuccess || per_cu < 1)
-                per_cu = 1;
-            g = std::min(nitems, per_cu * ctx->cus);
-        }
-        hipLaunchKernelGGL(k, dim3(g), dim3(nt), lds, stream, d_items, nitems, ctx->tw64, ctx->tw32, prm,
-                           extrapolate ? 1 : 0, d_res, d_queue);
-        CHECK_LAUNCH(ctx);
-        return SGN_OK;
+// k_batch_rk4 over nitems table entries (grid = 0: sharing the work queue d_queue,
+// zero at launch).
+sgn_status launch_batch_rk4(sgn_ctx* ctx, const StepItem* d_items, int nitems, int nmax, int mode, int grid,
+                            const BatchParams& prm, bool extrapolate, StepResult* d_res, int* d_queue) {
+    auto run = [&](auto launch) {
+        return launch(nmax, grid, ctx->cus, ctx->stream, d_items, nitems, ctx->tw64, ctx->tw32, prm,
+                      extrapolate ? 1 : 0, d_res, d_queue);
     };
-    const bool mx = mode == BATCH_MIXED;
-    if (nt == 256) return mx ? launch(k_batch_rk4<BATCH_MIXED, 256>) : launch(k_batch_rk4<BATCH_FP64, 256>);
-    return mx ? launch(k_batch_rk4<BATCH_MIXED, 512>) : launch(k_batch_rk4<BATCH_FP64, 512>);
+    HIPCHK(ctx, mode == BATCH_MIXED ? run(launch_batch_rk4_kernel<BATCH_MIXED>)
+                                    : run(launch_batch_rk4_kernel<BATCH_FP64>));
+    return SGN_OK;
 }
 
 static_assert(sizeof(StepItem) <= 512 && sizeof(StepResult) <= 512, "step table entries");
@@ -3554,7 +3486,7 @@ sgn_status rk4_block(sgn_state* st, double dt, int nsteps, const sgn_solve_opts&
     HIPCHK(ctx, hipMemcpyAsync(d_item, hit, sizeof(StepItem), hipMemcpyHostToDevice, ctx->stream));
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH_STEP);
-        if ((s = launch_batch_rk4(ctx, ctx->stream, step_threads(st->d.nx), d_item, 1, st->d.nx, mode, 1,
+        if ((s = launch_batch_rk4(ctx, d_item, 1, st->d.nx, mode, 1,
                                   step_params(o, 1), o.guess == SGN_GUESS_EXTRAPOLATE, d_res, nullptr)) != SGN_OK)
             return s;
     }
@@ -3666,11 +3598,8 @@ sgn_status sgn_batch_solve(sgn_ctx* ctx, int32_t nitems, const int32_t* n, const
     prm.flat = -1;
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH);
-        // every system of a batched call on 512 threads, whatever its size: a
-        // system's reductions, and so its result, do not depend on the batch
-        if ((s = launch_batch_solve(ctx, ctx->stream, BATCH_CALL_THREADS, d_items, nitems, nmax, mode, 0, eta, grad_h,
-                                    rhs, u, d_data, prm, d_res, d_queue)) != SGN_OK)
-            return s;
+        HIPCHK(ctx, launch_batch_solve_kernel(mode, nmax, 0, ctx->cus, ctx->stream, d_items, nitems, eta, grad_h, rhs,
+                                              u, d_data, ctx->tw64, ctx->tw32, prm, d_res, d_queue));
     }
     BatchResult* hres = static_cast<BatchResult*>(ctx->hbatch);
     HIPCHK(ctx, hipMemcpyAsync(hres, d_res, sizeof(BatchResult) * (size_t)nitems, hipMemcpyDeviceToHost, ctx->stream));
@@ -3795,10 +3724,8 @@ sgn_status sgn_batch_step_rk4(sgn_ctx* ctx, int32_t nitems, const int32_t* n, co
     const BatchParams prm = step_params(o, nitems);
     const bool ex = o.guess == SGN_GUESS_EXTRAPOLATE;
     {
-        // every run of a batched call on 512 threads, whatever its size: a run's
-        // reductions, and so its result, do not depend on the batch
         ProfScope ps(ctx, SGN_KERNEL_BATCH_STEP);
-        if ((s = launch_batch_rk4(ctx, ctx->stream, BATCH_CALL_THREADS, d_items, nitems, nmax, mode, 0, prm, ex, d_res,
+        if ((s = launch_batch_rk4(ctx, d_items, nitems, nmax, mode, 0, prm, ex, d_res,
                                   d_queue)) != SGN_OK)
             return s;
     }

@@ -21,6 +21,15 @@ constexpr int SMALL_MMAX = 32;                   // largest half length of the b
 
 enum { BATCH_FP64 = 0, BATCH_MIXED = 1 };
 
+// A pointer read from a table is known to be one to global memory: without this
+// the compiler emits flat accesses, which count as LDS accesses too and so make
+// every wait for an exchange wait for them.
+template <typename P>
+__device__ __forceinline__ P* gl(P* p) {
+    // (through an integer: a pair of pointer casts would be folded away)
+    return (P*)(__attribute__((address_space(1))) P*)reinterpret_cast<unsigned long long>(p);
+}
+
 struct BatchItem {
     int n;           // grid points, a power of two in [2, BATCH_NMAX]
     int index;       // position of the system in the caller's order
@@ -611,46 +620,76 @@ __host__ __device__ constexpr size_t batch_lds_bytes(int n) {
     return n < 2 * LINE_MMIN ? (size_t)2 * (SMALL_MMAX + 1) * 16 : line_lds_bytes(n);
 }
 
-// One system by the whole workgroup, on the engine of its size.
-template <int MODE>
-__device__ __forceinline__ BatchResult batch_solve_system(const BatchItem& it, const double* __restrict__ eta,
-                                                          const double* __restrict__ hx, const double* __restrict__ b,
-                                                          double* u, bool guess, double* w,
-                                                          const cpx<double>* __restrict__ tw64,
-                                                          const cpx<float>* __restrict__ tw32, const BatchParams& prm,
-                                                          void* lds, double* red) {
-    BatchResult out{};
-    const bool line = line_dispatch(it.n, [&](auto m) __attribute__((always_inline)) {
-        constexpr int M = decltype(m)::value;
-        // a system that fits one wave runs on the first, the others wait at the
-        // caller's barrier
-        if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
-        out = line_solve<MODE, M>(it.L, eta, hx, b, u, guess, w, tw64, tw32, prm, lds, red);
-    });
-    if (!line)
-        out = blk_solve_system<MODE>(it, eta, hx, b, u, guess, w, tw64, tw32, prm,
-                                     reinterpret_cast<cpx<double>*>(lds), reinterpret_cast<cpx<float>*>(lds), red);
-    return out;
+// The engine of every size is a function of its own: inlined side by side into one
+// kernel, the sizes' register needs add up and their loops reload spilled values
+// (n = 1024: 33 reloads an iteration).  Arguments arrive in vector registers;
+// they are the same in every lane and go back to scalar ones.
+typedef __attribute__((address_space(3))) unsigned char* lds_bytes;
+typedef __attribute__((address_space(3))) double* lds_doubles;
+__device__ __forceinline__ unsigned long long uniform_bits(const void* p) {
+    const unsigned long long b = reinterpret_cast<unsigned long long>(p);
+    const unsigned lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffu));
+    const unsigned hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+// a table that no kernel writes while it is read: scalar loads
+template <typename P>
+__device__ __forceinline__ const P& uniform_table(const P* p) {
+    return *(const P*)(const __attribute__((address_space(4))) P*)uniform_bits(p);
+}
+template <typename P>
+__device__ __forceinline__ P uniform_l(P p) {   // an LDS pointer
+    return (P)(unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned long long)p);
 }
 
+// What every system of a launch shares, in the launch's constant arguments.
+struct SolveShared {
+    const double *eta, *hx, *b;
+    double *u, *ws;
+    const cpx<double>* tw64;
+    const cpx<float>* tw32;
+    BatchParams prm;
+};
+
+template <int MODE, int M>
+static __device__ __noinline__ void line_solve_system(const BatchItem* item, const SolveShared* shared,
+                                                      BatchResult* res, lds_bytes lds, lds_doubles red) {
+    const BatchItem& it = uniform_table(item);
+    const SolveShared& a = uniform_table(shared);
+    const BatchResult out = line_solve<MODE, M>(it.L, gl(a.eta) + it.off, gl(a.hx) + it.off, gl(a.b) + it.off,
+                                                gl(a.u) + it.off, a.prm.x0_is_guess != 0, gl(a.ws) + it.wso,
+                                                gl(a.tw64), gl(a.tw32), a.prm,
+                                                (void*)uniform_l(lds), (double*)uniform_l(red));
+    if (threadIdx.x == 0) gl(res)[it.index] = out;
+}
+
+// items, then what they share: one table in device memory (the item table's
+// SolveShared sits at `shared`).
 template <int MODE>
 __global__ void __launch_bounds__(BATCH_THREADS) k_batch_solve(const BatchItem* __restrict__ items, int nitems,
-                                                               const double* __restrict__ eta_all,
-                                                               const double* __restrict__ hx_all,
-                                                               const double* __restrict__ b_all,
-                                                               double* __restrict__ u_all, double* __restrict__ ws,
-                                                               const cpx<double>* __restrict__ tw64,
-                                                               const cpx<float>* __restrict__ tw32, BatchParams prm,
+                                                               const SolveShared* __restrict__ shared,
                                                                BatchResult* __restrict__ res, int* queue) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[RED_DOUBLES];
     __shared__ int next_slot;
     for (int s = blockIdx.x; s < nitems; s = batch_next(queue, s, &next_slot)) {
         const BatchItem& it = items[__builtin_amdgcn_readfirstlane(s)];   // uniform: scalar loads
-        const BatchResult out =
-            batch_solve_system<MODE>(it, eta_all + it.off, hx_all + it.off, b_all + it.off, u_all + it.off,
-                                     prm.x0_is_guess != 0, ws + it.wso, tw64, tw32, prm, smem_raw, red);
-        if (threadIdx.x == 0) res[it.index] = out;
+        const bool line = line_dispatch(it.n, [&](auto m) __attribute__((always_inline)) {
+            constexpr int M = decltype(m)::value;
+            // a system that fits one wave runs on the first, the others wait at the
+            // barrier below
+            if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
+            line_solve_system<MODE, M>(&it, shared, res, (lds_bytes)smem_raw, (lds_doubles)red);
+        });
+        if (!line) {
+            const SolveShared& a = *shared;
+            const BatchResult out = blk_solve_system<MODE>(it, gl(a.eta) + it.off, gl(a.hx) + it.off, gl(a.b) + it.off,
+                                                           gl(a.u) + it.off, a.prm.x0_is_guess != 0, gl(a.ws) + it.wso,
+                                                           gl(a.tw64), gl(a.tw32), a.prm,
+                                                           reinterpret_cast<cpx<double>*>(smem_raw),
+                                                           reinterpret_cast<cpx<float>*>(smem_raw), red);
+            if (threadIdx.x == 0) res[it.index] = out;
+        }
         __syncthreads();
     }
 }
@@ -902,7 +941,7 @@ struct LineEngine {
         double ex[3] = {-1.0e308, -1.0e308, 0.0};
         if (L.act) {
             for (int i = threadIdx.x; i < 2 * M; i += LineGeo<double, M>::TH) {
-                const double v = it.h[i];
+                const double v = gl(it.h)[i];
                 if (!isfinite(v)) ex[2] = 1.0;
                 ex[0] = fmax(ex[0], -v);
                 ex[1] = fmax(ex[1], v);
@@ -912,23 +951,23 @@ struct LineEngine {
         if (ex[2] != 0.0) return false;
         flat = (-ex[0] == ex[1]) ? 1 : 0;
         if (flat) {
-            for (int i = threadIdx.x; i < 2 * M; i += threads()) it.hx[i] = 0.0;
+            for (int i = threadIdx.x; i < 2 * M; i += threads()) gl(it.hx)[i] = 0.0;
         } else {
-            line_slope<M>(it.L, it.h, it.hx, tw, lds, red);
+            line_slope<M>(it.L, gl(it.h), gl(it.hx), tw, lds, red);
         }
         sync();
-        line_momentum<M>(it.L, it.eta, it.hx, it.u, it.U, tw, lds, red);
+        line_momentum<M>(it.L, gl(it.eta), gl(it.hx), gl(it.u), gl(it.U), tw, lds, red);
         sync();
         return true;
     }
     static __device__ __forceinline__ BatchResult solve(const StepItem& it, const double* eta, const double* U,
                                                         double* u, const cpx<double>* tw64, const cpx<float>* tw32,
                                                         const BatchParams& prm, void* lds, double* red) {
-        return line_solve<MODE, M>(it.L, eta, it.hx, U, u, true, it.scr, tw64, tw32, prm, lds, red);
+        return line_solve<MODE, M>(it.L, eta, gl(it.hx), U, u, true, gl(it.scr), tw64, tw32, prm, lds, red);
     }
     static __device__ __forceinline__ void rhs(const StepItem& it, const double* eta, const double* u, double* eta_t,
                                                double* U_t, const cpx<double>* tw, void* lds, double* red) {
-        line_rhs<M>(it.L, eta, it.hx, u, eta_t, U_t, tw, lds, red);
+        line_rhs<M>(it.L, eta, gl(it.hx), u, eta_t, U_t, tw, lds, red);
     }
 };
 
@@ -945,11 +984,11 @@ __device__ __forceinline__ int step_solve(const StepItem& it, StepResult& out, i
     int& head = out.head[slot];
     const int nh = cnt == 0 ? head : head ^ 1;
     if (extrapolate) {
-        const double* o1 = it.off[slot][head];
-        const double* o2 = it.off[slot][head ^ 1];
+        const double* o1 = gl(it.off[slot][head]);
+        const double* o2 = gl(it.off[slot][head ^ 1]);
         for (int i = threadIdx.x; i < N; i += Eng::threads()) {
             const double b = u[i];
-            it.base[i] = b;
+            gl(it.base)[i] = b;
             if (cnt == 1) {
                 double s = 0.0;
                 s += 1.0 * o1[i];
@@ -972,10 +1011,10 @@ __device__ __forceinline__ int step_solve(const StepItem& it, StepResult& out, i
     if (r.status != 0) return -2;
     if (!r.converged) return -3;
     if (extrapolate) {
-        double* o = it.off[slot][nh];
+        double* o = gl(it.off[slot][nh]);
         for (int i = threadIdx.x; i < N; i += Eng::threads()) {
             double s = 0.0;
-            s += -1.0 * it.base[i];
+            s += -1.0 * gl(it.base)[i];
             o[i] = u[i] + 1.0 * s;
         }
         Eng::sync();
@@ -1023,26 +1062,26 @@ __device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapola
                 for (int i = threadIdx.x; i < N; i += Eng::threads()) {
                     if (!last) {
                         double s = 0.0;
-                        s += a[k - 1] * it.fe[k - 1][i];
-                        it.eta_s[i] = it.eta[i] + dt * s;
+                        s += a[k - 1] * gl(it.fe[k - 1])[i];
+                        gl(it.eta_s)[i] = gl(it.eta)[i] + dt * s;
                         double q = 0.0;
-                        q += a[k - 1] * it.fU[k - 1][i];
-                        it.U_s[i] = it.U[i] + dt * q;
+                        q += a[k - 1] * gl(it.fU[k - 1])[i];
+                        gl(it.U_s)[i] = gl(it.U)[i] + dt * q;
                     } else {
                         double s = 0.0, q = 0.0;
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
-                            s += w[j] * it.fe[j][i];
-                            q += w[j] * it.fU[j][i];
+                            s += w[j] * gl(it.fe[j])[i];
+                            q += w[j] * gl(it.fU[j])[i];
                         }
-                        it.eta[i] = it.eta[i] + dt * s;
-                        it.U[i] = it.U[i] + dt * q;
-                        it.u[i] = it.u_s[i];
+                        gl(it.eta)[i] = gl(it.eta)[i] + dt * s;
+                        gl(it.U)[i] = gl(it.U)[i] + dt * q;
+                        gl(it.u)[i] = gl(it.u_s)[i];
                     }
                 }
                 Eng::sync();
-                const int rc = step_solve<Eng>(it, out, k - 1, extrapolate, last ? it.eta : it.eta_s,
-                                               last ? it.U : it.U_s, last ? it.u : it.u_s, tw64, tw32, prm, lds, red);
+                const int rc = step_solve<Eng>(it, out, k - 1, extrapolate, gl(last ? it.eta : it.eta_s),
+                                               gl(last ? it.U : it.U_s), gl(last ? it.u : it.u_s), tw64, tw32, prm, lds, red);
                 if (last) out.steps += 1;
                 if (rc != 0) {
                     out.status = rc;
@@ -1050,10 +1089,10 @@ __device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapola
                 }
             }
             if (k < 4) {
-                Eng::rhs(it, k ? it.eta_s : it.eta, k ? it.u_s : it.u, it.fe[k], it.fU[k], tw64, lds, red);
+                Eng::rhs(it, gl(k ? it.eta_s : it.eta), gl(k ? it.u_s : it.u), gl(it.fe[k]), gl(it.fU[k]), tw64, lds, red);
                 Eng::sync();
                 if (k == 0) {
-                    for (int i = threadIdx.x; i < N; i += Eng::threads()) it.u_s[i] = it.u[i];
+                    for (int i = threadIdx.x; i < N; i += Eng::threads()) gl(it.u_s)[i] = gl(it.u)[i];
                     Eng::sync();
                 }
             }
@@ -1062,28 +1101,46 @@ __device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapola
     return out;
 }
 
+// What every run of a launch shares.
+struct StepShared {
+    const cpx<double>* tw64;
+    const cpx<float>* tw32;
+    BatchParams prm;
+    int extrapolate;
+};
+
+template <int MODE, int M>
+static __device__ __noinline__ void line_rk4_system(const StepItem* item, const StepShared* shared, StepResult* res,
+                                                    lds_bytes lds, lds_doubles red) {
+    const StepItem& it = uniform_table(item);
+    const StepShared& a = uniform_table(shared);
+    const StepResult out = rk4_run<LineEngine<MODE, M>>(it, a.extrapolate != 0, gl(a.tw64), gl(a.tw32), a.prm,
+                                                        (void*)uniform_l(lds), (double*)uniform_l(red));
+    if (threadIdx.x == 0) gl(res)[it.index] = out;
+}
+
 // Batched RK4 runs: workgroups take states from the table (a work queue when
 // queue is set, its counter zero at launch) until none is left.
 template <int MODE>
 __global__ void __launch_bounds__(BATCH_THREADS) k_batch_rk4(const StepItem* __restrict__ items, int nitems,
-                                                             const cpx<double>* __restrict__ tw64,
-                                                             const cpx<float>* __restrict__ tw32, BatchParams prm,
-                                                             int extrapolate, StepResult* __restrict__ res,
-                                                             int* queue) {
+                                                             const StepShared* __restrict__ shared,
+                                                             StepResult* __restrict__ res, int* queue) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ double red[RED_DOUBLES];
     __shared__ int next_slot;
     for (int s = blockIdx.x; s < nitems; s = batch_next(queue, s, &next_slot)) {
         // the table entry stays in memory and is read where used (uniform loads)
         const StepItem& it = items[__builtin_amdgcn_readfirstlane(s)];
-        StepResult out{};
         const bool line = line_dispatch(it.n, [&](auto m) __attribute__((always_inline)) {
             constexpr int M = decltype(m)::value;
             if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
-            out = rk4_run<LineEngine<MODE, M>>(it, extrapolate != 0, tw64, tw32, prm, smem_raw, red);
+            line_rk4_system<MODE, M>(&it, shared, res, (lds_bytes)smem_raw, (lds_doubles)red);
         });
-        if (!line) out = rk4_run<SmallEngine<MODE>>(it, extrapolate != 0, tw64, tw32, prm, smem_raw, red);
-        if (threadIdx.x == 0) res[it.index] = out;
+        if (!line) {
+            const StepShared& a = *shared;
+            const StepResult out = rk4_run<SmallEngine<MODE>>(it, a.extrapolate != 0, gl(a.tw64), gl(a.tw32), a.prm, smem_raw, red);
+            if (threadIdx.x == 0) res[it.index] = out;
+        }
         __syncthreads();
     }
 }
@@ -1093,16 +1150,13 @@ __global__ void __launch_bounds__(BATCH_THREADS) k_batch_rk4(const StepItem* __r
 // `cus` compute units (at most nitems).  n: points of the largest system, which
 // fixes the workgroup and its LDS.
 hipError_t launch_batch_solve_kernel(int mode, int n, int grid, int cus, hipStream_t stream, const BatchItem* items,
-                                     int nitems, const double* eta, const double* hx, const double* b, double* u,
-                                     double* ws, const cpx<double>* tw64, const cpx<float>* tw32,
-                                     const BatchParams& prm, BatchResult* res, int* queue);
+                                     int nitems, const SolveShared* shared, BatchResult* res, int* queue);
 hipError_t launch_rhs_1d_kernel(int n, hipStream_t stream, double L, const double* eta, const double* hx,
                                 const double* u, double* eta_t, double* U_t, cpx<double>* spec, double* st,
                                 const cpx<double>* tw);
 template <int MODE>   // defined for the two modes by their source files
 hipError_t launch_batch_rk4_kernel(int n, int grid, int cus, hipStream_t stream, const StepItem* items, int nitems,
-                                   const cpx<double>* tw64, const cpx<float>* tw32, const BatchParams& prm,
-                                   int extrapolate, StepResult* res, int* queue);
+                                   const StepShared* shared, StepResult* res, int* queue);
 
 // Grid of a batched launch of `kernel` and its LDS allowance.
 template <typename K>

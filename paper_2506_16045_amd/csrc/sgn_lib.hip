@@ -1856,7 +1856,9 @@ sgn_status solve_1d_block(sgn_ctx* ctx, const Dims& d, double L, const double* e
                           const double* rhs, double* u, const sgn_coeffs* coeffs, int flat, const sgn_solve_opts& o,
                           sgn_solve_info* info, void* ws) {
     sgn_status s;
-    if ((s = batch_staging(ctx, std::max(sizeof(BatchItem), sizeof(BatchResult)))) != SGN_OK) return s;
+    constexpr size_t SHARED_AT = 64;   // item | shared | (from 256) result | (from 512) region
+    static_assert(sizeof(BatchItem) <= SHARED_AT && SHARED_AT + sizeof(SolveShared) <= 256, "solve table");
+    if ((s = batch_staging(ctx, std::max((size_t)256, sizeof(BatchResult)))) != SGN_OK) return s;
     const int mode = o.precision == SGN_MIXED ? BATCH_MIXED : BATCH_FP64;
     BatchItem* hit = static_cast<BatchItem*>(ctx->hbatch);
     hit->n = d.nx;
@@ -1868,8 +1870,9 @@ sgn_status solve_1d_block(sgn_ctx* ctx, const Dims& d, double L, const double* e
     BatchItem* d_item = reinterpret_cast<BatchItem*>(base);
     BatchResult* d_res = reinterpret_cast<BatchResult*>(base + 256);
     double* d_data = reinterpret_cast<double*>(base + 512);
-    HIPCHK(ctx, hipMemcpyAsync(d_item, hit, sizeof(BatchItem), hipMemcpyHostToDevice, ctx->stream));
-    BatchParams prm{};
+    SolveShared* hsh = reinterpret_cast<SolveShared*>(static_cast<char*>(ctx->hbatch) + SHARED_AT);
+    *hsh = SolveShared{eta, gh, rhs, u, d_data, ctx->tw64, ctx->tw32, {}};
+    BatchParams& prm = hsh->prm;
     prm.tol = o.tol;
     prm.inner_tol = o.inner_tol > 0 ? o.inner_tol : 1e-5;
     prm.max_iter = o.max_iter;
@@ -1885,10 +1888,11 @@ sgn_status solve_1d_block(sgn_ctx* ctx, const Dims& d, double L, const double* e
         prm.kap = coeffs->kappa_ub;
         prm.flat = coeffs->flat ? 1 : 0;
     }
+    HIPCHK(ctx, hipMemcpyAsync(d_item, hit, 256, hipMemcpyHostToDevice, ctx->stream));
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH);
-        HIPCHK(ctx, launch_batch_solve_kernel(mode, d.nx, 1, ctx->cus, ctx->stream, d_item, 1, eta, gh, rhs, u, d_data,
-                                              ctx->tw64, ctx->tw32, prm, d_res, nullptr));
+        HIPCHK(ctx, launch_batch_solve_kernel(mode, d.nx, 1, ctx->cus, ctx->stream, d_item, 1,
+                                              reinterpret_cast<const SolveShared*>(base + SHARED_AT), d_res, nullptr));
     }
     BatchResult* hres = static_cast<BatchResult*>(ctx->hbatch);
     HIPCHK(ctx, hipMemcpyAsync(hres, d_res, sizeof(BatchResult), hipMemcpyDeviceToHost, ctx->stream));
@@ -3369,7 +3373,10 @@ namespace {
 struct BatchLayout {
     size_t queue, items, results, data, total;
 };
-constexpr size_t BATCH_HEAD = 256;   // bytes before the item table (the counter, padded)
+constexpr size_t BATCH_HEAD = 256;   // bytes before the item table: the counter, then what the systems share
+constexpr size_t BATCH_SHARED = 64;
+static_assert(BATCH_SHARED + sizeof(SolveShared) <= BATCH_HEAD && BATCH_SHARED + sizeof(StepShared) <= BATCH_HEAD,
+              "head of a batch table");
 
 BatchLayout batch_layout(int nitems, const int32_t* n, int mode) {
     BatchLayout l;
@@ -3429,10 +3436,9 @@ BatchParams step_params(const sgn_solve_opts& o, int nitems) {
 // k_batch_rk4 over nitems table entries (grid = 0: sharing the work queue d_queue,
 // zero at launch).
 sgn_status launch_batch_rk4(sgn_ctx* ctx, const StepItem* d_items, int nitems, int nmax, int mode, int grid,
-                            const BatchParams& prm, bool extrapolate, StepResult* d_res, int* d_queue) {
+                            const StepShared* d_shared, StepResult* d_res, int* d_queue) {
     auto run = [&](auto launch) {
-        return launch(nmax, grid, ctx->cus, ctx->stream, d_items, nitems, ctx->tw64, ctx->tw32, prm,
-                      extrapolate ? 1 : 0, d_res, d_queue);
+        return launch(nmax, grid, ctx->cus, ctx->stream, d_items, nitems, d_shared, d_res, d_queue);
     };
     HIPCHK(ctx, mode == BATCH_MIXED ? run(launch_batch_rk4_kernel<BATCH_MIXED>)
                                     : run(launch_batch_rk4_kernel<BATCH_FP64>));
@@ -3483,11 +3489,15 @@ sgn_status rk4_block(sgn_state* st, double dt, int nsteps, const sgn_solve_opts&
     hit->flat = st->flat ? 1 : 0;
     StepItem* d_item = reinterpret_cast<StepItem*>(base);
     StepResult* d_res = reinterpret_cast<StepResult*>(base + 512);
-    HIPCHK(ctx, hipMemcpyAsync(d_item, hit, sizeof(StepItem), hipMemcpyHostToDevice, ctx->stream));
+    constexpr size_t SHARED_AT = 384;
+    static_assert(sizeof(StepItem) <= SHARED_AT && SHARED_AT + sizeof(StepShared) <= 512, "step table");
+    *reinterpret_cast<StepShared*>(static_cast<char*>(ctx->hbatch) + SHARED_AT) =
+        StepShared{ctx->tw64, ctx->tw32, step_params(o, 1), o.guess == SGN_GUESS_EXTRAPOLATE ? 1 : 0};
+    HIPCHK(ctx, hipMemcpyAsync(d_item, hit, 512, hipMemcpyHostToDevice, ctx->stream));
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH_STEP);
         if ((s = launch_batch_rk4(ctx, d_item, 1, st->d.nx, mode, 1,
-                                  step_params(o, 1), o.guess == SGN_GUESS_EXTRAPOLATE, d_res, nullptr)) != SGN_OK)
+                                  reinterpret_cast<const StepShared*>(base + SHARED_AT), d_res, nullptr)) != SGN_OK)
             return s;
     }
     StepResult* hres = reinterpret_cast<StepResult*>(static_cast<char*>(ctx->hbatch) + 512);
@@ -3585,9 +3595,9 @@ sgn_status sgn_batch_solve(sgn_ctx* ctx, int32_t nitems, const int32_t* n, const
     BatchItem* d_items = reinterpret_cast<BatchItem*>(base + lay.items);
     BatchResult* d_res = reinterpret_cast<BatchResult*>(base + lay.results);
     double* d_data = reinterpret_cast<double*>(base + lay.data);
-    HIPCHK(ctx, hipMemcpyAsync(base, ctx->hbatch, BATCH_HEAD + sizeof(BatchItem) * (size_t)nitems,
-                               hipMemcpyHostToDevice, ctx->stream));
-    BatchParams prm{};
+    SolveShared* hsh = reinterpret_cast<SolveShared*>(static_cast<char*>(ctx->hbatch) + BATCH_SHARED);
+    *hsh = SolveShared{eta, grad_h, rhs, u, d_data, ctx->tw64, ctx->tw32, {}};
+    BatchParams& prm = hsh->prm;
     prm.tol = o.tol;
     prm.inner_tol = o.inner_tol > 0 ? o.inner_tol : 1e-5;
     prm.max_iter = o.max_iter;
@@ -3596,10 +3606,13 @@ sgn_status sgn_batch_solve(sgn_ctx* ctx, int32_t nitems, const int32_t* n, const
     prm.coeff_kind = o.coeff_kind;
     prm.nitems = nitems;
     prm.flat = -1;
+    HIPCHK(ctx, hipMemcpyAsync(base, ctx->hbatch, BATCH_HEAD + sizeof(BatchItem) * (size_t)nitems,
+                               hipMemcpyHostToDevice, ctx->stream));
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH);
-        HIPCHK(ctx, launch_batch_solve_kernel(mode, nmax, 0, ctx->cus, ctx->stream, d_items, nitems, eta, grad_h, rhs,
-                                              u, d_data, ctx->tw64, ctx->tw32, prm, d_res, d_queue));
+        HIPCHK(ctx, launch_batch_solve_kernel(mode, nmax, 0, ctx->cus, ctx->stream, d_items, nitems,
+                                              reinterpret_cast<const SolveShared*>(base + BATCH_SHARED), d_res,
+                                              d_queue));
     }
     BatchResult* hres = static_cast<BatchResult*>(ctx->hbatch);
     HIPCHK(ctx, hipMemcpyAsync(hres, d_res, sizeof(BatchResult) * (size_t)nitems, hipMemcpyDeviceToHost, ctx->stream));
@@ -3716,17 +3729,17 @@ sgn_status sgn_batch_step_rk4(sgn_ctx* ctx, int32_t nitems, const int32_t* n, co
         it.index = i;
         it.nsteps = nsteps[i];
     }
+    *reinterpret_cast<StepShared*>(static_cast<char*>(ctx->hbatch) + BATCH_SHARED) =
+        StepShared{ctx->tw64, ctx->tw32, step_params(o, nitems), o.guess == SGN_GUESS_EXTRAPOLATE ? 1 : 0};
     HIPCHK(ctx, hipMemcpyAsync(base, ctx->hbatch, BATCH_HEAD + sizeof(StepItem) * (size_t)nitems,
                                hipMemcpyHostToDevice, ctx->stream));
     const StepItem* d_items = reinterpret_cast<const StepItem*>(base + lay.items);
     StepResult* d_res = reinterpret_cast<StepResult*>(base + lay.results);
-    int* d_queue = reinterpret_cast<int*>(base);   // counters at bytes 0 and 128
-    const BatchParams prm = step_params(o, nitems);
-    const bool ex = o.guess == SGN_GUESS_EXTRAPOLATE;
+    int* d_queue = reinterpret_cast<int*>(base);
     {
         ProfScope ps(ctx, SGN_KERNEL_BATCH_STEP);
-        if ((s = launch_batch_rk4(ctx, d_items, nitems, nmax, mode, 0, prm, ex, d_res,
-                                  d_queue)) != SGN_OK)
+        if ((s = launch_batch_rk4(ctx, d_items, nitems, nmax, mode, 0,
+                                  reinterpret_cast<const StepShared*>(base + BATCH_SHARED), d_res, d_queue)) != SGN_OK)
             return s;
     }
     StepResult* hres = static_cast<StepResult*>(ctx->hbatch);

@@ -31,27 +31,91 @@ namespace sgn {
 
 constexpr int LINE_MMIN = 64, LINE_MMAX = 4096;   // half lengths this file takes
 
+constexpr int line_log2(int x) { return x <= 1 ? 0 : 1 + line_log2(x / 2); }
+
 template <typename T, int M_>
 struct LineGeo {
     static constexpr int M = M_, N = 2 * M_;
-    static constexpr int E = M >= 4096 ? 16 : 8;     // complex entries per thread of a field
+    // complex entries per thread of a field: the most that leave no lane of a wave
+    // idle on the short lines, and two exchanges on the longest
+    static constexpr int E = M >= 4096 ? 16 : M >= 256 ? 8 : 4;
     static constexpr int G = M / E;                  // threads of one field
     static constexpr int TH = 2 * G;                 // threads of a system
     static constexpr bool ONE = TH <= 64;            // one wave holds the system
     static constexpr bool WFLD = G <= 64;            // one wave holds a field
-    static constexpr bool PP = (size_t)4 * M * sizeof(cpx<T>) <= 128 * 1024;   // two buffers per field
     static constexpr int NP = M / 2 / TH;            // mode pairs per thread
     static constexpr int NW = ONE ? 1 : TH / 64;     // waves of a system
+    // LDS bank swizzle: the low bits of an entry's place are XORed with the bits
+    // above them, so that the first passes' writes, E entries apart, go to different
+    // banks and runs of entries stay permutations of themselves (a padded layout was
+    // measured with seven times the conflict cycles: it shifts the runs that one
+    // 16-byte access serves across the banks)
+    static constexpr int SH = E == 16 ? 4 : 3;
+    static constexpr int MK = sizeof(T) == 8 ? 7 : 15;
+    static constexpr int FS = M;                     // entries of one field buffer
+    static constexpr bool PP = (size_t)4 * FS * sizeof(cpx<T>) <= 128 * 1024;   // two buffers per field
+    // twiddle bases: in registers where a transform needs few, else staged in LDS
+    static constexpr bool TWREG = M <= 512;
+};
+
+// The pass of span NS (the product of the radices before it) of an M-point
+// Stockham transform: radix E while that fits, then what is left.
+template <int M, int NS>
+struct LinePass {
+    using Geo = LineGeo<double, M>;   // E, G and the plan do not depend on the type
+    static constexpr int E = Geo::E, G = Geo::G;
+    static constexpr int R = M / NS >= E ? E : M / NS;
+    static constexpr int NB = E / R;                   // butterflies per thread
+    static constexpr int LB = line_log2(R);            // twiddle bases per index
+    static constexpr int KI = NS > G ? NB : 1;         // distinct twiddle indices per thread
+    static constexpr int NK = NS < G ? NS : G;         // entries per base of the table
+    static constexpr bool LAST = NS * R == M;
+    // offsets of this pass's bases: per thread (registers) and in the LDS table
+    static constexpr int reg_off() {
+        if constexpr (NS == 1) return 0;
+        else return LinePass<M, NS / E>::reg_off() + (NS / E > 1 ? LinePass<M, NS / E>::LB : 0);
+    }
+    static constexpr int tab_off() {
+        if constexpr (NS == 1) return 0;
+        else return LinePass<M, NS / E>::tab_off() + (NS / E > 1 ? LinePass<M, NS / E>::LB * LinePass<M, NS / E>::NK : 0);
+    }
+    static constexpr int reg_all() {
+        if constexpr (LAST) return NS > 1 ? reg_off() + LB : 0;
+        else return LinePass<M, NS * R>::reg_all();
+    }
+    static constexpr int tab_all() {
+        if constexpr (LAST) return NS > 1 ? tab_off() + LB * NK : 0;
+        else return LinePass<M, NS * R>::tab_all();
+    }
 };
 
 // Threads of a workgroup that takes systems of n points (whole waves).
 __host__ __device__ constexpr int line_threads_for(int n) {
     return n / 2 >= 4096 ? 512 : n / 2 <= 256 ? 64 : n / 8;
 }
-// LDS bytes of the transform buffers of a system of n points.
-__host__ __device__ constexpr size_t line_lds_bytes(int n) {
-    return (size_t)(n / 2 >= 4096 ? 2 : 4) * (n / 2) * 16;
+// LDS bytes of the transform buffers of lines of half length M, and with the
+// twiddle table behind them (FP64; FP32 transforms round the entries they read).
+template <int M>
+__host__ __device__ constexpr size_t line_buf_bytes() {
+    using D = LineGeo<double, M>;
+    using F = LineGeo<float, M>;
+    constexpr size_t d = (size_t)(D::PP ? 4 : 2) * D::FS * 16, f = (size_t)(F::PP ? 4 : 2) * F::FS * 8;
+    return d > f ? d : f;
 }
+template <int M>
+__host__ __device__ constexpr size_t line_lds_of() {
+    return line_buf_bytes<M>() + (LineGeo<double, M>::TWREG ? 0 : (size_t)LinePass<M, 1>::tab_all() * 16);
+}
+// The largest over the sizes up to n (a batched launch holds any of them).
+__host__ __device__ constexpr size_t line_lds_bytes(int n) {
+    size_t b = 0;
+    const size_t all[7] = {line_lds_of<64>(),   line_lds_of<128>(),  line_lds_of<256>(), line_lds_of<512>(),
+                           line_lds_of<1024>(), line_lds_of<2048>(), line_lds_of<4096>()};
+    for (int i = 0; i < 7; ++i)
+        if ((128 << i) <= n && all[i] > b) b = all[i];
+    return b;
+}
+static_assert(line_lds_bytes(8192) <= 160 * 1024 - 2048, "LDS of a compute unit, less the static arrays");
 
 // ---- sums over a wave -------------------------------------------------------
 template <int CTRL>
@@ -91,6 +155,9 @@ __device__ __forceinline__ void line_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
 }
 
+template <typename T>
+__device__ __forceinline__ cpx<double> to_f64(cpx<T> v) { return C<double>((double)v.re, (double)v.im); }
+
 // Pair j of a real field (the caller's arrays: aligned to a double, not more).
 __device__ __forceinline__ cpx<double> ld2(const double* p, int j) { return C<double>(p[2 * j], p[2 * j + 1]); }
 __device__ __forceinline__ void st2(double* p, int j, cpx<double> v) {
@@ -101,39 +168,70 @@ __device__ __forceinline__ void st2(double* p, int j, cpx<double> v) {
 constexpr int LINE_RED = 64;   // doubles of reduction scratch: [0, 40) sums and maxima, [40, 56) p.Gp
 
 // One system's view of the workgroup: roles of the thread, exchange buffers.
+// Where one wave holds the system, lanes beyond its threads repeat the work of the
+// others (same values to the same places) and only stay out of the sums; larger
+// systems' extra waves skip the work and keep the barriers.
 template <typename T, int M>
 struct Line {
     using Geo = LineGeo<T, M>;
-    cpx<T>* buf;          // [buffer][field][M]
+    cpx<T>* buf;          // [buffer][field][FS], then the twiddle table
     double* red;
-    const cpx<T>* tw;     // twiddle tables of every size
+    const cpx<T>* tw;     // twiddle tables of every size (global)
+    int q;                // thread of the system
     int fld, t;           // field of this thread (0, 1) and its place in it
-    bool act;             // the thread belongs to the system
+    bool act;             // this wave works on the system
+    bool mine;            // this thread's values count in sums
     int cur;              // buffer of the exchange under way
+    static constexpr int NR = Geo::TWREG ? LinePass<M, 1>::reg_all() : 1;
+    cpx<T> twr[NR];       // twiddle bases of the passes after the first
 
+    // Stages the twiddle bases; the next block barrier publishes the LDS table (an
+    // FP32 line reads the one its FP64 line staged).
     __device__ __forceinline__ Line(void* lds, double* r, const cpx<T>* tables)
         : buf(reinterpret_cast<cpx<T>*>(lds)), red(r), tw(tables) {
         const int tid = threadIdx.x;
-        act = tid < Geo::TH;
-        fld = (tid / Geo::G) & 1;
-        t = tid & (Geo::G - 1);
+        q = tid & (Geo::TH - 1);
+        fld = q / Geo::G;
+        t = q & (Geo::G - 1);
+        mine = tid < Geo::TH;
+        act = Geo::ONE || __builtin_amdgcn_readfirstlane(tid) < Geo::TH;
         cur = 0;
+        fill<1>();
     }
-    // This thread's place in its field, and in the system, opaque to the compiler:
-    // the LDS addresses formed from them are recomputed where they are used (an
-    // operation or two each) instead of being hoisted out of the iteration into
-    // registers that the data needs.
+    __device__ __forceinline__ cpx<double>* table() const {
+        return reinterpret_cast<cpx<double>*>(reinterpret_cast<unsigned char*>(buf) + line_buf_bytes<M>());
+    }
+    template <int NS>
+    __device__ __forceinline__ void fill() {
+        using P = LinePass<M, NS>;
+        if constexpr (NS > 1) {
+            const cpx<T>* base = tw_size(tw, P::R * NS);   // W_{R NS}^{k 2^b}
+            if constexpr (Geo::TWREG) {
+#pragma unroll
+                for (int b = 0; b < P::LB; ++b) twr[P::reg_off() + b] = base[(t & (NS - 1)) << b];
+            } else if (act && sizeof(T) == 8) {
+                for (int i = q; i < P::LB * P::NK; i += Geo::TH)
+                    table()[P::tab_off() + i] = to_f64(base[(i & (P::NK - 1)) << (i / P::NK)]);
+            }
+        }
+        if constexpr (!P::LAST) fill<NS * P::R>();
+    }
+    // This thread's place in its field, opaque to the compiler: tables in global
+    // memory indexed by it are read where they are used instead of being hoisted out
+    // of the iteration into registers that the data needs.
     __device__ __forceinline__ int place() const {
         int x = t;
         asm volatile("" : "+v"(x));
         return x;
     }
-    static __device__ __forceinline__ int thread() {
-        int x = threadIdx.x;
+    __device__ __forceinline__ int thread() const {
+        int x = q;
         asm volatile("" : "+v"(x));
         return x;
     }
-    __device__ __forceinline__ cpx<T>* field(int f) const { return buf + (Geo::PP ? cur * 2 * M : 0) + f * M; }
+    __device__ __forceinline__ cpx<T>* field(int f) const {
+        return buf + (Geo::PP ? cur * 2 * Geo::FS : 0) + f * Geo::FS;
+    }
     __device__ __forceinline__ void sync_all() const {
         if (Geo::ONE) line_wave_sync(); else block_lds_barrier();
     }
@@ -153,13 +251,15 @@ struct Line {
     __device__ __forceinline__ void crossed() const {
         if (Geo::WFLD && !Geo::ONE) block_lds_barrier();
     }
-    // Bank swizzle of every buffer: the writes of the first pass go at strides of
-    // E entries; XORed with the bits above, neighbouring threads hit other banks
-    // (16-byte entries are served eight lanes at a time, 8-byte ones sixteen).
-    static __device__ __forceinline__ int sw(int i) {
-        constexpr int SH = Geo::E == 16 ? 4 : 3;
-        constexpr int MK = sizeof(T) == 8 ? 7 : 15;
-        return i ^ ((i >> SH) & MK);
+    // Place of entry i.  The map is linear over XOR, so entry i + d with d's bits
+    // outside i's is at el(b, at(i), d): one XOR where d reaches the low bits, and a
+    // constant offset.
+    static __device__ __forceinline__ constexpr int at(int i) { return i ^ ((i >> Geo::SH) & Geo::MK); }
+    static __device__ __forceinline__ cpx<T>& el(cpx<T>* b, int ai, int d) {
+        return b[(ai ^ (at(d) & Geo::MK)) + (d & ~Geo::MK)];
+    }
+    static __device__ __forceinline__ const cpx<T>& el(const cpx<T>* b, int ai, int d) {
+        return b[(ai ^ (at(d) & Geo::MK)) + (d & ~Geo::MK)];
     }
 };
 
@@ -200,75 +300,72 @@ __device__ __forceinline__ void line_dft(cpx<T> (&v)[R], bool inverse) {
     }
 }
 
-constexpr int line_log2(int x) { return x <= 1 ? 0 : 1 + line_log2(x / 2); }
+// W_8^i (E = 8) and W_4^i (E = 4), i < 4: the twiddle index of a thread's i-th
+// butterfly in a last pass of a smaller radix is its first's plus i G, G / M = 1 / E.
+template <typename T, int E>
+__device__ __forceinline__ cpx<T> line_wE(int i) {
+    const T h = (T)0.70710678118654752440;
+    if (E == 4) return i == 0 ? C<T>(1, 0) : C<T>(0, -1);   // i < 2
+    return i == 0 ? C<T>(1, 0) : i == 1 ? C<T>(h, -h) : i == 2 ? C<T>(0, -1) : C<T>(-h, -h);
+}
 
-// The pass of span NS (the product of the radices before it) of an M-point
-// Stockham transform: radix E while that fits, then what is left.
+// Twiddle bases of the pass: W_{R NS}^{k 2^b}, k the thread's (first) index; the
+// other powers by products (no table of all powers; three roundings at most).
 template <typename T, int M, int NS>
-struct LinePass {
-    using Geo = LineGeo<T, M>;
-    static constexpr int E = Geo::E, G = Geo::G;
-    static constexpr int R = M / NS >= E ? E : M / NS;
-    static constexpr int NB = E / R;                   // butterflies per thread
-    static constexpr int LB = line_log2(R);
-    static constexpr bool LAST = NS * R == M;
-    static constexpr int KI = NS > G ? NB : 1;         // distinct twiddle indices per thread
-    static constexpr int NTW = NS > 1 ? KI * LB : 1;
-};
-
-// Twiddle bases of the pass: W_{R NS}^{k 2^b}, the other powers by products (no
-// table of all powers in LDS or registers; three roundings at most per value).
-template <typename T, int M, int NS>
-__device__ __forceinline__ void line_tw(const Line<T, M>& L, cpx<T> (&a)[LinePass<T, M, NS>::NTW]) {
-    using P = LinePass<T, M, NS>;
-    if constexpr (NS > 1) {
-        const cpx<T>* base = tw_size(L.tw, P::R * NS);
-        const int t = L.place();
+__device__ __forceinline__ void line_tw(const Line<T, M>& L, cpx<T> (&a)[LinePass<M, NS>::LB]) {
+    using P = LinePass<M, NS>;
+    if constexpr (LineGeo<T, M>::TWREG) {
 #pragma unroll
-        for (int i = 0; i < P::KI; ++i) {
-            const int k = (t + i * P::G) & (NS - 1);
+        for (int b = 0; b < P::LB; ++b) a[b] = L.twr[P::reg_off() + b];
+    } else {
+        const cpx<double>* tb = L.table() + P::tab_off() + (L.t & (P::NK - 1));
 #pragma unroll
-            for (int b = 0; b < P::LB; ++b) a[i * P::LB + b] = base[k << b];
-        }
+        for (int b = 0; b < P::LB; ++b) a[b] = C<T>((T)tb[b * P::NK].re, (T)tb[b * P::NK].im);
     }
 }
 
 // Natural-layout entries of a field from and to its buffer.
 template <typename T, int M>
 __device__ __forceinline__ void line_load(const Line<T, M>& L, const cpx<T>* b, cpx<T> (&v)[LineGeo<T, M>::E]) {
-    const int t = L.place();
+    const int ai = L.at(L.t);
 #pragma unroll
-    for (int s = 0; s < LineGeo<T, M>::E; ++s) v[s] = b[L.sw(t + s * LineGeo<T, M>::G)];
+    for (int s = 0; s < LineGeo<T, M>::E; ++s) v[s] = L.el(b, ai, s * LineGeo<T, M>::G);
 }
 template <typename T, int M>
 __device__ __forceinline__ void line_store(const Line<T, M>& L, cpx<T>* b, const cpx<T> (&v)[LineGeo<T, M>::E]) {
-    const int t = L.place();
+    const int ai = L.at(L.t);
 #pragma unroll
-    for (int s = 0; s < LineGeo<T, M>::E; ++s) b[L.sw(t + s * LineGeo<T, M>::G)] = v[s];
+    for (int s = 0; s < LineGeo<T, M>::E; ++s) L.el(b, ai, s * LineGeo<T, M>::G) = v[s];
 }
 
 // Field transform, natural layout in and out (unnormalised), from the pass of
-// span NS on; `a` holds that pass's twiddle bases.  Waves that hold no system only
-// take part in the barriers.
+// span NS on; `a` holds that pass's twiddle bases.
 template <typename T, int M, bool INV, int NS = 1>
 __device__ __forceinline__ void line_fft(Line<T, M>& L, cpx<T> (&v)[LineGeo<T, M>::E],
-                                         const cpx<T> (&a)[LinePass<T, M, NS>::NTW]) {
-    using P = LinePass<T, M, NS>;
+                                         const cpx<T> (&a)[LinePass<M, NS>::LB]) {
+    using P = LinePass<M, NS>;
     if (L.act) {
 #pragma unroll
         for (int i = 0; i < P::NB; ++i) {
             cpx<T> w[P::R];
+            cpx<T> f[P::LB];
+            if constexpr (NS > 1) {
+#pragma unroll
+                for (int b = 0; b < P::LB; ++b) {
+                    // the i-th index is the first plus i G: W_{R NS}^{i G 2^b} = W_E^{i 2^b}
+                    f[b] = a[b];
+                    if (P::KI > 1 && i > 0 && b == 0) f[b] = a[b] * line_wE<T, P::E>(i);
+                    if (P::KI > 1 && i > 0 && b == 1) f[b] = a[b] * line_wE<T, P::E>(2 * i);
+                    if (INV) f[b] = cj(f[b]);
+                }
+            }
 #pragma unroll
             for (int r = 0; r < P::R; ++r) {
                 w[r] = v[i + r * P::NB];
                 if constexpr (NS > 1) {
 #pragma unroll
-                    for (int b = 0; b < P::LB; ++b) {
-                        if (r & (1 << b)) {
-                            const cpx<T> f = a[(P::KI > 1 ? i : 0) * P::LB + b];
-                            w[r] = w[r] * (INV ? cj(f) : f);
-                        }
-                    }
+                    for (int b = 0; b < P::LB; ++b)
+                        if (r & (1 << b)) w[r] = w[r] * f[b];
                 }
             }
             line_dft<T, P::R>(w, INV);
@@ -277,29 +374,28 @@ __device__ __forceinline__ void line_fft(Line<T, M>& L, cpx<T> (&v)[LineGeo<T, M
         }
     }
     if constexpr (!P::LAST) {
+        static_assert(P::NB == 1, "passes before the last take radix E");
         constexpr int NS2 = NS * P::R;
-        cpx<T> a2[LinePass<T, M, NS2>::NTW];
+        cpx<T> a2[LinePass<M, NS2>::LB];
         L.turn_fld();
         cpx<T>* b = L.field(L.fld);
         if (L.act) {
-            line_tw<T, M, NS2>(L, a2);   // in flight across the exchange
-            const int t = L.place();
+            const int k = L.t & (NS - 1);
+            const int ai = L.at((L.t - k) * P::R + k);
 #pragma unroll
-            for (int i = 0; i < P::NB; ++i) {
-                const int j = t + i * P::G, k = j & (NS - 1);
-                const int o = (j - k) * P::R + k;
-#pragma unroll
-                for (int q = 0; q < P::R; ++q) b[Line<T, M>::sw(o + q * NS)] = v[i + q * P::NB];
-            }
+            for (int r = 0; r < P::R; ++r) L.el(b, ai, r * NS) = v[r];
         }
         L.sync_fld();
-        if (L.act) line_load<T, M>(L, b, v);
+        if (L.act) {
+            line_tw<T, M, NS2>(L, a2);
+            line_load<T, M>(L, b, v);
+        }
         line_fft<T, M, INV, NS2>(L, v, a2);
     }
 }
 template <typename T, int M, bool INV>
 __device__ __forceinline__ void line_transform(Line<T, M>& L, cpx<T> (&v)[LineGeo<T, M>::E]) {
-    const cpx<T> none[1] = {};
+    const cpx<T> none[LinePass<M, 1>::LB] = {};
     line_fft<T, M, INV, 1>(L, v, none);
 }
 
@@ -311,13 +407,13 @@ struct LinePairs {
     using Geo = LineGeo<T, M>;
     static constexpr int NP = Geo::NP;
     T tp;                 // 2 pi / L
-    static constexpr bool HELD = NP <= 2;
+    static constexpr bool HELD = NP <= 2;   // else read where used
     const cpx<T>* t2;
     cpx<T> wh[HELD ? NP : 1];   // W_N^tau
     __device__ __forceinline__ LinePairs(const Line<T, M>& L, T tp_) : tp(tp_), t2(tw_size(L.tw, 2 * M)) {
         if constexpr (HELD) {
 #pragma unroll
-            for (int e = 0; e < NP; ++e) wh[e] = t2[tau(threadIdx.x, e) & (2 * M - 1)];
+            for (int e = 0; e < NP; ++e) wh[e] = t2[tau(L.q, e)];
         }
     }
     __device__ __forceinline__ cpx<T> w(int q, int e) const {
@@ -429,7 +525,7 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
     L.turn_all();
     if (L.act) {
         cpx<T>*fa = L.field(0), *fb = L.field(1);
-        const int q = L.thread();
+        const int q = K.HELD ? L.q : L.thread();
 #pragma unroll
         for (int e = 0; e < NP; ++e) {
             const bool z = K.tau(q, e) == 0;
@@ -437,7 +533,7 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
             cpx<T> z0, z1, y0, y1;
             pair_c2r(p0, p1, K.w(q, e), z, z0, z1);
             pair_c2r(ik(K.k0(q, e), p0), ik(K.k1(q, e), p1), K.w(q, e), z, y0, y1);
-            const int i0 = L.sw(K.tau(q, e)), i1 = L.sw(K.other(q, e));
+            const int i0 = L.at(K.tau(q, e)), i1 = L.at(K.other(q, e));
             fa[i0] = z0;
             fa[i1] = z1;
             fb[i0] = y0;
@@ -458,21 +554,37 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
     double acc = 0.0;
     if (L.act) {
         const cpx<T>* b = L.field(L.fld ^ 1);
-        const int t = L.place();
+        const int ai = L.at(L.t);
+        const int t = Coef::MEM ? L.place() : L.t;
+        // coefficients from memory: two slots in use, the next two in flight
+        constexpr int CH = Coef::MEM ? 2 : 4;
+        cpx<T> co[2][CH], cx[2][CH];
+        auto fetch = [&](int s0, int k) {
 #pragma unroll
-        for (int s = 0; s < E; ++s) {
-            // coefficients from memory come a few slots at a time, in registers the
-            // rest of the transform does not need
-            if (Coef::MEM && s % 4 == 0) __builtin_amdgcn_sched_barrier(0);
-            const int j = t + s * G;
-            const cpx<T> y = b[L.sw(j)], co = coef.own(s, j), cx = coef.cross(s, j);
-            const cpx<T> a = C<T>(co.re * v[s].re + cx.re * y.re, co.im * v[s].im + cx.im * y.im);
-            acc += (double)v[s].re * (double)a.re + (double)v[s].im * (double)a.im;
-            v[s] = a;
+            for (int i = 0; i < CH; ++i) {
+                co[k][i] = coef.own(s0 + i, t + (s0 + i) * G);
+                cx[k][i] = coef.cross(s0 + i, t + (s0 + i) * G);
+            }
+        };
+        fetch(0, 0);
+#pragma unroll
+        for (int s0 = 0; s0 < E; s0 += CH) {
+            const int k = (s0 / CH) & 1;
+            if (Coef::MEM) __builtin_amdgcn_sched_barrier(0);
+            if (s0 + CH < E) fetch(s0 + CH, k ^ 1);
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                const int s = s0 + i;
+                const cpx<T> y = L.el(b, ai, s * G);
+                const cpx<T> a = C<T>(co[k][i].re * v[s].re + cx[k][i].re * y.re,
+                                      co[k][i].im * v[s].im + cx[k][i].im * y.im);
+                acc += (double)v[s].re * (double)a.re + (double)v[s].im * (double)a.im;
+                v[s] = a;
+            }
         }
     }
     L.crossed();
-    acc = wave_sum(acc);
+    acc = wave_sum(L.mine ? acc : 0.0);
     if (!Geo::ONE && L.act && (threadIdx.x & 63) == 0) L.red[40 + (threadIdx.x >> 6)] = acc;
     line_transform<T, M, false>(L, v);
     L.turn_all();
@@ -490,11 +602,11 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
     }
     if (L.act) {
         const cpx<T>*fa = L.field(0), *fb = L.field(1);
-        const int q = L.thread();
+        const int q = K.HELD ? L.q : L.thread();
 #pragma unroll
         for (int e = 0; e < NP; ++e) {
             const bool z = K.tau(q, e) == 0;
-            const int i0 = L.sw(K.tau(q, e)), i1 = L.sw(K.other(q, e));
+            const int i0 = L.at(K.tau(q, e)), i1 = L.at(K.other(q, e));
             cpx<T> a0, a1, w0, w1;
             pair_r2c(fa[i0], fa[i1], K.w(q, e), z, a0, a1);
             pair_r2c(fb[i0], fb[i1], K.w(q, e), z, w0, w1);
@@ -563,11 +675,11 @@ __device__ __forceinline__ void line_to_pairs(Line<T, M>& L, const LinePairs<T, 
     L.sync_all();
     if (L.act) {
         const cpx<T>*fa = L.field(0), *fb = L.field(1);
-        const int q = L.thread();
+        const int q = K.HELD ? L.q : L.thread();
 #pragma unroll
         for (int e = 0; e < Geo::NP; ++e) {
             const bool z = K.tau(q, e) == 0;
-            const int i0 = L.sw(K.tau(q, e)), i1 = L.sw(K.other(q, e));
+            const int i0 = L.at(K.tau(q, e)), i1 = L.at(K.other(q, e));
             cpx<T> x0, x1, y0, y1;
             pair_r2c(fa[i0], fa[i1], K.w(q, e), z, x0, x1);
             pair_r2c(fb[i0], fb[i1], K.w(q, e), z, y0, y1);
@@ -578,7 +690,7 @@ __device__ __forceinline__ void line_to_pairs(Line<T, M>& L, const LinePairs<T, 
 
 // PCG of section 3.2 on G d = r in precision T from d = 0, preconditioned by the
 // diagonal A^{-1} (Def:A in 1D: factors z0, z1 per pair).  r is consumed; x
-// accumulates d: add(e, alpha p0, alpha p1).  Stops when r.r <= tol2 bbref or
+// accumulates d: add(alpha, p).  Stops when r.r <= tol2 bbref or
 // after max_iter iterations; returns the iterations, rr the last r.r.
 template <typename T, int M, typename Coef, typename Add>
 __device__ __forceinline__ int line_pcg(Line<T, M>& L, const LinePairs<T, M>& K, cpx<T> (&r)[LineGeo<T, M>::NP][2],
@@ -589,7 +701,7 @@ __device__ __forceinline__ int line_pcg(Line<T, M>& L, const LinePairs<T, M>& K,
     const double dinvN = 1.0 / (double)Geo::N;
     cpx<T> p[NP][2];
     T z0[NP], z1[NP];
-    const int q = threadIdx.x;
+    const int q = L.q;
 #pragma unroll
     for (int e = 0; e < NP; ++e) {
         const T a = K.k0(q, e), b = K.k1(q, e);
@@ -599,7 +711,7 @@ __device__ __forceinline__ int line_pcg(Line<T, M>& L, const LinePairs<T, M>& K,
     }
     auto dots = [&](double& rz, double& r2) {
         double s0 = 0.0, s1 = 0.0;
-        if (L.act) {
+        if (L.mine) {
 #pragma unroll
             for (int e = 0; e < NP; ++e) {
                 const double q0 = K.w0(q, e) * ((double)r[e][0].re * (double)r[e][0].re + (double)r[e][0].im * (double)r[e][0].im);
@@ -627,16 +739,12 @@ __device__ __forceinline__ int line_pcg(Line<T, M>& L, const LinePairs<T, M>& K,
         }
         double pq;
         T alpha = (T)0;
-        bool have = false;
         line_apply<T, M>(L, K, p, coef, pq, [&](int e, cpx<T> q0, cpx<T> q1) {
-            if (!have) {
-                alpha = (T)(rz / pq);
-                have = true;
-            }
-            add(e, alpha * p[e][0], alpha * p[e][1]);
+            if (e == 0) alpha = (T)(rz / pq);
             r[e][0] = r[e][0] - alpha * q0;
             r[e][1] = r[e][1] - alpha * q1;
         });
+        if (L.act) add(alpha, p);
         rho_prev = rz;
         dots(rz, rr);
         ++it;
@@ -685,7 +793,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
             }
         }
     }
-    line_max<double, M, 5>(L, ex);
+    line_max<double, M, 5>(L, ex);   // (its barriers publish the twiddle table)
     const double emin = -ex[0];
     if (ex[4] != 0.0 || !(emin > 0.0)) {
         out.status = -2;
@@ -730,7 +838,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
             bh[K.other(q, e)] = b1;
         }
     });
-    bb *= 1.0 / (double)N;
+    bb = L.mine ? bb * (1.0 / (double)N) : 0.0;
     line_sum2(L, bb, dum);
     const double tol2 = prm.tol * prm.tol;
     const bool from_u = guess && bb > 0.0;
@@ -769,14 +877,26 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
                 L.sync_all();
             }
             out.iters = line_pcg<double, M>(L, K, r, coef, sig, alp, tol2, bb, prm.max_iter, rr,
-                                            [&](int e, cpx<double> d0, cpx<double> d1) {
+                                            [&](double alpha, const cpx<double> (&p)[NP][2]) {
                 if constexpr (XREG) {
-                    x[e][0] = x[e][0] + d0;
-                    x[e][1] = x[e][1] + d1;
-                } else {
+#pragma unroll
+                    for (int e = 0; e < NP; ++e) {
+                        x[e][0] = x[e][0] + alpha * p[e][0];
+                        x[e][1] = x[e][1] + alpha * p[e][1];
+                    }
+                } else {   // every load ahead of the first store
                     const int q = L.thread();
-                    xh[K.tau(q, e)] = xh[K.tau(q, e)] + d0;
-                    xh[K.other(q, e)] = xh[K.other(q, e)] + d1;
+                    cpx<double> y[NP][2];
+#pragma unroll
+                    for (int e = 0; e < NP; ++e) {
+                        y[e][0] = xh[K.tau(q, e)];
+                        y[e][1] = xh[K.other(q, e)];
+                    }
+#pragma unroll
+                    for (int e = 0; e < NP; ++e) {
+                        xh[K.tau(q, e)] = y[e][0] + alpha * p[e][0];
+                        xh[K.other(q, e)] = y[e][1] + alpha * p[e][1];
+                    }
                 }
             });
         };
@@ -807,7 +927,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
                 r[e][1] = bh[K.other(q, e)] - q1;
             });
             double s = 0.0, d = 0.0;
-            if (L.act) {
+            if (L.mine) {
                 const int q = L.thread();
 #pragma unroll
                 for (int e = 0; e < NP; ++e)
@@ -855,9 +975,12 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
             }
             const LineCoefReg<float, M> coef32(F, own32, own32 + M);
             out.iters += line_pcg<float, M>(F, KF, r32, coef32, (float)sig, (float)alp, t2, rr, prm.max_iter, irr,
-                                            [&](int e, cpx<float> d0, cpx<float> d1) {
-                d32[e][0] = d32[e][0] + d0;
-                d32[e][1] = d32[e][1] + d1;
+                                            [&](float alpha, const cpx<float> (&p)[NP][2]) {
+#pragma unroll
+                for (int e = 0; e < NP; ++e) {
+                    d32[e][0] = d32[e][0] + alpha * p[e][0];
+                    d32[e][1] = d32[e][1] + alpha * p[e][1];
+                }
             });
             if (L.act) {
                 const int q = L.thread();
@@ -894,7 +1017,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
                 y0 = xh[K.tau(q, e)];
                 y1 = xh[K.other(q, e)];
             }
-            const int i0 = L.sw(K.tau(q, e)), i1 = L.sw(K.other(q, e));
+            const int i0 = L.at(K.tau(q, e)), i1 = L.at(K.other(q, e));
             cpx<double> q0, q1;
             pair_c2r(invN * y0, invN * y1, K.w(q, e), K.tau(q, e) == 0, q0, q1);
             fa[i0] = q0;
@@ -935,7 +1058,7 @@ __device__ __forceinline__ void line_derivative(Line<double, M>& L, cpx<double> 
 #pragma unroll
         for (int s = 0; s < E; ++s) {
             const int k = L.t + s * G;
-            const cpx<double> zm = b[L.sw((M - k) & (M - 1))], w = t2[k];
+            const cpx<double> zm = b[L.at((M - k) & (M - 1))], w = t2[k];
             const cpx<double> S = sc * (v[s] + cj(zm)), Q = mul_i(w * (sc * (v[s] - cj(zm))));
             const cpx<double> xk = S - Q, xm = S + Q;   // X_k and X*_{M-k}, over N
             const double kk = tp * (double)k, km = tp * (double)(M - k);
@@ -1011,8 +1134,8 @@ __device__ __forceinline__ void line_rhs(double L_, const double* __restrict__ e
         cpx<double>*fa = L.field(0), *fb = L.field(1);
 #pragma unroll
         for (int s = 0; s < E; ++s) {
-            fb[L.sw(L.t + s * G)] = d[s];
-            fa[L.sw(L.t + s * G)] = T[s];
+            L.el(fb, L.at(L.t), s * G) = d[s];
+            L.el(fa, L.at(L.t), s * G) = T[s];
         }
     }
     L.sync_all();
@@ -1022,8 +1145,8 @@ __device__ __forceinline__ void line_rhs(double L_, const double* __restrict__ e
         for (int s = 0; s < E; ++s) {
             const int j = L.t + s * G;
             if (!L.fld) {
-                v[s] = d[s] + fb[L.sw(j)];
-                T[s] = T[s] + fa[L.sw(j)];
+                v[s] = d[s] + L.el(fb, L.at(L.t), s * G);
+                T[s] = T[s] + L.el(fa, L.at(L.t), s * G);
             } else {
                 v[s] = ld2(eta, j);
             }
@@ -1038,7 +1161,7 @@ __device__ __forceinline__ void line_rhs(double L_, const double* __restrict__ e
         for (int s = 0; s < E; ++s) {
             const int j = L.t + s * G;
             const cpx<double> ee = ld2(eta, j), hh = ld2(hx, j);
-            fb[L.sw(j)] = C<double>(-ee.re * (v[s].re - hh.re), -ee.im * (v[s].im - hh.im));
+            L.el(fb, L.at(L.t), s * G) = C<double>(-ee.re * (v[s].re - hh.re), -ee.im * (v[s].im - hh.im));
         }
     }
     L.sync_all();
@@ -1047,7 +1170,7 @@ __device__ __forceinline__ void line_rhs(double L_, const double* __restrict__ e
 #pragma unroll
         for (int s = 0; s < E; ++s) {
             const int j = L.t + s * G;
-            const cpx<double> hh = ld2(hx, j), gr = fb[L.sw(j)];
+            const cpx<double> hh = ld2(hx, j), gr = L.el(fb, L.at(L.t), s * G);
             st2(U_t, j, C<double>(v[s].re + (gr.re - hh.re * T[s].re), v[s].im + (gr.im - hh.im * T[s].im)));
         }
     }
@@ -1107,7 +1230,7 @@ __device__ __forceinline__ void line_momentum(double L_, const double* eta, cons
         const int q = L.thread();
 #pragma unroll
         for (int e = 0; e < NP; ++e) {
-            const int i0 = L.sw(K.tau(q, e)), i1 = L.sw(K.other(q, e));
+            const int i0 = L.at(K.tau(q, e)), i1 = L.at(K.other(q, e));
             cpx<double> q0, q1;
             pair_c2r(invN * g[e][0], invN * g[e][1], K.w(q, e), K.tau(q, e) == 0, q0, q1);
             fa[i0] = fb[i0] = q0;

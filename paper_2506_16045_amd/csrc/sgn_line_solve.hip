@@ -4,16 +4,13 @@
 namespace sgn {
 
 hipError_t launch_batch_solve_kernel(int mode, int n, int grid, int cus, hipStream_t stream, const BatchItem* items,
-                                     int nitems, const double* eta, const double* hx, const double* b, double* u,
-                                     double* ws, const cpx<double>* tw64, const cpx<float>* tw32,
-                                     const BatchParams& prm, BatchResult* res, int* queue) {
+                                     int nitems, const SolveShared* shared, BatchResult* res, int* queue) {
     const int nt = batch_threads_for(n);
     const size_t lds = batch_lds_bytes(n);
     auto launch = [&](auto k) -> hipError_t {
         const hipError_t e = batch_grid(k, nt, lds, cus, nitems, grid);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k, dim3(grid), dim3(nt), lds, stream, items, nitems, eta, hx, b, u, ws, tw64, tw32, prm,
-                           res, queue);
+        hipLaunchKernelGGL(k, dim3(grid), dim3(nt), lds, stream, items, nitems, shared, res, queue);
         return hipGetLastError();
     };
     return mode == BATCH_MIXED ? launch(k_batch_solve<BATCH_MIXED>) : launch(k_batch_solve<BATCH_FP64>);

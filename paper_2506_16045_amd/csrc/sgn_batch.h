@@ -971,6 +971,24 @@ struct LineEngine {
     }
 };
 
+// Pointwise passes of a run: f(at, n) takes up to four points at a time, at[0..n),
+// the others repeating a valid one, so that their loads are all in flight before
+// the first store (one point at a time, each waited for its own).
+template <typename Eng, typename F>
+__device__ __forceinline__ void step_each(int N, F&& f) {
+    const int nt = Eng::threads();
+    for (int i = threadIdx.x; i < N; i += 4 * nt) {
+        int at[4], n = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool in = i + k * nt < N;
+            at[k] = in ? i + k * nt : i;
+            n += in ? 1 : 0;
+        }
+        f(at, n);
+    }
+}
+
 // G_{eta,h} u = U for stepper slot `slot`, u holding the base velocity on entry.
 // With extrapolation the solve starts from base + o_1 (one recorded offset) or
 // base + (2 o_1 - o_2) (two), and records u - base afterwards.  0, -2 or -3.
@@ -986,20 +1004,23 @@ __device__ __forceinline__ int step_solve(const StepItem& it, StepResult& out, i
     if (extrapolate) {
         const double* o1 = gl(it.off[slot][head]);
         const double* o2 = gl(it.off[slot][head ^ 1]);
-        for (int i = threadIdx.x; i < N; i += Eng::threads()) {
-            const double b = u[i];
-            gl(it.base)[i] = b;
-            if (cnt == 1) {
-                double s = 0.0;
-                s += 1.0 * o1[i];
-                u[i] = b + 1.0 * s;
-            } else if (cnt >= 2) {
-                double s = 0.0;
-                s += 2.0 * o1[i];
-                s += -1.0 * o2[i];
-                u[i] = b + 1.0 * s;
+        double* base = gl(it.base);
+        step_each<Eng>(N, [&](const int (&at)[4], int n) {
+            double b[4], p[4], q[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                b[k] = u[at[k]];
+                if (cnt >= 1) p[k] = o1[at[k]];
+                if (cnt >= 2) q[k] = o2[at[k]];
             }
-        }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < n) {
+                base[at[k]] = b[k];
+                if (cnt == 1) u[at[k]] = b[k] + p[k];
+                if (cnt >= 2) u[at[k]] = b[k] + (2.0 * p[k] - q[k]);
+            }
+        });
         Eng::sync();
     }
     const BatchResult r = Eng::solve(it, eta, U, u, tw64, tw32, prm, lds, red);
@@ -1012,11 +1033,18 @@ __device__ __forceinline__ int step_solve(const StepItem& it, StepResult& out, i
     if (!r.converged) return -3;
     if (extrapolate) {
         double* o = gl(it.off[slot][nh]);
-        for (int i = threadIdx.x; i < N; i += Eng::threads()) {
-            double s = 0.0;
-            s += -1.0 * gl(it.base)[i];
-            o[i] = u[i] + 1.0 * s;
-        }
+        const double* base = gl(it.base);
+        step_each<Eng>(N, [&](const int (&at)[4], int n) {
+            double b[4], v[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                b[k] = base[at[k]];
+                v[k] = u[at[k]];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < n) o[at[k]] = v[k] - b[k];
+        });
         Eng::sync();
         head = nh;
         if (cnt < 2) cnt += 1;
@@ -1059,25 +1087,51 @@ __device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapola
         for (int k = 0; k <= 4; ++k) {
             if (k > 0) {
                 const bool last = k == 4;
-                for (int i = threadIdx.x; i < N; i += Eng::threads()) {
-                    if (!last) {
-                        double s = 0.0;
-                        s += a[k - 1] * gl(it.fe[k - 1])[i];
-                        gl(it.eta_s)[i] = gl(it.eta)[i] + dt * s;
-                        double q = 0.0;
-                        q += a[k - 1] * gl(it.fU[k - 1])[i];
-                        gl(it.U_s)[i] = gl(it.U)[i] + dt * q;
-                    } else {
-                        double s = 0.0, q = 0.0;
+                if (!last) {
+                    const double *e0 = gl(it.eta), *U0 = gl(it.U), *f = gl(it.fe[k - 1]), *g = gl(it.fU[k - 1]);
+                    double *e1 = gl(it.eta_s), *U1 = gl(it.U_s);
+                    const double ak = a[k - 1];
+                    step_each<Eng>(N, [&](const int (&at)[4], int n) {
+                        double e[4], U[4], fe[4], fU[4];
 #pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            s += w[j] * gl(it.fe[j])[i];
-                            q += w[j] * gl(it.fU[j])[i];
+                        for (int q = 0; q < 4; ++q) {
+                            e[q] = e0[at[q]];
+                            U[q] = U0[at[q]];
+                            fe[q] = f[at[q]];
+                            fU[q] = g[at[q]];
                         }
-                        gl(it.eta)[i] = gl(it.eta)[i] + dt * s;
-                        gl(it.U)[i] = gl(it.U)[i] + dt * q;
-                        gl(it.u)[i] = gl(it.u_s)[i];
-                    }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (q < n) {
+                            e1[at[q]] = e[q] + dt * (ak * fe[q]);
+                            U1[at[q]] = U[q] + dt * (ak * fU[q]);
+                        }
+                    });
+                } else {
+                    double *e0 = gl(it.eta), *U0 = gl(it.U), *u0 = gl(it.u);
+                    const double* us = gl(it.u_s);
+                    step_each<Eng>(N, [&](const int (&at)[4], int n) {
+                        double e[4], U[4], v[4], s[4], z[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            e[q] = e0[at[q]];
+                            U[q] = U0[at[q]];
+                            v[q] = us[at[q]];
+                            s[q] = z[q] = 0.0;
+#pragma unroll
+                            for (int j = 0; j < 4; ++j) {
+                                s[q] += w[j] * gl(it.fe[j])[at[q]];
+                                z[q] += w[j] * gl(it.fU[j])[at[q]];
+                            }
+                        }
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (q < n) {
+                            e0[at[q]] = e[q] + dt * s[q];
+                            U0[at[q]] = U[q] + dt * z[q];
+                            u0[at[q]] = v[q];
+                        }
+                    });
                 }
                 Eng::sync();
                 const int rc = step_solve<Eng>(it, out, k - 1, extrapolate, gl(last ? it.eta : it.eta_s),
@@ -1092,7 +1146,16 @@ __device__ __forceinline__ StepResult rk4_run(const StepItem& it, bool extrapola
                 Eng::rhs(it, gl(k ? it.eta_s : it.eta), gl(k ? it.u_s : it.u), gl(it.fe[k]), gl(it.fU[k]), tw64, lds, red);
                 Eng::sync();
                 if (k == 0) {
-                    for (int i = threadIdx.x; i < N; i += Eng::threads()) gl(it.u_s)[i] = gl(it.u)[i];
+                    const double* u0 = gl(it.u);
+                    double* us = gl(it.u_s);
+                    step_each<Eng>(N, [&](const int (&at)[4], int n) {
+                        double v[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) v[q] = u0[at[q]];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            if (q < n) us[at[q]] = v[q];
+                    });
                     Eng::sync();
                 }
             }

@@ -36,9 +36,13 @@ constexpr int line_log2(int x) { return x <= 1 ? 0 : 1 + line_log2(x / 2); }
 template <typename T, int M_>
 struct LineGeo {
     static constexpr int M = M_, N = 2 * M_;
-    // complex entries per thread of a field: the most that leave no lane of a wave
-    // idle on the short lines, and two exchanges on the longest
-    static constexpr int E = M >= 4096 ? 16 : M >= 256 ? 8 : 4;
+    // complex entries per thread of a field: four, which spreads a line over the most
+    // waves, while that takes at most 512 threads (FP64 solve per iteration at
+    // n = 512: 3.8 us with eight entries in one wave, 3.0 with four in two; n = 1024:
+    // 5.5 -> 4.4; n = 2048: 7.6 -> 6.0); then what 512 threads hold (workgroups of
+    // 1024 leave 128 registers a thread, and the spills cost more than the waves
+    // give: n = 4096 10.5 -> 15.2 us, n = 8192 20 -> 28)
+    static constexpr int E = M >= 4096 ? 16 : M >= 2048 ? 8 : 4;
     static constexpr int G = M / E;                  // threads of one field
     static constexpr int TH = 2 * G;                 // threads of a system
     static constexpr bool ONE = TH <= 64;            // one wave holds the system
@@ -54,6 +58,8 @@ struct LineGeo {
     static constexpr int MK = sizeof(T) == 8 ? 7 : 15;
     static constexpr int FS = M;                     // entries of one field buffer
     static constexpr bool PP = (size_t)4 * FS * sizeof(cpx<T>) <= 128 * 1024;   // two buffers per field
+    // FP64 coefficients and x in registers (the longest line reads them from memory)
+    static constexpr bool CREG = M < 4096;
     // twiddle bases: in registers where a transform needs few, else staged in LDS
     static constexpr bool TWREG = M <= 512;
 };
@@ -91,7 +97,13 @@ struct LinePass {
 
 // Threads of a workgroup that takes systems of n points (whole waves).
 __host__ __device__ constexpr int line_threads_for(int n) {
-    return n / 2 >= 4096 ? 512 : n / 2 <= 256 ? 64 : n / 8;
+    const int th[7] = {LineGeo<double, 64>::TH,   LineGeo<double, 128>::TH,  LineGeo<double, 256>::TH,
+                       LineGeo<double, 512>::TH,  LineGeo<double, 1024>::TH, LineGeo<double, 2048>::TH,
+                       LineGeo<double, 4096>::TH};
+    int t = 64;
+    for (int i = 0; i < 7; ++i)
+        if ((128 << i) <= n && th[i] > t) t = th[i];
+    return t;
 }
 // LDS bytes of the transform buffers of lines of half length M, and with the
 // twiddle table behind them (FP64; FP32 transforms round the entries they read).
@@ -165,7 +177,7 @@ __device__ __forceinline__ void st2(double* p, int j, cpx<double> v) {
     p[2 * j + 1] = v.im;
 }
 
-constexpr int LINE_RED = 64;   // doubles of reduction scratch: [0, 40) sums and maxima, [40, 56) p.Gp
+// Reduction scratch: doubles [0, 80) for sums and maxima, [96, 112) for p.Gp.
 
 // One system's view of the workgroup: roles of the thread, exchange buffers.
 // Where one wave holds the system, lanes beyond its threads repeat the work of the
@@ -585,7 +597,7 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
     }
     L.crossed();
     acc = wave_sum(L.mine ? acc : 0.0);
-    if (!Geo::ONE && L.act && (threadIdx.x & 63) == 0) L.red[40 + (threadIdx.x >> 6)] = acc;
+    if (!Geo::ONE && L.act && (threadIdx.x & 63) == 0) L.red[96 + (threadIdx.x >> 6)] = acc;
     line_transform<T, M, false>(L, v);
     L.turn_all();
     if (L.act) {
@@ -597,7 +609,7 @@ __device__ __forceinline__ void line_apply(Line<T, M>& L, const LinePairs<T, M>&
     } else {
         double sum = 0.0;
 #pragma unroll
-        for (int w = 0; w < Geo::NW; ++w) sum += L.red[40 + w];
+        for (int w = 0; w < Geo::NW; ++w) sum += L.red[96 + w];
         pq = uniform_d(sum);
     }
     if (L.act) {
@@ -647,14 +659,14 @@ __device__ __forceinline__ void line_max(const Line<T, M>& L, double (&v)[NV]) {
     if (Geo::ONE) return;
     if (L.act && (threadIdx.x & 63) == 0) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) L.red[i * 8 + (threadIdx.x >> 6)] = v[i];
+        for (int i = 0; i < NV; ++i) L.red[i * 16 + (threadIdx.x >> 6)] = v[i];
     }
     L.sync_all();
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        double m = L.red[i * 8];
+        double m = L.red[i * 16];
 #pragma unroll
-        for (int w = 1; w < Geo::NW; ++w) m = fmax(m, L.red[i * 8 + w]);
+        for (int w = 1; w < Geo::NW; ++w) m = fmax(m, L.red[i * 16 + w]);
         v[i] = uniform_d(m);
     }
     L.sync_all();
@@ -818,7 +830,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
     // x and (mixed) b in memory, each thread's own entries only
     cpx<double>* bh = reinterpret_cast<cpx<double>*>(w);
     cpx<double>* xh = bh + M;
-    constexpr bool XREG = E == 8 && MODE == BATCH_FP64;
+    constexpr bool XREG = Geo::CREG && MODE == BATCH_FP64;
     cpx<double> r[NP][2], x[XREG ? NP : 1][2];
     double bb = 0.0, dum = 0.0;
 #pragma unroll
@@ -900,7 +912,7 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
                 }
             });
         };
-        if constexpr (E == 8) {
+        if constexpr (Geo::CREG) {
             const LineCoefReg<double, M> coef(L, eta, hx);
             solve(coef);
         } else {
@@ -973,15 +985,18 @@ __device__ __forceinline__ BatchResult line_solve(double L_, const double* __res
                     d32[e][c] = C<float>(0, 0);
                 }
             }
-            const LineCoefReg<float, M> coef32(F, own32, own32 + M);
-            out.iters += line_pcg<float, M>(F, KF, r32, coef32, (float)sig, (float)alp, t2, rr, prm.max_iter, irr,
-                                            [&](float alpha, const cpx<float> (&p)[NP][2]) {
+            auto inner = [&](const auto& coef32) {
+                out.iters += line_pcg<float, M>(F, KF, r32, coef32, (float)sig, (float)alp, t2, rr, prm.max_iter, irr,
+                                                [&](float alpha, const cpx<float> (&p)[NP][2]) {
 #pragma unroll
-                for (int e = 0; e < NP; ++e) {
-                    d32[e][0] = d32[e][0] + alpha * p[e][0];
-                    d32[e][1] = d32[e][1] + alpha * p[e][1];
-                }
-            });
+                    for (int e = 0; e < NP; ++e) {
+                        d32[e][0] = d32[e][0] + alpha * p[e][0];
+                        d32[e][1] = d32[e][1] + alpha * p[e][1];
+                    }
+                });
+            };
+            if constexpr (Geo::CREG) inner(LineCoefReg<float, M>(F, own32, own32 + M));
+            else inner(LineCoefMem<float, M>{own32, own32 + M});
             if (L.act) {
                 const int q = L.thread();
 #pragma unroll

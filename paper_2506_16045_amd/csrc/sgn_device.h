@@ -11,14 +11,14 @@
 // A 1D field is the ny = 1 case: the column pass is then a plain per-mode loop.
 // All transforms are unnormalised; callers apply 1/(nx*ny) once per round trip.
 //
-// FFTs run in LDS as radix-4 Stockham passes (autosort, decimation in time)
-// with a final radix-2 pass when log2 M is odd; the fields a pass needs are
-// transformed in lockstep so they share the block barriers.  A real row of
+// FFTs hold their data in registers, four (eight) entries per thread, as radix-4 (8)
+// Stockham passes with one LDS exchange between two of them (reg_fft).  A real row of
 // length nx is transformed as a complex sequence of length M = nx/2
 // (z_j = x_2j + i x_2j+1) followed by the usual even/odd split.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace sgn {
 
@@ -44,6 +44,14 @@ template <typename T> __device__ __forceinline__ cpx<T> mul_mi(cpx<T> a) { retur
 // i k a for a real wavenumber k
 template <typename T> __device__ __forceinline__ cpx<T> ik(T k, cpx<T> a) { return C(-k * a.im, k * a.re); }
 
+// Element i of a field at `p`, the same for every lane: a 32-bit byte offset from a
+// scalar base (one field of the largest grid is under 2^27 bytes), where a 64-bit
+// index would hold two registers and an addition per access.
+template <typename V>
+__device__ __forceinline__ V& at32(V* p, unsigned i) {
+    return *reinterpret_cast<V*>(reinterpret_cast<char*>(const_cast<std::remove_const_t<V>*>(p)) + i * (unsigned)sizeof(V));
+}
+
 __device__ __forceinline__ int ilog2(int x) { return 31 - __clz(x); }
 
 // Signed wavenumber of FFT index j on an axis of n points and length L, with
@@ -58,32 +66,19 @@ __device__ __forceinline__ T wavenumber(int j, int n, T two_pi_over_L) {
 // ---------------------------------------------------------------------------
 // Twiddles.  The global table holds, for every power of two L <= TW_SIZE, the
 // L-th roots of unity W_L^j = exp(-2 pi i j / L) contiguously at offset L - 1
-// (2 TW_SIZE - 1 entries).  An FFT of length M reads W_M^m; kernels copy the M
-// entries into LDS once per block when they fit (see twl_setup).
+// (2 TW_SIZE - 1 entries).
 // ---------------------------------------------------------------------------
 template <typename T>
 __device__ __forceinline__ const cpx<T>* tw_size(const cpx<T>* __restrict__ tw_all, int L) {
     return tw_all + (L - 1);
 }
 
-constexpr int TWL_MAX = 0;     // largest FFT length whose twiddles are staged in LDS (0: read from the global table)
-
-// Stage W_M^m (m < M) in LDS when M <= TWL_MAX; returns the table to use (LDS or
-// global).  Contains a block barrier; every thread must call it.
-template <typename T>
-__device__ __forceinline__ const cpx<T>* twl_setup(const cpx<T>* __restrict__ tw_all, int M, cpx<T>* lds_tw) {
-    const cpx<T>* g = tw_size(tw_all, M);
-    if (M > TWL_MAX || M < 4) return g;
-    for (int j = threadIdx.x; j < M; j += blockDim.x) lds_tw[j] = g[j];
-    __syncthreads();
-    return lds_tw;
-}
-
 // ---------------------------------------------------------------------------
-// Stockham FFT of length M (power of two) on NF buffers at buf + f * fstride,
-// transformed in lockstep by TPX cooperating threads (thread index t): radix-8
-// (few fields) or radix-4 (many fields) passes while they fit, then one
-// radix-4 or radix-2 pass for the remaining factor (mixed-radix Stockham: a pass of radix R over span Ns reads
+// The transform of the short 1D lines (sgn_batch.h): Stockham FFT of length M (power
+// of two) on NF buffers in LDS at buf + f * fstride, in lockstep by TPX cooperating
+// threads (thread index t): radix-8 (few fields) or radix-4 (many fields) passes while
+// they fit, then one radix-4 or radix-2 pass for the remaining factor (a pass of radix
+// R over span Ns reads
 // x[j + r M/R], twiddles by W_{R Ns}^{k r} with k = j mod Ns, and writes the
 // R-point DFT to y[(j - k) R + k + q Ns]).  Every thread of the block must call
 // it (it contains block barriers); M <= EPC * TPX.  twm[m] = W_M^m.
@@ -133,19 +128,9 @@ __device__ __forceinline__ void dft_small(cpx<T> (&v)[R], bool inverse) {
     }
 }
 
-// LDS index swizzle of the intermediate Stockham layouts: bits 0-2 of an index
-// are XORed with a function of bits 3-5, which permutes every aligned group of 8
-// entries.  The first passes write at strides R and R^2 entries; swizzled, eight
-// consecutive threads then write eight different 16-byte bank groups (radix 4
-// and radix 8).
-__device__ __forceinline__ int lds_swz(int i) {
-    return i ^ (((i >> 3) & 7) ^ (((i >> 4) & 1) << 2));
-}
-
 template <typename T, int R, int NB, int NF>
 __device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t, int TPX,
-                                         const cpx<T>* __restrict__ twm, bool inverse, int Ns, int sh,
-                                         bool swz_in = false, bool swz_out = false) {
+                                         const cpx<T>* __restrict__ twm, bool inverse, int Ns, int sh) {
     const int MR = M / R;
     cpx<T> v[NB][NF][R];
 #pragma unroll
@@ -162,11 +147,11 @@ __device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t,
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 const cpx<T>* bf = buf + f * fstride;
-                v[i][f][0] = bf[swz_in ? lds_swz(j) : j];
+                v[i][f][0] = bf[j];
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
                     const int a = j + r * MR;
-                    v[i][f][r] = bf[swz_in ? lds_swz(a) : a] * w[r];
+                    v[i][f][r] = bf[a] * w[r];
                 }
             }
         }
@@ -185,7 +170,7 @@ __device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t,
 #pragma unroll
                 for (int q = 0; q < R; ++q) {
                     const int a = o + q * Ns;
-                    bf[swz_out ? lds_swz(a) : a] = v[i][f][q];
+                    bf[a] = v[i][f][q];
                 }
             }
         }
@@ -193,9 +178,7 @@ __device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t,
     __syncthreads();
 }
 
-// SWZ: the passes between the first and the last keep their data in the
-// swizzled layout (lds_swz); input and output are in the natural layout.
-template <typename T, int EPC, int NF, bool SWZ = false>
+template <typename T, int EPC, int NF>
 __device__ __forceinline__ void lds_fft(cpx<T>* buf, int fstride, int M, int t, int TPX,
                                         const cpx<T>* __restrict__ twm, bool inverse) {
     constexpr int NB8 = EPC / 8 > 0 ? EPC / 8 : 1;
@@ -207,35 +190,165 @@ __device__ __forceinline__ void lds_fft(cpx<T>* buf, int fstride, int M, int t, 
     const int logM = ilog2(M);
     int Ns = 1;
     int logNs = 0;
-    bool sw = false;   // the layout the next pass reads
-    auto last = [&](int R) { return Ns * R == M; };
     if (R8) {
-        for (; Ns * 8 <= M; Ns <<= 3, logNs += 3) {
-            const bool so = SWZ && !last(8);
-            fft_pass<T, 8, NB8, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 3), sw, so);
-            sw = so;
-        }
+        for (; Ns * 8 <= M; Ns <<= 3, logNs += 3)
+            fft_pass<T, 8, NB8, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 3));
     } else {
-        for (; Ns * 16 <= M; Ns <<= 2, logNs += 2) {
-            const bool so = SWZ && !last(4);
-            fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2), sw, so);
-            sw = so;
-        }
+        for (; Ns * 16 <= M; Ns <<= 2, logNs += 2)
+            fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2));
     }
     if (Ns * 4 <= M) {
-        const bool so = SWZ && !last(4);
-        fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2), sw, so);
-        sw = so;
+        fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2));
         Ns <<= 2;
         logNs += 2;
     }
-    if (Ns * 2 <= M) fft_pass<T, 2, NB2, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 1), sw, false);
+    if (Ns * 2 <= M) fft_pass<T, 2, NB2, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 1));
 }
 
-// Column transforms take the swizzled intermediate layouts in FP64 (16-byte
-// entries, where the first passes' strided writes conflict).
+// Block barrier that orders LDS only.  __syncthreads() fences all memory, which
+// makes every wave wait for its global loads in flight (vmcnt(0)) at the
+// barrier; kernels that issue their data loads before a reduction or an LDS
+// exchange keep them in flight across such barriers.
+__device__ __forceinline__ void block_lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Orders LDS accesses of the G threads of one transform (thread indices t in
+// [0, G), G a power of two): within a wave LDS runs in issue order and only the
+// compiler needs fencing; wider transforms take the block barrier (every thread of
+// the block must call it).
+__device__ __forceinline__ void fft_sync(int G) {
+    if (G <= 64) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    } else {
+        block_lds_barrier();
+    }
+}
+
+// Place of entry i in an exchange: the low bits XORed with the bits above, so that
+// the strided writes of the first passes and the contiguous reads both spread over
+// the banks (16-byte entries are served eight lanes at a time, 8-byte ones
+// sixteen).  Linear over XOR.
 template <typename T>
-constexpr bool col_swz() { return sizeof(T) == 8; }
+__device__ __forceinline__ int fft_at(int i) { return i ^ ((i >> 3) & (sizeof(T) == 8 ? 7 : 15)); }
+
+// FFT of M points (a power of two) of NF fields held in the registers of G =
+// max(M / E, 1) threads, natural layout in and out: v[f][e] is entry t + G e.
+// Radix-E Stockham passes in registers and one LDS exchange between two of them
+// (field f at buf + f fstride); the remaining factor is the last pass.  Against
+// the same transform with its data in LDS (lds_fft) it saves the way in and out and
+// half the barriers, and its barriers leave global accesses in flight: columns of 1024
+// (three fields, FP64) 51 -> 40 us for 513 x 3, columns of 2048 262 -> 157 us for
+// 1025 x 3; 256 x 128, the right-hand side's inverse row pass 56 -> 27 us.  twm[m] =
+// W_M^m inside the table of all sizes.  Loading the twiddles a further pass ahead cost
+// more in occupancy than it saved (513 x 3 columns of 1024: 40 -> 49 us).  Starts with a sync (buf may still be read by
+// the same threads), ends without one.
+template <typename T, int E, int NF>
+__device__ __forceinline__ void reg_fft(cpx<T> (*v)[E], cpx<T>* buf, int fstride, int M, int t, int G,
+                                        const cpx<T>* __restrict__ twm, bool inverse) {
+    constexpr int LE = E == 8 ? 3 : 2;
+    static_assert(E == 4 || E == 8, "radix of the passes");
+    if (M < E) {   // one thread holds all of it
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            if (M == 2) {
+                const cpx<T> a = v[f][0], b = v[f][1];
+                v[f][0] = a + b;
+                v[f][1] = a - b;
+            } else if (M == 4) {
+                cpx<T> w[4] = {v[f][0], v[f][1], v[f][2], v[f][3]};
+                dft_small<T, 4>(w, inverse);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[f][e] = w[e];
+            }
+        }
+        return;
+    }
+    const cpx<T>* all = twm - (M - 1);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) dft_small<T, E>(v[f], inverse);
+    const int at_t = fft_at<T>(t);
+    int Np = 1;   // span of the pass just done
+    while (Np * E < M) {
+        const int Ns = Np * E, rem = M / Ns;   // this pass: span Ns, radix min(E, rem)
+        // twiddle bases W_{R Ns}^{k 2^b} (the other powers by products), in flight
+        // across the exchange; in a last pass of a smaller radix each of the thread's
+        // butterflies has its own index t + i G
+        cpx<T> a[4];
+        if (rem >= E) {
+            const cpx<T>* base = all + (E * Ns - 1);
+            const int k = t & (Ns - 1);
+#pragma unroll
+            for (int b = 0; b < LE; ++b) a[b] = base[k << b];
+        } else if (E == 8 && rem == 4) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                a[2 * i] = twm[t + i * G];
+                a[2 * i + 1] = twm[2 * (t + i * G)];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < E / 2; ++i) a[i] = twm[t + i * G];
+        }
+        if (inverse) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) a[b].im = -a[b].im;
+        }
+        fft_sync(G);
+        {
+            const int k = t & (Np - 1);
+            const int at_o = fft_at<T>((t - k) * E + k);
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int q = 0; q < E; ++q) buf[f * fstride + (at_o ^ fft_at<T>(q * Np))] = v[f][q];
+        }
+        fft_sync(G);
+        int at_r = at_t;
+        asm volatile("" : "+v"(at_r));   // addresses formed here, not held across the passes
+#pragma unroll
+        for (int f = 0; f < NF; ++f)
+#pragma unroll
+            for (int e = 0; e < E; ++e) v[f][e] = buf[f * fstride + (at_r ^ fft_at<T>(e * G))];
+        if (rem >= E) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+#pragma unroll
+                for (int r = 1; r < E; ++r)
+#pragma unroll
+                    for (int b = 0; b < LE; ++b)
+                        if (r & (1 << b)) v[f][r] = v[f][r] * a[b];
+                dft_small<T, E>(v[f], inverse);
+            }
+        } else if (E == 8 && rem == 4) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const cpx<T> a1 = a[2 * i], a2 = a[2 * i + 1];
+                    cpx<T> w[4] = {v[f][i], v[f][(i + 2) % E] * a1, v[f][(i + 4) % E] * a2,
+                                   (v[f][(i + 6) % E] * a1) * a2};
+                    dft_small<T, 4>(w, inverse);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[f][(i + 2 * r) % E] = w[r];
+                }
+        } else {
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+#pragma unroll
+                for (int i = 0; i < E / 2; ++i) {
+                    const cpx<T> x = v[f][i], y = v[f][i + E / 2] * a[i];
+                    v[f][i] = x + y;
+                    v[f][i + E / 2] = x - y;
+                }
+        }
+        Np = Ns;
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Row geometry: a block holds R rows of TPR threads each; row r of the block is
@@ -245,13 +358,15 @@ constexpr bool col_swz() { return sizeof(T) == 8; }
 // ---------------------------------------------------------------------------
 struct RowGeom {
     int nx, ny, M, TPR, R, nblocks;
+    int lgR, lgT;   // log2 of R and TPR
 };
 
 template <typename T>
 struct RowThread {
     int r, t, y, row0;
+    int tid;      // thread within the R TPR threads of the rows
     bool valid;
-    cpx<T>* lds;  // block LDS base
+    cpx<T>* lds;  // LDS base of field 0
     int fstride;  // R (M+1)
 };
 
@@ -263,13 +378,14 @@ __device__ __forceinline__ int xcd_remap(int b, int nb) {
     return (b & 7) * (nb >> 3) + (b >> 3);
 }
 
-// Row thread of row block `blk` (blockIdx.x, or the block within one part of a
-// launch that runs several independent row jobs side by side).
+// Row thread `tid` (of R TPR) of row block `blk` (blockIdx.x, or the block within one
+// part of a launch that runs several independent row jobs side by side).
 template <typename T>
-__device__ __forceinline__ RowThread<T> row_thread_at(const RowGeom& g, cpx<T>* lds, int blk) {
+__device__ __forceinline__ RowThread<T> row_thread_at(const RowGeom& g, cpx<T>* lds, int blk, int tid) {
     RowThread<T> rt;
-    rt.r = threadIdx.x / g.TPR;
-    rt.t = threadIdx.x - rt.r * g.TPR;
+    rt.tid = tid;
+    rt.r = tid >> g.lgT;
+    rt.t = tid & (g.TPR - 1);
     rt.row0 = xcd_remap(blk, g.nblocks) * g.R;
     rt.y = rt.row0 + rt.r;
     rt.valid = rt.y < g.ny;
@@ -279,136 +395,146 @@ __device__ __forceinline__ RowThread<T> row_thread_at(const RowGeom& g, cpx<T>* 
 }
 template <typename T>
 __device__ __forceinline__ RowThread<T> row_thread(const RowGeom& g, cpx<T>* lds) {
-    return row_thread_at<T>(g, lds, blockIdx.x);
+    return row_thread_at<T>(g, lds, blockIdx.x, threadIdx.x);
 }
 
 // LDS entries a row kernel with NF fields needs before its twiddle table.
 __host__ __device__ inline int row_lds_data(const RowGeom& g, int NF) { return NF * g.R * (g.M + 1); }
 
+// row_inverse in pieces, for passes that overlap a field's transposed loads with
+// other work: row_fetch issues the loads of this thread's mirrored pairs (k, M - k)
+// (R (M/2 + 1) pairs over R M / EPC threads: EPC/2 each, R more for the first
+// threads), row_join forms the inverse transform's input from them in the field's
+// LDS region; row_inverse_lds transforms what a barrier has made visible there.
+template <typename T, int EPC>
+struct RowPairs {
+    static constexpr int Q = EPC / 2 + 1;
+    cpx<T> Xk[Q], Xm[Q];
+};
+// The thread index, opaque to the compiler: what is formed from it (pair indices,
+// offsets, split twiddles) is formed again for each field instead of being held in
+// registers across the fields' transforms.
+__device__ __forceinline__ int row_tid(int tid) {
+    int t = tid;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+template <typename T, int EPC>
+__device__ __forceinline__ void row_fetch(const RowGeom& g, const RowThread<T>& rt, const cpx<T>* __restrict__ H,
+                                          RowPairs<T, EPC>& X) {
+    const int tid = row_tid(rt.tid), nt = g.R << g.lgT;
+    const int M = g.M, ny = g.ny, totalp = (M / 2 + 1) << g.lgR;
+    const int y = rt.row0 + (tid & (g.R - 1));   // nt is a multiple of R
+#pragma unroll
+    for (int q = 0; q < RowPairs<T, EPC>::Q; ++q) {
+        const int i = tid + q * nt, p = i >> g.lgR;
+        const bool ok = i < totalp && y < ny;
+        X.Xk[q] = ok ? at32(H, p * ny + y) : C<T>(0, 0);
+        X.Xm[q] = ok ? at32(H, (M - p) * ny + y) : C<T>(0, 0);
+    }
+}
+// One pair of the real split each way.  With S = X_k + X*_m, D = i (X_k - X*_m)
+// W^{-k} (m = M - k): Z_k = S + D, Z_m = (S - D)*; and back with S = (Z_k + Z*_m) / 2,
+// D = i W^k (Z_k - Z*_m) / 2: X_k = S - D, X_m = (S + D)*.  One product serves both.
+template <typename T>
+__device__ __forceinline__ void split_join(cpx<T> Xk, cpx<T> Xm, cpx<T> w, cpx<T>& Zk, cpx<T>& Zm) {
+    const cpx<T> S = Xk + cj(Xm), Dd = mul_i((Xk - cj(Xm)) * cj(w));
+    Zk = S + Dd;
+    Zm = cj(S - Dd);
+}
+template <typename T>
+__device__ __forceinline__ void split_part(cpx<T> Zk, cpx<T> Zm, cpx<T> w, cpx<T>& Xk, cpx<T>& Xm) {
+    const T half = (T)0.5;
+    const cpx<T> S = half * (Zk + cj(Zm)), Dd = mul_i(w * (half * (Zk - cj(Zm))));
+    Xk = S - Dd;
+    Xm = cj(S + Dd);
+}
+// dx != 0: the entries are first multiplied by i k_x dx (tpx = 2 pi / Lx; the
+// Nyquist entry has no wavenumber).
+template <typename T, int EPC>
+__device__ __forceinline__ void row_join(const RowGeom& g, const RowThread<T>& rt, const RowPairs<T, EPC>& X,
+                                         cpx<T>* field, const cpx<T>* __restrict__ tw_all, T dx = (T)0,
+                                         T tpx = (T)0) {
+    const int tid = row_tid(rt.tid), nt = g.R << g.lgT;
+    const int M = g.M, totalp = (M / 2 + 1) << g.lgR;
+    const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
+    cpx<T>* b = field + (tid & (g.R - 1)) * (M + 1);
+    cpx<T> w[RowPairs<T, EPC>::Q];
+#pragma unroll
+    for (int q = 0; q < RowPairs<T, EPC>::Q; ++q) {
+        const int k = (tid + q * nt) >> g.lgR;
+        w[q] = tw2[k < M ? k : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < RowPairs<T, EPC>::Q; ++q) {
+        const int i = tid + q * nt;
+        if (i >= totalp) continue;
+        const int k = i >> g.lgR, m = M - k;
+        cpx<T> xk = X.Xk[q], xm = X.Xm[q];
+        if (dx != (T)0) {
+            xk = ik(dx * (tpx * (T)k), xk);
+            xm = ik(k == 0 ? (T)0 : dx * (tpx * (T)m), xm);
+        }
+        if (k == 0) {
+            b[0] = C<T>(xk.re + xm.re, xk.re - xm.re);
+        } else {
+            cpx<T> zk, zm;
+            split_join(xk, xm, w[q], zk, zm);
+            b[m] = zm;
+            b[k] = zk;
+        }
+    }
+}
+template <typename T, int EPC, int NF>
+__device__ __forceinline__ void row_inverse_lds(const RowGeom& g, const RowThread<T>& rt, const cpx<T>* twm,
+                                                cpx<T> (*z)[EPC]) {
+    const int M = g.M;
+    cpx<T>* rowb = rt.lds + rt.r * (M + 1);
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const int j = rt.t + g.TPR * e;
+            if (j < M) z[f][e] = rowb[f * rt.fstride + j];
+        }
+    }
+    reg_fft<T, EPC, NF>(z, rowb, rt.fstride, M, rt.t, g.TPR, twm, true);
+}
+
 // Inverse row transforms of NF fields: H_f[kx][y] (kx = 0..M) -> real pairs
 // z[f][e] = (x_2j, x_2j+1), unnormalised (nx times the inverse DFT).  The
 // imaginary parts of the kx = 0 and kx = nx/2 entries are ignored (real signal).
 // The even/odd recombination Z_k = (X_k + X*_{M-k}) + i (X_k - X*_{M-k}) W_nx^{-k}
-// is formed while the mirrored pair (k, M - k) is loaded from H, so it costs no
-// LDS pass of its own.
+// is formed from each mirrored pair (k, M - k) as it goes to LDS, so it costs no
+// LDS pass of its own; the transposed loads of all fields are in flight together.
 template <typename T, int EPC, int NF>
 __device__ __forceinline__ void row_inverse(const RowGeom& g, const RowThread<T>& rt,
                                             const cpx<T>* const (&H)[NF],
                                             const cpx<T>* __restrict__ tw_all, const cpx<T>* twm,
                                             cpx<T> (&z)[NF][EPC]) {
-    const int M = g.M, R = g.R, ny = g.ny;
-    const int totalp = R * (M / 2 + 1);
-    const cpx<T>* tw2 = tw_size(tw_all, 2 * M);  // W_nx^k
+    RowPairs<T, EPC> X[NF];
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-        for (int i = threadIdx.x; i < totalp; i += blockDim.x) {
-            const int r = i & (R - 1);
-            const int p = i / R;
-            const int y = rt.row0 + r;
-            const int k = p, m = M - p;
-            const cpx<T> Xk = (y < ny) ? H[f][(size_t)k * ny + y] : C<T>(0, 0);
-            const cpx<T> Xm = (y < ny) ? H[f][(size_t)m * ny + y] : C<T>(0, 0);
-            cpx<T>* b = rt.lds + f * rt.fstride + r * (M + 1);
-            if (p == 0) {
-                b[0] = C<T>(Xk.re + Xm.re, Xk.re - Xm.re);
-            } else {
-                cpx<T> wk = tw2[k], wm = tw2[m];
-                wk.im = -wk.im;
-                wm.im = -wm.im;
-                const cpx<T> Zk = (Xk + cj(Xm)) + mul_i((Xk - cj(Xm)) * wk);
-                if (m != k) b[m] = (Xm + cj(Xk)) + mul_i((Xm - cj(Xk)) * wm);
-                b[k] = Zk;
-            }
-        }
-    }
-    __syncthreads();
-    cpx<T>* rowb = rt.lds + rt.r * (M + 1);
-    lds_fft<T, EPC, NF>(rowb, rt.fstride, M, rt.t, g.TPR, twm, true);
+    for (int f = 0; f < NF; ++f) row_fetch<T, EPC>(g, rt, H[f], X[f]);
 #pragma unroll
-    for (int f = 0; f < NF; ++f) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = rt.t + g.TPR * e;
-            if (j < M) z[f][e] = rowb[f * rt.fstride + j];
-        }
-    }
-    __syncthreads();
-}
-
-// row_inverse with every transposed load of the block issued before the first
-// LDS store: each thread keeps its mirrored pairs (k, M - k) of all NF fields in
-// registers (EPC/2 + 1 pairs per field), so the loads of all fields are in
-// flight together.  For the short rows of the Krylov row pass, whose launch
-// leaves few waves per CU to hide the latency of the transposed accesses.
-template <typename T, int EPC, int NF>
-__device__ __forceinline__ void row_inverse_batched(const RowGeom& g, const RowThread<T>& rt,
-                                                    const cpx<T>* const (&H)[NF],
-                                                    const cpx<T>* __restrict__ tw_all, const cpx<T>* twm,
-                                                    cpx<T> (&z)[NF][EPC]) {
-    const int M = g.M, R = g.R, ny = g.ny;
-    // R (M/2 + 1) pairs over R M / EPC threads: EPC/2 pairs each, R more for the first threads
-    constexpr int Q = EPC / 2 + 1;
-    const int totalp = R * (M / 2 + 1);
-    const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
-    cpx<T> Xk[Q][NF], Xm[Q][NF];
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int i = threadIdx.x + q * blockDim.x;
-        const int y = rt.row0 + (i & (R - 1));
-        const int p = i / R;
-        const bool ok = i < totalp && y < ny;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            Xk[q][f] = ok ? H[f][(size_t)p * ny + y] : C<T>(0, 0);
-            Xm[q][f] = ok ? H[f][(size_t)(M - p) * ny + y] : C<T>(0, 0);
-        }
-    }
-#pragma unroll
-    for (int q = 0; q < Q; ++q) {
-        const int i = threadIdx.x + q * blockDim.x;
-        if (i >= totalp) continue;
-        const int r = i & (R - 1);
-        const int k = i / R, m = M - k;
-        cpx<T> wk = tw2[k], wm = tw2[m];
-        wk.im = -wk.im;
-        wm.im = -wm.im;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            cpx<T>* b = rt.lds + f * rt.fstride + r * (M + 1);
-            const cpx<T> xk = Xk[q][f], xm = Xm[q][f];
-            if (k == 0) {
-                b[0] = C<T>(xk.re + xm.re, xk.re - xm.re);
-            } else {
-                const cpx<T> Zk = (xk + cj(xm)) + mul_i((xk - cj(xm)) * wk);
-                if (m != k) b[m] = (xm + cj(xk)) + mul_i((xm - cj(xk)) * wm);
-                b[k] = Zk;
-            }
-        }
-    }
-    __syncthreads();
-    cpx<T>* rowb = rt.lds + rt.r * (M + 1);
-    lds_fft<T, EPC, NF>(rowb, rt.fstride, M, rt.t, g.TPR, twm, true);
-#pragma unroll
-    for (int f = 0; f < NF; ++f) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = rt.t + g.TPR * e;
-            if (j < M) z[f][e] = rowb[f * rt.fstride + j];
-        }
-    }
-    __syncthreads();
+    for (int f = 0; f < NF; ++f) row_join<T, EPC>(g, rt, X[f], rt.lds + f * rt.fstride, tw_all);
+    fft_sync(g.R << g.lgT);
+    row_inverse_lds<T, EPC, NF>(g, rt, twm, z);
+    fft_sync(g.R << g.lgT);
 }
 
 // Forward row transforms of NF fields: real pairs z[f][e] -> H_f[kx][y] for
-// kx = 0..M, each value multiplied by `scale`.  The recombination
+// kx = 0..M, each value multiplied by `scale` (z is used up).  The recombination
 // X_k = (Z_k + Z*_{M-k})/2 - i W_nx^k (Z_k - Z*_{M-k})/2 is formed as each entry
 // is stored (no LDS pass of its own).
 template <typename T, int EPC, int NF>
-__device__ __forceinline__ void row_forward(const RowGeom& g, const RowThread<T>& rt, const cpx<T> (&z)[NF][EPC],
+__device__ __forceinline__ void row_forward(const RowGeom& g, const RowThread<T>& rt, cpx<T> (&z)[NF][EPC],
                                             cpx<T>* const (&H)[NF], const cpx<T>* __restrict__ tw_all,
                                             const cpx<T>* twm, T scale) {
-    const int M = g.M, R = g.R, ny = g.ny;
+    const int M = g.M, R = g.R, ny = g.ny, nt = g.R << g.lgT;
+    const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
     cpx<T>* rowb = rt.lds + rt.r * (M + 1);
+    reg_fft<T, EPC, NF>(z, rowb, rt.fstride, M, rt.t, g.TPR, twm, false);
+    fft_sync(g.TPR);
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
 #pragma unroll
@@ -417,31 +543,38 @@ __device__ __forceinline__ void row_forward(const RowGeom& g, const RowThread<T>
             if (j < M) rowb[f * rt.fstride + j] = z[f][e];
         }
     }
-    __syncthreads();
-    lds_fft<T, EPC, NF>(rowb, rt.fstride, M, rt.t, g.TPR, twm, false);
-    const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
-    const T half = (T)0.5;
-    const int total = R * (M + 1);
+    fft_sync(nt);
+    constexpr int Q = EPC / 2 + 1;
+    const int tid = row_tid(rt.tid);
+    const int totalp = (M / 2 + 1) << g.lgR;
+    const int ry = tid & (R - 1), y = rt.row0 + ry;
+    cpx<T> w[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int k = (tid + q * nt) >> g.lgR;
+        w[q] = tw2[k < M ? k : 0];
+    }
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-        for (int i = threadIdx.x; i < total; i += blockDim.x) {
-            const int r = i & (R - 1);
-            const int kx = i / R;
-            const int y = rt.row0 + r;
-            const cpx<T>* b = rt.lds + f * rt.fstride + r * (M + 1);
-            cpx<T> X;
-            if (kx == 0 || kx == M) {
-                const cpx<T> Z0 = b[0];
-                X = C<T>(kx == 0 ? Z0.re + Z0.im : Z0.re - Z0.im, 0);
+        const cpx<T>* b = rt.lds + f * rt.fstride + ry * (M + 1);
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = tid + q * nt;
+            if (i >= totalp || y >= ny) continue;
+            const int k = i >> g.lgR, m = M - k;
+            const cpx<T> zk = b[k];
+            cpx<T> xk, xm;
+            if (k == 0) {
+                xk = C<T>(zk.re + zk.im, 0);
+                xm = C<T>(zk.re - zk.im, 0);
             } else {
-                const cpx<T> wk = tw2[kx];
-                const cpx<T> Zk = b[kx], Zm = b[M - kx];
-                X = half * (Zk + cj(Zm)) - half * mul_i(wk * (Zk - cj(Zm)));
+                split_part(zk, b[m], w[q], xk, xm);
             }
-            if (y < ny) H[f][(size_t)kx * ny + y] = scale * X;
+            at32(H[f], k * ny + y) = scale * xk;
+            if (m != k) at32(H[f], m * ny + y) = scale * xm;
         }
     }
-    __syncthreads();
+    fft_sync(nt);
 }
 
 // ---------------------------------------------------------------------------
@@ -452,6 +585,7 @@ __device__ __forceinline__ void row_forward(const RowGeom& g, const RowThread<T>
 // ---------------------------------------------------------------------------
 struct ColGeom {
     int nx, ny, nxh, TPC, Cb, nblocks;
+    int lgT;   // log2 of TPC
 };
 
 template <typename T>
@@ -469,8 +603,8 @@ __host__ __device__ inline int col_lds_data(const ColGeom& g, int NF) { return N
 template <typename T>
 __device__ __forceinline__ ColThread<T> col_thread_at(const ColGeom& g, cpx<T>* lds, int blk) {
     ColThread<T> ct;
-    ct.c = threadIdx.x / g.TPC;
-    ct.t = threadIdx.x - ct.c * g.TPC;
+    ct.c = threadIdx.x >> g.lgT;
+    ct.t = threadIdx.x & (g.TPC - 1);
     ct.kx = blk * g.Cb + ct.c;
     ct.valid = ct.kx < g.nxh;
     ct.buf = lds + ct.c * g.ny;
@@ -489,9 +623,9 @@ __device__ __forceinline__ ColThread<T> col_thread(const ColGeom& g, cpx<T>* lds
 // The loads through it are unconditional: predicated loads make the compiler
 // wait for every load in flight (see partials_fetch).
 template <typename T>
-__device__ __forceinline__ size_t col_index(const ColGeom& g, const ColThread<T>& ct, int j, bool& ok) {
+__device__ __forceinline__ unsigned col_index(const ColGeom& g, const ColThread<T>& ct, int j, bool& ok) {
     ok = ct.valid && j < g.ny;
-    return ok ? (size_t)ct.kx * g.ny + j : 0;
+    return ok ? (unsigned)(ct.kx * g.ny + j) : 0u;
 }
 // A lane without an entry (a column past nx/2 in the last block) holds a copy
 // of entry 0: finite, transformed with its column and never stored or summed
@@ -502,35 +636,17 @@ __device__ __forceinline__ void col_fetch(const ColGeom& g, const ColThread<T>& 
 #pragma unroll
     for (int e = 0; e < EPC; ++e) {
         bool ok;
-        const size_t idx = col_index(g, ct, ct.t + g.TPC * e, ok);
+        const unsigned idx = col_index(g, ct, ct.t + g.TPC * e, ok);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) v[f][e] = H[f][idx];
+        for (int f = 0; f < NF; ++f) v[f][e] = at32(H[f], idx);
     }
 }
 template <typename T, int EPC, int NF>
 __device__ __forceinline__ void col_fft(const ColGeom& g, const ColThread<T>& ct, const cpx<T>* twm,
                                         cpx<T> (&v)[NF][EPC]) {
-    const int ny = g.ny;
-    if (ny > 1) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const int j = ct.t + g.TPC * e;
-                if (j < ny) ct.buf[f * ct.fstride + j] = v[f][e];
-            }
-        }
-        __syncthreads();
-        lds_fft<T, EPC, NF, col_swz<T>()>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, false);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const int j = ct.t + g.TPC * e;
-                if (j < ny) v[f][e] = ct.buf[f * ct.fstride + j];
-            }
-        }
-        __syncthreads();
+    if (g.ny > 1) {
+        reg_fft<T, EPC, NF>(v, ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, false);
+        fft_sync(g.TPC);
     }
 }
 // col_load: lanes without an entry hold zeros.
@@ -542,7 +658,7 @@ __device__ __forceinline__ void col_load(const ColGeom& g, const ColThread<T>& c
         const int j = ct.t + g.TPC * e;
 #pragma unroll
         for (int f = 0; f < NF; ++f)
-            if (j < g.ny) v[f][e] = ct.valid ? H[f][(size_t)ct.kx * g.ny + j] : C<T>(0, 0);
+            if (j < g.ny) v[f][e] = ct.valid ? at32(H[f], ct.kx * g.ny + j) : C<T>(0, 0);
     }
     if (fft) col_fft<T, EPC, NF>(g, ct, twm, v);
 }
@@ -553,25 +669,8 @@ __device__ __forceinline__ void col_store(const ColGeom& g, const ColThread<T>& 
                                           cpx<T>* const (&H)[NF], bool ifft, const cpx<T>* twm) {
     const int ny = g.ny;
     if (ifft && ny > 1) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const int j = ct.t + g.TPC * e;
-                if (j < ny) ct.buf[f * ct.fstride + j] = v[f][e];
-            }
-        }
-        __syncthreads();
-        lds_fft<T, EPC, NF, col_swz<T>()>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const int j = ct.t + g.TPC * e;
-                if (j < ny) v[f][e] = ct.buf[f * ct.fstride + j];
-            }
-        }
-        __syncthreads();
+        reg_fft<T, EPC, NF>(v, ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
+        fft_sync(g.TPC);
     }
     if (ct.valid) {
 #pragma unroll
@@ -579,20 +678,41 @@ __device__ __forceinline__ void col_store(const ColGeom& g, const ColThread<T>& 
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
                 const int j = ct.t + g.TPC * e;
-                if (j < ny) H[f][(size_t)ct.kx * ny + j] = v[f][e];
+                if (j < ny) at32(H[f], ct.kx * ny + j) = v[f][e];
             }
         }
     }
 }
 
-// Block barrier that orders LDS only.  __syncthreads() fences all memory, which
-// makes every wave wait for its global loads in flight (vmcnt(0)) at the
-// barrier; kernels that issue their data loads before a reduction or an LDS
-// exchange keep them in flight across such barriers.
-__device__ __forceinline__ void block_lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+__device__ __forceinline__ double lane_d(double v, int lane) {
+    const long long b = __double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), lane);
+    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
+}
+// Sum over the 64 lanes (all active), the same in every lane: a tree inside each
+// row of 16 by data-parallel moves, then the four rows through scalar registers
+// (six shuffles of a double through LDS cost about five times as long).
+__device__ __forceinline__ double wave_sum(double v) {
+    v += dpp_d<0xB1>(v);     // lanes ^ 1
+    v += dpp_d<0x4E>(v);     // lanes ^ 2
+    v += dpp_d<0x141>(v);    // the other four of eight
+    v += dpp_d<0x140>(v);    // the other eight of sixteen
+    return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
+}
+__device__ __forceinline__ double wave_max(double v) {
+    v = fmax(v, dpp_d<0xB1>(v));
+    v = fmax(v, dpp_d<0x4E>(v));
+    v = fmax(v, dpp_d<0x141>(v));
+    v = fmax(v, dpp_d<0x140>(v));
+    return fmax(fmax(lane_d(v, 0), lane_d(v, 16)), fmax(lane_d(v, 32), lane_d(v, 48)));
 }
 
 // ---------------------------------------------------------------------------
@@ -603,15 +723,22 @@ __device__ __forceinline__ void block_lds_barrier() {
 // ---------------------------------------------------------------------------
 // LDS_ONLY: the barriers order LDS only (global loads in flight stay in flight);
 // the arithmetic, and so the result, is the same.
+template <int NACC>
+__device__ __forceinline__ void block_wave_sums(double (&v)[NACC]) {
+    if ((blockDim.x & 63) == 0) {
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) v[a] = wave_sum(v[a]);
+        return;
+    }
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) {   // blocks with lanes missing (the smallest grids)
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[a] += __shfl_xor(v[a], off, 64);
+    }
+}
 template <int NACC, bool LDS_ONLY = false>
 __device__ __forceinline__ void block_sum(double (&v)[NACC], double* red /*LDS, NACC*16*/) {
-#pragma unroll
-    for (int a = 0; a < NACC; ++a) {
-        double x = v[a];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-        v[a] = x;
-    }
+    block_wave_sums<NACC>(v);
     const int wave = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
     const int nw = (blockDim.x + 63) >> 6;
@@ -637,6 +764,25 @@ __device__ __forceinline__ void block_sum(double (&v)[NACC], double* red /*LDS, 
         __syncthreads();
 }
 
+// block_sum with the same result in every thread, behind one LDS-only barrier: red
+// must not be written again before another barrier of the block.
+template <int NACC>
+__device__ __forceinline__ void block_sum_all(double (&v)[NACC], double* red /*LDS, NACC*16*/) {
+    block_wave_sums<NACC>(v);
+    const int nw = (blockDim.x + 63) >> 6;
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) red[a * 16 + (threadIdx.x >> 6)] = v[a];
+    }
+    block_lds_barrier();
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) {
+        double s = 0.0;
+        for (int w = 0; w < nw; ++w) s += red[a * 16 + w];
+        v[a] = s;
+    }
+}
+
 // Sum of the per-block partials (layout partials[NACC*b + a]) by the whole
 // last block: thread t < 256 adds blocks t, t+256, ... in order, then the fixed
 // block tree (further threads and waves add zeros); the result is in thread 0.
@@ -657,11 +803,12 @@ __device__ __forceinline__ void final_sum(const double* __restrict__ partials, u
 
 // final_sum in two steps, so that a kernel can issue the partials' loads ahead
 // of its data loads (a wait for a load also waits for every load issued before
-// it): partials_fetch loads the partials of up to 256 PF_K blocks (every
-// reducing launch: PARTIALS_MAX) into registers, partials_sum adds them in
-// final_sum's order, so the result is the same bits.  No loop: a load inside a
-// loop makes the compiler wait for every load in flight at the loop entry.
-constexpr int PF_K = 16;
+// it): partials_fetch loads the partials of up to 256 PF_K blocks into registers,
+// partials_sum adds them, and those of any further blocks, in final_sum's order, so
+// the result is the same bits; it is in every thread (see block_sum_all for red).
+// No loop over the first ones: a load inside a loop makes the compiler wait for every
+// load in flight at the loop entry.
+constexpr int PF_K = 3;   // the column launches of 1024-point rows: 513 blocks
 template <int NACC>
 __device__ __forceinline__ void partials_fetch(const double* __restrict__ partials, unsigned nblocks,
                                                double (&pb)[PF_K][NACC]) {
@@ -675,7 +822,7 @@ __device__ __forceinline__ void partials_fetch(const double* __restrict__ partia
         for (int a = 0; a < NACC; ++a) pb[k][a] = partials[(size_t)NACC * bc + a];
     }
 }
-template <int NACC, bool LDS_ONLY = false>
+template <int NACC>
 __device__ __forceinline__ void partials_sum(const double* __restrict__ partials, unsigned nblocks,
                                              const double (&pb)[PF_K][NACC], double (&v)[NACC], double* red) {
 #pragma unroll
@@ -686,7 +833,13 @@ __device__ __forceinline__ void partials_sum(const double* __restrict__ partials
 #pragma unroll
         for (int a = 0; a < NACC; ++a) v[a] += ok ? pb[k][a] : 0.0;
     }
-    block_sum<NACC, LDS_ONLY>(v, red);
+    if (nblocks > 256u * PF_K) {
+        for (unsigned b = threadIdx.x + 256u * PF_K; threadIdx.x < 256 && b < nblocks; b += 256) {
+#pragma unroll
+            for (int a = 0; a < NACC; ++a) v[a] += partials[(size_t)NACC * b + a];
+        }
+    }
+    block_sum_all<NACC>(v, red);
 }
 
 // Maximum of the per-block partials by the whole last block (order independent);

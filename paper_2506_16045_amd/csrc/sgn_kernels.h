@@ -24,8 +24,12 @@ struct SolveScal {
     int outer;                // refinement steps taken (mixed precision)
 };
 
-constexpr int PARTIALS_MAX = 4096;  // blocks of a reducing launch (256 PF_K)
-static_assert(PARTIALS_MAX <= 256 * PF_K, "prefetched partials cover every reducing launch");
+// Waves per SIMD the column kernels leave room for: three, so that three blocks of
+// a column each fit a compute unit (1024-point columns: 513 blocks, which two per
+// compute unit would take in two rounds); the columns of 2048 take two.
+template <int EPC>
+constexpr int COL_WAVES = EPC <= 4 ? 3 : 2;
+constexpr int PARTIALS_MAX = 4096;  // blocks of a reducing launch
 // regions of the partials buffer (doubles)
 constexpr int PART_C2 = 0;                       // p.Gp of the row pass (one per row block)
 constexpr int PART_C3 = 4096;                    // (r.z, r.r) of the update pass (two per column block)
@@ -83,111 +87,87 @@ struct RowCombo {
     int first;
 };
 
-// Forward row transforms of n physical fields (Tin = double or T) into H fields,
-// NFG fields at a time in lockstep (the remainder one by one).
-template <typename T, typename Tin, int EPC, int NFG>
-__device__ __forceinline__ void rows_fwd_group(const RowGeom& g, const RowThread<T>& rt,
-                                               const PtrList<const Tin, MAXF>& src, const PtrList<cpx<T>, MAXF>& dst,
-                                               int f0, const cpx<T>* __restrict__ tw, const cpx<T>* twm, T scale,
-                                               const RowCombo<Tin>& cmb) {
-    cpx<T> z[NFG][EPC];
-    cpx<T>* H[NFG];
-#pragma unroll
-    for (int f = 0; f < NFG; ++f) {
-        H[f] = dst.p[f0 + f];
-        const int k = f0 + f - cmb.first;
-        const bool comb = cmb.first >= 0 && k >= 0;
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = rt.t + g.TPR * e;
-            z[f][e] = C<T>(0, 0);
-            if (j < g.M && rt.valid) {
-                const size_t o = (size_t)rt.y * g.nx + 2 * j;
-                if (comb) {
-                    double v[2];
-#pragma unroll
-                    for (int s = 0; s < 2; ++s) {
-                        double t = cmb.c1 * (double)cmb.a[k][o + s];
-                        if (cmb.b[k]) t += cmb.c2 * (double)cmb.b[k][o + s];
-                        v[s] = (double)src.p[f0 + f][o + s] + t;
-                    }
-                    z[f][e] = C<T>((T)v[0], (T)v[1]);
-                } else {
-                    z[f][e] = C<T>((T)src.p[f0 + f][o], (T)src.p[f0 + f][o + 1]);
-                }
-            }
-        }
-    }
-    row_forward<T, EPC, NFG>(g, rt, z, H, tw, twm, scale);
-}
-
-template <typename T, typename Tin, int EPC, int NFG, int MAXT = 1024>
+// Forward row transforms of n physical fields (Tin = double or T) into H fields.  A
+// block takes its rows of one field (blocks [f nblocks, (f + 1) nblocks): field f):
+// small grids fill more of the chip than with a block's fields in lockstep, and a
+// field's registers leave room for twice the waves (256 x 128, three fields: forward
+// 14.8 -> 6.6 us, inverse 8.2 -> 5.0; 512 x 512, inverse: 11.5 -> 7.8).
+template <typename T, typename Tin, int EPC, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_rows_fwd(RowGeom g, PtrList<const Tin, MAXF> src,
                                                    PtrList<cpx<T>, MAXF> dst,
                                                    const cpx<T>* __restrict__ tw, T scale, RowCombo<Tin> cmb) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.M, lds + row_lds_data(g, NFG));
-    const RowThread<T> rt = row_thread<T>(g, lds);
-    int f = 0;
-    for (; f + NFG <= src.n; f += NFG) rows_fwd_group<T, Tin, EPC, NFG>(g, rt, src, dst, f, tw, twm, scale, cmb);
-    for (; f < src.n; ++f) rows_fwd_group<T, Tin, EPC, 1>(g, rt, src, dst, f, tw, twm, scale, cmb);
-}
-
-// Inverse row transforms of n H fields into physical fields (Tout):
-// dst = acc * dst + scale * value  (acc = 0 overwrites).  With offs.n > 0,
-// offs_f = new - old value of dst_f is written too (the offset of a solve's
-// result from its base, recorded for the next extrapolated guess); with
-// oacc != 0 it is added to offs_f instead (a result stored a second time).
-template <typename T, typename Tout, int EPC, int NFG>
-__device__ __forceinline__ void rows_inv_group(const RowGeom& g, const RowThread<T>& rt,
-                                               const PtrList<const cpx<T>, MAXF>& src, const PtrList<Tout, MAXF>& dst,
-                                               int f0, const cpx<T>* __restrict__ tw, const cpx<T>* twm, T scale,
-                                               T acc, const PtrList<Tout, MAXF>& offs, int oacc) {
-    cpx<T> z[NFG][EPC];
-    const cpx<T>* H[NFG];
+    const cpx<T>* twm = tw_size(tw, g.M);
+    const int f = (int)blockIdx.x / g.nblocks;
+    const RowThread<T> rt = row_thread_at<T>(g, lds, (int)blockIdx.x - f * g.nblocks, threadIdx.x);
+    const Tin* in = src.p[f];
+    const int k = f - cmb.first;
+    const bool comb = cmb.first >= 0 && k >= 0;
+    cpx<T> z[1][EPC];
 #pragma unroll
-    for (int f = 0; f < NFG; ++f) H[f] = src.p[f0 + f];
-    row_inverse<T, EPC, NFG>(g, rt, H, tw, twm, z);
+    for (int e = 0; e < EPC; ++e) {
+        const int j = rt.t + g.TPR * e;
+        z[0][e] = C<T>(0, 0);
+        if (j < g.M && rt.valid) {
+            const unsigned o = rt.y * g.nx + 2 * j;
+            if (comb) {
+                double v[2];
 #pragma unroll
-    for (int f = 0; f < NFG; ++f) {
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = rt.t + g.TPR * e;
-            if (j < g.M && rt.valid) {
-                const size_t o = (size_t)rt.y * g.nx + 2 * j;
-                Tout* d = dst.p[f0 + f];
-                T v0 = scale * z[f][e].re, v1 = scale * z[f][e].im;
-                if (acc != (T)0) {
-                    v0 += acc * (T)d[o];
-                    v1 += acc * (T)d[o + 1];
+                for (int s = 0; s < 2; ++s) {
+                    double t = cmb.c1 * (double)cmb.a[k][o + s];
+                    if (cmb.b[k]) t += cmb.c2 * (double)cmb.b[k][o + s];
+                    v[s] = (double)at32(in, o + s) + t;
                 }
-                if (offs.n > 0) {
-                    Tout* od = offs.p[f0 + f];
-                    const Tout d0 = (Tout)v0 - d[o], d1 = (Tout)v1 - d[o + 1];
-                    od[o] = oacc ? od[o] + d0 : d0;
-                    od[o + 1] = oacc ? od[o + 1] + d1 : d1;
-                }
-                d[o] = (Tout)v0;
-                d[o + 1] = (Tout)v1;
+                z[0][e] = C<T>((T)v[0], (T)v[1]);
+            } else {
+                z[0][e] = C<T>((T)at32(in, o), (T)at32(in, o + 1));
             }
         }
     }
+    cpx<T>* H[1] = {dst.p[f]};
+    row_forward<T, EPC, 1>(g, rt, z, H, tw, twm, scale);
 }
 
-template <typename T, typename Tout, int EPC, int NFG, int MAXT = 1024>
+// Inverse row transforms of n H fields into physical fields (Tout), blocks as in
+// k_rows_fwd: dst = acc * dst + scale * value  (acc = 0 overwrites).  With offs.n > 0,
+// offs_f = new - old value of dst_f is written too (the offset of a solve's
+// result from its base, recorded for the next extrapolated guess); with
+// oacc != 0 it is added to offs_f instead (a result stored a second time).
+template <typename T, typename Tout, int EPC, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_rows_inv(RowGeom g, PtrList<const cpx<T>, MAXF> src,
                                                    PtrList<Tout, MAXF> dst,
                                                    const cpx<T>* __restrict__ tw, T scale, T acc,
                                                    PtrList<Tout, MAXF> offs, int oacc) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.M, lds + row_lds_data(g, NFG));
-    const RowThread<T> rt = row_thread<T>(g, lds);
-    int f = 0;
-    for (; f + NFG <= src.n; f += NFG)
-        rows_inv_group<T, Tout, EPC, NFG>(g, rt, src, dst, f, tw, twm, scale, acc, offs, oacc);
-    for (; f < src.n; ++f) rows_inv_group<T, Tout, EPC, 1>(g, rt, src, dst, f, tw, twm, scale, acc, offs, oacc);
+    const cpx<T>* twm = tw_size(tw, g.M);
+    const int f = (int)blockIdx.x / g.nblocks;
+    const RowThread<T> rt = row_thread_at<T>(g, lds, (int)blockIdx.x - f * g.nblocks, threadIdx.x);
+    cpx<T> z[1][EPC];
+    const cpx<T>* H[1] = {src.p[f]};
+    row_inverse<T, EPC, 1>(g, rt, H, tw, twm, z);
+    Tout* d = dst.p[f];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+        const int j = rt.t + g.TPR * e;
+        if (j < g.M && rt.valid) {
+            const unsigned o = rt.y * g.nx + 2 * j;
+            T v0 = scale * z[0][e].re, v1 = scale * z[0][e].im;
+            if (acc != (T)0) {
+                v0 += acc * (T)d[o];
+                v1 += acc * (T)d[o + 1];
+            }
+            if (offs.n > 0) {
+                Tout* od = offs.p[f];
+                const Tout d0 = (Tout)v0 - d[o], d1 = (Tout)v1 - d[o + 1];
+                od[o] = oacc ? od[o] + d0 : d0;
+                od[o + 1] = oacc ? od[o + 1] + d1 : d1;
+            }
+            d[o] = (Tout)v0;
+            d[o + 1] = (Tout)v1;
+        }
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -223,13 +203,13 @@ __device__ __forceinline__ double rhs_source(int i, double e, const double (&uc)
 // blocks, whose register budget is smaller, read them again for every group.
 // MAXT bounds the workgroup size (256 lets the compiler use more registers).
 template <int D, int EPC, int NFG, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_rhs_rows_fwd(RowGeom g, const double* __restrict__ eta,
+__global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_fwd(RowGeom g, const double* __restrict__ eta,
                                                        const double* __restrict__ u, const double* __restrict__ gh,
                                                        PtrList<cpx<double>, MAXF> dst,
                                                        const cpx<double>* __restrict__ tw) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<double>* lds = reinterpret_cast<cpx<double>*>(smem_raw);
-    const cpx<double>* twm = twl_setup<double>(tw, g.M, lds + row_lds_data(g, NFG));
+    const cpx<double>* twm = tw_size(tw, g.M);
     const RowThread<double> rt = row_thread<double>(g, lds);
     const size_t npts = (size_t)g.nx * g.ny;
     constexpr int NFLD = 2 * D + 3;
@@ -240,13 +220,13 @@ __global__ void __launch_bounds__(MAXT) k_rhs_rows_fwd(RowGeom g, const double* 
     auto load = [&](int e, int s, double& et, double (&uc)[D], double (&hc)[D]) {
         const int j = rt.t + g.TPR * e;
         const bool ok = j < g.M && rt.valid;
-        const size_t o = ok ? (size_t)rt.y * g.nx + 2 * j : 0;
+        const unsigned o = ok ? rt.y * g.nx + 2 * j : 0;
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-            uc[c] = ok ? u[c * npts + o + s] : 0.0;
-            hc[c] = ok ? gh[c * npts + o + s] : 0.0;
+            uc[c] = ok ? at32(u + c * npts, o + s) : 0.0;
+            hc[c] = ok ? at32(gh + c * npts, o + s) : 0.0;
         }
-        et = ok ? eta[o + s] : 0.0;
+        et = ok ? at32(eta, o + s) : 0.0;
     };
     if (KEEP) {
 #pragma unroll
@@ -311,9 +291,18 @@ __global__ void __launch_bounds__(MAXT) k_rhs_rows_fwd(RowGeom g, const double* 
     }
 }
 
+// x-derivatives formed by an inverse row pass: a nonzero f[i] means that field i
+// is given as another spectrum (delta's column output, f = 1, or a forward row
+// transform, f = 1/nx, the column pass's scale of 1/(nx ny) times the ny of its y
+// round trip) whose entry kx is multiplied by i k_x f before the transform (the
+// Nyquist entry has no wavenumber), so the column pass writes three outputs fewer.
+struct RowDx {
+    double f[8];
+};
+
 // Inverse row transforms of the derivative fields Q, in the order m =
-// div(eta u), delta = div u, d_c delta, d_c eta, d_c beta, in groups of NFG,
-// consumed into the pointwise right-hand side as they arrive: eta_t = -m,
+// div(eta u), delta = div u, d_c delta, d_c beta, d_c eta, one at a time (the next
+// one's loads in flight), consumed into the pointwise right-hand side as they arrive: eta_t = -m,
 // U_t = -eta grad(eta - h) - T grad h (grad S - div(eta u (x) u) is added later),
 // and S, T of Def:bigF accumulated as S = e^3/3 P + e^2 m delta + e m beta +
 // e^2/2 Q, T = e^2/2 P + e m delta + m beta + e Q with P = u.grad(delta) -
@@ -321,85 +310,117 @@ __global__ void __launch_bounds__(MAXT) k_rhs_rows_fwd(RowGeom g, const double* 
 // four values per point are live.  S's forward row transform goes to Sdst
 // (grad S is added to U_t later); in 2D S_x = S - eta u_x^2 goes to Sdst and
 // S_y = S - eta u_y^2 to Sydst (see rhs_source).
-template <int D, int EPC, int NFG, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_rhs_rows_inv(RowGeom g, PtrList<const cpx<double>, MAXF> src,
+// dx: fields with dx.f[i] != 0 are given as row spectra (or another field's column
+// output) whose x-derivative is wanted (see RowDx).
+template <int D, int EPC, int MAXT>
+__global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowGeom g, PtrList<const cpx<double>, MAXF> src,
                                                        const double* __restrict__ eta, const double* __restrict__ u,
                                                        const double* __restrict__ gh, double* __restrict__ eta_t,
                                                        double* __restrict__ U_t, cpx<double>* __restrict__ Sdst,
                                                        cpx<double>* __restrict__ Sydst,
-                                                       const cpx<double>* __restrict__ tw, double scale) {
+                                                       const cpx<double>* __restrict__ tw, double scale, RowDx dx,
+                                                       double tpx) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<double>* lds = reinterpret_cast<cpx<double>*>(smem_raw);
-    const cpx<double>* twm = twl_setup<double>(tw, g.M, lds + row_lds_data(g, NFG));
+    const cpx<double>* twm = tw_size(tw, g.M);
     const RowThread<double> rt = row_thread<double>(g, lds);
     const size_t npts = (size_t)g.nx * g.ny;
     constexpr int NQ = 3 * D + 2;
-    // live state per point: (m, delta, P) while the first 2 + D fields arrive,
-    // then (S, T) and U_t (D)
-    double A0[EPC][2], A1[EPC][2], A2[EPC][2], Ut[D][EPC][2];
-    for (int f0 = 0; f0 < NQ; f0 += NFG) {
-        const int nf = NQ - f0 < NFG ? NQ - f0 : NFG;
-        cpx<double> z[NFG][EPC];
-        if (nf == NFG) {
-            const cpx<double>* Hs[NFG];
+    // live state per point: eta and (m, delta, P) while the first 2 + D fields arrive,
+    // then (S, T); d_c eta comes last, when T is complete, so U_t goes straight out
+    double A0[EPC][2], A1[EPC][2], A2[EPC][2], e0[EPC][2];
+    // (the index is opaque: addresses are formed where they are used)
+    auto point = [&](int e, bool& ok) -> unsigned {
+        int t = rt.t;
+        asm volatile("" : "+v"(t));
+        const int j = t + g.TPR * e;
+        ok = j < g.M && rt.valid;
+        return ok ? (unsigned)(rt.y * g.nx + 2 * j) : 0u;
+    };
 #pragma unroll
-            for (int k = 0; k < NFG; ++k) Hs[k] = src.p[f0 + k];
-            row_inverse<double, EPC, NFG>(g, rt, Hs, tw, twm, z);
-        } else {
-            for (int k = 0; k < nf; ++k) {
-                const cpx<double>* H1[1] = {src.p[f0 + k]};
-                cpx<double> z1[1][EPC];
-                row_inverse<double, EPC, 1>(g, rt, H1, tw, twm, z1);
-#pragma unroll
-                for (int e = 0; e < EPC; ++e) z[k][e] = z1[0][e];
-            }
-        }
+    for (int e = 0; e < EPC; ++e) {
+        bool ok;
+        const unsigned o = point(e, ok);
+        e0[e][0] = at32(eta, o);
+        e0[e][1] = at32(eta, o + 1);
+    }
+    RowPairs<double, EPC> X;
+    row_fetch<double, EPC>(g, rt, src.p[0], X);
+#pragma unroll 1
+    for (int i = 0; i < NQ; ++i) {
+        row_join<double, EPC>(g, rt, X, rt.lds, tw, dx.f[i], tpx);
+        // in flight across the transform: the next field's entries, and the factor
+        // this field is consumed with (u_c for d_c delta and d_c beta, (grad h)_c for
+        // d_c eta)
+        const int c = i < 2 ? 0 : (i - 2) % D;
+        if (i + 1 < NQ) row_fetch<double, EPC>(g, rt, src.p[i + 1], X);
+        const double* fac = i < 2 ? eta : (i <= 1 + 2 * D ? u : gh) + c * npts;
+        double fv[EPC][2];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
-            const int j = rt.t + g.TPR * e;
-            if (j < g.M && rt.valid) {
-                const size_t o = (size_t)rt.y * g.nx + 2 * j;
+            bool ok;
+            const unsigned o = point(e, ok);
+            fv[e][0] = at32(fac, o);
+            fv[e][1] = at32(fac, o + 1);
+        }
+        block_lds_barrier();
+        cpx<double> z[1][EPC];
+        row_inverse_lds<double, EPC, 1>(g, rt, twm, z);
+        block_lds_barrier();
+        // eta, opaque: its powers are formed where they are used, not held across the
+        // loop over the fields
+        auto depth = [&](int e, int s) {
+            double v = e0[e][s];
+            asm volatile("" : "+v"(v));
+            return v;
+        };
+        // f(e, s, q, o, ok): value q of point e, component s
+        auto each = [&](auto&& f) {
 #pragma unroll
-                for (int s = 0; s < 2; ++s) {
+            for (int e = 0; e < EPC; ++e) {
+                __builtin_amdgcn_sched_barrier(0);   // one entry's loads at a time
+                bool ok;
+                const unsigned o = point(e, ok);
 #pragma unroll
-                    for (int k = 0; k < NFG; ++k) {
-                        const int i = f0 + k;
-                        if (k >= nf) continue;
-                        const double q = scale * (s ? z[k][e].im : z[k][e].re);
-                        if (i == 0) {                       // m
-                            A0[e][s] = q;
-                            eta_t[o + s] = -q;
-                        } else if (i == 1) {                // delta
-                            A1[e][s] = q;
-                            A2[e][s] = -q * q;
-                        } else if (i <= 1 + D) {            // d_c delta: P += u_c d_c delta
-                            const int c = i - 2;
-                            A2[e][s] += u[c * npts + o + s] * q;
-                            if (c == D - 1) {               // P complete: fold into S, T
-                                const double e0 = eta[o + s];
-                                double bt = 0.0;
-#pragma unroll
-                                for (int cc = 0; cc < D; ++cc) bt += gh[cc * npts + o + s] * u[cc * npts + o + s];
-                                const double e2 = e0 * e0, mm = A0[e][s], d0 = A1[e][s], pp = A2[e][s];
-                                A0[e][s] = e2 * e0 / 3.0 * pp + e2 * mm * d0 + e0 * mm * bt;   // S
-                                A1[e][s] = e2 / 2.0 * pp + e0 * mm * d0 + mm * bt;            // T
-                            }
-                        } else if (i <= 1 + 2 * D) {        // d_c eta
-                            const int c = i - 2 - D;
-                            Ut[c][e][s] = -eta[o + s] * (q - gh[c * npts + o + s]);
-                        } else {                            // d_c beta: Q += u_c d_c beta
-                            const int c = i - 2 - 2 * D;
-                            const double e0 = eta[o + s];
-                            const double t = u[c * npts + o + s] * q;
-                            A0[e][s] += e0 * e0 / 2.0 * t;
-                            A1[e][s] += e0 * t;
-                        }
-                    }
-                }
+                for (int s = 0; s < 2; ++s) f(e, s, scale * (s ? z[0][e].im : z[0][e].re), o + s, ok);
             }
+        };
+        if (i == 0) {                       // m
+            each([&](int e, int s, double q, unsigned o, bool ok) {
+                A0[e][s] = q;
+                if (ok) at32(eta_t, o) = -q;
+            });
+        } else if (i == 1) {                // delta
+            each([&](int e, int s, double q, unsigned, bool) {
+                A1[e][s] = q;
+                A2[e][s] = -q * q;
+            });
+        } else if (i <= 1 + D) {            // d_c delta: P += u_c d_c delta
+            each([&](int e, int s, double q, unsigned, bool) { A2[e][s] += fv[e][s] * q; });
+            if (i == 1 + D) {               // P complete: fold into S, T
+                each([&](int e, int s, double, unsigned o, bool) {
+                    const double et = depth(e, s);
+                    double bt = 0.0;
+#pragma unroll
+                    for (int cc = 0; cc < D; ++cc) bt += at32(gh + cc * npts, o) * at32(u + cc * npts, o);
+                    const double e2 = et * et, mm = A0[e][s], d0 = A1[e][s], pp = A2[e][s];
+                    A0[e][s] = e2 * et / 3.0 * pp + e2 * mm * d0 + et * mm * bt;   // S
+                    A1[e][s] = e2 / 2.0 * pp + et * mm * d0 + mm * bt;            // T
+                });
+            }
+        } else if (i <= 1 + 2 * D) {        // d_c beta: Q += u_c d_c beta
+            each([&](int e, int s, double q, unsigned, bool) {
+                const double et = depth(e, s), t = fv[e][s] * q;
+                A0[e][s] += et * et / 2.0 * t;
+                A1[e][s] += et * t;
+            });
+        } else {                            // d_c eta: U_t less the flux and grad S
+            each([&](int e, int s, double q, unsigned o, bool ok) {
+                if (ok) at32(U_t + c * npts, o) = -e0[e][s] * (q - fv[e][s]) - fv[e][s] * A1[e][s];
+            });
         }
     }
-    // U_t = U_t - T grad h; S (2D: S_x, S_y) forward-transformed
+    // S (2D: S_x, S_y) forward-transformed
     cpx<double> zs[D][EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) {
@@ -407,16 +428,15 @@ __global__ void __launch_bounds__(MAXT) k_rhs_rows_inv(RowGeom g, PtrList<const 
 #pragma unroll
         for (int c = 0; c < D; ++c) zs[c][e] = C<double>(0, 0);
         if (j < g.M && rt.valid) {
-            const size_t o = (size_t)rt.y * g.nx + 2 * j;
+            const unsigned o = rt.y * g.nx + 2 * j;
             double sc[D][2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    U_t[c * npts + o + s] = Ut[c][e][s] - gh[c * npts + o + s] * A1[e][s];
                     if (D == 2) {
-                        const double uc = u[c * npts + o + s];
-                        sc[c][s] = A0[e][s] - eta[o + s] * uc * uc;
+                        const double uc = at32(u + c * npts, o + s);
+                        sc[c][s] = A0[e][s] - e0[e][s] * uc * uc;
                     } else {
                         sc[c][s] = A0[e][s];
                     }
@@ -426,7 +446,7 @@ __global__ void __launch_bounds__(MAXT) k_rhs_rows_inv(RowGeom g, PtrList<const 
             for (int c = 0; c < D; ++c) zs[c][e] = C<double>(sc[c][0], sc[c][1]);
         }
     }
-    // one field at a time: the launch's LDS holds NFG fields
+    // one field at a time: the launch's LDS holds one
 #pragma unroll
     for (int c = 0; c < D; ++c) {
         cpx<double> z1[1][EPC];
@@ -504,7 +524,7 @@ __global__ void __launch_bounds__(256) k_cols_lin(ColGeom g, PtrList<const cpx<T
                                                    T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, G));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     cpx<T> in[NI][EPC];
 #pragma unroll
@@ -555,47 +575,12 @@ struct LinJobs {
     int n;
 };
 
-template <typename T, int EPC>
-__device__ __forceinline__ void col_fft_regs(const ColGeom& g, const ColThread<T>& ct, const cpx<T>* twm,
-                                             cpx<T> (&v)[EPC], bool inverse) {
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-        const int j = ct.t + g.TPC * e;
-        if (j < g.ny) ct.buf[j] = v[e];
-    }
-    __syncthreads();
-    lds_fft<T, EPC, 1, col_swz<T>()>(ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, inverse);
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-        const int j = ct.t + g.TPC * e;
-        if (j < g.ny) v[e] = ct.buf[j];
-    }
-    __syncthreads();
-}
-
-// NF register columns of a block through one y-FFT in lockstep (shared barriers):
-// fields f < nf of v go to LDS (field stride ct.fstride), are transformed and
-// read back.
+// NF register columns of a block through one y-FFT in lockstep (shared barriers).
 template <typename T, int EPC, int NF>
 __device__ __forceinline__ void col_fft_group(const ColGeom& g, const ColThread<T>& ct, const cpx<T>* twm,
                                               cpx<T> (*v)[EPC], bool inverse) {
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = ct.t + g.TPC * e;
-            if (j < g.ny) ct.buf[f * ct.fstride + j] = v[f][e];
-        }
-    __syncthreads();
-    lds_fft<T, EPC, NF, col_swz<T>()>(ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, inverse);
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = ct.t + g.TPC * e;
-            if (j < g.ny) v[f][e] = ct.buf[f * ct.fstride + j];
-        }
-    __syncthreads();
+    reg_fft<T, EPC, NF>(v, ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, inverse);
+    fft_sync(g.TPC);
 }
 
 // The first nf (1..3) register columns of v through one lockstep y-FFT.
@@ -610,7 +595,7 @@ __device__ __forceinline__ void col_fft_first(const ColGeom& g, const ColThread<
 // LK: columns per lockstep transform, 3 (LDS holds three columns per block) or 1
 // (one at a time, for columns of 2048 where three would leave one block per CU).
 template <typename T, int EPC, int NI, int LK>
-__global__ void __launch_bounds__(256) k_cols_lin_jobs(ColGeom g, LinJobs<T> jobs, const cpx<T>* __restrict__ tw,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_cols_lin_jobs(ColGeom g, LinJobs<T> jobs, const cpx<T>* __restrict__ tw,
                                                         T tpx, T tpy, T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -618,14 +603,8 @@ __global__ void __launch_bounds__(256) k_cols_lin_jobs(ColGeom g, LinJobs<T> job
     if (jb >= jobs.n) return;
     const LinJob<T>& J = jobs.j[jb];
     constexpr int NL = LK == 1 ? 1 : (NI < 3 ? NI : 3);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, NL));
-    ColThread<T> ct;
-    ct.c = threadIdx.x / g.TPC;
-    ct.t = threadIdx.x - ct.c * g.TPC;
-    ct.kx = (blockIdx.x - jb * g.nblocks) * g.Cb + ct.c;
-    ct.valid = ct.kx < g.nxh;
-    ct.buf = lds + ct.c * g.ny;
-    ct.fstride = g.Cb * g.ny;
+    const cpx<T>* twm = tw_size(tw, g.ny);
+    const ColThread<T> ct = col_thread_at<T>(g, lds, (int)blockIdx.x - jb * g.nblocks);
     const int ny = g.ny;
     cpx<T> in[NI][EPC];
 #pragma unroll
@@ -633,7 +612,7 @@ __global__ void __launch_bounds__(256) k_cols_lin_jobs(ColGeom g, LinJobs<T> job
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             const int j = ct.t + g.TPC * e;
-            in[i][e] = (i < J.ni && ct.valid && j < ny) ? J.src[i][(size_t)ct.kx * ny + j] : C<T>(0, 0);
+            in[i][e] = (i < J.ni && ct.valid && j < ny) ? at32(J.src[i], ct.kx * ny + j) : C<T>(0, 0);
         }
     }
     if (ny > 1 && LK == 1) {
@@ -679,7 +658,7 @@ __global__ void __launch_bounds__(256) k_cols_lin_jobs(ColGeom g, LinJobs<T> job
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
                 const int j = ct.t + g.TPC * e;
-                if (j < ny) J.dst[o][(size_t)ct.kx * ny + j] = out[o][e];
+                if (j < ny) at32(J.dst[o], ct.kx * ny + j) = out[o][e];
             }
         }
     }
@@ -693,7 +672,7 @@ __global__ void __launch_bounds__(256) k_cols_precond(ColGeom g, PtrList<const c
                                                        T sig, T alp, T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     cpx<T> in[D][EPC];
     const cpx<T>* srcs[D];
@@ -737,37 +716,28 @@ __global__ void __launch_bounds__(256) k_cols_precond(ColGeom g, PtrList<const c
 // Every kernel returns at once when the solve is done.
 // ---------------------------------------------------------------------------
 
-// Broadcast thread 0's value to the block.
-template <bool LDS_ONLY = false>
-__device__ __forceinline__ double bcast(double v, double* slot) {
-    if (threadIdx.x == 0) *slot = v;
-    if (LDS_ONLY)
-        block_lds_barrier();
-    else
-        __syncthreads();
-    const double r = *slot;
-    if (LDS_ONLY)
-        block_lds_barrier();
-    else
-        __syncthreads();
-    return r;
+// The scalars a column pass reads, in one batch of scalar loads.
+struct PcgScal {
+    double rho, rho_prev, bb, tol2, sig, alp, inv_n;
+    int iter, max_iter, done, first, init_bb;
+};
+__device__ __forceinline__ PcgScal pcg_scalars(const SolveScal* sc) {
+    return PcgScal{sc->rho,  sc->rho_prev, sc->bb,   sc->tol2,  sc->sig,    sc->alp,
+                   sc->inv_n, sc->iter,     sc->max_iter, sc->done, sc->first, sc->init_bb};
 }
 
-// Stop test and beta from the partials of the last update pass (or of the
+// Stop test and beta from the sums (r.z, r.r) of the last update pass (or of the
 // initial residual).  Identical in every block; block 0 publishes.  Returns done.
-__device__ __forceinline__ bool pcg_iterate_state(SolveScal* __restrict__ sc, const double* __restrict__ part,
-                                                  int nb3, double* red, double* slot, double& beta_out) {
-    double tot[2];
-    final_sum<2>(part + PART_C3, nb3, tot, red);
-    const double rz = bcast(tot[0], slot) * sc->inv_n;
-    const double rr = bcast(tot[1], slot + 1) * sc->inv_n;
-    const int first = sc->first;
+__device__ __forceinline__ bool pcg_iterate_state(SolveScal* __restrict__ sc, const PcgScal& s, const double (&tot)[2],
+                                                  double& beta_out) {
+    const double rz = tot[0] * s.inv_n;
+    const double rr = tot[1] * s.inv_n;
     // init_bb: ||b||^2 is the first r.r seen (r_0 = b); taken once, while bb is unset
-    const double bb = (sc->init_bb && first && sc->iter == 0 && sc->bb == 0.0) ? rr : sc->bb;
+    const double bb = (s.init_bb && s.first && s.iter == 0 && s.bb == 0.0) ? rr : s.bb;
     const bool bad = !(rr == rr) || !(rz == rz) || !(rr <= 1.0e300);
-    const bool conv = !bad && (bb == 0.0 || rr <= sc->tol2 * bb);
-    const bool done = bad || conv || sc->iter >= sc->max_iter;
-    const double beta = first ? 0.0 : rz / sc->rho_prev;
+    const bool conv = !bad && (bb == 0.0 || rr <= s.tol2 * bb);
+    const bool done = bad || conv || s.iter >= s.max_iter;
+    const double beta = s.first ? 0.0 : rz / s.rho_prev;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         sc->rr = rr;
         sc->bb = bb;
@@ -789,66 +759,78 @@ __device__ __forceinline__ bool pcg_iterate_state(SolveScal* __restrict__ sc, co
 enum { C1_UPDATE = 0, C1_COPY = 1, C1_ACCUM = 2 };
 
 template <typename T, int EPC, int D, int MODE>
-__global__ void __launch_bounds__(256) k_pcg_c1(ColGeom g, const cpx<T>* __restrict__ tw,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, const double* __restrict__ part,
                                                  int nb3, const cpx<T>* __restrict__ rh, cpx<T>* __restrict__ ph,
                                                  const cpx<T>* __restrict__ xsrc, cpx<T>* __restrict__ H,
                                                  size_t NS, T tpx, T tpy, const cpx<float>* __restrict__ dx) {
-    if (sc->done) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     __shared__ double red[32];
-    __shared__ double slot[2];
+    const PcgScal s0 = pcg_scalars(sc);
+    if (s0.done) return;
+    const cpx<T>* twm = tw_size(tw, g.ny);
+    const ColThread<T> ct = col_thread<T>(g, lds);
+    // the partials, r and the last p, in flight across the reduction
+    double pb[PF_K][2];
+    cpx<T> in[D][EPC], last[D][EPC];
+    if (MODE == C1_UPDATE) {
+        partials_fetch<2>(part + PART_C3, nb3, pb);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const cpx<T>* src = MODE == C1_UPDATE ? rh : MODE == C1_COPY ? xsrc : ph;
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+        bool ok;
+        const unsigned idx = col_index(g, ct, ct.t + g.TPC * e, ok);
+#pragma unroll
+        for (int c = 0; c < D; ++c) {
+            in[c][e] = at32(src + c * NS, idx);
+            if (MODE == C1_UPDATE) last[c][e] = at32(ph + c * NS, idx);
+            if (MODE == C1_ACCUM) {
+                const cpx<float> x = at32(dx + c * NS, idx);
+                last[c][e] = C<T>((T)x.re, (T)x.im);
+            }
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
     double beta_d = 0.0;
     if (MODE == C1_UPDATE) {
-        if (pcg_iterate_state(sc, part, nb3, red, slot, beta_d)) return;
+        double tot[2];
+        partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+        if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
     }
-    // (loading r and p ahead of this reduction, in flight across it, measured
-    // slower: 17.0 -> 18.5 us at 1024^2 FP64)
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D + 1));
-    const ColThread<T> ct = col_thread<T>(g, lds);
-    const T beta = (T)beta_d, sig = (T)sc->sig, alp = (T)sc->alp, inv_n = (T)sc->inv_n;
+    const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
     const T kx = wavenumber<T>(ct.kx, g.nx, tpx);
     cpx<T> o[D + 1][EPC];
 #pragma unroll
     for (int e = 0; e < EPC; ++e) {
         const int j = ct.t + g.TPC * e;
+        const bool ok = ct.valid && j < g.ny;
+        const unsigned idx = ok ? (unsigned)(ct.kx * g.ny + j) : 0u;
+        const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
+        cpx<T> p[D];
+        if (MODE == C1_UPDATE) {
+            cpx<T> r[D], z[D];
 #pragma unroll
-        for (int c = 0; c <= D; ++c) o[c][e] = C<T>(0, 0);
-        if (ct.valid && j < g.ny) {
-            const size_t idx = (size_t)ct.kx * g.ny + j;
-            const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
-            cpx<T> p[D];
-            if (MODE == C1_COPY) {
+            for (int c = 0; c < D; ++c) r[c] = in[c][e];
+            precond_mode<T, D>(kx, ky, sig, alp, r, z);
+            // beta = 0 on the first iteration: p = z, the unset direction is not used
 #pragma unroll
-                for (int c = 0; c < D; ++c) p[c] = xsrc[c * NS + idx];
-            } else if (MODE == C1_ACCUM) {
+            for (int c = 0; c < D; ++c) p[c] = (beta != (T)0) ? z[c] + beta * last[c][e] : z[c];
+        } else {
 #pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    const cpx<T> x = ph[c * NS + idx];
-                    const cpx<float> e = dx[c * NS + idx];
-                    p[c] = cpx<T>{x.re + (T)e.re, x.im + (T)e.im};
-                    ph[c * NS + idx] = p[c];
-                }
-            } else {
-                cpx<T> r[D], z[D];
-#pragma unroll
-                for (int c = 0; c < D; ++c) r[c] = rh[c * NS + idx];
-                precond_mode<T, D>(kx, ky, sig, alp, r, z);
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    // beta = 0 on the first iteration: p = z without reading the
-                    // previous (unset) direction
-                    p[c] = (beta != (T)0) ? z[c] + beta * ph[c * NS + idx] : z[c];
-                    ph[c * NS + idx] = p[c];
-                }
-            }
-            cpx<T> dv = ik(kx, p[0]);
-            if (D == 2) dv = dv + ik(ky, p[1 % D]);
-#pragma unroll
-            for (int c = 0; c < D; ++c) o[c][e] = inv_n * p[c];
-            o[D][e] = inv_n * dv;
+            for (int c = 0; c < D; ++c) p[c] = MODE == C1_ACCUM ? in[c][e] + last[c][e] : in[c][e];
         }
+        if (MODE != C1_COPY && ok) {
+#pragma unroll
+            for (int c = 0; c < D; ++c) at32(ph + c * NS, idx) = p[c];
+        }
+        cpx<T> dv = ik(kx, p[0]);
+        if (D == 2) dv = dv + ik(ky, p[1 % D]);
+#pragma unroll
+        for (int c = 0; c < D; ++c) o[c][e] = inv_n * p[c];
+        o[D][e] = inv_n * dv;
     }
     cpx<T>* dsts[D + 1];
 #pragma unroll
@@ -879,11 +861,13 @@ __global__ void __launch_bounds__(256) k_pcg_check(SolveScal* __restrict__ sc, c
         if (threadIdx.x == 0) inner_close(sc, inner);
         __syncthreads();
     }
-    if (!sc->done) {
+    const PcgScal s0 = pcg_scalars(sc);
+    if (!s0.done) {
         __shared__ double red[32];
-        __shared__ double slot[2];
-        double beta;
-        pcg_iterate_state(sc, part, nb3, red, slot, beta);
+        double beta, pb[PF_K][2], tot[2];
+        partials_fetch<2>(part + PART_C3, nb3, pb);
+        partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+        pcg_iterate_state(sc, s0, tot, beta);
     }
     // block 0 thread 0 wrote the scalars above and reads them back here
     if (pub && blockIdx.x == 0 && threadIdx.x == 0) publish_flags(sc, pub, seq);
@@ -898,37 +882,31 @@ __global__ void k_publish_flags(const SolveScal* __restrict__ sc, int* d, int se
     if (threadIdx.x == 0 && blockIdx.x == 0) publish_flags(sc, d, seq);
 }
 
-template <typename T, int EPC, int D, bool SEQ, int MAXT = 1024>
+// Row pass R1 on rows of 256 threads and more: a block's fields one after another,
+// the next one's loads in flight meanwhile (three fields of LDS do not fit).
+template <typename T, int D, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_pcg_r1(RowGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, cpx<T>* H, size_t NS,
                                                  const T* __restrict__ eta, const T* __restrict__ gh,
                                                  double* __restrict__ part) {
+    constexpr int EPC = 4;
     if (sc->done) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     __shared__ double red[16];
-    constexpr int NF = SEQ ? 1 : D + 1;
-    const cpx<T>* twm = twl_setup<T>(tw, g.M, lds + row_lds_data(g, NF));
+    const cpx<T>* twm = tw_size(tw, g.M);
     const RowThread<T> rt = row_thread<T>(g, lds);
     double acc[1] = {0.0};
     cpx<T> v[D + 1][EPC];
-    if (SEQ) {
+    RowPairs<T, EPC> X;
+    row_fetch<T, EPC>(g, rt, H, X);
 #pragma unroll
-        for (int c = 0; c <= D; ++c) {
-            const cpx<T>* Hc[1] = {H + c * NS};
-            cpx<T> vc[1][EPC];
-            row_inverse<T, EPC, 1>(g, rt, Hc, tw, twm, vc);
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) v[c][e] = vc[0][e];
-        }
-    } else {
-        const cpx<T>* Hs[D + 1];
-#pragma unroll
-        for (int c = 0; c <= D; ++c) Hs[c] = H + c * NS;
-        if (EPC <= 2)
-            row_inverse_batched<T, EPC, D + 1>(g, rt, Hs, tw, twm, v);
-        else
-            row_inverse<T, EPC, D + 1>(g, rt, Hs, tw, twm, v);
+    for (int c = 0; c <= D; ++c) {
+        row_join<T, EPC>(g, rt, X, rt.lds, tw);
+        if (c < D) row_fetch<T, EPC>(g, rt, H + (c + 1) * NS, X);
+        block_lds_barrier();
+        row_inverse_lds<T, EPC, 1>(g, rt, twm, v + c);
+        block_lds_barrier();
     }
     const size_t npts = (size_t)g.nx * g.ny;
     const T third = (T)1 / (T)3, half = (T)0.5;
@@ -936,15 +914,15 @@ __global__ void __launch_bounds__(MAXT) k_pcg_r1(RowGeom g, const cpx<T>* __rest
     for (int e = 0; e < EPC; ++e) {
         const int j = rt.t + g.TPR * e;
         if (j < g.M && rt.valid) {
-            const size_t o = (size_t)rt.y * g.nx + 2 * j;
+            const unsigned o = rt.y * g.nx + 2 * j;
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
-                const T et = eta[o + s];
+                const T et = at32(eta, o + s);
                 T hc[D], pc[D];
                 T bt = 0;
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
-                    hc[c] = gh[c * npts + o + s];
+                    hc[c] = at32(gh + c * npts, o + s);
                     pc[c] = s ? v[c][e].im : v[c][e].re;
                     bt += hc[c] * pc[c];
                 }
@@ -966,24 +944,233 @@ __global__ void __launch_bounds__(MAXT) k_pcg_r1(RowGeom g, const cpx<T>* __rest
             }
         }
     }
-    if (SEQ) {
 #pragma unroll
-        for (int c = 0; c <= D; ++c) {
-            cpx<T>* Hc[1] = {H + c * NS};
-            cpx<T> vc[1][EPC];
+    for (int c = 0; c <= D; ++c) {
+        cpx<T>* Hc[1] = {H + c * NS};
+        cpx<T> vc[1][EPC];
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) vc[0][e] = v[c][e];
-            row_forward<T, EPC, 1>(g, rt, vc, Hc, tw, twm, (T)1);
-        }
-    } else {
-        cpx<T>* Hs[D + 1];
-#pragma unroll
-        for (int c = 0; c <= D; ++c) Hs[c] = H + c * NS;
-        row_forward<T, EPC, D + 1>(g, rt, v, Hs, tw, twm, (T)1);
+        for (int e = 0; e < EPC; ++e) vc[0][e] = v[c][e];
+        row_forward<T, EPC, 1>(g, rt, vc, Hc, tw, twm, (T)1);
     }
     if (part) {
         block_sum<1>(acc, red);
         if (threadIdx.x == 0) part[PART_C2 + blockIdx.x] = acc[0];
+    }
+}
+
+// Row pass R1 on shorter rows: each of the D + 1 fields has R TPR threads of its own
+// (whole waves), which transform it, exchange the values with the other fields'
+// through LDS and form that field's row of M(x).  Against all fields in lockstep on
+// the same threads, three times the waves on a third of the serial work each
+// (FP64 256 x 128 12.0 -> 8.0 us, 512 x 512 15.2 -> 13.7, FP32 512 x 512 7.4 -> 6.5).
+template <typename T, int D>
+__global__ void __launch_bounds__((D + 1) * 256) k_pcg_r1f(RowGeom g, const cpx<T>* __restrict__ tw,
+                                                           SolveScal* __restrict__ sc, cpx<T>* H, size_t NS,
+                                                           const T* __restrict__ eta, const T* __restrict__ gh,
+                                                           double* __restrict__ part) {
+    if (sc->done) return;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
+    __shared__ double red[16];
+    constexpr int EPC = 4;
+    const cpx<T>* twm = tw_size(tw, g.M);
+    const int lgG = g.lgR + g.lgT, G = 1 << lgG;
+    const int f = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> lgG);
+    const int fs = g.R * (g.M + 1);
+    const RowThread<T> rt = row_thread_at<T>(g, lds + f * fs, blockIdx.x, threadIdx.x & (G - 1));
+    cpx<T>* Hf = H + f * NS;
+    RowPairs<T, EPC> X;
+    row_fetch<T, EPC>(g, rt, Hf, X);
+    // eta and grad h at this thread's points, in flight across the transform
+    const size_t npts = (size_t)g.nx * g.ny;
+    cpx<T> et2[EPC], hc2[D][EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+        const int j = rt.t + g.TPR * e;
+        const unsigned o = (j < g.M && rt.valid) ? rt.y * g.nx + 2 * j : 0u;
+        et2[e] = C<T>(at32(eta, o), at32(eta, o + 1));
+#pragma unroll
+        for (int c = 0; c < D; ++c) hc2[c][e] = C<T>(at32(gh + c * npts, o), at32(gh + c * npts, o + 1));
+    }
+    row_join<T, EPC>(g, rt, X, rt.lds, tw);
+    fft_sync(G);
+    cpx<T> z[1][EPC];
+    row_inverse_lds<T, EPC, 1>(g, rt, twm, z);
+    fft_sync(g.TPR);
+    cpx<T>* rowb = lds + rt.r * (g.M + 1);   // this row of field 0
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+        const int j = rt.t + g.TPR * e;
+        if (j < g.M) rowb[f * fs + j] = z[0][e];
+    }
+    block_lds_barrier();
+    double acc[1] = {0.0};
+    const T third = (T)1 / (T)3, half = (T)0.5;
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) {
+        const int j = rt.t + g.TPR * e;
+        if (j < g.M && rt.valid) {
+            cpx<T> p[D + 1];
+#pragma unroll
+            for (int c = 0; c <= D; ++c) p[c] = rowb[c * fs + j];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const T et = s ? et2[e].im : et2[e].re;
+                T hf = 0, pf = 0, bt = 0;
+#pragma unroll
+                for (int c = 0; c < D; ++c) {
+                    const T hc = s ? hc2[c][e].im : hc2[c][e].re, pc = s ? p[c].im : p[c].re;
+                    bt += hc * pc;
+                    if (c == f) {
+                        hf = hc;
+                        pf = pc;
+                    }
+                }
+                const T dl = s ? p[D].im : p[D].re;
+                const T e2 = et * et;
+                const T w1 = third * e2 * et * dl + half * e2 * bt;
+                const T w2 = half * e2 * dl + et * bt;
+                // B-density: eta |p|^2 + eta^3/3 dl^2 + eta^2 dl bt + eta bt^2 = p.a + dl w1
+                acc[0] += f < D ? (double)et * ((double)pf * (double)pf)
+                                : (double)dl * (double)w1 + (double)bt * (double)w2;
+                const T out = f < D ? et * pf + hf * w2 : w1;
+                if (s) z[0][e].im = out; else z[0][e].re = out;
+            }
+        }
+    }
+    block_lds_barrier();   // the other fields' threads have read this field's values
+    cpx<T>* Hc[1] = {Hf};
+    row_forward<T, EPC, 1>(g, rt, z, Hc, tw, twm, (T)1);
+    if (part) {
+        block_sum<1>(acc, red);
+        if (threadIdx.x == 0) part[PART_C2 + blockIdx.x] = acc[0];
+    }
+}
+
+// Row pass R1 of the line of 16384 points (M = 8192 = 64 x 128), which fits one
+// workgroup only with its registers spilled and keeps one compute unit busy (88 us
+// against 11.6 for these three launches): in place over 64 waves, as 64-point transforms of the columns
+// k = 128 a + b of the spectrum (k_pcg_long_cols<true>: real split, then over a), the
+// 128-point transforms of the rows c (k_pcg_long_rows, with the pointwise operator) at
+// the pairs j = c + 64 d, and the way back (k_pcg_long_cols<false>).
+//   z_{c + 64 d} = sum_b W_128^{-db} W_M^{-cb} sum_a Z_{128 a + b} W_64^{-ac}.
+// A block of one wave takes both fields of column b and of the column of its mirrored
+// entries, 128 - b (0 and 64 together), 16 threads each.
+constexpr int LONG_M = 8192, LONG_A = 64, LONG_B = 128;
+template <typename T, bool INV>
+__global__ void __launch_bounds__(64) k_pcg_long_cols(const cpx<T>* __restrict__ tw,
+                                                      const SolveScal* __restrict__ sc, cpx<T>* H, size_t NS) {
+    if (sc->done) return;
+    __shared__ cpx<T> lds[4 * LONG_A];
+    const int col = threadIdx.x >> 4, t = threadIdx.x & 15, s = col & 1, u = blockIdx.x;
+    const int b = s == 0 ? u : (u == 0 ? LONG_B / 2 : LONG_B - u);
+    cpx<T>* Hf = H + (col >> 1) * NS;
+    const cpx<T>* tw2 = tw_size(tw, 2 * LONG_M);
+    const cpx<T>* twM = tw_size(tw, LONG_M);
+    const cpx<T>* twA = tw_size(tw, LONG_A);
+    cpx<T>* buf = lds + col * LONG_A;
+    cpx<T> v[1][4], w[4], wc[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        w[e] = tw2[LONG_B * (t + 16 * e) + b];
+        wc[e] = twM[(t + 16 * e) * b];
+    }
+    if (INV) {
+        cpx<T> xm[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int k = LONG_B * (t + 16 * e) + b;
+            v[0][e] = Hf[k];
+            xm[e] = Hf[LONG_M - k];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const cpx<T> xk = v[0][e];
+            if (e == 0 && t == 0 && b == 0) {
+                v[0][e] = C<T>(xk.re + xm[e].re, xk.re - xm[e].re);
+            } else {
+                cpx<T> zm;
+                split_join(xk, xm[e], w[e], v[0][e], zm);
+            }
+        }
+        reg_fft<T, 4, 1>(v, buf, 0, LONG_A, t, 16, twA, true);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) Hf[LONG_B * (t + 16 * e) + b] = v[0][e] * cj(wc[e]);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[0][e] = Hf[LONG_B * (t + 16 * e) + b] * wc[e];
+    reg_fft<T, 4, 1>(v, buf, 0, LONG_A, t, 16, twA, false);
+    fft_sync(16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) buf[t + 16 * e] = v[0][e];
+    fft_sync(16);
+    const cpx<T>* mir = u == 0 ? buf : lds + (col ^ 1) * LONG_A;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int a = t + 16 * e, k = LONG_B * a + b;
+        const cpx<T> zk = v[0][e];
+        if (k == 0) {
+            Hf[0] = C<T>(zk.re + zk.im, 0);
+            Hf[LONG_M] = C<T>(zk.re - zk.im, 0);
+        } else {
+            cpx<T> xk, xm;
+            split_part(zk, mir[b == 0 ? LONG_A - a : LONG_A - 1 - a], w[e], xk, xm);
+            Hf[k] = xk;
+        }
+    }
+}
+// Rows c of the line of 16384 points: one wave per row, 32 threads per field; the
+// pointwise operator as in k_pcg_r1f.
+template <typename T>
+__global__ void __launch_bounds__(64) k_pcg_long_rows(const cpx<T>* __restrict__ tw,
+                                                      const SolveScal* __restrict__ sc, cpx<T>* H, size_t NS,
+                                                      const T* __restrict__ eta, const T* __restrict__ gh,
+                                                      double* __restrict__ part) {
+    if (sc->done) return;
+    __shared__ cpx<T> lds[2 * LONG_B];
+    __shared__ double red[16];
+    const int f = threadIdx.x >> 5, t = threadIdx.x & 31, c = blockIdx.x;
+    cpx<T>* row = H + f * NS + LONG_B * c;
+    const cpx<T>* twB = tw_size(tw, LONG_B);
+    cpx<T> v[1][4], et2[4], h2[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[0][e] = row[t + 32 * e];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int o = 2 * (c + LONG_A * (t + 32 * e));
+        et2[e] = C<T>(eta[o], eta[o + 1]);
+        h2[e] = C<T>(gh[o], gh[o + 1]);
+    }
+    cpx<T>* buf = lds + f * LONG_B;
+    reg_fft<T, 4, 1>(v, buf, 0, LONG_B, t, 32, twB, true);
+    fft_sync(32);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) buf[t + 32 * e] = v[0][e];
+    fft_sync(32);
+    double acc[1] = {0.0};
+    const T third = (T)1 / (T)3, half = (T)0.5;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const cpx<T> p2 = lds[t + 32 * e], d2 = lds[LONG_B + t + 32 * e];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const T et = s ? et2[e].im : et2[e].re, h = s ? h2[e].im : h2[e].re;
+            const T p = s ? p2.im : p2.re, dl = s ? d2.im : d2.re;
+            const T bt = h * p, e2 = et * et;
+            const T w1 = third * e2 * et * dl + half * e2 * bt;
+            const T w2 = half * e2 * dl + et * bt;
+            acc[0] += f == 0 ? (double)et * ((double)p * (double)p) : (double)dl * (double)w1 + (double)bt * (double)w2;
+            const T out = f == 0 ? et * p + h * w2 : w1;
+            if (s) v[0][e].im = out; else v[0][e].re = out;
+        }
+    }
+    reg_fft<T, 4, 1>(v, buf, 0, LONG_B, t, 32, twB, false);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) row[t + 32 * e] = v[0][e];
+    if (part) {
+        block_sum<1>(acc, red);
+        if (threadIdx.x == 0) part[PART_C2 + c] = acc[0];
     }
 }
 
@@ -1045,7 +1232,7 @@ __device__ __forceinline__ cpx<T> wall_project(int c, cpx<T> a, cpx<T> b, int kx
 // projected onto the symmetric modes before it is used (rounding would otherwise
 // seed the other parity, which the iteration amplifies at low wavenumbers).
 template <typename T, int EPC, int D, int MODE, bool WALL = false>
-__global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restrict__ tw,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c2(ColGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, const cpx<T>* __restrict__ H,
                                                  size_t NS, cpx<T>* __restrict__ qh, const cpx<T>* __restrict__ ph,
                                                  cpx<T>* __restrict__ xh, const cpx<T>* __restrict__ bh,
@@ -1053,13 +1240,13 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
                                                  T tpx, T tpy) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    __shared__ double red[32];
-    __shared__ double slot[1];
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D + 1));
+    __shared__ double red[64];
+    const PcgScal s0 = pcg_scalars(sc);
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     // the row pass's columns do not depend on alpha: loaded right after the
     // partials of the reduction, in flight across it (LDS-only barriers)
-    if (sc->done) return;
+    if (s0.done) return;
     double pb[PF_K][1];
     if (MODE == C2_UPDATE) partials_fetch<1>(part + PART_C2, nb_r1, pb);
     if (MODE == C2_RESID_INIT) partials_fetch<1>(part + PART_GEN, nb_r1, pb);
@@ -1076,8 +1263,8 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
     bool zero_x = false;
     if (MODE == C2_RESID_INIT) {
         double tot[1];
-        partials_sum<1, true>(part + PART_GEN, nb_r1, pb, tot, red);
-        const double bb = bcast<true>(tot[0], slot) * sc->inv_n;
+        partials_sum<1>(part + PART_GEN, nb_r1, pb, tot, red);
+        const double bb = tot[0] * s0.inv_n;
         const bool bad = !(bb == bb) || bb > 1.0e300;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->bb = bb;
@@ -1087,25 +1274,25 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
             }
         }
         if (bad) return;
-        zero_x = !sc->init_bb && bb == 0.0;
+        zero_x = !s0.init_bb && bb == 0.0;
     }
     if (MODE == C2_UPDATE) {
         double tot[1];
-        partials_sum<1, true>(part + PART_C2, nb_r1, pb, tot, red);
-        const double pq = bcast<true>(tot[0], slot);
-        const double a = sc->rho / pq;
+        partials_sum<1>(part + PART_C2, nb_r1, pb, tot, red);
+        const double pq = tot[0];
+        const double a = s0.rho / pq;
         alpha = (T)a;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pq = pq;
             sc->alpha = a;
-            sc->rho_prev = sc->rho;
-            sc->iter = sc->iter + 1;
+            sc->rho_prev = s0.rho;
+            sc->iter = s0.iter + 1;
             sc->first = 0;
         }
     }
     col_fft<T, EPC, D + 1>(g, ct, twm, in);
     const T kx = wavenumber<T>(ct.kx, g.nx, tpx);
-    const T sig = (T)sc->sig, alp = (T)sc->alp;
+    const T sig = (T)s0.sig, alp = (T)s0.alp;
     const double w = ct.valid ? half_weight(ct.kx, g.nx) : 0.0;
     double acc[2] = {0.0, 0.0};
     if (WALL && MODE != C2_STORE) {
@@ -1117,7 +1304,7 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
 #pragma unroll
             for (int c = 0; c < D; ++c) rn[c][e] = C<T>(0, 0);
             if (ct.valid && j < g.ny) {
-                const size_t idx = (size_t)ct.kx * g.ny + j;
+                const unsigned idx = ct.kx * g.ny + j;
                 const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
                 const cpx<T> wv = in[D][e];
 #pragma unroll
@@ -1125,13 +1312,13 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
                     const T kc = (c == 0) ? kx : ky;
                     const cpx<T> q = in[c][e] - ik(kc, wv);
                     if (MODE == C2_RESID) {
-                        rn[c][e] = bh[c * NS + idx] - q;
+                        rn[c][e] = at32(bh + c * NS, idx) - q;
                     } else if (MODE == C2_RESID_INIT) {
-                        rn[c][e] = zero_x ? C<T>(0, 0) : bh[c * NS + idx] - q;
-                        if (zero_x) xh[c * NS + idx] = C<T>(0, 0);
+                        rn[c][e] = zero_x ? C<T>(0, 0) : at32(bh + c * NS, idx) - q;
+                        if (zero_x) at32(xh + c * NS, idx) = C<T>(0, 0);
                     } else {
-                        xh[c * NS + idx] = xh[c * NS + idx] + alpha * ph[c * NS + idx];
-                        rn[c][e] = rh[c * NS + idx] - alpha * q;
+                        at32(xh + c * NS, idx) = at32(xh + c * NS, idx) + alpha * at32(ph + c * NS, idx);
+                        rn[c][e] = at32(rh + c * NS, idx) - alpha * q;
                     }
                     ct.buf[c * ct.fstride + j] = rn[c][e];
                 }
@@ -1142,14 +1329,14 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
         for (int e = 0; e < EPC; ++e) {
             const int j = ct.t + g.TPC * e;
             if (ct.valid && j < g.ny) {
-                const size_t idx = (size_t)ct.kx * g.ny + j;
+                const unsigned idx = ct.kx * g.ny + j;
                 const int jm = (g.ny - j) & (g.ny - 1);
                 const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
                 cpx<T> r[D], z[D];
 #pragma unroll
                 for (int c = 0; c < D; ++c) {
                     r[c] = wall_project<T, D>(c, rn[c][e], ct.buf[c * ct.fstride + jm], ct.kx, g.nx, j, g.ny);
-                    rh[c * NS + idx] = r[c];
+                    at32(rh + c * NS, idx) = r[c];
                 }
                 precond_mode<T, D>(kx, ky, sig, alp, r, z);
 #pragma unroll
@@ -1159,7 +1346,7 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
                 }
             }
         }
-        block_sum<2>(acc, red);
+        block_sum<2>(acc, red + 32);
         if (threadIdx.x == 0) {
             part[PART_C3 + 2 * blockIdx.x] = acc[0];
             part[PART_C3 + 2 * blockIdx.x + 1] = acc[1];
@@ -1170,7 +1357,7 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
     for (int e = 0; e < EPC; ++e) {
         const int j = ct.t + g.TPC * e;
         if (ct.valid && j < g.ny) {
-            const size_t idx = (size_t)ct.kx * g.ny + j;
+            const unsigned idx = ct.kx * g.ny + j;
             const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
             const cpx<T> wv = in[D][e];
             cpx<T> r[D], z[D];
@@ -1179,18 +1366,18 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
                 const T kc = (c == 0) ? kx : ky;
                 const cpx<T> q = in[c][e] - ik(kc, wv);
                 if (MODE == C2_STORE) {
-                    qh[c * NS + idx] = q;
+                    at32(qh + c * NS, idx) = q;
                 } else if (MODE == C2_RESID) {
-                    r[c] = bh[c * NS + idx] - q;
-                    rh[c * NS + idx] = r[c];
+                    r[c] = at32(bh + c * NS, idx) - q;
+                    at32(rh + c * NS, idx) = r[c];
                 } else if (MODE == C2_RESID_INIT) {
-                    r[c] = zero_x ? C<T>(0, 0) : bh[c * NS + idx] - q;
-                    rh[c * NS + idx] = r[c];
-                    if (zero_x) xh[c * NS + idx] = C<T>(0, 0);
+                    r[c] = zero_x ? C<T>(0, 0) : at32(bh + c * NS, idx) - q;
+                    at32(rh + c * NS, idx) = r[c];
+                    if (zero_x) at32(xh + c * NS, idx) = C<T>(0, 0);
                 } else {
-                    xh[c * NS + idx] = xh[c * NS + idx] + alpha * ph[c * NS + idx];
-                    r[c] = rh[c * NS + idx] - alpha * q;
-                    rh[c * NS + idx] = r[c];
+                    at32(xh + c * NS, idx) = at32(xh + c * NS, idx) + alpha * at32(ph + c * NS, idx);
+                    r[c] = at32(rh + c * NS, idx) - alpha * q;
+                    at32(rh + c * NS, idx) = r[c];
                 }
             }
             if (MODE != C2_STORE) {
@@ -1204,7 +1391,7 @@ __global__ void __launch_bounds__(256) k_pcg_c2(ColGeom g, const cpx<T>* __restr
         }
     }
     if (MODE != C2_STORE) {
-        block_sum<2>(acc, red);
+        block_sum<2>(acc, red + 32);
         if (threadIdx.x == 0) {
             part[PART_C3 + 2 * blockIdx.x] = acc[0];
             part[PART_C3 + 2 * blockIdx.x + 1] = acc[1];
@@ -1229,7 +1416,7 @@ __global__ void __launch_bounds__(256) k_pcg_setup(ColGeom g, const cpx<T>* __re
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     __shared__ double red[32];
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D + 1));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const int job = GUESS ? (int)blockIdx.x / g.nblocks : 0;
     const ColThread<T> ct = col_thread_at<T>(g, lds, (int)blockIdx.x - job * g.nblocks);
     const double w = ct.valid ? half_weight(ct.kx, g.nx) : 0.0;
@@ -1264,10 +1451,10 @@ __global__ void __launch_bounds__(256) k_pcg_setup(ColGeom g, const cpx<T>* __re
             const int j = ct.t + g.TPC * e;
             o[0][e] = C<T>(0, 0);
             if (ct.valid && j < g.ny) {
-                const size_t idx = (size_t)ct.kx * g.ny + j;
+                const unsigned idx = ct.kx * g.ny + j;
                 const T ky = (D == 2) ? wavenumber<T>(j, g.ny, tpy) : (T)0;
 #pragma unroll
-                for (int c = 0; c < D; ++c) xh[c * NS + idx] = vu[c][e];
+                for (int c = 0; c < D; ++c) at32(xh + c * NS, idx) = vu[c][e];
                 cpx<T> dv = ik(kx, vu[0][e]);
                 if (D == 2) dv = dv + ik(ky, vu[1 % D][e]);
                 o[0][e] = inv_n * dv;
@@ -1289,14 +1476,14 @@ __global__ void __launch_bounds__(256) k_pcg_setup(ColGeom g, const cpx<T>* __re
     for (int e = 0; e < EPC; ++e) {
         const int j = ct.t + g.TPC * e;
         if (ct.valid && j < g.ny) {
-            const size_t idx = (size_t)ct.kx * g.ny + j;
+            const unsigned idx = ct.kx * g.ny + j;
             cpx<T> r[D], z[D];
 #pragma unroll
             for (int c = 0; c < D; ++c) {
                 r[c] = vb[c][e];
-                if (bh) bh[c * NS + idx] = r[c];
-                rh[c * NS + idx] = r[c];
-                if (!GUESS) xh[c * NS + idx] = C<T>(0, 0);
+                if (bh) at32(bh + c * NS, idx) = r[c];
+                at32(rh + c * NS, idx) = r[c];
+                if (!GUESS) at32(xh + c * NS, idx) = C<T>(0, 0);
             }
             if (GUESS) {
 #pragma unroll
@@ -1334,7 +1521,7 @@ __global__ void __launch_bounds__(256) k_cols_to_S(ColGeom g, const cpx<T>* __re
                                                     cpx<T>* __restrict__ Sdst) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     cpx<T> v[D][EPC];
     const cpx<T>* srcs[D];
@@ -1355,7 +1542,7 @@ __global__ void __launch_bounds__(256) k_cols_from_S(ColGeom g, const cpx<T>* __
                                                       cpx<T>* __restrict__ H, T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, D));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     cpx<T> v[D][EPC];
     const cpx<T>* srcs[D];
@@ -1387,7 +1574,7 @@ __global__ void __launch_bounds__(256) k_cols_resample(ColGeom g, const cpx<T>* 
                                                         T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, NF));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     const bool col_kept = ct.valid && ct.kx < kx_keep;
     cpx<T> v[NF][EPC];

@@ -220,33 +220,32 @@ struct RowLaunch {
     size_t lds;
     int epc;
 };
-// wide: on 2D rows of 64 to 1024 points, two entries per thread and up to
-// 512-thread blocks, so that more waves are resident to hide the transposed
-// accesses' latency (the grid has only ny / R blocks); taken by the Krylov row
-// pass and the plain row transforms.
+// Rows per block: 256 threads where a row has fewer, and on 2D grids fewer rows
+// (down to 64 threads) while the launch has fewer than 256 blocks, one per compute
+// unit.  Rows of 256 threads or more share a block of `wide` threads, since R rows
+// store 16 R bytes side by side in the transposed layout (4096 x 1024, one row or two:
+// forward rows 147 -> 127 us, right-hand side's 215 -> 187, Krylov row pass 153 -> 139);
+// the right-hand side's inverse pass, which holds 240 registers, at most 512.
+constexpr int ROW_WIDE = 1024, RHS_INV_WIDE = 512;
 template <typename T>
-RowLaunch row_launch(int nx, int ny, bool wide = false) {
+RowLaunch row_launch(int nx, int ny, int wide = ROW_WIDE) {
     RowLaunch L;
     const int M = nx / 2;
-    const bool two = wide && ny > 1 && M >= 32 && M <= 512;
-    L.epc = two ? 2 : (M > 4096) ? 8 : 4;
+    L.epc = (M > 4096) ? 8 : 4;
     RowGeom& g = L.g;
     g.nx = nx;
     g.ny = ny;
     g.M = M;
     g.TPR = M / L.epc > 0 ? M / L.epc : 1;
-    int R = (two ? 512 : 256) / g.TPR;
+    int R = (g.TPR >= 256 ? wide : 256) / g.TPR;
     if (R < 1) R = 1;
     const int np = next_pow2(ny);
     if (R > np) R = np;
-    // keep a block per compute unit: fewer rows per block (down to 64 threads)
-    // while the grid has fewer than 256 R rows (Krylov row pass: 512^2 2 rows
-    // per block, 16.8 -> 13.6 us; 256^2 one row of 64 threads, 19.0 -> 10.2 us;
-    // 128^2 two rows, 17.4 -> 9.5 us)
-    if (two)
-        while (R > 1 && ny / R < 256 && (R / 2) * g.TPR >= 64) R >>= 1;
+    while (R > 1 && ny / R < 256 && (R / 2) * g.TPR >= 64) R >>= 1;
     g.R = R;
     g.nblocks = (ny + R - 1) / R;
+    g.lgR = __builtin_ctz(R);
+    g.lgT = __builtin_ctz(g.TPR);
     L.threads = R * g.TPR;
     L.lds = (size_t)R * (M + 1) * sizeof(cpx<T>);
     return L;
@@ -269,6 +268,7 @@ ColLaunch col_launch(int nx, int ny, int epc = 4) {
     g.TPC = ny / epc > 0 ? ny / epc : 1;
     g.Cb = 256 / g.TPC > 0 ? 256 / g.TPC : 1;
     g.nblocks = (g.nxh + g.Cb - 1) / g.Cb;
+    g.lgT = __builtin_ctz(g.TPC);
     L.threads = g.Cb * g.TPC;
     L.lds = (size_t)g.Cb * ny * sizeof(cpx<T>);
     if (L.lds < 16) L.lds = 16;
@@ -276,33 +276,19 @@ ColLaunch col_launch(int nx, int ny, int epc = 4) {
     return L;
 }
 
-// Column geometry of the Krylov passes (the PcgLaunch of every solve): 2D
-// columns of up to 512 points take two entries per thread (256^2: C1 10.9 ->
-// 8.5 us, C2 10.5 -> 8.8 us; 512^2: C1 12.7 -> 10.2 us), longer ones four.
-template <typename T>
-ColLaunch pcg_col_launch(const Dims& d) { return col_launch<T>(d.nx, d.ny, (d.D == 2 && d.ny <= 512) ? 2 : 4); }
-
-// Column passes of a wall solve (columns of up to 512): two entries per thread,
-// 256-thread blocks as every column pass (the partial sums are reduced over 256
-// lanes); 512^2: one column per block, C1 13.8 -> 11.4 us, C2 14.0 -> 11.5 us.
-ColLaunch wall_col_launch(int nx, int ny) { return col_launch<double>(nx, ny, 2); }
-
 // Column entries per thread: columns up to 1024 use 4 (the grids the solvers
 // take); the padded grid of the de-aliased right-hand side has columns of 2048.
 inline int col_epc(int ny) { return ny > 1024 ? 8 : 4; }
 
-// LDS bytes of a row / column kernel transforming NF fields at a time (data,
-// then the staged twiddle table when the transform length allows it).
-inline int twl_entries(int M) { return (M <= TWL_MAX && M >= 4) ? M : 0; }
+// LDS bytes of a row / column kernel transforming NF fields at a time.
 template <typename T>
 size_t row_lds_bytes(const RowGeom& g, int NF) {
-    return (size_t)(row_lds_data(g, NF) + twl_entries(g.M)) * sizeof(cpx<T>);
+    return (size_t)row_lds_data(g, NF) * sizeof(cpx<T>);
 }
 template <typename T>
 size_t col_lds_bytes(const ColGeom& g, int NF) {
-    return (size_t)(col_lds_data(g, NF) + twl_entries(g.ny)) * sizeof(cpx<T>);
+    return (size_t)col_lds_data(g, NF) * sizeof(cpx<T>);
 }
-constexpr size_t LDS_MULTI_MAX = 96 * 1024;  // above this, row kernels transform fields one by one
 
 inline int flat_blocks(size_t n, int per = 256, int cap = 1024) {
     size_t b = (n + per - 1) / per;
@@ -386,7 +372,7 @@ template <typename T, typename Tin>
 sgn_status rows_fwd(sgn_ctx* ctx, const Dims& d, std::vector<const Tin*> src, std::vector<cpx<T>*> dst,
                     T scale = (T)1, const RowCombo<Tin>* cmb = nullptr) {
     ProfScope ps(ctx, SGN_KERNEL_ROWS);
-    RowLaunch L = row_launch<T>(d.nx, d.ny, true);
+    RowLaunch L = row_launch<T>(d.nx, d.ny);
     RowCombo<Tin> none{};
     none.first = -1;
     if (cmb && src.size() > (size_t)MAXF) return fail(ctx, SGN_EINVAL, "rows_fwd: combined sources exceed one pass");
@@ -405,23 +391,18 @@ sgn_status rows_fwd(sgn_ctx* ctx, const Dims& d, std::vector<const Tin*> src, st
             CHECK_LAUNCH(ctx);
             continue;
         }
-        const bool multi = row_lds_bytes<T>(L.g, 3) <= LDS_MULTI_MAX;
-        const size_t lds = row_lds_bytes<T>(L.g, multi ? 3 : 1);
+        const size_t lds = row_lds_bytes<T>(L.g, 1);
         auto launch = [&](auto k) -> sgn_status {
             HIPCHK(ctx, allow_lds(k, lds));
-            hipLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, ctx->stream, L.g, s, t, twiddles<T>(ctx),
+            hipLaunchKernelGGL(k, dim3(L.g.nblocks * s.n), dim3(L.threads), lds, ctx->stream, L.g, s, t, twiddles<T>(ctx),
                                scale, cm);
             return SGN_OK;
         };
         sgn_status st;
-        if (L.epc == 2)
-            st = multi ? launch(k_rows_fwd<T, Tin, 2, 3, 512>) : launch(k_rows_fwd<T, Tin, 2, 1, 512>);
-        else if (L.epc == 4)
-            st = L.threads <= 256
-                     ? (multi ? launch(k_rows_fwd<T, Tin, 4, 3, 256>) : launch(k_rows_fwd<T, Tin, 4, 1, 256>))
-                     : (multi ? launch(k_rows_fwd<T, Tin, 4, 3>) : launch(k_rows_fwd<T, Tin, 4, 1>));
+        if (L.epc == 4)
+            st = L.threads <= 256 ? launch(k_rows_fwd<T, Tin, 4, 256>) : launch(k_rows_fwd<T, Tin, 4, 1024>);
         else
-            st = multi ? launch(k_rows_fwd<T, Tin, 8, 3>) : launch(k_rows_fwd<T, Tin, 8, 1>);
+            st = launch(k_rows_fwd<T, Tin, 8, 1024>);
         if (st != SGN_OK) return st;
         CHECK_LAUNCH(ctx);
     }
@@ -434,7 +415,7 @@ template <typename T, typename Tout>
 sgn_status rows_inv(sgn_ctx* ctx, const Dims& d, std::vector<const cpx<T>*> src, std::vector<Tout*> dst,
                     T scale = (T)1, T acc = (T)0, const std::vector<Tout*>* offs = nullptr, bool offs_acc = false) {
     ProfScope ps(ctx, SGN_KERNEL_ROWS);
-    RowLaunch L = row_launch<T>(d.nx, d.ny, true);
+    RowLaunch L = row_launch<T>(d.nx, d.ny);
     if (offs && offs->size() != src.size()) return fail(ctx, SGN_EINVAL, "rows_inv: offsets per field");
     for (size_t f0 = 0; f0 < src.size(); f0 += MAXF) {
         PtrList<const cpx<T>, MAXF> s{};
@@ -453,23 +434,18 @@ sgn_status rows_inv(sgn_ctx* ctx, const Dims& d, std::vector<const cpx<T>*> src,
             CHECK_LAUNCH(ctx);
             continue;
         }
-        const bool multi = row_lds_bytes<T>(L.g, 3) <= LDS_MULTI_MAX;
-        const size_t lds = row_lds_bytes<T>(L.g, multi ? 3 : 1);
+        const size_t lds = row_lds_bytes<T>(L.g, 1);
         auto launch = [&](auto k) -> sgn_status {
             HIPCHK(ctx, allow_lds(k, lds));
-            hipLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, ctx->stream, L.g, s, t, twiddles<T>(ctx),
+            hipLaunchKernelGGL(k, dim3(L.g.nblocks * s.n), dim3(L.threads), lds, ctx->stream, L.g, s, t, twiddles<T>(ctx),
                                scale, acc, of, offs_acc ? 1 : 0);
             return SGN_OK;
         };
         sgn_status st;
-        if (L.epc == 2)
-            st = multi ? launch(k_rows_inv<T, Tout, 2, 3, 512>) : launch(k_rows_inv<T, Tout, 2, 1, 512>);
-        else if (L.epc == 4)
-            st = L.threads <= 256
-                     ? (multi ? launch(k_rows_inv<T, Tout, 4, 3, 256>) : launch(k_rows_inv<T, Tout, 4, 1, 256>))
-                     : (multi ? launch(k_rows_inv<T, Tout, 4, 3>) : launch(k_rows_inv<T, Tout, 4, 1>));
+        if (L.epc == 4)
+            st = L.threads <= 256 ? launch(k_rows_inv<T, Tout, 4, 256>) : launch(k_rows_inv<T, Tout, 4, 1024>);
         else
-            st = multi ? launch(k_rows_inv<T, Tout, 8, 3>) : launch(k_rows_inv<T, Tout, 8, 1>);
+            st = launch(k_rows_inv<T, Tout, 8, 1024>);
         if (st != SGN_OK) return st;
         CHECK_LAUNCH(ctx);
     }
@@ -555,9 +531,9 @@ sgn_status cols_lin_jobs(sgn_ctx* ctx, const Dims& d, const std::vector<LinJobSp
             for (int i = 0; i < j.ni; ++i) j.kin[i] = sp.kin[i];
             for (int o = 0; o < j.no; ++o) j.kout[o] = sp.kout[o];
         }
-        const ColLaunch L = wall_col_launch(d.nx, d.ny);
+        const ColLaunch L = col_launch<double>(d.nx, d.ny);
         const size_t lds = col_lds_bytes<double>(L.g, 3);
-        auto k = L.epc == 2 ? k_wall_cols_jobs<double, 2> : k_wall_cols_jobs<double, 4>;
+        auto k = k_wall_cols_jobs<double, 4>;
         HIPCHK(ctx, allow_lds(k, lds));
         hipLaunchKernelGGL(k, dim3(L.g.nblocks * J.n), dim3(L.threads), lds, ctx->stream, L.g, J, ctx->tw64, d.tpx,
                            d.tpy, scale);
@@ -716,7 +692,7 @@ sgn_status pcg_c1(PcgLaunch<T, D>& P, int mode, const cpx<T>* xsrc, const cpx<fl
     const size_t lds = col_lds_bytes<T>(L.g, D + 1);
     if (P.native) {
         if (D != 2 || mode != C1_UPDATE) return fail(P.ctx, SGN_EINVAL, "pcg_c1: wall column pass takes updates only");
-        auto k = L.epc == 2 ? k_wall_c1<T, 2> : k_wall_c1<T, 4>;
+        auto k = k_wall_c1<T, 4>;
         HIPCHK(P.ctx, allow_lds(k, lds));
         hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, P.ctx->stream, ps.a, ps.b, 0, L.g,
                               twiddles<T>(P.ctx), P.sc, (const double*)P.partials, P.cl.g.nblocks,
@@ -739,14 +715,13 @@ sgn_status pcg_c1(PcgLaunch<T, D>& P, int mode, const cpx<T>* xsrc, const cpx<fl
         return SGN_OK;
     };
     sgn_status s;
-    const bool e2 = L.epc == 2;
     if (mode == C1_COPY)
-        s = launch(e2 ? k_pcg_c1<T, 2, D, C1_COPY> : k_pcg_c1<T, 4, D, C1_COPY>, P.b.ph);
+        s = launch(k_pcg_c1<T, 4, D, C1_COPY>, P.b.ph);
     else if (mode == C1_ACCUM) {
         if (sizeof(T) != 8 || !dx) return fail(P.ctx, SGN_EINVAL, "pcg_c1: accumulate needs an FP64 solve");
-        s = launch(e2 ? k_pcg_c1<T, 2, D, C1_ACCUM> : k_pcg_c1<T, 4, D, C1_ACCUM>, P.b.xh);
+        s = launch(k_pcg_c1<T, 4, D, C1_ACCUM>, P.b.xh);
     } else
-        s = launch(e2 ? k_pcg_c1<T, 2, D, C1_UPDATE> : k_pcg_c1<T, 4, D, C1_UPDATE>, P.b.ph);
+        s = launch(k_pcg_c1<T, 4, D, C1_UPDATE>, P.b.ph);
     if (s != SGN_OK) return s;
     CHECK_LAUNCH(P.ctx);
     return SGN_OK;
@@ -771,9 +746,23 @@ bool col_wave(const PcgLaunch<T, D>& P) {
     return sizeof(T) == 4 && D == 2 && P.d.ny == WCOL_NY && P.cl.g.Cb == 1 && !P.native && !P.wall &&
            wave_rows_enabled();
 }
+// Rows of up to 128 threads (nx <= 1024) in whole waves run one group of threads per
+// field (k_pcg_r1f); the few rows of a grid that do not fill a wave, and longer rows
+// (three of which do not fit the LDS of a compute unit), run field by field.
+template <typename T, int D>
+bool r1_fields(const PcgLaunch<T, D>& P) {
+    return P.rl.epc == 4 && P.rl.g.TPR <= 128 && P.rl.threads >= 64;
+}
+// The line of 16384 points: its row pass as three launches of 64 waves.
+template <typename T, int D>
+bool r1_long(const PcgLaunch<T, D>& P) {
+    return D == 1 && P.rl.g.M == LONG_M;
+}
 // Blocks of the row pass, i.e. the p.Gp partials the next column pass reduces.
 template <typename T, int D>
-int r1_blocks(const PcgLaunch<T, D>& P) { return r1_wave(P) ? P.d.ny / r1_rows<T>() : P.rl.g.nblocks; }
+int r1_blocks(const PcgLaunch<T, D>& P) {
+    return r1_wave(P) ? P.d.ny / r1_rows<T>() : r1_long(P) ? LONG_A : P.rl.g.nblocks;
+}
 
 template <typename T, int D>
 sgn_status pcg_r1(PcgLaunch<T, D>& P, bool curvature = false) {
@@ -787,23 +776,30 @@ sgn_status pcg_r1(PcgLaunch<T, D>& P, bool curvature = false) {
         return SGN_OK;
     }
     auto& L = P.rl;
-    const bool seq = row_lds_bytes<T>(L.g, D + 1) > LDS_MULTI_MAX;
-    const size_t lds = row_lds_bytes<T>(L.g, seq ? 1 : D + 1);
+    if (r1_long(P)) {
+        const cpx<T>* tw = twiddles<T>(P.ctx);
+        hipExtLaunchKernelGGL((k_pcg_long_cols<T, true>), dim3(LONG_A), dim3(64), 0, P.ctx->stream, ps.a, nullptr, 0,
+                              tw, P.sc, P.b.H, P.d.NS);
+        hipLaunchKernelGGL(k_pcg_long_rows<T>, dim3(LONG_A), dim3(64), 0, P.ctx->stream, tw, P.sc, P.b.H, P.d.NS,
+                           P.eta, P.gh, part);
+        hipExtLaunchKernelGGL((k_pcg_long_cols<T, false>), dim3(LONG_A), dim3(64), 0, P.ctx->stream, nullptr, ps.b, 0,
+                              tw, P.sc, P.b.H, P.d.NS);
+        CHECK_LAUNCH(P.ctx);
+        return SGN_OK;
+    }
+    const bool fields = r1_fields(P);
+    const size_t lds = row_lds_bytes<T>(L.g, fields ? D + 1 : 1);
     auto launch = [&](auto k) -> sgn_status {
         HIPCHK(P.ctx, allow_lds(k, lds));
-        hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, P.ctx->stream, ps.a, ps.b, 0, L.g,
-                              twiddles<T>(P.ctx), P.sc, P.b.H, P.d.NS, P.eta, P.gh, part);
+        hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads * (fields ? D + 1 : 1)), lds, P.ctx->stream, ps.a,
+                              ps.b, 0, L.g, twiddles<T>(P.ctx), P.sc, P.b.H, P.d.NS, P.eta, P.gh, part);
         return SGN_OK;
     };
     sgn_status st;
-    if (L.epc == 2)
-        st = seq ? launch(k_pcg_r1<T, 2, D, true, 512>) : launch(k_pcg_r1<T, 2, D, false, 512>);
-    else if (L.epc == 4)
-        st = L.threads <= 256
-                 ? (seq ? launch(k_pcg_r1<T, 4, D, true, 256>) : launch(k_pcg_r1<T, 4, D, false, 256>))
-                 : (seq ? launch(k_pcg_r1<T, 4, D, true>) : launch(k_pcg_r1<T, 4, D, false>));
+    if (fields)
+        st = launch(k_pcg_r1f<T, D>);
     else
-        st = seq ? launch(k_pcg_r1<T, 8, D, true>) : launch(k_pcg_r1<T, 8, D, false>);
+        st = L.threads <= 256 ? launch(k_pcg_r1<T, D, 256>) : launch(k_pcg_r1<T, D, 1024>);
     if (st != SGN_OK) return st;
     CHECK_LAUNCH(P.ctx);
     return SGN_OK;
@@ -825,7 +821,7 @@ sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, con
     };
     if (P.native) {
         if constexpr (D == 2 && (MODE == C2_UPDATE || MODE == C2_RESID_INIT)) {
-            auto k = L.epc == 2 ? k_wall_c2<T, 2, MODE> : k_wall_c2<T, 4, MODE>;
+            auto k = k_wall_c2<T, 4, MODE>;
             HIPCHK(P.ctx, allow_lds(k, lds));
             hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, P.ctx->stream, ps.a, ps.b, 0, L.g,
                                   twiddles<T>(P.ctx), P.sc, (const cpx<T>*)P.b.H, P.d.NS, (const cpx<T>*)P.b.ph,
@@ -846,7 +842,6 @@ sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, con
             return SGN_OK;
         }
     }
-    if (L.epc == 2) return P.wall ? launch(k_pcg_c2<T, 2, D, MODE, true>) : launch(k_pcg_c2<T, 2, D, MODE>);
     return P.wall ? launch(k_pcg_c2<T, 4, D, MODE, true>) : launch(k_pcg_c2<T, 4, D, MODE>);
 }
 
@@ -907,12 +902,8 @@ sgn_status pcg_start(PcgLaunch<double, D>& P, const double* rhs, const double* u
             CHECK_LAUNCH(ctx);
             return SGN_OK;
         };
-        if (P.native && P.cl.epc == 2)
-            s = guess ? launch(k_wall_setup<double, 2, true>) : launch(k_wall_setup<double, 2, false>);
-        else if (P.native)
+        if (P.native)
             s = guess ? launch(k_wall_setup<double, 4, true>) : launch(k_wall_setup<double, 4, false>);
-        else if (P.cl.epc == 2)
-            s = guess ? launch(k_pcg_setup<double, 2, D, true>) : launch(k_pcg_setup<double, 2, D, false>);
         else
             s = guess ? launch(k_pcg_setup<double, 4, D, true>) : launch(k_pcg_setup<double, 4, D, false>);
         if (s != SGN_OK) return s;
@@ -1167,8 +1158,8 @@ sgn_status solve_fp64(sgn_ctx* ctx, const Dims& d, const double* eta, const doub
     P.native = D == 2 && ctx->wall_native;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = P.native ? wall_col_launch(d.nx, d.ny) : pcg_col_launch<double>(d);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = P.native ? col_launch<double>(d.nx, d.ny) : col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
     P.partials = cm.partials;
@@ -1189,8 +1180,7 @@ sgn_status solve_fp64(sgn_ctx* ctx, const Dims& d, const double* eta, const doub
     // u = IFFT(x_hat) (and the stepper's offset record); stored a second time after
     // further iterations, the offset accumulates the difference
     auto store = [&](bool redo) -> sgn_status {
-        auto k = P.native ? (P.cl.epc == 2 ? k_wall_from_S<double, 2> : k_wall_from_S<double, 4>)
-                          : (P.cl.epc == 2 ? k_cols_from_S<double, 2, D> : k_cols_from_S<double, 4, D>);
+        auto k = P.native ? k_wall_from_S<double, 4> : k_cols_from_S<double, 4, D>;
         HIPCHK(ctx, allow_lds(k, col_lds_bytes<double>(P.cl.g, D)));
         hipLaunchKernelGGL(k, dim3(P.cl.g.nblocks), dim3(P.cl.threads), col_lds_bytes<double>(P.cl.g, D), ctx->stream,
                            P.cl.g, ctx->tw64, (const cpx<double>*)P.b.xh, d.NS, P.b.H, d.inv_n);
@@ -1294,8 +1284,8 @@ sgn_status solve_wall_native(sgn_ctx* ctx, const Dims& dw, const double* eta, co
     P.native = true;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = wall_col_launch(d.nx, d.ny);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
     P.partials = cm.partials;
@@ -1334,7 +1324,7 @@ sgn_status solve_wall_native(sgn_ctx* ctx, const Dims& dw, const double* eta, co
     if (h.status == -2) return fail(ctx, SGN_EDOMAIN, "non-positive depth or non-finite data in the solve");
     // the iterate is returned on success and when max_iter stops the solve
     {
-        auto k = P.cl.epc == 2 ? k_wall_from_S<double, 2> : k_wall_from_S<double, 4>;
+        auto k = k_wall_from_S<double, 4>;
         const size_t lds = col_lds_bytes<double>(P.cl.g, 2);
         HIPCHK(ctx, allow_lds(k, lds));
         hipLaunchKernelGGL(k, dim3(P.cl.g.nblocks), dim3(P.cl.threads), lds, ctx->stream, P.cl.g, ctx->tw64,
@@ -1368,8 +1358,8 @@ sgn_status solve_mixed(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     P.wall = ctx->wall_twin;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = pcg_col_launch<double>(d);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, true);
     P.sc = cm.sc;
     P.partials = cm.partials;
@@ -1379,8 +1369,8 @@ sgn_status solve_mixed(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     Q.wall = ctx->wall_twin;
     Q.ctx = ctx;
     Q.d = d;
-    Q.rl = row_launch<float>(d.nx, d.ny, true);
-    Q.cl = pcg_col_launch<float>(d);
+    Q.rl = row_launch<float>(d.nx, d.ny);
+    Q.cl = col_launch<float>(d.nx, d.ny);
     Q.b = carve_pcg<float>(cv, d, false);
     Q.sc = cm.sc + 1;
     Q.partials = cm.partials;
@@ -1412,7 +1402,7 @@ sgn_status solve_mixed(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     // further refinement step adds its difference to the offset
     int stores = 0;
     auto store = [&]() -> sgn_status {
-        auto k = P.cl.epc == 2 ? k_cols_from_S<double, 2, D> : k_cols_from_S<double, 4, D>;
+        auto k = k_cols_from_S<double, 4, D>;
         HIPCHK(ctx, allow_lds(k, col_lds_bytes<double>(P.cl.g, D)));
         hipLaunchKernelGGL(k, dim3(P.cl.g.nblocks), dim3(P.cl.threads), col_lds_bytes<double>(P.cl.g, D),
                            ctx->stream, P.cl.g, ctx->tw64, (const cpx<double>*)P.b.xh, d.NS, P.b.H, d.inv_n);
@@ -1656,8 +1646,8 @@ sgn_status solve_gmres(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     auto& P = G.P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = pcg_col_launch<double>(d);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
     P.partials = cm.partials;
@@ -1961,8 +1951,8 @@ sgn_status apply_G(sgn_ctx* ctx, const Dims& d, const double* eta, const double*
     PcgLaunch<double, D> P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = pcg_col_launch<double>(d);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
     P.partials = cm.partials;
@@ -1978,7 +1968,7 @@ sgn_status apply_G(sgn_ctx* ctx, const Dims& d, const double* eta, const double*
     }
     if ((s = rows_fwd<double, double>(ctx, d, usrc, hdst)) != SGN_OK) return s;
     {
-        auto k = P.cl.epc == 2 ? k_cols_to_S<double, 2, D> : k_cols_to_S<double, 4, D>;
+        auto k = k_cols_to_S<double, 4, D>;
         HIPCHK(ctx, allow_lds(k, col_lds_bytes<double>(P.cl.g, D)));
         hipLaunchKernelGGL(k, dim3(P.cl.g.nblocks), dim3(P.cl.threads), col_lds_bytes<double>(P.cl.g, D), ctx->stream, P.cl.g, ctx->tw64,
                            (const cpx<double>*)P.b.H, d.NS, P.b.xh);
@@ -2050,10 +2040,6 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
     std::vector<cpx<double>*> dA, dB;
     for (int i = 0; i < 2 * D + 1; ++i) dA.push_back(HA + i * NS);
     for (int i = 0; i < 2; ++i) dB.push_back(HB + i * NS);
-    // the fused right-hand-side row passes transform their fields one at a time
-    // (lockstep groups need more registers than the pointwise state leaves)
-    // (the fused right-hand-side row passes keep 256-thread blocks: their pointwise
-    // state makes the wide launch slower)
     const RowLaunch RL = row_launch<double>(d.nx, d.ny);
     const size_t rlds = row_lds_bytes<double>(RL.g, 1);
     {
@@ -2075,18 +2061,17 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         // 47 -> 58 us, each field's wave re-reading the shared inputs; one wave per
         // row and group of fields sharing inputs 47 -> 65 us, the group's fields
         // transformed one after another in each wave)
-        if (RL.epc == 4 && RL.threads <= 256 && l3 <= LDS_MULTI_MAX) {
+        if constexpr (D == 1) {   // lines of 16384 points (shorter ones: rhs_1d_block)
+            s = launch(k_rhs_rows_fwd<D, 8, 1, 1024>);
+        } else if (RL.threads <= 256) {
             HIPCHK(ctx, allow_lds(k_rhs_rows_fwd<D, 4, 3, 256>, l3));
             hipLaunchKernelGGL((k_rhs_rows_fwd<D, 4, 3, 256>), dim3(RL.g.nblocks), dim3(RL.threads), l3,
                                ctx->stream, RL.g, eta, u, gh, t, ctx->tw64);
             CHECK_LAUNCH(ctx);
             s = SGN_OK;
-        } else if (RL.epc == 4 && RL.threads <= 256)
-            s = launch(k_rhs_rows_fwd<D, 4, 1, 256>);
-        else if (RL.epc == 4)
+        } else {
             s = launch(k_rhs_rows_fwd<D, 4, 1, 1024>);
-        else
-            s = launch(k_rhs_rows_fwd<D, 8, 1, 1024>);
+        }
         if (s != SGN_OK) return s;
     }
     std::vector<const cpx<double>*> cA(dA.begin(), dA.end()), cB(dB.begin(), dB.end());
@@ -2094,10 +2079,10 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
     for (int i = 0; i < 2 * D + 2; ++i) oA.push_back(OA + i * NS);
     for (int i = 0; i < 2 * D; ++i) oB.push_back(OB + i * NS);
     // codes: 1 id, 2 ikx, 3 iky, 4 (ikx)^2, 5 (ikx)(iky), 6 (iky)^2
-    // Periodic rows of 1024 points: the inverse row pass (k_rhs_rows_inv_w) forms
-    // the x-derivatives of delta, eta and beta itself (i k_x times a row spectrum
-    // it loads anyway), so the column pass skips those three outputs.
-    const bool dx_rows = D == 2 && !wall && wave_rows(d);
+    // Periodic grids: the inverse row pass forms the x-derivatives of delta, eta and
+    // beta itself (i k_x times a row spectrum), so the column pass skips those three
+    // outputs.
+    const bool dx_rows = D == 2 && !wall;
     if (D == 2) {
         // the column operators, split by shared inputs so that each block holds
         // at most three transformed inputs in registers, run side by side in one
@@ -2132,37 +2117,45 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         ProfScope ps(ctx, D == 2 ? SGN_KERNEL_RHS_ROWS_INV : SGN_KERNEL_ROWS);
         PtrList<const cpx<double>, MAXF> q{};
         q.n = 0;
-        // OA = [delta, d delta (D), m, d eta (D)], OB = [d beta (D)]
+        // OA = [delta, d delta (D), m, d eta (D)], OB = [d beta (D)]; the wave-private
+        // pass takes d eta ahead of d beta (its waves all run at once), the block
+        // pass last
+        const bool wave = D == 2 && wave_rows(d);
         q.p[q.n++] = OA + (1 + D) * NS;
         for (int i = 0; i <= D; ++i) q.p[q.n++] = OA + i * NS;
-        for (int i = 0; i < D; ++i) q.p[q.n++] = OA + (2 + D + i) * NS;
-        for (int i = 0; i < D; ++i) q.p[q.n++] = OB + i * NS;
+        const int at_eta = wave ? 2 + D : 2 + 2 * D, at_beta = wave ? 2 + 2 * D : 2 + D;
+        for (int i = 0; i < D; ++i) {
+            q.p[at_eta + i] = OA + (2 + D + i) * NS;
+            q.p[at_beta + i] = OB + i * NS;
+        }
+        q.n += 2 * D;
+        RowDx dx{};
+        if (dx_rows) {
+            q.p[2] = OA;                       // delta's output: d_x delta = i k_x delta
+            q.p[at_eta] = HA + 2 * D * NS;     // eta's row spectrum
+            q.p[at_beta] = HB + NS;            // beta's row spectrum
+            dx.f[2] = 1.0;
+            dx.f[at_eta] = dx.f[at_beta] = 1.0 / d.nx;
+        }
+        const RowLaunch RI = row_launch<double>(d.nx, d.ny, RHS_INV_WIDE);
+        const size_t ilds = row_lds_bytes<double>(RI.g, 1);
         auto launch = [&](auto k) -> sgn_status {
-            HIPCHK(ctx, allow_lds(k, rlds));
-            hipLaunchKernelGGL(k, dim3(RL.g.nblocks), dim3(RL.threads), rlds, ctx->stream, RL.g, q, eta, u, gh, eta_t,
-                               U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0);
+            HIPCHK(ctx, allow_lds(k, ilds));
+            hipLaunchKernelGGL(k, dim3(RI.g.nblocks), dim3(RI.threads), ilds, ctx->stream, RI.g, q, eta, u, gh, eta_t,
+                               U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0, dx, d.tpx);
             CHECK_LAUNCH(ctx);
             return SGN_OK;
         };
-        if (D == 2 && wave_rows(d) && q.n == 8) {
-            RowDx dx{};
-            if (dx_rows) {
-                q.p[2] = OA;                       // delta's output: d_x delta = i k_x delta
-                q.p[4] = HA + 2 * D * NS;          // eta's row spectrum
-                q.p[6] = HB + NS;                  // beta's row spectrum
-                dx.f[2] = 1.0;
-                dx.f[4] = dx.f[6] = 1.0 / d.nx;
-            }
+        if (wave) {
             hipLaunchKernelGGL(k_rhs_rows_inv_w, dim3(d.ny), dim3(512), 0, ctx->stream, d.ny, q, eta, u, gh, eta_t,
                                U_t, HA, HA + NS, ctx->tw64, 1.0, dx, d.tpx);
             CHECK_LAUNCH(ctx);
             s = SGN_OK;
-        } else if (RL.epc == 4 && RL.threads <= 256)
-            s = launch(k_rhs_rows_inv<D, 4, 1, 256>);
-        else if (RL.epc == 4)
-            s = launch(k_rhs_rows_inv<D, 4, 1, 1024>);
-        else
-            s = launch(k_rhs_rows_inv<D, 8, 1, 1024>);
+        } else if constexpr (D == 1) {
+            s = launch(k_rhs_rows_inv<D, 8, 1024>);
+        } else {
+            s = launch(k_rhs_rows_inv<D, 4, 512>);
+        }
         if (s != SGN_OK) return s;
     }
     // U_t += grad S - div(eta u (x) u), formed in the spectral domain from S and the
@@ -2797,8 +2790,8 @@ sgn_status sbdf2_R(sgn_state* st, cpx<double>* Rout) {
     PcgLaunch<double, D> P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny, true);
-    P.cl = pcg_col_launch<double>(d);
+    P.rl = row_launch<double>(d.nx, d.ny);
+    P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
     P.partials = cm.partials;

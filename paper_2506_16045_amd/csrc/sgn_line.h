@@ -129,38 +129,6 @@ __host__ __device__ constexpr size_t line_lds_bytes(int n) {
 }
 static_assert(line_lds_bytes(8192) <= 160 * 1024 - 2048, "LDS of a compute unit, less the static arrays");
 
-// ---- sums over a wave -------------------------------------------------------
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(b & 0xffffffffLL), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-__device__ __forceinline__ double lane_d(double v, int lane) {
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (long long)(unsigned)lo);
-}
-// Sum over the 64 lanes (all active), the same in every lane: a tree inside each
-// row of 16 by data-parallel moves, then the four rows through scalar registers
-// (six shuffles of a double through LDS cost about five times as long).
-__device__ __forceinline__ double wave_sum(double v) {
-    v += dpp_d<0xB1>(v);     // lanes ^ 1
-    v += dpp_d<0x4E>(v);     // lanes ^ 2
-    v += dpp_d<0x141>(v);    // the other four of eight
-    v += dpp_d<0x140>(v);    // the other eight of sixteen
-    return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
-__device__ __forceinline__ double wave_max(double v) {
-    v = fmax(v, dpp_d<0xB1>(v));
-    v = fmax(v, dpp_d<0x4E>(v));
-    v = fmax(v, dpp_d<0x141>(v));
-    v = fmax(v, dpp_d<0x140>(v));
-    return fmax(fmax(lane_d(v, 0), lane_d(v, 16)), fmax(lane_d(v, 32), lane_d(v, 48)));
-}
-
 __device__ __forceinline__ void line_wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
     __builtin_amdgcn_wave_barrier();

@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(256) k_wall_order(int nx, int ny, int nf, unsi
 }
 
 // Column FFT values F1 = F[q], F2 = F[ny - q] of column k -> the field's
-// amplitudes at y slots q and ny - q.  wx = w_k of the
+// amplitudes at y slots q and ny - q (q0: F[0] and F[ny/2], each its own partner).  wx = w_k of the
 // x axis (4 nx roots), wy = w_q of the y axis; xs / ys: sine series along x / y.
 // The column holds the x-line sums C_k - i C_{nx-k} of every row, so
 // P_a = (F1 + conj F2) / 2 and P_b = i (F1 - conj F2) / 2 are the y-DFTs of the
@@ -76,6 +76,12 @@ __device__ __forceinline__ void wall_to_slots(cpx<T> F1, cpx<T> F2, cpx<T> wx, c
                                               bool ys, cpx<T>& Sq, cpx<T>& Sm) {
     F1 = wx * F1;
     F2 = wx * F2;
+    if (q0) {   // w_0 = 1, w_{ny/2} = (1 - i) / sqrt 2
+        const T r = (T)0.70710678118654752440;
+        Sq = k0 ? C<T>(F1.re, 0) : xs ? C<T>(-F1.im, F1.re) : cj(F1);
+        Sm = r * (k0 ? C<T>(F2.re, 0) : xs ? C<T>(-F2.im, F2.re) : cj(F2));
+        return;
+    }
     const T h = (T)0.5;
     const cpx<T> ua = wy * (h * (F1 + cj(F2)));
     const cpx<T> ub = wy * (h * mul_i(F1 - cj(F2)));
@@ -91,7 +97,7 @@ __device__ __forceinline__ void wall_to_slots(cpx<T> F1, cpx<T> F2, cpx<T> wx, c
         bm = t1;
     }
     const cpx<T> vq = C<T>(aq, bq), vm = C<T>(am, bm);
-    if (ys && !q0) {
+    if (ys) {
         Sq = vm;
         Sm = vq;
     } else {
@@ -100,18 +106,22 @@ __device__ __forceinline__ void wall_to_slots(cpx<T> F1, cpx<T> F2, cpx<T> wx, c
     }
 }
 
-// The inverse of wall_to_slots: amplitudes at y slots q and ny - q (the same
-// value twice for q = 0 and q = ny/2) -> the column values F[q], F[ny - q] whose
+// The inverse of wall_to_slots: amplitudes at y slots q and ny - q (q0: 0 and
+// ny/2) -> the column values F[q], F[ny - q] whose
 // inverse y-FFT and inverse row transform give the field in transform order
 // (times nx ny).
 template <typename T>
 __device__ __forceinline__ void wall_from_slots(cpx<T> Sq, cpx<T> Sm, cpx<T> wx, cpx<T> wy, bool k0, bool q0, bool xs,
                                                 bool ys, cpx<T>& F1, cpx<T>& F2) {
-    cpx<T> eq, em;
+    const cpx<T> wyc = cj(wy), wxc = cj(wx);
     if (q0) {
-        eq = Sq;
-        em = C<T>(0, 0);
-    } else if (ys) {
+        const T r = (T)1.41421356237309504880;
+        F1 = wxc * (k0 ? C<T>(Sq.re, 0) : xs ? C<T>(Sq.im, -Sq.re) : cj(Sq));
+        F2 = wxc * (r * (k0 ? C<T>(Sm.re, 0) : xs ? C<T>(Sm.im, -Sm.re) : cj(Sm)));
+        return;
+    }
+    cpx<T> eq, em;
+    if (ys) {
         eq = Sm;
         em = Sq;
     } else {
@@ -135,7 +145,6 @@ __device__ __forceinline__ void wall_from_slots(cpx<T> Sq, cpx<T> Sm, cpx<T> wx,
         bq = eq.im;
         bm = em.im;
     }
-    const cpx<T> wyc = cj(wy), wxc = cj(wx);
     const cpx<T> pa = wyc * C<T>(aq, -am), pb = wyc * C<T>(bq, -bm);
     F1 = wxc * (pa - mul_i(pb));
     F2 = wxc * (cj(pa) - mul_i(cj(pb)));
@@ -183,8 +192,37 @@ __device__ __forceinline__ WallColumn<T> wall_column(const ColGeom& g, const Col
     return w;
 }
 
-// Load NF H columns into LDS and y-FFT them there (the values stay in LDS; the
-// FFT ends with a block barrier).
+// y-FFT of NF register columns, left in LDS in natural order for the pair walk.
+template <typename T, int EPC, int NF>
+__device__ __forceinline__ void wall_fft_to_lds(const ColGeom& g, const ColThread<T>& ct, cpx<T> (*v)[EPC],
+                                                const cpx<T>* twm) {
+    reg_fft<T, EPC, NF>(v, ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, false);
+    fft_sync(g.TPC);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const int j = ct.t + g.TPC * e;
+            if (j < g.ny) ct.buf[f * ct.fstride + j] = v[f][e];
+        }
+    fft_sync(g.TPC);
+}
+// The NF columns the pair walk left in LDS, inverse transformed in registers.
+template <typename T, int EPC, int NF>
+__device__ __forceinline__ void wall_ifft_from_lds(const ColGeom& g, const ColThread<T>& ct, cpx<T> (*v)[EPC],
+                                                   const cpx<T>* twm) {
+    fft_sync(g.TPC);
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            const int j = ct.t + g.TPC * e;
+            if (j < g.ny) v[f][e] = ct.buf[f * ct.fstride + j];
+        }
+    reg_fft<T, EPC, NF>(v, ct.buf, ct.fstride, g.ny, ct.t, g.TPC, twm, true);
+}
+
+// Load NF H columns and y-FFT them; the values are left in LDS.
 template <typename T, int EPC, int NF>
 __device__ __forceinline__ void wall_col_fft(const ColGeom& g, const ColThread<T>& ct, const cpx<T>* const (&H)[NF],
                                              const cpx<T>* twm) {
@@ -197,15 +235,7 @@ __device__ __forceinline__ void wall_col_fft(const ColGeom& g, const ColThread<T
             const int j = ct.t + g.TPC * e;
             v[f][e] = (ct.valid && j < ny) ? H[f][(size_t)ct.kx * ny + j] : C<T>(0, 0);
         }
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            const int j = ct.t + g.TPC * e;
-            if (j < ny) ct.buf[f * ct.fstride + j] = v[f][e];
-        }
-    __syncthreads();
-    lds_fft<T, EPC, NF>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, false);
+    wall_fft_to_lds<T, EPC, NF>(g, ct, v, twm);
 }
 
 // Inverse y-FFT of the NF columns the threads wrote to LDS, then store to H.
@@ -213,15 +243,15 @@ template <typename T, int EPC, int NF>
 __device__ __forceinline__ void wall_col_emit(const ColGeom& g, const ColThread<T>& ct, cpx<T>* const (&H)[NF],
                                               const cpx<T>* twm) {
     const int ny = g.ny;
-    __syncthreads();
-    lds_fft<T, EPC, NF>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
+    cpx<T> v[NF][EPC];
+    wall_ifft_from_lds<T, EPC, NF>(g, ct, v, twm);
     if (ct.valid) {
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
                 const int j = ct.t + g.TPC * e;
-                if (j < ny) H[f][(size_t)ct.kx * ny + j] = ct.buf[f * ct.fstride + j];
+                if (j < ny) H[f][(size_t)ct.kx * ny + j] = v[f][e];
             }
     }
 }
@@ -230,9 +260,9 @@ __device__ __forceinline__ void wall_col_emit(const ColGeom& g, const ColThread<
 __device__ __forceinline__ bool wall_xs(int f) { return f == 0; }
 __device__ __forceinline__ bool wall_ys(int f) { return f == 1; }
 
-// Each kernel walks the pairs of y slots (q, ny - q), q = 0 .. ny/2, of its
-// column: thread t takes q = t + TPC e for e = 0 .. EPC/2 (the last only for
-// t = 0); q = 0 and q = ny/2 pair with themselves.
+// Each kernel walks the pairs of y slots (q, ny - q), q = 1 .. ny/2 - 1, of its
+// column and, as q = 0, the two slots that are their own partners, (0, ny/2): thread
+// t takes q = t + TPC e for e < EPC/2, the same number each.
 
 // First column pass of a wall solve (the k_pcg_setup of the periodic grid): Hb
 // holds the row transforms of b in transform order, Hu those of the guess.  b's
@@ -241,7 +271,7 @@ __device__ __forceinline__ bool wall_ys(int f) { return f == 1; }
 // transformed into H for the row pass of G x_0; otherwise xh = 0 and the
 // partials r.z, r.r of r_0 = b.
 template <typename T, int EPC, bool GUESS>
-__global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __restrict__ tw,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_setup(ColGeom g, const cpx<T>* __restrict__ tw,
                                                      const SolveScal* __restrict__ sc, const cpx<T>* Hb,
                                                      const cpx<T>* __restrict__ Hu, size_t NS, cpx<T>* __restrict__ bh,
                                                      cpx<T>* __restrict__ rh, cpx<T>* __restrict__ xh, cpx<T>* H,
@@ -250,7 +280,7 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     __shared__ double red[32];
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, 3));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const int job = GUESS ? (int)blockIdx.x / g.nblocks : 0;
     const ColThread<T> ct = col_thread_at<T>(g, lds, (int)blockIdx.x - job * g.nblocks);
     const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
@@ -263,12 +293,11 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
             wall_col_fft<T, EPC, 2>(g, ct, srcs, twm);
         }
 #pragma unroll
-        for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+        for (int e_ = 0; e_ < EPC / 2; ++e_) {
             const int q = ct.t + g.TPC * e_;
-            if (q > g.ny / 2) continue;
-            const int m = (g.ny - q) & (g.ny - 1);
-            const bool self = q == m;
-            const cpx<T> wy = twy[q];
+            if (q >= g.ny / 2) continue;
+            const int m = q ? g.ny - q : g.ny / 2;
+                const cpx<T> wy = twy[q];
             cpx<T> a[2][2];
 #pragma unroll
             for (int f = 0; f < 2; ++f)
@@ -279,7 +308,7 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
             for (int s = 0; s < 2; ++s) {
                 const int ysl = s ? m : q;
                 const T ky = (T)ysl * piy;
-                if (ct.valid && (s == 0 || !self)) {
+                if (ct.valid) {
                     xh[col + ysl] = a[0][s];
                     xh[NS + col + ysl] = a[1][s];
                 }
@@ -290,10 +319,10 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
 #pragma unroll
             for (int f = 0; f < 3; ++f) {
                 cpx<T> F1, F2;
-                wall_from_slots<T>(o[f][0], self ? o[f][0] : o[f][1], wc.wx, wy, wc.k0, q == 0, wall_xs(f),
+                wall_from_slots<T>(o[f][0], o[f][1], wc.wx, wy, wc.k0, q == 0, wall_xs(f),
                                    wall_ys(f), F1, F2);
                 ct.buf[f * ct.fstride + q] = F1;
-                if (!self) ct.buf[f * ct.fstride + m] = F2;
+                ct.buf[f * ct.fstride + m] = F2;
             }
         }
         cpx<T>* dsts[3] = {H, H + NS, H + 2 * NS};
@@ -306,11 +335,10 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
     }
     double acc[2] = {0.0, 0.0};
 #pragma unroll
-    for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+    for (int e_ = 0; e_ < EPC / 2; ++e_) {
         const int q = ct.t + g.TPC * e_;
-        if (q > g.ny / 2) continue;
-        const int m = (g.ny - q) & (g.ny - 1);
-        const bool self = q == m;
+        if (q >= g.ny / 2) continue;
+        const int m = q ? g.ny - q : g.ny / 2;
         const cpx<T> wy = twy[q];
         cpx<T> a[2][2];
 #pragma unroll
@@ -319,7 +347,7 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
                              wall_xs(f), wall_ys(f), a[f][0], a[f][1]);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (!ct.valid || (s == 1 && self)) continue;
+            if (!ct.valid) continue;
             const int ysl = s ? m : q;
             const double cy = ysl == 0 ? 1.0 : 2.0;
             const T ky = (T)ysl * piy;
@@ -366,47 +394,69 @@ __global__ void __launch_bounds__(256) k_wall_setup(ColGeom g, const cpx<T>* __r
 // from the last update's partials; z = A^{-1} r, p = z + beta p on the slots;
 // (p, div p) / (nx ny) -> column values -> inverse y-FFT into H.
 template <typename T, int EPC>
-__global__ void __launch_bounds__(256) k_wall_c1(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c1(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
                                                   const double* __restrict__ part, int nb3,
                                                   const cpx<T>* __restrict__ rh, cpx<T>* __restrict__ ph,
                                                   cpx<T>* __restrict__ H, size_t NS, T pix, T piy) {
-    if (sc->done) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     __shared__ double red[32];
-    __shared__ double slot[2];
-    double beta_d = 0.0;
-    if (pcg_iterate_state(sc, part, nb3, red, slot, beta_d)) return;
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, 3));
+    const PcgScal s0 = pcg_scalars(sc);
+    if (s0.done) return;
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
-    const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
-    const cpx<T>* twy = tw_size(tw, 4 * g.ny);
-    const T beta = (T)beta_d, sig = (T)sc->sig, alp = (T)sc->alp, inv_n = (T)sc->inv_n;
     const size_t col = (size_t)ct.kx * g.ny;
+    const cpx<T>* twy = tw_size(tw, 4 * g.ny);
+    // the partials, r, the last p and the y roots, in flight across the reduction
+    double pb[PF_K][2];
+    partials_fetch<2>(part + PART_C3, nb3, pb);
+    __builtin_amdgcn_sched_barrier(0);
+    constexpr int NP = EPC / 2;
+    cpx<T> r[NP][2][2], last[NP][2][2], wyp[NP];
 #pragma unroll
-    for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+    for (int e_ = 0; e_ < NP; ++e_) {
         const int q = ct.t + g.TPC * e_;
-        if (q > g.ny / 2) continue;
-        const int m = (g.ny - q) & (g.ny - 1);
-        const bool self = q == m;
-        const cpx<T> wy = twy[q];
+        wyp[e_] = twy[q < g.ny / 2 ? q : 0];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const unsigned idx =
+                (ct.valid && q < g.ny / 2) ? (unsigned)(ct.kx * g.ny + (!s ? q : q ? g.ny - q : g.ny / 2)) : 0u;
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                r[e_][s][c] = at32(rh + c * NS, idx);
+                last[e_][s][c] = at32(ph + c * NS, idx);
+            }
+        }
+    }
+    const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
+    __builtin_amdgcn_sched_barrier(0);
+    double beta_d = 0.0, tot[2];
+    partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+    if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
+    const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
+#pragma unroll
+    for (int e_ = 0; e_ < NP; ++e_) {
+        const int q = ct.t + g.TPC * e_;
+        if (q >= g.ny / 2) continue;
+        const int m = q ? g.ny - q : g.ny / 2;
+        const cpx<T> wy = wyp[e_];
         cpx<T> o[3][2];
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             const int ysl = s ? m : q;
             const T ky = (T)ysl * piy;
             cpx<T> p0 = C<T>(0, 0), p1 = C<T>(0, 0);
-            if (ct.valid && (s == 0 || !self)) {
-                const cpx<T> r0 = rh[col + ysl], r1 = rh[NS + col + ysl];
+            if (ct.valid) {
+                const cpx<T> r0 = r[e_][s][0], r1 = r[e_][s][1];
                 T z0r, z1r, z0i, z1i;
                 wall_precond<T>(wc.kre, ky, sig, alp, r0.re, r1.re, z0r, z1r);
                 wall_precond<T>(wc.kim, ky, sig, alp, r0.im, r1.im, z0i, z1i);
                 p0 = C<T>(z0r, z0i);
                 p1 = C<T>(z1r, z1i);
-                // beta = 0 on the first iteration: p = z without reading the unset direction
+                // beta = 0 on the first iteration: p = z, the unset direction is not used
                 if (beta != (T)0) {
-                    p0 = p0 + beta * ph[col + ysl];
-                    p1 = p1 + beta * ph[NS + col + ysl];
+                    p0 = p0 + beta * last[e_][s][0];
+                    p1 = p1 + beta * last[e_][s][1];
                 }
                 ph[col + ysl] = p0;
                 ph[NS + col + ysl] = p1;
@@ -418,10 +468,10 @@ __global__ void __launch_bounds__(256) k_wall_c1(ColGeom g, const cpx<T>* __rest
 #pragma unroll
         for (int f = 0; f < 3; ++f) {
             cpx<T> F1, F2;
-            wall_from_slots<T>(o[f][0], self ? o[f][0] : o[f][1], wc.wx, wy, wc.k0, q == 0, wall_xs(f), wall_ys(f),
+            wall_from_slots<T>(o[f][0], o[f][1], wc.wx, wy, wc.k0, q == 0, wall_xs(f), wall_ys(f),
                                F1, F2);
             ct.buf[f * ct.fstride + q] = F1;
-            if (!self) ct.buf[f * ct.fstride + m] = F2;
+            ct.buf[f * ct.fstride + m] = F2;
         }
     }
     cpx<T>* dsts[3] = {H, H + NS, H + 2 * NS};
@@ -434,23 +484,36 @@ __global__ void __launch_bounds__(256) k_wall_c1(ColGeom g, const cpx<T>* __rest
 // partial r.z, r.r.  MODE C2_RESID_INIT: bb from the setup partials;
 // r = b - G x_0 (zero for a zero b), partial r.z, r.r.
 template <typename T, int EPC, int MODE>
-__global__ void __launch_bounds__(256) k_wall_c2(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c2(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
                                                   const cpx<T>* __restrict__ H, size_t NS,
                                                   const cpx<T>* __restrict__ ph, cpx<T>* __restrict__ xh,
                                                   const cpx<T>* bh, cpx<T>* rh, double* __restrict__ part,
                                                   int nb_red, T pix, T piy) {
     static_assert(MODE == C2_UPDATE || MODE == C2_RESID_INIT, "wall column pass mode");
-    if (sc->done) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    __shared__ double red[32];
-    __shared__ double slot[1];
+    __shared__ double red[64];
+    const PcgScal s0 = pcg_scalars(sc);
+    if (s0.done) return;
+    const cpx<T>* twm = tw_size(tw, g.ny);
+    const ColThread<T> ct = col_thread<T>(g, lds);
+    // the partials, then the row pass's columns, in flight across the reduction
+    const double* red_part = part + (MODE == C2_RESID_INIT ? PART_GEN : PART_C2);
+    double pb[PF_K][1], tot[1];
+    partials_fetch<1>(red_part, nb_red, pb);
+    __builtin_amdgcn_sched_barrier(0);
+    cpx<T> in[3][EPC];
+    {
+        const cpx<T>* srcs[3] = {H, H + NS, H + 2 * NS};
+        col_fetch<T, EPC, 3>(g, ct, srcs, in);
+    }
+    const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
+    __builtin_amdgcn_sched_barrier(0);
+    partials_sum<1>(red_part, nb_red, pb, tot, red);
     T alpha = (T)0;
     bool zero_x = false;
     if (MODE == C2_RESID_INIT) {
-        double tot[1];
-        final_sum<1>(part + PART_GEN, nb_red, tot, red);
-        const double bb = bcast(tot[0], slot) * sc->inv_n;
+        const double bb = tot[0] * s0.inv_n;
         const bool bad = !(bb == bb) || bb > 1.0e300;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->bb = bb;
@@ -460,38 +523,29 @@ __global__ void __launch_bounds__(256) k_wall_c2(ColGeom g, const cpx<T>* __rest
             }
         }
         if (bad) return;
-        zero_x = !sc->init_bb && bb == 0.0;
+        zero_x = !s0.init_bb && bb == 0.0;
     } else {
-        double tot[1];
-        final_sum<1>(part + PART_C2, nb_red, tot, red);
-        const double pq = bcast(tot[0], slot);
-        const double a = sc->rho / pq;
+        const double pq = tot[0];
+        const double a = s0.rho / pq;
         alpha = (T)a;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
             sc->pq = pq;
             sc->alpha = a;
-            sc->rho_prev = sc->rho;
-            sc->iter = sc->iter + 1;
+            sc->rho_prev = s0.rho;
+            sc->iter = s0.iter + 1;
             sc->first = 0;
         }
     }
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, 3));
-    const ColThread<T> ct = col_thread<T>(g, lds);
-    const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
     const cpx<T>* twy = tw_size(tw, 4 * g.ny);
-    const T sig = (T)sc->sig, alp = (T)sc->alp;
+    const T sig = (T)s0.sig, alp = (T)s0.alp;
     const size_t col = (size_t)ct.kx * g.ny;
-    {
-        const cpx<T>* srcs[3] = {H, H + NS, H + 2 * NS};
-        wall_col_fft<T, EPC, 3>(g, ct, srcs, twm);
-    }
+    wall_fft_to_lds<T, EPC, 3>(g, ct, in, twm);
     double acc[2] = {0.0, 0.0};
 #pragma unroll
-    for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+    for (int e_ = 0; e_ < EPC / 2; ++e_) {
         const int q = ct.t + g.TPC * e_;
-        if (q > g.ny / 2) continue;
-        const int m = (g.ny - q) & (g.ny - 1);
-        const bool self = q == m;
+        if (q >= g.ny / 2) continue;
+        const int m = q ? g.ny - q : g.ny / 2;
         const cpx<T> wy = twy[q];
         cpx<T> a[3][2];
 #pragma unroll
@@ -500,7 +554,7 @@ __global__ void __launch_bounds__(256) k_wall_c2(ColGeom g, const cpx<T>* __rest
                              wall_xs(f), wall_ys(f), a[f][0], a[f][1]);
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
-            if (!ct.valid || (s == 1 && self)) continue;
+            if (!ct.valid) continue;
             const int ysl = s ? m : q;
             const double cy = ysl == 0 ? 1.0 : 2.0;
             const T ky = (T)ysl * piy;
@@ -533,7 +587,7 @@ __global__ void __launch_bounds__(256) k_wall_c2(ColGeom g, const cpx<T>* __rest
                       wim * ((double)r0.im * r0.im + (double)r1.im * r1.im);
         }
     }
-    block_sum<2>(acc, red);
+    block_sum<2>(acc, red + 32);
     if (threadIdx.x == 0) {
         part[PART_C3 + 2 * blockIdx.x] = acc[0];
         part[PART_C3 + 2 * blockIdx.x + 1] = acc[1];
@@ -549,29 +603,28 @@ __global__ void __launch_bounds__(256) k_wall_from_S(ColGeom g, const cpx<T>* __
                                                       T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, 2));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     const WallColumn<T> wc = wall_column<T>(g, ct, tw, (T)0);
     const cpx<T>* twy = tw_size(tw, 4 * g.ny);
     const size_t col = (size_t)ct.kx * g.ny;
 #pragma unroll
-    for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+    for (int e_ = 0; e_ < EPC / 2; ++e_) {
         const int q = ct.t + g.TPC * e_;
-        if (q > g.ny / 2) continue;
-        const int m = (g.ny - q) & (g.ny - 1);
-        const bool self = q == m;
+        if (q >= g.ny / 2) continue;
+        const int m = q ? g.ny - q : g.ny / 2;
         const cpx<T> wy = twy[q];
 #pragma unroll
         for (int f = 0; f < 2; ++f) {
             cpx<T> sq = C<T>(0, 0), sm = C<T>(0, 0);
             if (ct.valid) {
                 sq = scale * S[f * NS + col + q];
-                sm = self ? sq : scale * S[f * NS + col + m];
+                sm = scale * S[f * NS + col + m];
             }
             cpx<T> F1, F2;
             wall_from_slots<T>(sq, sm, wc.wx, wy, wc.k0, q == 0, wall_xs(f), wall_ys(f), F1, F2);
             ct.buf[f * ct.fstride + q] = F1;
-            if (!self) ct.buf[f * ct.fstride + m] = F2;
+            ct.buf[f * ct.fstride + m] = F2;
         }
     }
     cpx<T>* dsts[2] = {H, H + NS};
@@ -606,14 +659,14 @@ __device__ __forceinline__ T wall_coef(int code, T kx, T ky, int kind) {
 // back and inverse-transformed together.  At most three inputs and three
 // outputs per job (the LDS holds three columns per block column).
 template <typename T, int EPC>
-__global__ void __launch_bounds__(256) k_wall_cols_jobs(ColGeom g, LinJobs<T> jobs, const cpx<T>* __restrict__ tw,
+__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_cols_jobs(ColGeom g, LinJobs<T> jobs, const cpx<T>* __restrict__ tw,
                                                          T pix, T piy, T scale) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
     const int jb = blockIdx.x / g.nblocks;
     if (jb >= jobs.n) return;
     const LinJob<T>& J = jobs.j[jb];
-    const cpx<T>* twm = twl_setup<T>(tw, g.ny, lds + col_lds_data(g, 3));
+    const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread_at<T>(g, lds, (int)blockIdx.x - jb * g.nblocks);
     const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
     const cpx<T>* twy = tw_size(tw, 4 * g.ny);
@@ -627,27 +680,15 @@ __global__ void __launch_bounds__(256) k_wall_cols_jobs(ColGeom g, LinJobs<T> jo
                 const int j = ct.t + g.TPC * e;
                 v[i][e] = (i < J.ni && ct.valid && j < ny) ? J.src[i][(size_t)ct.kx * ny + j] : C<T>(0, 0);
             }
-#pragma unroll
-        for (int i = 0; i < 3; ++i)
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) {
-                const int j = ct.t + g.TPC * e;
-                if (j < ny) ct.buf[i * ct.fstride + j] = v[i][e];
-            }
+        if (J.ni == 1) wall_fft_to_lds<T, EPC, 1>(g, ct, v, twm);
+        else if (J.ni == 2) wall_fft_to_lds<T, EPC, 2>(g, ct, v, twm);
+        else wall_fft_to_lds<T, EPC, 3>(g, ct, v, twm);
     }
-    __syncthreads();
-    if (J.ni == 1)
-        lds_fft<T, EPC, 1>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, false);
-    else if (J.ni == 2)
-        lds_fft<T, EPC, 2>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, false);
-    else
-        lds_fft<T, EPC, 3>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, false);
 #pragma unroll
-    for (int e_ = 0; e_ <= EPC / 2; ++e_) {
+    for (int e_ = 0; e_ < EPC / 2; ++e_) {
         const int q = ct.t + g.TPC * e_;
-        if (q > ny / 2) continue;
-        const int m = (ny - q) & (ny - 1);
-        const bool self = q == m;
+        if (q >= ny / 2) continue;
+        const int m = q ? ny - q : ny / 2;
         const cpx<T> wy = twy[q];
         cpx<T> a[3][2];
 #pragma unroll
@@ -679,19 +720,16 @@ __global__ void __launch_bounds__(256) k_wall_cols_jobs(ColGeom g, LinJobs<T> jo
         for (int k = 0; k < 3; ++k) {
             if (k >= J.no) continue;
             cpx<T> F1, F2;
-            wall_from_slots<T>(o[k][0], self ? o[k][0] : o[k][1], wc.wx, wy, wc.k0, q == 0, (J.kout[k] & 1) != 0,
+            wall_from_slots<T>(o[k][0], o[k][1], wc.wx, wy, wc.k0, q == 0, (J.kout[k] & 1) != 0,
                                (J.kout[k] & 2) != 0, F1, F2);
             ct.buf[k * ct.fstride + q] = F1;
-            if (!self) ct.buf[k * ct.fstride + m] = F2;
+            ct.buf[k * ct.fstride + m] = F2;
         }
     }
-    __syncthreads();
-    if (J.no == 1)
-        lds_fft<T, EPC, 1>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
-    else if (J.no == 2)
-        lds_fft<T, EPC, 2>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
-    else
-        lds_fft<T, EPC, 3>(ct.buf, ct.fstride, ny, ct.t, g.TPC, twm, true);
+    cpx<T> v[3][EPC];
+    if (J.no == 1) wall_ifft_from_lds<T, EPC, 1>(g, ct, v, twm);
+    else if (J.no == 2) wall_ifft_from_lds<T, EPC, 2>(g, ct, v, twm);
+    else wall_ifft_from_lds<T, EPC, 3>(g, ct, v, twm);
     if (ct.valid) {
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
@@ -699,7 +737,7 @@ __global__ void __launch_bounds__(256) k_wall_cols_jobs(ColGeom g, LinJobs<T> jo
 #pragma unroll
             for (int e = 0; e < EPC; ++e) {
                 const int j = ct.t + g.TPC * e;
-                if (j < ny) J.dst[k][(size_t)ct.kx * ny + j] = ct.buf[k * ct.fstride + j];
+                if (j < ny) J.dst[k][(size_t)ct.kx * ny + j] = v[k][e];
             }
         }
     }

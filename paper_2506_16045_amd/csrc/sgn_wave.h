@@ -576,9 +576,6 @@ __global__ void __launch_bounds__(64 * WROW_WPB) k_rows_inv_w(int ny, PtrList<co
 // pass output, f = 1, or a forward row transform, f = 1/nx, the column pass's
 // scale of 1/(nx ny) times the ny of its y round trip) and multiplies entry kx
 // by i k_x f before the inverse transform (the Nyquist entry has no wavenumber).
-struct RowDx {
-    double f[8];
-};
 __global__ void __launch_bounds__(512) k_rhs_rows_inv_w(int ny, PtrList<const cpx<double>, MAXF> src,
                                                         const double* __restrict__ eta,
                                                         const double* __restrict__ u,
@@ -717,8 +714,7 @@ __global__ void __launch_bounds__(WCOL_THREADS) k_pcg_c2w(int nx, const cpx<T>* 
     if (sc->done) return;
     __shared__ cpx<T> ldsb[6][WROW_BUF];
     __shared__ WaveTwl<T> tl;
-    __shared__ double red[32];
-    __shared__ double slot[1];
+    __shared__ double red[64];
     constexpr int NY = WCOL_NY;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int f = wv >> 1, h = wv & 1;
@@ -737,8 +733,8 @@ __global__ void __launch_bounds__(WCOL_THREADS) k_pcg_c2w(int nx, const cpx<T>* 
     }
     __builtin_amdgcn_sched_barrier(0);
     double tot[1];
-    partials_sum<1, true>(part + PART_C2, nb_r1, pb, tot, red);
-    const double pq = bcast<true>(tot[0], slot);
+    partials_sum<1>(part + PART_C2, nb_r1, pb, tot, red);
+    const double pq = tot[0];
     const double a = sc->rho / pq;
     const T alpha = (T)a;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -782,7 +778,7 @@ __global__ void __launch_bounds__(WCOL_THREADS) k_pcg_c2w(int nx, const cpx<T>* 
             }
         }
     }
-    block_sum<2>(acc, red);
+    block_sum<2>(acc, red + 32);
     if (threadIdx.x == 0) {
         part[PART_C3 + 2 * blockIdx.x] = acc[0];
         part[PART_C3 + 2 * blockIdx.x + 1] = acc[1];
@@ -802,15 +798,17 @@ __global__ void __launch_bounds__(WCOL_THREADS) k_pcg_c1w(int nx, const cpx<T>* 
     __shared__ cpx<T> ldsb[6][WROW_BUF];
     __shared__ WaveTwl<T> tl;
     __shared__ double red[32];
-    __shared__ double slot[2];
     constexpr int NY = WCOL_NY;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int f = wv >> 1, h = wv & 1;
     const int kx = blockIdx.x;
     if (threadIdx.x < WAVE_TWL_ENTRIES) (&tl.a[0][0])[threadIdx.x] = wave_twl_entry<T>(tw, threadIdx.x);
-    double beta_d = 0.0;
-    if (pcg_iterate_state(sc, part, nb3, red, slot, beta_d)) return;
-    const T beta = (T)beta_d, sig = (T)sc->sig, alp = (T)sc->alp, inv_n = (T)sc->inv_n;
+    const PcgScal s0 = pcg_scalars(sc);
+    double beta_d = 0.0, pb[PF_K][2], tot[2];
+    partials_fetch<2>(part + PART_C3, nb3, pb);
+    partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+    if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
+    const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
     const T kxw = wavenumber<T>(kx, nx, tpx);
 #pragma unroll
     for (int i = 0; i < 3; ++i) {

@@ -577,6 +577,23 @@ __device__ __forceinline__ void row_forward(const RowGeom& g, const RowThread<T>
     fft_sync(nt);
 }
 
+// The block barriers of row_forward, for threads of the block that have no row to
+// transform meanwhile.
+template <int EPC>
+__device__ __forceinline__ void row_forward_idle(const RowGeom& g) {
+    if (g.TPR > 64) {
+        for (int Np = 1; Np * EPC < g.M; Np *= EPC) {
+            block_lds_barrier();
+            block_lds_barrier();
+        }
+        block_lds_barrier();
+    }
+    if ((g.R << g.lgT) > 64) {
+        block_lds_barrier();
+        block_lds_barrier();
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Column geometry: a block holds Cb columns (kx) of TPC threads each; column c
 // is kx = blockIdx.x * Cb + c.  Thread t owns modes j = t + TPC*e (e < EPC,

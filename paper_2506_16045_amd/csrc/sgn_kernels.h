@@ -91,9 +91,10 @@ struct RowCombo {
 // block takes its rows of one field (blocks [f nblocks, (f + 1) nblocks): field f):
 // small grids fill more of the chip than with a block's fields in lockstep, and a
 // field's registers leave room for twice the waves (256 x 128, three fields: forward
-// 14.8 -> 6.6 us, inverse 8.2 -> 5.0; 512 x 512, inverse: 11.5 -> 7.8).
+// 14.8 -> 6.6 us, inverse 8.2 -> 5.0; 512 x 512, inverse: 11.5 -> 7.8).  64 registers,
+// so that two blocks of 1024 threads fit a compute unit (2048 x 2048: 60 -> 51 us).
 template <typename T, typename Tin, int EPC, int MAXT>
-__global__ void __launch_bounds__(MAXT) k_rows_fwd(RowGeom g, PtrList<const Tin, MAXF> src,
+__global__ void __launch_bounds__(MAXT, EPC <= 4 ? 8 : 4) k_rows_fwd(RowGeom g, PtrList<const Tin, MAXF> src,
                                                    PtrList<cpx<T>, MAXF> dst,
                                                    const cpx<T>* __restrict__ tw, T scale, RowCombo<Tin> cmb) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -291,6 +292,45 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_fwd(RowG
     }
 }
 
+// The same, a block's rows of one field (blocks [f nblocks, (f + 1) nblocks): field f),
+// for launches of less than 512 blocks, which leave most of the chip idle with a row's
+// seven fields on the same threads: 256 x 128 13.3 -> 5.9 us, 512 x 512 18.1 -> 12.4.
+__global__ void __launch_bounds__(256, 4) k_rhs_rows_fwd_f(RowGeom g, const double* __restrict__ eta,
+                                                           const double* __restrict__ u,
+                                                           const double* __restrict__ gh,
+                                                           PtrList<cpx<double>, MAXF> dst,
+                                                           const cpx<double>* __restrict__ tw) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cpx<double>* lds = reinterpret_cast<cpx<double>*>(smem_raw);
+    constexpr int EPC = 4;
+    const int f = (int)blockIdx.x / g.nblocks;
+    const RowThread<double> rt = row_thread_at<double>(g, lds, (int)blockIdx.x - f * g.nblocks, threadIdx.x);
+    const size_t npts = (size_t)g.nx * g.ny;
+    const bool use_e = f >= 2 && f < 6, use_h = f == 6;
+    cpx<double> z[1][EPC];
+#pragma unroll
+    for (int i = 0; i < EPC; ++i) {
+        const int j = rt.t + g.TPR * i;
+        const bool ok = j < g.M && rt.valid;
+        const unsigned o = ok ? rt.y * g.nx + 2 * j : 0u;
+        double v[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            const double e = use_e ? at32(eta, o + s) : 0.0;
+            double uc[2] = {0.0, 0.0}, hc[2] = {0.0, 0.0};
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                if (f != 4) uc[c] = at32(u + c * npts, o + s);
+                if (use_h) hc[c] = at32(gh + c * npts, o + s);
+            }
+            v[s] = ok ? rhs_source<2>(f, e, uc, hc) : 0.0;
+        }
+        z[0][i] = C<double>(v[0], v[1]);
+    }
+    cpx<double>* H[1] = {dst.p[f]};
+    row_forward<double, EPC, 1>(g, rt, z, H, tw, tw_size(tw, g.M), 1.0);
+}
+
 // x-derivatives formed by an inverse row pass: a nonzero f[i] means that field i
 // is given as another spectrum (delta's column output, f = 1, or a forward row
 // transform, f = 1/nx, the column pass's scale of 1/(nx ny) times the ny of its y
@@ -467,6 +507,88 @@ struct LinCodes {
     int code[LIN_MAXO][LIN_MAXI];
     int no;
 };
+
+// The same on 2D grids with rows of up to 1024 points, the fields side by side (order
+// m, delta, grad delta, grad eta, grad beta): each of eight groups of R TPR threads
+// transforms a field into LDS, then every thread forms the right-hand side at one point
+// from the eight values there, and the first two groups transform S_x and S_y forward.
+// The eight fields one after another on the same threads, with the accumulated state of
+// eight points each, took 27 us at 256 x 128 and 32 at 512 x 512; here 8.2 and 15.
+// Longer rows (eight entries per thread, one row per block, two batches of four fields
+// at 2048 pairs) were slower than one field after another: 514 against 293 us at
+// 2048 x 2048, 536 against 367 at 4096 x 1024.
+__global__ void __launch_bounds__(1024) k_rhs_rows_inv_f(RowGeom g, PtrList<const cpx<double>, MAXF> src,
+                                                         const double* __restrict__ eta, const double* __restrict__ u,
+                                                         const double* __restrict__ gh, double* __restrict__ eta_t,
+                                                         double* __restrict__ U_t, cpx<double>* __restrict__ Sdst,
+                                                         cpx<double>* __restrict__ Sydst,
+                                                         const cpx<double>* __restrict__ tw, double scale, RowDx dx,
+                                                         double tpx) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    cpx<double>* lds = reinterpret_cast<cpx<double>*>(smem_raw);
+    constexpr int EPC = 4;   // 8 groups of R M / 4 threads: as many as points
+    const cpx<double>* twm = tw_size(tw, g.M);
+    const int lgG = g.lgR + g.lgT, G = 1 << lgG, M = g.M;
+    const int f = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> lgG);
+    const int fs = g.R * (M + 1);
+    const RowThread<double> rt = row_thread_at<double>(g, lds + f * fs, blockIdx.x, threadIdx.x & (G - 1));
+    RowPairs<double, EPC> X;
+    row_fetch<double, EPC>(g, rt, src.p[f], X);
+    // this thread's point: value s of pair j of row r, its place in a field's LDS and
+    // the inputs there, in flight across the transform
+    const size_t npts = (size_t)g.nx * g.ny;
+    const int pr = (int)threadIdx.x >> 1, s = threadIdx.x & 1, r = pr >> ilog2(M), j = pr & (M - 1);
+    const bool ok = r < g.R && rt.row0 + r < g.ny;
+    const unsigned o = ok ? (rt.row0 + r) * g.nx + 2 * j + s : 0u, at = r < g.R ? 2 * (r * (M + 1) + j) + s : 0u;
+    const double e = at32(eta, o);
+    double uc[2], hc[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        uc[c] = at32(u + c * npts, o);
+        hc[c] = at32(gh + c * npts, o);
+    }
+    row_join<double, EPC>(g, rt, X, rt.lds, tw, dx.f[f], tpx);
+    fft_sync(G);
+    cpx<double> z[1][EPC];
+    row_inverse_lds<double, EPC, 1>(g, rt, twm, z);
+    fft_sync(g.TPR);
+    cpx<double>* rowb = rt.lds + rt.r * (M + 1);
+#pragma unroll
+    for (int i = 0; i < EPC; ++i) {
+        const int jj = rt.t + g.TPR * i;
+        if (jj < M) rowb[jj] = z[0][i];
+    }
+    block_lds_barrier();
+    double q[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) q[k] = scale * reinterpret_cast<const double*>(lds + k * fs)[at];
+    if (ok) {
+        const double e2 = e * e, m = q[0], dl = q[1];
+        const double bt = hc[0] * uc[0] + hc[1] * uc[1];
+        const double P = -dl * dl + uc[0] * q[2] + uc[1] * q[3];   // u.grad(delta) - delta^2
+        const double Q = uc[0] * q[6] + uc[1] * q[7];              // u.grad(beta)
+        const double S = e2 * e / 3.0 * P + e2 * m * dl + e * m * bt + e2 / 2.0 * Q;
+        const double T = e2 / 2.0 * P + e * m * dl + m * bt + e * Q;
+        at32(eta_t, o) = -m;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) at32(U_t + c * npts, o) = -e * (q[4 + c] - hc[c]) - hc[c] * T;
+        // this place of the first two fields is read by this thread only
+        reinterpret_cast<double*>(lds)[at] = S - e * uc[0] * uc[0];
+        reinterpret_cast<double*>(lds + fs)[at] = S - e * uc[1] * uc[1];
+    }
+    block_lds_barrier();
+    if (f < 2) {
+#pragma unroll
+        for (int i = 0; i < EPC; ++i) {
+            const int jj = rt.t + g.TPR * i;
+            z[0][i] = jj < M ? rowb[jj] : C<double>(0, 0);
+        }
+        cpx<double>* H[1] = {f == 0 ? Sdst : Sydst};
+        row_forward<double, EPC, 1>(g, rt, z, H, tw, twm, 1.0);
+    } else {
+        row_forward_idle<EPC>(g);
+    }
+}
 
 template <typename T>
 __device__ __forceinline__ cpx<T> lin_coef(int code, T kx, T ky) {
@@ -842,15 +964,12 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const
 // read the done flag.  Idempotent with the C1 that follows.  With pub set,
 // thread 0 then publishes the loop flags as k_publish_flags does.
 __device__ __forceinline__ void publish_flags(const SolveScal* sc, int* d, int seq) {
-    volatile int* v = d;
-    v[0] = sc->iter;
-    v[1] = sc->max_iter;
-    v[2] = sc->done;
-    v[3] = sc->converged;
-    v[4] = sc->flat;
-    v[5] = sc->status;
-    v[7] = sc->outer;
-    v[6] = seq;
+    const int v[8] = {sc->iter, sc->max_iter, sc->done, sc->converged, sc->flat, sc->status, seq, sc->outer};
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if (i != 6) __hip_atomic_store(d + i, v[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the values are there before seq
+    __hip_atomic_store(d + 6, v[6], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ void inner_close(SolveScal* s, const SolveScal* d);
 // With inner set (the FP32 inner solve of a refinement step that has just
@@ -875,21 +994,21 @@ __global__ void __launch_bounds__(256) k_pcg_check(SolveScal* __restrict__ sc, c
 
 // Publish iter, max_iter, done, converged, flat, status of a solve into host
 // memory (d: device address of a host-coherent pinned buffer), then the
-// sequence number seq in d[6].  The stores are volatile and system-coherent:
-// each completes before the next is issued, so a host that sees seq also sees
-// the values (no cache-wide fence needed for one thread's ordered stores).
+// sequence number seq in d[6].  System-scope stores: the values go out together, and
+// seq once all of them have completed, so a host that sees seq also sees the values
+// (no cache-wide fence needed for one thread's stores; one completed store after
+// another made the check kernel take 7.1 us, 4.0 so).
 __global__ void k_publish_flags(const SolveScal* __restrict__ sc, int* d, int seq) {
     if (threadIdx.x == 0 && blockIdx.x == 0) publish_flags(sc, d, seq);
 }
 
 // Row pass R1 on rows of 256 threads and more: a block's fields one after another,
 // the next one's loads in flight meanwhile (three fields of LDS do not fit).
-template <typename T, int D, int MAXT>
+template <typename T, int EPC, int D, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_pcg_r1(RowGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, cpx<T>* H, size_t NS,
                                                  const T* __restrict__ eta, const T* __restrict__ gh,
                                                  double* __restrict__ part) {
-    constexpr int EPC = 4;
     if (sc->done) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
     cpx<T>* lds = reinterpret_cast<cpx<T>*>(smem_raw);
@@ -1231,8 +1350,16 @@ __device__ __forceinline__ cpx<T> wall_project(int c, cpx<T> a, cpx<T> b, int kx
 // WALL: the solve runs on the periodic twin of a wall grid; the new residual is
 // projected onto the symmetric modes before it is used (rounding would otherwise
 // seed the other parity, which the iteration amplifies at low wavenumbers).
-template <typename T, int EPC, int D, int MODE, bool WALL = false>
-__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c2(ColGeom g, const cpx<T>* __restrict__ tw,
+// FEW (launches of at most one block per compute unit, where only latency counts): two
+// waves per SIMD instead of three, which ends the last spills (a kernel that uses
+// scratch memory takes 1 to 2 us longer), and the fields the new residual needs loaded
+// with the columns, in flight across the transform, where that fits the registers (all
+// but the FP64 update, which spills again: 9.1 -> 10.2 us at 256 x 128).  FP64 512 x 512:
+// residual 10.7 -> 9.2 us, initial residual 12.6 -> 10.7; FP32 update 5.6 -> 5.3.
+template <typename T, int MODE, bool FEW>
+constexpr bool C2_PRE = FEW && (sizeof(T) == 4 || MODE != C2_UPDATE);
+template <typename T, int EPC, int D, int MODE, bool WALL = false, bool FEW = false>
+__global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_pcg_c2(ColGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, const cpx<T>* __restrict__ H,
                                                  size_t NS, cpx<T>* __restrict__ qh, const cpx<T>* __restrict__ ph,
                                                  cpx<T>* __restrict__ xh, const cpx<T>* __restrict__ bh,
@@ -1257,6 +1384,24 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c2(ColGeom g, const
 #pragma unroll
         for (int c = 0; c <= D; ++c) srcs[c] = H + c * NS;
         col_fetch<T, EPC, D + 1>(g, ct, srcs, in);
+    }
+    constexpr bool PRE = C2_PRE<T, MODE, FEW>;
+    constexpr int EP = PRE ? EPC : 1;
+    cpx<T> r_pre[D][EP], x_pre[D][EP], p_pre[D][EP];   // r (or b), x, p
+    if (PRE) {
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            bool ok;
+            const unsigned idx = col_index(g, ct, ct.t + g.TPC * e, ok);
+#pragma unroll
+            for (int c = 0; c < D; ++c) {
+                r_pre[c][e] = at32((MODE == C2_UPDATE ? (const cpx<T>*)rh : bh) + c * NS, idx);
+                if (MODE == C2_UPDATE) {
+                    x_pre[c][e] = at32(xh + c * NS, idx);
+                    p_pre[c][e] = at32(ph + c * NS, idx);
+                }
+            }
+        }
     }
     __builtin_amdgcn_sched_barrier(0);   // keep the data loads ahead of the reduction
     T alpha = (T)0;
@@ -1368,15 +1513,16 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c2(ColGeom g, const
                 if (MODE == C2_STORE) {
                     at32(qh + c * NS, idx) = q;
                 } else if (MODE == C2_RESID) {
-                    r[c] = at32(bh + c * NS, idx) - q;
+                    r[c] = (PRE ? r_pre[c][e % EP] : at32(bh + c * NS, idx)) - q;
                     at32(rh + c * NS, idx) = r[c];
                 } else if (MODE == C2_RESID_INIT) {
-                    r[c] = zero_x ? C<T>(0, 0) : at32(bh + c * NS, idx) - q;
+                    r[c] = zero_x ? C<T>(0, 0) : (PRE ? r_pre[c][e % EP] : at32(bh + c * NS, idx)) - q;
                     at32(rh + c * NS, idx) = r[c];
                     if (zero_x) at32(xh + c * NS, idx) = C<T>(0, 0);
                 } else {
-                    at32(xh + c * NS, idx) = at32(xh + c * NS, idx) + alpha * at32(ph + c * NS, idx);
-                    r[c] = at32(rh + c * NS, idx) - alpha * q;
+                    at32(xh + c * NS, idx) = (PRE ? x_pre[c][e % EP] : at32(xh + c * NS, idx)) +
+                                             alpha * (PRE ? p_pre[c][e % EP] : at32(ph + c * NS, idx));
+                    r[c] = (PRE ? r_pre[c][e % EP] : at32(rh + c * NS, idx)) - alpha * q;
                     at32(rh + c * NS, idx) = r[c];
                 }
             }

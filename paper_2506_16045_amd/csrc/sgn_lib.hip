@@ -226,22 +226,23 @@ struct RowLaunch {
 // store 16 R bytes side by side in the transposed layout (4096 x 1024, one row or two:
 // forward rows 147 -> 127 us, right-hand side's 215 -> 187, Krylov row pass 153 -> 139);
 // the right-hand side's inverse pass, which holds 240 registers, at most 512.
-constexpr int ROW_WIDE = 1024, RHS_INV_WIDE = 512;
 template <typename T>
-RowLaunch row_launch(int nx, int ny, int wide = ROW_WIDE) {
+RowLaunch row_launch(int nx, int ny, int epc_wide = 4, int narrow = 256, int wide = 0, bool waves = false) {
     RowLaunch L;
     const int M = nx / 2;
-    L.epc = (M > 4096) ? 8 : 4;
+    L.epc = M > 4096 ? 8 : M >= 1024 && ny > 1 ? epc_wide : 4;
+    if (!wide) wide = L.epc == 8 ? 512 : 1024;
     RowGeom& g = L.g;
     g.nx = nx;
     g.ny = ny;
     g.M = M;
     g.TPR = M / L.epc > 0 ? M / L.epc : 1;
-    int R = (g.TPR >= 256 ? wide : 256) / g.TPR;
+    int R = (M >= 1024 ? wide : narrow) / g.TPR;
     if (R < 1) R = 1;
     const int np = next_pow2(ny);
     if (R > np) R = np;
     while (R > 1 && ny / R < 256 && (R / 2) * g.TPR >= 64) R >>= 1;
+    while (waves && R * g.TPR < 64) R <<= 1;
     g.R = R;
     g.nblocks = (ny + R - 1) / R;
     g.lgR = __builtin_ctz(R);
@@ -249,6 +250,20 @@ RowLaunch row_launch(int nx, int ny, int wide = ROW_WIDE) {
     L.threads = R * g.TPR;
     L.lds = (size_t)R * (M + 1) * sizeof(cpx<T>);
     return L;
+}
+
+// Row pass R1.  Long rows of 2D grids take eight entries per thread: a quarter fewer LDS
+// exchanges (4096 x 1024: 141 -> 127 us; their plain row transforms gain nothing, 126
+// -> 140 forward).
+template <typename T>
+RowLaunch r1_launch(const Dims& d) {
+    return row_launch<T>(d.nx, d.ny, 8, 256, 0, true);
+}
+// The right-hand side's inverse row pass: eight groups of threads per block, each of a
+// wave or two (k_rhs_rows_inv_f); on rows above 1024 points 512 threads with one field
+// after another (240 registers).
+RowLaunch rhs_inv_launch(const Dims& d) {
+    return row_launch<double>(d.nx, d.ny, 4, 128, 512, d.nx <= 1024);
 }
 
 struct ColLaunch {
@@ -746,12 +761,12 @@ bool col_wave(const PcgLaunch<T, D>& P) {
     return sizeof(T) == 4 && D == 2 && P.d.ny == WCOL_NY && P.cl.g.Cb == 1 && !P.native && !P.wall &&
            wave_rows_enabled();
 }
-// Rows of up to 128 threads (nx <= 1024) in whole waves run one group of threads per
-// field (k_pcg_r1f); the few rows of a grid that do not fill a wave, and longer rows
-// (three of which do not fit the LDS of a compute unit), run field by field.
+// Rows of up to 512 points pairs (nx <= 1024) run one group of threads per field
+// (k_pcg_r1f, at least a wave each); longer ones, three of which do not fit the LDS of
+// a compute unit, run field by field.
 template <typename T, int D>
 bool r1_fields(const PcgLaunch<T, D>& P) {
-    return P.rl.epc == 4 && P.rl.g.TPR <= 128 && P.rl.threads >= 64;
+    return P.rl.g.M <= 512;
 }
 // The line of 16384 points: its row pass as three launches of 64 waves.
 template <typename T, int D>
@@ -799,12 +814,14 @@ sgn_status pcg_r1(PcgLaunch<T, D>& P, bool curvature = false) {
     if (fields)
         st = launch(k_pcg_r1f<T, D>);
     else
-        st = L.threads <= 256 ? launch(k_pcg_r1<T, D, 256>) : launch(k_pcg_r1<T, D, 1024>);
+        st = L.epc == 8 ? launch(k_pcg_r1<T, 8, D, 512>) : launch(k_pcg_r1<T, 4, D, 1024>);
     if (st != SGN_OK) return st;
     CHECK_LAUNCH(P.ctx);
     return SGN_OK;
 }
 
+// Column launches of up to one block per compute unit (see k_pcg_c2).
+constexpr int C2_FEW_BLOCKS = 256;
 template <typename T, int D, int MODE>
 sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, const ProfScope& ps) {
     auto& L = P.cl;
@@ -821,7 +838,7 @@ sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, con
     };
     if (P.native) {
         if constexpr (D == 2 && (MODE == C2_UPDATE || MODE == C2_RESID_INIT)) {
-            auto k = k_wall_c2<T, 4, MODE>;
+            auto k = L.g.nblocks <= C2_FEW_BLOCKS ? k_wall_c2<T, 4, MODE, true> : k_wall_c2<T, 4, MODE, false>;
             HIPCHK(P.ctx, allow_lds(k, lds));
             hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, P.ctx->stream, ps.a, ps.b, 0, L.g,
                                   twiddles<T>(P.ctx), P.sc, (const cpx<T>*)P.b.H, P.d.NS, (const cpx<T>*)P.b.ph,
@@ -842,7 +859,11 @@ sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, con
             return SGN_OK;
         }
     }
-    return P.wall ? launch(k_pcg_c2<T, 4, D, MODE, true>) : launch(k_pcg_c2<T, 4, D, MODE>);
+    if (P.wall) return launch(k_pcg_c2<T, 4, D, MODE, true>);
+    if constexpr (MODE != C2_STORE) {
+        if (L.g.nblocks <= C2_FEW_BLOCKS) return launch(k_pcg_c2<T, 4, D, MODE, false, true>);
+    }
+    return launch(k_pcg_c2<T, 4, D, MODE>);
 }
 
 template <typename T, int D>
@@ -1158,7 +1179,7 @@ sgn_status solve_fp64(sgn_ctx* ctx, const Dims& d, const double* eta, const doub
     P.native = D == 2 && ctx->wall_native;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = P.native ? col_launch<double>(d.nx, d.ny) : col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
@@ -1284,7 +1305,7 @@ sgn_status solve_wall_native(sgn_ctx* ctx, const Dims& dw, const double* eta, co
     P.native = true;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
@@ -1358,7 +1379,7 @@ sgn_status solve_mixed(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     P.wall = ctx->wall_twin;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, true);
     P.sc = cm.sc;
@@ -1369,7 +1390,7 @@ sgn_status solve_mixed(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     Q.wall = ctx->wall_twin;
     Q.ctx = ctx;
     Q.d = d;
-    Q.rl = row_launch<float>(d.nx, d.ny);
+    Q.rl = r1_launch<float>(d);
     Q.cl = col_launch<float>(d.nx, d.ny);
     Q.b = carve_pcg<float>(cv, d, false);
     Q.sc = cm.sc + 1;
@@ -1646,7 +1667,7 @@ sgn_status solve_gmres(sgn_ctx* ctx, const Dims& d, const double* eta, const dou
     auto& P = G.P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
@@ -1951,7 +1972,7 @@ sgn_status apply_G(sgn_ctx* ctx, const Dims& d, const double* eta, const double*
     PcgLaunch<double, D> P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;
@@ -2063,6 +2084,11 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         // transformed one after another in each wave)
         if constexpr (D == 1) {   // lines of 16384 points (shorter ones: rhs_1d_block)
             s = launch(k_rhs_rows_fwd<D, 8, 1, 1024>);
+        } else if (RL.threads <= 256 && RL.g.nblocks < 512) {
+            hipLaunchKernelGGL(k_rhs_rows_fwd_f, dim3(RL.g.nblocks * t.n), dim3(RL.threads), rlds, ctx->stream, RL.g,
+                               eta, u, gh, t, ctx->tw64);
+            CHECK_LAUNCH(ctx);
+            s = SGN_OK;
         } else if (RL.threads <= 256) {
             HIPCHK(ctx, allow_lds(k_rhs_rows_fwd<D, 4, 3, 256>, l3));
             hipLaunchKernelGGL((k_rhs_rows_fwd<D, 4, 3, 256>), dim3(RL.g.nblocks), dim3(RL.threads), l3,
@@ -2117,13 +2143,12 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         ProfScope ps(ctx, D == 2 ? SGN_KERNEL_RHS_ROWS_INV : SGN_KERNEL_ROWS);
         PtrList<const cpx<double>, MAXF> q{};
         q.n = 0;
-        // OA = [delta, d delta (D), m, d eta (D)], OB = [d beta (D)]; the wave-private
-        // pass takes d eta ahead of d beta (its waves all run at once), the block
-        // pass last
-        const bool wave = D == 2 && wave_rows(d);
+        // OA = [delta, d delta (D), m, d eta (D)], OB = [d beta (D)]; the passes with
+        // the fields side by side take d eta ahead of d beta, the others last
+        const bool wave = D == 2 && wave_rows(d), side = D == 2 && d.nx <= 1024;
         q.p[q.n++] = OA + (1 + D) * NS;
         for (int i = 0; i <= D; ++i) q.p[q.n++] = OA + i * NS;
-        const int at_eta = wave ? 2 + D : 2 + 2 * D, at_beta = wave ? 2 + 2 * D : 2 + D;
+        const int at_eta = side ? 2 + D : 2 + 2 * D, at_beta = side ? 2 + 2 * D : 2 + D;
         for (int i = 0; i < D; ++i) {
             q.p[at_eta + i] = OA + (2 + D + i) * NS;
             q.p[at_beta + i] = OB + i * NS;
@@ -2137,12 +2162,13 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
             dx.f[2] = 1.0;
             dx.f[at_eta] = dx.f[at_beta] = 1.0 / d.nx;
         }
-        const RowLaunch RI = row_launch<double>(d.nx, d.ny, RHS_INV_WIDE);
-        const size_t ilds = row_lds_bytes<double>(RI.g, 1);
+        const RowLaunch RI = D == 1 ? RL : rhs_inv_launch(d);
+        const int groups = D == 2 && RI.g.M <= 512 ? 8 : 1;
+        const size_t ilds = row_lds_bytes<double>(RI.g, groups);
         auto launch = [&](auto k) -> sgn_status {
             HIPCHK(ctx, allow_lds(k, ilds));
-            hipLaunchKernelGGL(k, dim3(RI.g.nblocks), dim3(RI.threads), ilds, ctx->stream, RI.g, q, eta, u, gh, eta_t,
-                               U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0, dx, d.tpx);
+            hipLaunchKernelGGL(k, dim3(RI.g.nblocks), dim3(RI.threads * groups), ilds, ctx->stream, RI.g, q, eta, u,
+                               gh, eta_t, U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0, dx, d.tpx);
             CHECK_LAUNCH(ctx);
             return SGN_OK;
         };
@@ -2154,7 +2180,7 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         } else if constexpr (D == 1) {
             s = launch(k_rhs_rows_inv<D, 8, 1024>);
         } else {
-            s = launch(k_rhs_rows_inv<D, 4, 512>);
+            s = groups == 8 ? launch(k_rhs_rows_inv_f) : launch(k_rhs_rows_inv<D, 4, 512>);
         }
         if (s != SGN_OK) return s;
     }
@@ -2790,7 +2816,7 @@ sgn_status sbdf2_R(sgn_state* st, cpx<double>* Rout) {
     PcgLaunch<double, D> P;
     P.ctx = ctx;
     P.d = d;
-    P.rl = row_launch<double>(d.nx, d.ny);
+    P.rl = r1_launch<double>(d);
     P.cl = col_launch<double>(d.nx, d.ny);
     P.b = carve_pcg<double>(cv, d, false);
     P.sc = cm.sc;

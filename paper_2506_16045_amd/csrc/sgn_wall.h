@@ -483,8 +483,8 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c1(ColGeom g, cons
 // MODE C2_UPDATE: alpha from p.Gp; x += alpha p, r -= alpha q, z = A^{-1} r,
 // partial r.z, r.r.  MODE C2_RESID_INIT: bb from the setup partials;
 // r = b - G x_0 (zero for a zero b), partial r.z, r.r.
-template <typename T, int EPC, int MODE>
-__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c2(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+template <typename T, int EPC, int MODE, bool FEW>
+__global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_wall_c2(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
                                                   const cpx<T>* __restrict__ H, size_t NS,
                                                   const cpx<T>* __restrict__ ph, cpx<T>* __restrict__ xh,
                                                   const cpx<T>* bh, cpx<T>* rh, double* __restrict__ part,
@@ -508,6 +508,29 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c2(ColGeom g, cons
         col_fetch<T, EPC, 3>(g, ct, srcs, in);
     }
     const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
+    // the fields of the update too, r (or b), x, p, where they fit (see k_pcg_c2)
+    constexpr bool PRE = C2_PRE<T, MODE, FEW>;
+    constexpr int NP = PRE ? EPC / 2 : 1;
+    cpx<T> pre[NP][2][3][2];
+    if (PRE) {
+#pragma unroll
+        for (int e_ = 0; e_ < NP; ++e_) {
+            const int q = ct.t + g.TPC * e_;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const unsigned idx =
+                    (ct.valid && q < g.ny / 2) ? (unsigned)(ct.kx * g.ny + (!s ? q : q ? g.ny - q : g.ny / 2)) : 0u;
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    pre[e_][s][0][c] = at32((MODE == C2_UPDATE ? (const cpx<T>*)rh : bh) + c * NS, idx);
+                    if (MODE == C2_UPDATE) {
+                        pre[e_][s][1][c] = at32(xh + c * NS, idx);
+                        pre[e_][s][2][c] = at32(ph + c * NS, idx);
+                    }
+                }
+            }
+        }
+    }
     __builtin_amdgcn_sched_barrier(0);
     partials_sum<1>(red_part, nb_red, pb, tot, red);
     T alpha = (T)0;
@@ -563,17 +586,19 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c2(ColGeom g, cons
             const cpx<T> q1 = C<T>(a[1][s].re + ky * wv.re, a[1][s].im + ky * wv.im);
             cpx<T> r0, r1;
             if (MODE == C2_RESID_INIT) {
-                r0 = zero_x ? C<T>(0, 0) : bh[col + ysl] - q0;
-                r1 = zero_x ? C<T>(0, 0) : bh[NS + col + ysl] - q1;
+                r0 = zero_x ? C<T>(0, 0) : (PRE ? pre[e_ % NP][s][0][0] : bh[col + ysl]) - q0;
+                r1 = zero_x ? C<T>(0, 0) : (PRE ? pre[e_ % NP][s][0][1] : bh[NS + col + ysl]) - q1;
                 if (zero_x) {
                     xh[col + ysl] = C<T>(0, 0);
                     xh[NS + col + ysl] = C<T>(0, 0);
                 }
             } else {
-                xh[col + ysl] = xh[col + ysl] + alpha * ph[col + ysl];
-                xh[NS + col + ysl] = xh[NS + col + ysl] + alpha * ph[NS + col + ysl];
-                r0 = rh[col + ysl] - alpha * q0;
-                r1 = rh[NS + col + ysl] - alpha * q1;
+                const cpx<T>(&f)[3][2] = pre[e_ % NP][s];
+                xh[col + ysl] = (PRE ? f[1][0] : xh[col + ysl]) + alpha * (PRE ? f[2][0] : ph[col + ysl]);
+                xh[NS + col + ysl] =
+                    (PRE ? f[1][1] : xh[NS + col + ysl]) + alpha * (PRE ? f[2][1] : ph[NS + col + ysl]);
+                r0 = (PRE ? f[0][0] : rh[col + ysl]) - alpha * q0;
+                r1 = (PRE ? f[0][1] : rh[NS + col + ysl]) - alpha * q1;
             }
             rh[col + ysl] = r0;
             rh[NS + col + ysl] = r1;

@@ -2,6 +2,7 @@
 #include "sgn.h"
 #include "sgn_kernels.h"
 #include "sgn_batch.h"
+#include "sgn_linimp.h"
 #include "sgn_wall.h"
 #include "sgn_wave.h"
 #include <hip/hip_ext.h>
@@ -2916,7 +2917,6 @@ sgn_status linimp_steps(sgn_state* st, const LinimpScheme& sch, double scheme_r,
     for (int n = 0; n < nsteps; ++n) {
         // the current level n+s-1 is the state: f and R from eta, U and u_hat (b.uh)
         if ((s = state_rhs(st, st->eta, st->u, b.rk_fe[0], b.rk_fU[0])) != SGN_OK) return s;
-        if ((s = sbdf2_R<D>(st, b.R_cur)) != SGN_OK) return s;
         std::vector<const double*> te, tU;
         std::vector<double> cw;
         for (int j = 0; j < S; ++j) {
@@ -2929,6 +2929,49 @@ sgn_status linimp_steps(sgn_state* st, const LinimpScheme& sch, double scheme_r,
             tU.push_back(j < slots ? b.lv_fU[slot(j)] : b.rk_fU[0]);
             cw.push_back(dt * sch.b[j]);
         }
+        const int old = slot(0);
+        if (D == 1 && N >= LINIMP_NMIN && N <= LINIMP_NMAX) {   // the rest of the step in one launch
+            LinimpLine P{};
+            P.L = d.Lx;
+            P.sig = st->sb_sig;
+            P.alp = st->sb_alp;
+            P.hx = st->gh;
+            P.eta = st->eta;
+            P.U = st->U;
+            P.u = st->u;
+            P.eta_to = b.lv_eta[old];
+            P.U_to = b.lv_U[old];
+            P.nterms = (int)te.size();
+            for (int k = 0; k < P.nterms; ++k) {
+                P.fe[k] = te[k];
+                P.fU[k] = tU[k];
+                P.w[k] = cw[k];
+            }
+            P.div = sch.a[S];
+            P.s = S;
+            for (int j = 0; j < S; ++j) {
+                if (j < slots) P.Rj[j] = b.lv_R[slot(j)];
+                P.uhj[j] = j < slots ? b.lv_uh[slot(j)] : b.uh;
+                P.b[j] = sch.b[j];
+                P.c[j] = sch.c[j];
+            }
+            P.inv_cs = 1.0 / sch.c[S];
+            P.R = b.R_cur;
+            P.uh_new = b.lv_uh[old];
+            {
+                ProfScope ps(ctx, SGN_KERNEL_ROWS);
+                HIPCHK(ctx, launch_linimp_line((int)N, ctx->stream, P, ctx->tw64));
+            }
+            std::swap(b.lv_fe[old], b.rk_fe[0]);
+            std::swap(b.lv_fU[old], b.rk_fU[0]);
+            std::swap(b.lv_R[old], b.R_cur);
+            std::swap(b.lv_uh[old], b.uh);
+            st->lm_head = (st->lm_head + 1) % slots;
+            st->t += dt;
+            st->steps += 1;
+            continue;
+        }
+        if ((s = sbdf2_R<D>(st, b.R_cur)) != SGN_OK) return s;
         if ((s = lincomb(ctx, N, nullptr, 1.0, te, cw, b.tmp_e, sch.a[S])) != SGN_OK) return s;
         if ((s = lincomb(ctx, DN, nullptr, 1.0, tU, cw, b.tmp_U, sch.a[S])) != SGN_OK) return s;
         // u_hat of level n+s into the oldest slot's u_hat buffer (read first per mode)
@@ -2940,7 +2983,6 @@ sgn_status linimp_steps(sgn_state* st, const LinimpScheme& sch, double scheme_r,
             lv.b[j] = sch.b[j];
             lv.c[j] = sch.c[j];
         }
-        const int old = slot(0);
         hipLaunchKernelGGL(k_linimp_solve<D>, dim3(flat_blocks(d.NS)), dim3(256), 0, ctx->stream, d.nx, d.ny, d.NS,
                            d.tpx, d.tpy, st->sb_sig, st->sb_alp, 1.0 / sch.c[S], lv, b.lv_uh[old]);
         CHECK_LAUNCH(ctx);

@@ -1,10 +1,12 @@
 """GPU parity of the one-workgroup 1D engine at every line length it takes (128 to
 8192 points, each its own radix plan, thread count and exchange scheme) and at the
 longest line of the short-line path beside it (64): FP64 and mixed solves from a
-zero guess and from a guess, the right-hand side, and RK4 steps, against the oracle."""
+zero guess and from a guess, the right-hand side, RK4 steps and linearly implicit
+steps of two and three levels, against the oracle."""
 import numpy as np
 import pytest
 
+from oracle import linimp as L
 from oracle import operators as op
 from oracle import rhs as orhs
 from oracle import stepping as ost
@@ -88,3 +90,28 @@ def test_rk4_at_every_length(ctx, n):
     assert info.converged and info.solves == 4 * steps
     for a, r in zip((e, Ud, v), ref):
         assert np.linalg.norm(a.cpu().numpy() - r) <= 1e-10 * np.linalg.norm(r)
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("scheme", ["sbdf2", "linimp3"])
+def test_linearly_implicit_steps_at_every_length(ctx, n, scheme):
+    from paper_2506_16045_amd import sgn
+    g, h, eta, u, gh, flat = _problem(n)
+    tol, dt, steps = 1e-12, 0.01, 6
+    pb = ost.Problem.from_h(g, h, tol=tol)
+    U = pb.G(eta, u)
+    e, Ud, v = _t(eta), _t(U), _t(u)
+    st = sgn.State(ctx, g, _t(h), _t(gh), bool(flat), e, Ud, v)
+    opts = sgn.solve_opts(tol=tol, max_iter=3000)
+    if scheme == "sbdf2":
+        ref = ost.run_sbdf2(pb, eta, U, u, dt, steps)
+        for k in (2, steps - 2):   # a history carried over calls
+            st.step_linimp(dt, k, None, opts)
+    else:
+        r, th = 0.6, 0.9
+        ref = L.run_linimp(pb, L.sbdf3r(r), eta, U, u, dt, steps, theta=th)
+        for k in (3, steps - 3):
+            st.step_linimp3(r, th, dt, k, None, opts)
+    for a, b in zip((e, Ud, v), ref):
+        assert np.linalg.norm(a.cpu().numpy() - b) <= 1e-10 * np.linalg.norm(b)
+    st.close()

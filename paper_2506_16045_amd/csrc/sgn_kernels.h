@@ -1293,6 +1293,196 @@ __global__ void __launch_bounds__(64) k_pcg_long_rows(const cpx<T>* __restrict__
     }
 }
 
+// The iteration on that line with the column passes fused in (three launches instead of
+// five): k_pcg_long_c1 is k_pcg_c1's update (mode C1_UPDATE) and k_pcg_long_cols<true>,
+// k_pcg_long_c2 is k_pcg_long_cols<false> and k_pcg_c2's update (C2_UPDATE).  A mode's
+// two fields are in one wave, so what the passes exchanged through memory goes through
+// LDS.  20 -> 15.4 us per iteration.
+struct LongCol {
+    int col, t, s, f, u, b;
+    bool edge;   // the thread of modes 0 and M
+};
+__device__ __forceinline__ LongCol long_col(int lane, int u) {
+    LongCol c;
+    c.col = lane >> 4;
+    c.t = lane & 15;
+    c.s = c.col & 1;
+    c.f = c.col >> 1;
+    c.u = u;
+    c.b = c.s == 0 ? u : (u == 0 ? LONG_B / 2 : LONG_B - u);
+    c.edge = u == 0 && c.s == 0 && c.t == 0;
+    return c;
+}
+template <typename T>
+__global__ void __launch_bounds__(64) k_pcg_long_c1(const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+                                                    const double* __restrict__ part, int nb3,
+                                                    const cpx<T>* __restrict__ rh, cpx<T>* __restrict__ ph,
+                                                    cpx<T>* __restrict__ H, size_t NS, T tpx) {
+    __shared__ cpx<T> lds[4 * LONG_A];
+    __shared__ double red[32];
+    const PcgScal s0 = pcg_scalars(sc);
+    if (s0.done) return;
+    const LongCol c = long_col(threadIdx.x, blockIdx.x);
+    constexpr int NX = 2 * LONG_M;
+    const cpx<T>* tw2 = tw_size(tw, NX);
+    const cpx<T>* twM = tw_size(tw, LONG_M);
+    double pb[PF_K][2], tot[2], beta_d;
+    partials_fetch<2>(part + PART_C3, nb3, pb);
+    __builtin_amdgcn_sched_barrier(0);
+    cpx<T> r[5], last[5], w[4], wc[4];   // modes 128 a + b, a = t + 16 e; entry 4: mode M
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+        const int k = e < 4 ? LONG_B * (c.t + 16 * e) + c.b : (c.edge ? LONG_M : 0);
+        r[e] = rh[k];
+        last[e] = ph[k];
+        if (e < 4) {
+            w[e] = tw2[k];
+            wc[e] = twM[(c.t + 16 * e) * c.b];
+        }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+    if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
+    const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
+    cpx<T>* buf = lds + c.col * LONG_A;
+    cpx<T> p[5], v[1][4];
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+        const int k = e < 4 ? LONG_B * (c.t + 16 * e) + c.b : LONG_M;
+        const cpx<T> ri[1] = {r[e]};
+        cpx<T> z[1];
+        precond_mode<T, 1>(wavenumber<T>(k, NX, tpx), (T)0, sig, alp, ri, z);
+        // beta = 0 on the first iteration: p = z, the unset direction is not used
+        p[e] = (beta != (T)0) ? z[0] + beta * last[e] : z[0];
+        if (c.f == 0 && (e < 4 || c.edge)) ph[k] = p[e];
+        if (e < 4) buf[c.t + 16 * e] = p[e];
+    }
+    fft_sync(16);
+    const cpx<T>* mir = c.u == 0 ? buf : lds + (c.col ^ 1) * LONG_A;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int a = c.t + 16 * e, k = LONG_B * a + c.b;
+        const bool zero = k == 0;
+        cpx<T> xk = inv_n * p[e];
+        cpx<T> pm = mir[c.b == 0 ? (LONG_A - a) & (LONG_A - 1) : LONG_A - 1 - a];
+        pm.re = zero ? p[4].re : pm.re;
+        pm.im = zero ? p[4].im : pm.im;
+        cpx<T> xm = inv_n * pm;
+        if (c.f) {   // div p
+            xk = ik(wavenumber<T>(k, NX, tpx), xk);
+            xm = ik(wavenumber<T>(LONG_M - k, NX, tpx), xm);
+        }
+        cpx<T> zm;
+        split_join(xk, xm, w[e], v[0][e], zm);
+        if (zero) v[0][e] = C<T>(xk.re + xm.re, xk.re - xm.re);
+    }
+    reg_fft<T, 4, 1>(v, buf, 0, LONG_A, c.t, 16, tw_size(tw, LONG_A), true);
+    cpx<T>* Hf = H + c.f * NS;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Hf[LONG_B * (c.t + 16 * e) + c.b] = v[0][e] * cj(wc[e]);
+}
+// 32 blocks of two waves: as many partials as the column launches of this line write
+// less one, whose place the first block clears.
+template <typename T>
+__global__ void __launch_bounds__(128) k_pcg_long_c2(const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+                                                     const cpx<T>* __restrict__ H, size_t NS,
+                                                     const cpx<T>* __restrict__ ph, cpx<T>* __restrict__ xh,
+                                                     cpx<T>* __restrict__ rh, double* __restrict__ part, int nb_r1,
+                                                     int nb3, T tpx) {
+    __shared__ cpx<T> ldsb[2][4 * LONG_A];
+    __shared__ double red[64];
+    const PcgScal s0 = pcg_scalars(sc);
+    if (s0.done) return;
+    const int wv = threadIdx.x >> 6;
+    const LongCol c = long_col(threadIdx.x & 63, 2 * blockIdx.x + wv);
+    constexpr int NX = 2 * LONG_M;
+    const cpx<T>* tw2 = tw_size(tw, NX);
+    const cpx<T>* twM = tw_size(tw, LONG_M);
+    const cpx<T>* Hf = H + c.f * NS;
+    double pb[PF_K][1], tot[1];
+    partials_fetch<1>(part + PART_C2, nb_r1, pb);
+    __builtin_amdgcn_sched_barrier(0);
+    cpx<T> v[1][4], w[4], wc[4], x[5], p[5], r[5];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int k = LONG_B * (c.t + 16 * e) + c.b;
+        v[0][e] = Hf[k];
+        wc[e] = twM[(c.t + 16 * e) * c.b];
+        w[e] = tw2[k];
+    }
+#pragma unroll
+    for (int e = 0; e < 5; ++e) {
+        const int k = e < 4 ? LONG_B * (c.t + 16 * e) + c.b : (c.edge ? LONG_M : 0);
+        x[e] = xh[k];
+        p[e] = ph[k];
+        r[e] = rh[k];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    partials_sum<1>(part + PART_C2, nb_r1, pb, tot, red);
+    const double a_d = s0.rho / tot[0];
+    const T alpha = (T)a_d, sig = (T)s0.sig, alp = (T)s0.alp;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        sc->pq = tot[0];
+        sc->alpha = a_d;
+        sc->rho_prev = s0.rho;
+        sc->iter = s0.iter + 1;
+        sc->first = 0;
+    }
+    cpx<T>* lds = ldsb[wv];
+    cpx<T>* buf = lds + c.col * LONG_A;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[0][e] = v[0][e] * wc[e];
+    reg_fft<T, 4, 1>(v, buf, 0, LONG_A, c.t, 16, tw_size(tw, LONG_A), false);
+    fft_sync(16);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) buf[c.t + 16 * e] = v[0][e];
+    fft_sync(16);
+    const cpx<T>* mir = c.u == 0 ? buf : lds + (c.col ^ 1) * LONG_A;
+    cpx<T> X[5];   // this field's modes
+    X[4] = C<T>(v[0][0].re - v[0][0].im, 0);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const int a = c.t + 16 * e;
+        const cpx<T> zk = v[0][e];
+        cpx<T> xm;
+        split_part(zk, mir[c.b == 0 ? (LONG_A - a) & (LONG_A - 1) : LONG_A - 1 - a], w[e], X[e], xm);
+        if (c.edge && e == 0) X[e] = C<T>(zk.re + zk.im, 0);
+    }
+    // the second field's modes go to the first one's threads (w_0 and w_M do not count:
+    // their wavenumbers are zero)
+    fft_sync(64);
+    if (c.f) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) buf[c.t + 16 * e] = X[e];
+    }
+    fft_sync(64);
+    double acc[2] = {0.0, 0.0};
+    if (c.f == 0) {
+#pragma unroll
+        for (int e = 0; e < 5; ++e) {
+            if (e == 4 && !c.edge) continue;
+            const int k = e < 4 ? LONG_B * (c.t + 16 * e) + c.b : LONG_M;
+            const T kx = wavenumber<T>(k, NX, tpx);
+            const cpx<T> q = e < 4 ? X[e] - ik(kx, lds[(c.col + 2) * LONG_A + c.t + 16 * (e & 3)]) : X[e];
+            xh[k] = x[e] + alpha * p[e];
+            const cpx<T> rn[1] = {r[e] - alpha * q};
+            rh[k] = rn[0];
+            cpx<T> z[1];
+            precond_mode<T, 1>(kx, (T)0, sig, alp, rn, z);
+            const double wt = half_weight(k, NX);
+            acc[0] += wt * ((double)rn[0].re * (double)z[0].re + (double)rn[0].im * (double)z[0].im);
+            acc[1] += wt * ((double)rn[0].re * (double)rn[0].re + (double)rn[0].im * (double)rn[0].im);
+        }
+    }
+    block_sum<2>(acc, red + 32);
+    if (threadIdx.x == 0) {
+        part[PART_C3 + 2 * blockIdx.x] = acc[0];
+        part[PART_C3 + 2 * blockIdx.x + 1] = acc[1];
+        if (blockIdx.x == 0)
+            for (int i = LONG_A / 2; i < nb3; ++i) part[PART_C3 + 2 * i] = part[PART_C3 + 2 * i + 1] = 0.0;
+    }
+}
+
 enum { C2_RESID = 1, C2_STORE = 2, C2_UPDATE = 3, C2_RESID_INIT = 4 };
 
 // MODE C2_UPDATE: reduce p.Gp (row-pass partials, nb_r1 blocks) -> alpha;

@@ -699,6 +699,18 @@ struct PcgLaunch {
     bool native = false;  // a 2D grid between walls on its own points (the wall column passes)
 };
 
+// The line of 16384 points: its row pass as three launches of 64 waves, and in the
+// iteration the column passes fused into the outer two (k_pcg_long_c1, k_pcg_long_c2;
+// the twin of a wall grid projects its residual in between and keeps them apart).
+template <typename T, int D>
+bool r1_long(const PcgLaunch<T, D>& P) {
+    return D == 1 && P.rl.g.M == LONG_M;
+}
+template <typename T, int D>
+bool iter_long(const PcgLaunch<T, D>& P) {
+    return r1_long(P) && !P.wall && P.cl.g.nblocks == LONG_A / 2 + 1;   // their partials
+}
+
 // mode C1_ACCUM (T = double only): x_hat += dx (FP32) and G is applied to the
 // corrected x_hat.
 template <typename T, int D>
@@ -713,6 +725,13 @@ sgn_status pcg_c1(PcgLaunch<T, D>& P, int mode, const cpx<T>* xsrc, const cpx<fl
         hipExtLaunchKernelGGL(k, dim3(L.g.nblocks), dim3(L.threads), lds, P.ctx->stream, ps.a, ps.b, 0, L.g,
                               twiddles<T>(P.ctx), P.sc, (const double*)P.partials, P.cl.g.nblocks,
                               (const cpx<T>*)P.b.rh, P.b.ph, P.b.H, P.d.NS, (T)P.d.tpx, (T)P.d.tpy);
+        CHECK_LAUNCH(P.ctx);
+        return SGN_OK;
+    }
+    if (mode == C1_UPDATE && iter_long(P)) {
+        hipExtLaunchKernelGGL(k_pcg_long_c1<T>, dim3(LONG_A), dim3(64), 0, P.ctx->stream, ps.a, ps.b, 0,
+                              twiddles<T>(P.ctx), P.sc, (const double*)P.partials, P.cl.g.nblocks,
+                              (const cpx<T>*)P.b.rh, P.b.ph, P.b.H, P.d.NS, (T)P.d.tpx);
         CHECK_LAUNCH(P.ctx);
         return SGN_OK;
     }
@@ -769,11 +788,6 @@ template <typename T, int D>
 bool r1_fields(const PcgLaunch<T, D>& P) {
     return P.rl.g.M <= 512;
 }
-// The line of 16384 points: its row pass as three launches of 64 waves.
-template <typename T, int D>
-bool r1_long(const PcgLaunch<T, D>& P) {
-    return D == 1 && P.rl.g.M == LONG_M;
-}
 // Blocks of the row pass, i.e. the p.Gp partials the next column pass reduces.
 template <typename T, int D>
 int r1_blocks(const PcgLaunch<T, D>& P) {
@@ -792,6 +806,12 @@ sgn_status pcg_r1(PcgLaunch<T, D>& P, bool curvature = false) {
         return SGN_OK;
     }
     auto& L = P.rl;
+    if (curvature && iter_long(P)) {
+        hipExtLaunchKernelGGL(k_pcg_long_rows<T>, dim3(LONG_A), dim3(64), 0, P.ctx->stream, ps.a, ps.b, 0,
+                              twiddles<T>(P.ctx), P.sc, P.b.H, P.d.NS, P.eta, P.gh, part);
+        CHECK_LAUNCH(P.ctx);
+        return SGN_OK;
+    }
     if (r1_long(P)) {
         const cpx<T>* tw = twiddles<T>(P.ctx);
         hipExtLaunchKernelGGL((k_pcg_long_cols<T, true>), dim3(LONG_A), dim3(64), 0, P.ctx->stream, ps.a, nullptr, 0,
@@ -851,6 +871,13 @@ sgn_status pcg_c2_mode(PcgLaunch<T, D>& P, const cpx<T>* bh, cpx<T>* rh_out, con
         }
     }
     if constexpr (MODE == C2_UPDATE) {
+        if (iter_long(P)) {
+            hipExtLaunchKernelGGL(k_pcg_long_c2<T>, dim3(LONG_A / 2), dim3(128), 0, P.ctx->stream, ps.a, ps.b, 0,
+                                  twiddles<T>(P.ctx), P.sc, (const cpx<T>*)P.b.H, P.d.NS, (const cpx<T>*)P.b.ph,
+                                  P.b.xh, rh_out, P.partials, nb_red, L.g.nblocks, (T)P.d.tpx);
+            CHECK_LAUNCH(P.ctx);
+            return SGN_OK;
+        }
         if (col_wave(P)) {
             hipExtLaunchKernelGGL(k_pcg_c2w<T>, dim3(L.g.nblocks), dim3(WCOL_THREADS), 0, P.ctx->stream, ps.a, ps.b,
                                   0, P.d.nx, twiddles<T>(P.ctx), P.sc, (const cpx<T>*)P.b.H, P.d.NS,

@@ -87,9 +87,9 @@ def kernel_bytes(kind: str, d: int, nx: int, ny: int, word: int) -> float:
     # the diagonal momentum fluxes are folded into S_x = S - eta u_x^2 and
     # S_y = S - eta u_y^2 by the inverse pass, so one flux field is transformed
     ns_s = 2 if d == 2 else 1   # S spectra: S_x, S_y (2D) or S (1D)
-    # periodic 2D rows of 1024 points: the inverse row pass forms d_x delta, d_x eta
-    # and d_x beta from spectra it reads anyway, so the column pass writes 3 fewer
-    dxr = 3 if (d == 2 and nx == 1024) else 0
+    # periodic 2D grids: the inverse row pass forms d_x delta, d_x eta and d_x beta
+    # from spectra it reads anyway, so the column pass writes 3 fewer
+    dxr = 3 if d == 2 else 0
     if base == "rhs_rows_fwd":  # read eta, u (d), grad h (d); write [u, eta u, eta, eta u_1 u_d, beta] spectra
         return (1 + 2 * d) * n * word + ((2 * d + 1) + 2) * ns * cw
     if base == "rhs_cols":      # read u, eta u, eta, beta spectra; write delta, grad delta, m, grad eta, grad beta

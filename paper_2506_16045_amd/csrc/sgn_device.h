@@ -826,37 +826,66 @@ __device__ __forceinline__ void final_sum(const double* __restrict__ partials, u
 // No loop over the first ones: a load inside a loop makes the compiler wait for every
 // load in flight at the loop entry.
 constexpr int PF_K = 3;   // the column launches of 1024-point rows: 513 blocks
-template <int NACC>
+// V = 2: a block of 128 threads, each standing for two of the 256 (the same order).
+template <int NACC, int V = 1>
 __device__ __forceinline__ void partials_fetch(const double* __restrict__ partials, unsigned nblocks,
-                                               double (&pb)[PF_K][NACC]) {
+                                               double (&pb)[PF_K * V][NACC]) {
     // branch-free: every lane loads an in-range entry (predicated loads would
     // make the compiler wait for all loads); partials_sum drops the extra ones
 #pragma unroll
-    for (int k = 0; k < PF_K; ++k) {
-        const unsigned b = threadIdx.x + 256u * k;
+    for (int k = 0; k < PF_K * V; ++k) {
+        const unsigned b = threadIdx.x + (256u / V) * k;
         const unsigned bc = (threadIdx.x < 256 && b < nblocks) ? b : 0u;
 #pragma unroll
         for (int a = 0; a < NACC; ++a) pb[k][a] = partials[(size_t)NACC * bc + a];
     }
 }
-template <int NACC>
+template <int NACC, int V = 1>
 __device__ __forceinline__ void partials_sum(const double* __restrict__ partials, unsigned nblocks,
-                                             const double (&pb)[PF_K][NACC], double (&v)[NACC], double* red) {
+                                             const double (&pb)[PF_K * V][NACC], double (&v)[NACC], double* red) {
+    double acc[V][NACC];
 #pragma unroll
-    for (int a = 0; a < NACC; ++a) v[a] = 0.0;
+    for (int i = 0; i < V; ++i)
 #pragma unroll
-    for (int k = 0; k < PF_K; ++k) {
-        const bool ok = threadIdx.x < 256 && threadIdx.x + 256u * k < nblocks;
+        for (int a = 0; a < NACC; ++a) acc[i][a] = 0.0;
 #pragma unroll
-        for (int a = 0; a < NACC; ++a) v[a] += ok ? pb[k][a] : 0.0;
+    for (int k = 0; k < PF_K * V; ++k) {
+        const bool ok = threadIdx.x < 256 && threadIdx.x + (256u / V) * k < nblocks;
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) acc[k % V][a] += ok ? pb[k][a] : 0.0;
     }
     if (nblocks > 256u * PF_K) {
-        for (unsigned b = threadIdx.x + 256u * PF_K; threadIdx.x < 256 && b < nblocks; b += 256) {
 #pragma unroll
-            for (int a = 0; a < NACC; ++a) v[a] += partials[(size_t)NACC * b + a];
+        for (int i = 0; i < V; ++i) {
+            for (unsigned b = threadIdx.x + (256u / V) * i + 256u * PF_K; threadIdx.x < 256 && b < nblocks; b += 256) {
+#pragma unroll
+                for (int a = 0; a < NACC; ++a) acc[i][a] += partials[(size_t)NACC * b + a];
+            }
         }
     }
-    block_sum_all<NACC>(v, red);
+    if (V == 1) {
+#pragma unroll
+        for (int a = 0; a < NACC; ++a) v[a] = acc[0][a];
+        block_sum_all<NACC>(v, red);
+        return;
+    }
+    const int wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+        block_wave_sums<NACC>(acc[i]);
+        if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+            for (int a = 0; a < NACC; ++a) red[a * 16 + i * (4 / V) + wave] = acc[i][a];
+        }
+    }
+    block_lds_barrier();
+#pragma unroll
+    for (int a = 0; a < NACC; ++a) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) s += red[a * 16 + w];
+        v[a] = s;
+    }
 }
 
 // Maximum of the per-block partials by the whole last block (order independent);

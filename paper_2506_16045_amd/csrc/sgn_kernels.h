@@ -880,8 +880,9 @@ __device__ __forceinline__ bool pcg_iterate_state(SolveScal* __restrict__ sc, co
 // the correction.
 enum { C1_UPDATE = 0, C1_COPY = 1, C1_ACCUM = 2 };
 
-template <typename T, int EPC, int D, int MODE>
-__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const cpx<T>* __restrict__ tw,
+// FEW: blocks of 128 threads (see k_pcg_c2).
+template <typename T, int EPC, int D, int MODE, bool FEW = false>
+__global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, const double* __restrict__ part,
                                                  int nb3, const cpx<T>* __restrict__ rh, cpx<T>* __restrict__ ph,
                                                  const cpx<T>* __restrict__ xsrc, cpx<T>* __restrict__ H,
@@ -894,10 +895,11 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const
     const cpx<T>* twm = tw_size(tw, g.ny);
     const ColThread<T> ct = col_thread<T>(g, lds);
     // the partials, r and the last p, in flight across the reduction
-    double pb[PF_K][2];
+    constexpr int V = FEW ? 2 : 1;
+    double pb[PF_K * V][2];
     cpx<T> in[D][EPC], last[D][EPC];
     if (MODE == C1_UPDATE) {
-        partials_fetch<2>(part + PART_C3, nb3, pb);
+        partials_fetch<2, V>(part + PART_C3, nb3, pb);
         __builtin_amdgcn_sched_barrier(0);
     }
     const cpx<T>* src = MODE == C1_UPDATE ? rh : MODE == C1_COPY ? xsrc : ph;
@@ -919,7 +921,7 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_pcg_c1(ColGeom g, const
     double beta_d = 0.0;
     if (MODE == C1_UPDATE) {
         double tot[2];
-        partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+        partials_sum<2, V>(part + PART_C3, nb3, pb, tot, red);
         if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
     }
     const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
@@ -1540,8 +1542,8 @@ __device__ __forceinline__ cpx<T> wall_project(int c, cpx<T> a, cpx<T> b, int kx
 // WALL: the solve runs on the periodic twin of a wall grid; the new residual is
 // projected onto the symmetric modes before it is used (rounding would otherwise
 // seed the other parity, which the iteration amplifies at low wavenumbers).
-// FEW (launches of at most one block per compute unit, where only latency counts): two
-// waves per SIMD instead of three, which ends the last spills (a kernel that uses
+// FEW (blocks of 128 threads, launches of at most one block of 256 per compute unit, where
+// only latency counts): two waves per SIMD instead of three, which ends the last spills (a kernel that uses
 // scratch memory takes 1 to 2 us longer), and the fields the new residual needs loaded
 // with the columns, in flight across the transform, where that fits the registers (all
 // but the FP64 update, which spills again: 9.1 -> 10.2 us at 256 x 128).  FP64 512 x 512:
@@ -1564,9 +1566,10 @@ __global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_pcg_c2(ColGeo
     // the row pass's columns do not depend on alpha: loaded right after the
     // partials of the reduction, in flight across it (LDS-only barriers)
     if (s0.done) return;
-    double pb[PF_K][1];
-    if (MODE == C2_UPDATE) partials_fetch<1>(part + PART_C2, nb_r1, pb);
-    if (MODE == C2_RESID_INIT) partials_fetch<1>(part + PART_GEN, nb_r1, pb);
+    constexpr int V = FEW ? 2 : 1;
+    double pb[PF_K * V][1];
+    if (MODE == C2_UPDATE) partials_fetch<1, V>(part + PART_C2, nb_r1, pb);
+    if (MODE == C2_RESID_INIT) partials_fetch<1, V>(part + PART_GEN, nb_r1, pb);
     __builtin_amdgcn_sched_barrier(0);   // the partials' loads first
     cpx<T> in[D + 1][EPC];
     {
@@ -1598,7 +1601,7 @@ __global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_pcg_c2(ColGeo
     bool zero_x = false;
     if (MODE == C2_RESID_INIT) {
         double tot[1];
-        partials_sum<1>(part + PART_GEN, nb_r1, pb, tot, red);
+        partials_sum<1, V>(part + PART_GEN, nb_r1, pb, tot, red);
         const double bb = tot[0] * s0.inv_n;
         const bool bad = !(bb == bb) || bb > 1.0e300;
         if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -1613,7 +1616,7 @@ __global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_pcg_c2(ColGeo
     }
     if (MODE == C2_UPDATE) {
         double tot[1];
-        partials_sum<1>(part + PART_C2, nb_r1, pb, tot, red);
+        partials_sum<1, V>(part + PART_C2, nb_r1, pb, tot, red);
         const double pq = tot[0];
         const double a = s0.rho / pq;
         alpha = (T)a;

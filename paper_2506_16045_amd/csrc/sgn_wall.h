@@ -393,8 +393,8 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_setup(ColGeom g, c
 // Column pass C1 of a wall solve (k_pcg_c1, mode C1_UPDATE): stop test and beta
 // from the last update's partials; z = A^{-1} r, p = z + beta p on the slots;
 // (p, div p) / (nx ny) -> column values -> inverse y-FFT into H.
-template <typename T, int EPC>
-__global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c1(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
+template <typename T, int EPC, bool FEW>
+__global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_wall_c1(ColGeom g, const cpx<T>* __restrict__ tw, SolveScal* __restrict__ sc,
                                                   const double* __restrict__ part, int nb3,
                                                   const cpx<T>* __restrict__ rh, cpx<T>* __restrict__ ph,
                                                   cpx<T>* __restrict__ H, size_t NS, T pix, T piy) {
@@ -408,8 +408,9 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c1(ColGeom g, cons
     const size_t col = (size_t)ct.kx * g.ny;
     const cpx<T>* twy = tw_size(tw, 4 * g.ny);
     // the partials, r, the last p and the y roots, in flight across the reduction
-    double pb[PF_K][2];
-    partials_fetch<2>(part + PART_C3, nb3, pb);
+    constexpr int V = FEW ? 2 : 1;
+    double pb[PF_K * V][2];
+    partials_fetch<2, V>(part + PART_C3, nb3, pb);
     __builtin_amdgcn_sched_barrier(0);
     constexpr int NP = EPC / 2;
     cpx<T> r[NP][2][2], last[NP][2][2], wyp[NP];
@@ -431,7 +432,7 @@ __global__ void __launch_bounds__(256, COL_WAVES<EPC>) k_wall_c1(ColGeom g, cons
     const WallColumn<T> wc = wall_column<T>(g, ct, tw, pix);
     __builtin_amdgcn_sched_barrier(0);
     double beta_d = 0.0, tot[2];
-    partials_sum<2>(part + PART_C3, nb3, pb, tot, red);
+    partials_sum<2, V>(part + PART_C3, nb3, pb, tot, red);
     if (pcg_iterate_state(sc, s0, tot, beta_d)) return;
     const T beta = (T)beta_d, sig = (T)s0.sig, alp = (T)s0.alp, inv_n = (T)s0.inv_n;
 #pragma unroll
@@ -499,8 +500,9 @@ __global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_wall_c2(ColGe
     const ColThread<T> ct = col_thread<T>(g, lds);
     // the partials, then the row pass's columns, in flight across the reduction
     const double* red_part = part + (MODE == C2_RESID_INIT ? PART_GEN : PART_C2);
-    double pb[PF_K][1], tot[1];
-    partials_fetch<1>(red_part, nb_red, pb);
+    constexpr int V = FEW ? 2 : 1;
+    double pb[PF_K * V][1], tot[1];
+    partials_fetch<1, V>(red_part, nb_red, pb);
     __builtin_amdgcn_sched_barrier(0);
     cpx<T> in[3][EPC];
     {
@@ -532,7 +534,7 @@ __global__ void __launch_bounds__(256, FEW ? 2 : COL_WAVES<EPC>) k_wall_c2(ColGe
         }
     }
     __builtin_amdgcn_sched_barrier(0);
-    partials_sum<1>(red_part, nb_red, pb, tot, red);
+    partials_sum<1, V>(red_part, nb_red, pb, tot, red);
     T alpha = (T)0;
     bool zero_x = false;
     if (MODE == C2_RESID_INIT) {

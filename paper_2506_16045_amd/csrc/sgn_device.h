@@ -738,8 +738,6 @@ __device__ __forceinline__ double wave_max(double v) {
 // the last block to finish sums the partials in block order, so the result
 // does not depend on scheduling.
 // ---------------------------------------------------------------------------
-// LDS_ONLY: the barriers order LDS only (global loads in flight stay in flight);
-// the arithmetic, and so the result, is the same.
 template <int NACC>
 __device__ __forceinline__ void block_wave_sums(double (&v)[NACC]) {
     if ((blockDim.x & 63) == 0) {
@@ -753,7 +751,7 @@ __device__ __forceinline__ void block_wave_sums(double (&v)[NACC]) {
         for (int off = 32; off > 0; off >>= 1) v[a] += __shfl_xor(v[a], off, 64);
     }
 }
-template <int NACC, bool LDS_ONLY = false>
+template <int NACC>
 __device__ __forceinline__ void block_sum(double (&v)[NACC], double* red /*LDS, NACC*16*/) {
     block_wave_sums<NACC>(v);
     const int wave = threadIdx.x >> 6;
@@ -763,10 +761,7 @@ __device__ __forceinline__ void block_sum(double (&v)[NACC], double* red /*LDS, 
 #pragma unroll
         for (int a = 0; a < NACC; ++a) red[a * 16 + wave] = v[a];
     }
-    if (LDS_ONLY)
-        block_lds_barrier();
-    else
-        __syncthreads();
+    __syncthreads();
     if (threadIdx.x == 0) {
 #pragma unroll
         for (int a = 0; a < NACC; ++a) {
@@ -775,10 +770,7 @@ __device__ __forceinline__ void block_sum(double (&v)[NACC], double* red /*LDS, 
             v[a] = s;
         }
     }
-    if (LDS_ONLY)
-        block_lds_barrier();
-    else
-        __syncthreads();
+    __syncthreads();
 }
 
 // block_sum with the same result in every thread, behind one LDS-only barrier: red
@@ -800,29 +792,16 @@ __device__ __forceinline__ void block_sum_all(double (&v)[NACC], double* red /*L
     }
 }
 
-// Sum of the per-block partials (layout partials[NACC*b + a]) by the whole
-// last block: thread t < 256 adds blocks t, t+256, ... in order, then the fixed
-// block tree (further threads and waves add zeros); the result is in thread 0.
-// The order, and so the value, is the same in every kernel that reduces the same
-// partials, whatever its block size (at least 256 threads).  Every thread of the
-// block must call it.
-template <int NACC, bool LDS_ONLY = false>
-__device__ __forceinline__ void final_sum(const double* __restrict__ partials, unsigned nblocks,
-                                          double (&v)[NACC], double* red) {
-#pragma unroll
-    for (int a = 0; a < NACC; ++a) v[a] = 0.0;
-    for (unsigned b = threadIdx.x; threadIdx.x < 256 && b < nblocks; b += 256) {
-#pragma unroll
-        for (int a = 0; a < NACC; ++a) v[a] += partials[(size_t)NACC * b + a];
-    }
-    block_sum<NACC, LDS_ONLY>(v, red);
-}
-
-// final_sum in two steps, so that a kernel can issue the partials' loads ahead
+// Sum of the per-block partials (layout partials[NACC*b + a]): place t of 256 adds blocks
+// t, t+256, ... in order, then the fixed block tree.  The order, and so the value, is
+// the same in every kernel that reduces the same partials, whatever its block size (128,
+// or at least 256 threads; on 64 threads for up to 64 blocks).  Every thread of the
+// block must call both steps.
+// Two steps, so that a kernel can issue the partials' loads ahead
 // of its data loads (a wait for a load also waits for every load issued before
 // it): partials_fetch loads the partials of up to 256 PF_K blocks into registers,
-// partials_sum adds them, and those of any further blocks, in final_sum's order, so
-// the result is the same bits; it is in every thread (see block_sum_all for red).
+// partials_sum adds them and those of any further blocks; the result is in every thread
+// (see block_sum_all for red).
 // No loop over the first ones: a load inside a loop makes the compiler wait for every
 // load in flight at the loop entry.
 constexpr int PF_K = 3;   // the column launches of 1024-point rows: 513 blocks

@@ -227,6 +227,9 @@ struct RowLaunch {
 // store 16 R bytes side by side in the transposed layout (4096 x 1024, one row or two:
 // forward rows 147 -> 127 us, right-hand side's 215 -> 187, Krylov row pass 153 -> 139);
 // the right-hand side's inverse pass, which holds 240 registers, at most 512.
+// epc_wide: entries per thread of 2D rows of 2048 points and more; narrow, wide: the
+// block sizes (wide 0: by the entries per thread); waves: at least one whole wave per
+// group of rows, rows past the grid included.
 template <typename T>
 RowLaunch row_launch(int nx, int ny, int epc_wide = 4, int narrow = 256, int wide = 0, bool waves = false) {
     RowLaunch L;

@@ -2241,6 +2241,7 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
 }
 
 
+sgn_status copy_d(sgn_ctx* ctx, double* dst, const double* src, size_t n);
 // A 1D right-hand side of up to BATCH_NMAX points by one workgroup in one launch.
 sgn_status rhs_1d_block(sgn_ctx* ctx, const Dims& d, const double* eta, const double* gh, const double* u,
                         double* eta_t, double* U_t, void* ws) {
@@ -2249,9 +2250,13 @@ sgn_status rhs_1d_block(sgn_ctx* ctx, const Dims& d, const double* eta, const do
     const int M1 = d.nx / 2 + 1;
     cpx<double>* spec = cv.take<cpx<double>>((size_t)5 * M1);
     double* st = cv.take<double>((size_t)5 * d.nx);
+    // the line engine stores eta_t while its other threads still read the inputs: where
+    // eta_t is one of them, it goes through st, which only the shorter lines use (they
+    // read every input before they store, and so does the engine for U_t)
+    const bool staged = d.nx >= 2 * LINE_MMIN && (eta_t == eta || eta_t == gh || eta_t == u);
     ProfScope ps(ctx, SGN_KERNEL_ROWS);
-    HIPCHK(ctx, launch_rhs_1d_kernel(d.nx, ctx->stream, d.Lx, eta, gh, u, eta_t, U_t, spec, st, ctx->tw64));
-    return SGN_OK;
+    HIPCHK(ctx, launch_rhs_1d_kernel(d.nx, ctx->stream, d.Lx, eta, gh, u, staged ? st : eta_t, U_t, spec, st, ctx->tw64));
+    return staged ? copy_d(ctx, eta_t, st, d.N) : SGN_OK;
 }
 
 sgn_status rhs_dispatch(sgn_ctx* ctx, const Dims& d, const double* eta, const double* gh, const double* u,

@@ -367,7 +367,8 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
     const size_t npts = (size_t)g.nx * g.ny;
     constexpr int NQ = 3 * D + 2;
     // live state per point: eta and (m, delta, P) while the first 2 + D fields arrive,
-    // then (S, T); d_c eta comes last, when T is complete, so U_t goes straight out
+    // then (S, T), in 2D (S_x, S_y, T) once d_c beta is in; d_c eta comes last, when T is
+    // complete, so U_t goes straight out
     double A0[EPC][2], A1[EPC][2], A2[EPC][2], e0[EPC][2];
     // (the index is opaque: addresses are formed where they are used)
     auto point = [&](int e, bool& ok) -> unsigned {
@@ -454,44 +455,28 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
                 A0[e][s] += et * et / 2.0 * t;
                 A1[e][s] += et * t;
             });
+            if (D == 2 && i == 1 + 2 * D) {   // S_x, S_y, while u is whole: U_t may be written over it
+                each([&](int e, int s, double, unsigned o, bool) {
+                    const double et = depth(e, s), u0 = at32(u, o), u1 = fv[e][s], S = A0[e][s];
+                    A0[e][s] = S - et * u0 * u0;
+                    A2[e][s] = S - et * u1 * u1;
+                });
+            }
         } else {                            // d_c eta: U_t less the flux and grad S
             each([&](int e, int s, double q, unsigned o, bool ok) {
                 if (ok) at32(U_t + c * npts, o) = -e0[e][s] * (q - fv[e][s]) - fv[e][s] * A1[e][s];
             });
         }
     }
-    // S (2D: S_x, S_y) forward-transformed
-    cpx<double> zs[D][EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-        const int j = rt.t + g.TPR * e;
-#pragma unroll
-        for (int c = 0; c < D; ++c) zs[c][e] = C<double>(0, 0);
-        if (j < g.M && rt.valid) {
-            const unsigned o = rt.y * g.nx + 2 * j;
-            double sc[D][2];
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-#pragma unroll
-                for (int c = 0; c < D; ++c) {
-                    if (D == 2) {
-                        const double uc = at32(u + c * npts, o + s);
-                        sc[c][s] = A0[e][s] - e0[e][s] * uc * uc;
-                    } else {
-                        sc[c][s] = A0[e][s];
-                    }
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < D; ++c) zs[c][e] = C<double>(sc[c][0], sc[c][1]);
-        }
-    }
-    // one field at a time: the launch's LDS holds one
+    // S (2D: S_x, S_y) forward-transformed, one field at a time (the launch's LDS holds one)
 #pragma unroll
     for (int c = 0; c < D; ++c) {
         cpx<double> z1[1][EPC];
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) z1[0][e] = zs[c][e];
+        for (int e = 0; e < EPC; ++e) {
+            const bool ok = rt.t + g.TPR * e < g.M && rt.valid;
+            z1[0][e] = !ok ? C<double>(0, 0) : c == 0 ? C<double>(A0[e][0], A0[e][1]) : C<double>(A2[e][0], A2[e][1]);
+        }
         cpx<double>* H1[1] = {c == 0 ? Sdst : Sydst};
         row_forward<double, EPC, 1>(g, rt, z1, H1, tw, twm, 1.0);
     }

@@ -1,6 +1,7 @@
 """The right-hand side written over its own inputs equals the one written elsewhere, bit
 for bit, where that has always been so: on 1D lines of up to 8192 points either output
-over any input (the short-line path and the one-workgroup engine beside it)."""
+over any input (the short-line path and the one-workgroup engine beside it), on 2D grids
+U_t over u (each of the three forms of the inverse row pass)."""
 import numpy as np
 import pytest
 
@@ -46,3 +47,8 @@ def test_lines(ctx, n):
         for U_t in (None, "eta", "gh", "u"):
             if eta_t is None or eta_t != U_t:
                 _check(ctx, fields, eta_t, U_t)
+
+
+@pytest.mark.parametrize("nx,ny", ((8, 8), (512, 16), (1024, 8), (2048, 4), (2048, 512), (4096, 4)))
+def test_velocity_on_grids(ctx, nx, ny):
+    _check(ctx, _fields(ctx, nx, ny), None, "u")

@@ -91,10 +91,13 @@ struct RowCombo {
 // block takes its rows of one field (blocks [f nblocks, (f + 1) nblocks): field f):
 // small grids fill more of the chip than with a block's fields in lockstep, and a
 // field's registers leave room for twice the waves (256 x 128, three fields: forward
-// 14.8 -> 6.6 us, inverse 8.2 -> 5.0; 512 x 512, inverse: 11.5 -> 7.8).  64 registers,
-// so that two blocks of 1024 threads fit a compute unit (2048 x 2048: 60 -> 51 us).
+// 14.8 -> 6.6 us, inverse 8.2 -> 5.0; 512 x 512, inverse: 11.5 -> 7.8).  In blocks of 1024
+// threads 64 registers, so that two fit a compute unit (2048 x 2048: 60 -> 51 us) though a
+// few values go to scratch; blocks of 256 take the 69 they need and none, since a launch
+// of a kernel that uses scratch costs the small calls, which wait for it, more than an
+// eighth wave gives (grad h of a closed 64 x 64 basin 85 -> 78 us, of 1024 points 82 -> 78).
 template <typename T, typename Tin, int EPC, int MAXT>
-__global__ void __launch_bounds__(MAXT, EPC <= 4 ? 8 : 4) k_rows_fwd(RowGeom g, PtrList<const Tin, MAXF> src,
+__global__ void __launch_bounds__(MAXT, EPC > 4 ? 4 : MAXT <= 256 ? 7 : 8) k_rows_fwd(RowGeom g, PtrList<const Tin, MAXF> src,
                                                    PtrList<cpx<T>, MAXF> dst,
                                                    const cpx<T>* __restrict__ tw, T scale, RowCombo<Tin> cmb) {
     extern __shared__ __align__(16) unsigned char smem_raw[];

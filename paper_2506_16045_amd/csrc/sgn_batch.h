@@ -1182,6 +1182,18 @@ static __device__ __noinline__ void line_rk4_system(const StepItem* item, const 
     if (threadIdx.x == 0) gl(res)[it.index] = out;
 }
 
+// The same of a short line (inlined into the kernel beside the calls it read 475 values
+// back from scratch memory).
+template <int MODE>
+static __device__ __noinline__ void small_rk4_system(const StepItem* item, const StepShared* shared, StepResult* res,
+                                                     lds_bytes lds, lds_doubles red) {
+    const StepItem& it = uniform_table(item);
+    const StepShared& a = uniform_table(shared);
+    const StepResult out = rk4_run<SmallEngine<MODE>>(it, a.extrapolate != 0, gl(a.tw64), gl(a.tw32), a.prm,
+                                                      (void*)uniform_l(lds), (double*)uniform_l(red));
+    if (threadIdx.x == 0) gl(res)[it.index] = out;
+}
+
 // Batched RK4 runs: workgroups take states from the table (a work queue when
 // queue is set, its counter zero at launch) until none is left.
 template <int MODE>
@@ -1199,11 +1211,7 @@ __global__ void __launch_bounds__(BATCH_THREADS) k_batch_rk4(const StepItem* __r
             if (LineGeo<double, M>::ONE && threadIdx.x >= 64) return;
             line_rk4_system<MODE, M>(&it, shared, res, (lds_bytes)smem_raw, (lds_doubles)red);
         });
-        if (!line) {
-            const StepShared& a = *shared;
-            const StepResult out = rk4_run<SmallEngine<MODE>>(it, a.extrapolate != 0, gl(a.tw64), gl(a.tw32), a.prm, smem_raw, red);
-            if (threadIdx.x == 0) res[it.index] = out;
-        }
+        if (!line) small_rk4_system<MODE>(&it, shared, res, (lds_bytes)smem_raw, (lds_doubles)red);
         __syncthreads();
     }
 }

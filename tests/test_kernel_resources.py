@@ -1,6 +1,8 @@
 """Kernels that every small call goes through use no scratch memory: a launch of one that
 does takes the longer (a few microseconds, on calls of some tens), whatever it computes.
-Read from the metadata of the built library's own code objects."""
+And a kernel that only picks a function by the line's length does not do a length's work
+itself, where the registers left beside the calls make it spill.  Read from the metadata
+of the built library's own code objects."""
 import glob
 import os
 import shutil
@@ -14,8 +16,8 @@ LLVM = "/opt/rocm/llvm/bin"
 
 
 @pytest.fixture(scope="module")
-def scratch(tmp_path_factory):
-    """{mangled kernel name: bytes of scratch per lane} of the built library."""
+def metadata(tmp_path_factory):
+    """{mangled kernel name: {entry: number}} of the built library."""
     tools = [os.path.join(LLVM, t) for t in ("llvm-objdump", "llvm-readelf")]
     if not all(os.path.exists(t) for t in tools):
         pytest.skip("no LLVM tools to read the code objects with")
@@ -30,13 +32,25 @@ def scratch(tmp_path_factory):
             key, _, value = line.strip().partition(":")
             if key == ".name" and value.strip().startswith("_Z"):
                 name = value.strip()
-            elif key == ".private_segment_fixed_size" and name:
-                out[name] = int(value)
+            elif key in (".private_segment_fixed_size", ".vgpr_spill_count") and name:
+                out.setdefault(name, {})[key] = int(value)
     assert out
     return out
 
 
+def entries(metadata, kernel, key):
+    found = {n: m[key] for n, m in metadata.items() if kernel in n}
+    assert found
+    return found
+
+
 @pytest.mark.parametrize("kernel", ("k_rows_fwdIddLi4ELi256EE", "k_rows_invIddLi4ELi256EE"))
-def test_no_scratch(scratch, kernel):
-    found = {n: b for n, b in scratch.items() if kernel in n}
-    assert found and not any(found.values()), found
+def test_no_scratch(metadata, kernel):
+    found = entries(metadata, kernel, ".private_segment_fixed_size")
+    assert not any(found.values()), found
+
+
+def test_batched_runs_only_dispatch(metadata):
+    # a few registers are saved around the calls; a length inlined beside them spilled some 300
+    found = entries(metadata, "k_batch_rk4", ".vgpr_spill_count")
+    assert len(found) == 2 and max(found.values()) <= 16, found

@@ -21,11 +21,14 @@ hipError_t launch_rhs_1d_kernel(int n, hipStream_t stream, double L, const doubl
                                 const cpx<double>* tw) {
     const size_t lds = batch_lds_bytes(n);
     int grid = 1;
-    const hipError_t e = batch_grid(k_rhs_1d<0>, batch_threads_for(n), lds, 1, 1, grid);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_rhs_1d<0>, dim3(1), dim3(batch_threads_for(n)), lds, stream, n, L, eta, hx, u, eta_t, U_t,
-                       spec, st, tw);
-    return hipGetLastError();
+    auto launch = [&](auto k) -> hipError_t {
+        const hipError_t e = batch_grid(k, batch_threads_for(n), lds, 1, 1, grid);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k, dim3(1), dim3(batch_threads_for(n)), lds, stream, n, L, eta, hx, u, eta_t, U_t, spec, st,
+                           tw);
+        return hipGetLastError();
+    };
+    return n < 2 * LINE_MMIN ? launch(k_rhs_1d<true>) : launch(k_rhs_1d<false>);
 }
 
 }  // namespace sgn

@@ -32,7 +32,7 @@ def metadata(tmp_path_factory):
             key, _, value = line.strip().partition(":")
             if key == ".name" and value.strip().startswith("_Z"):
                 name = value.strip()
-            elif key in (".private_segment_fixed_size", ".vgpr_spill_count") and name:
+            elif key in (".private_segment_fixed_size", ".vgpr_count", ".vgpr_spill_count") and name:
                 out.setdefault(name, {})[key] = int(value)
     assert out
     return out
@@ -54,3 +54,8 @@ def test_batched_runs_only_dispatch(metadata):
     # a few registers are saved around the calls; a length inlined beside them spilled some 300
     found = entries(metadata, "k_batch_rk4", ".vgpr_spill_count")
     assert len(found) == 2 and max(found.values()) <= 16, found
+
+
+def test_right_hand_side_of_short_lines_is_its_own_kernel(metadata):
+    # in one kernel with the longer lines (some 250 registers, 29000 instructions) it starts later
+    assert sorted(entries(metadata, "k_rhs_1d", ".vgpr_count").values())[0] <= 128

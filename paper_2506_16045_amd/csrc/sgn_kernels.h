@@ -355,6 +355,10 @@ struct RowDx {
 // S_y = S - eta u_y^2 to Sydst (see rhs_source).
 // dx: fields with dx.f[i] != 0 are given as row spectra (or another field's column
 // output) whose x-derivative is wanted (see RowDx).
+// The line of 16384 points (D = 1) is one block of 1024 threads of 128 registers, 64 of
+// which the accumulated state of 16 points takes: nothing is held or loaded ahead across
+// its transforms, where 541 spilled registers cost more than the loads' latency (367 ->
+// 207 us).
 template <int D, int EPC, int MAXT>
 __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowGeom g, PtrList<const cpx<double>, MAXF> src,
                                                        const double* __restrict__ eta, const double* __restrict__ u,
@@ -372,7 +376,10 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
     // live state per point: eta and (m, delta, P) while the first 2 + D fields arrive,
     // then (S, T), in 2D (S_x, S_y, T) once d_c beta is in; d_c eta comes last, when T is
     // complete, so U_t goes straight out
-    double A0[EPC][2], A1[EPC][2], A2[EPC][2], e0[EPC][2];
+    // (LEAN: (m, delta), then (S, T), and nothing else held or in flight across a
+    // transform, see above)
+    constexpr bool LEAN = D == 1;
+    double A0[EPC][2], A1[EPC][2], A2[LEAN ? 1 : EPC][2], e0[LEAN ? 1 : EPC][2];
     // (the index is opaque: addresses are formed where they are used)
     auto point = [&](int e, bool& ok) -> unsigned {
         int t = rt.t;
@@ -381,40 +388,47 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
         ok = j < g.M && rt.valid;
         return ok ? (unsigned)(rt.y * g.nx + 2 * j) : 0u;
     };
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-        bool ok;
-        const unsigned o = point(e, ok);
-        e0[e][0] = at32(eta, o);
-        e0[e][1] = at32(eta, o + 1);
-    }
     RowPairs<double, EPC> X;
-    row_fetch<double, EPC>(g, rt, src.p[0], X);
+    if (!LEAN) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+            bool ok;
+            const unsigned o = point(e, ok);
+            e0[LEAN ? 0 : e][0] = at32(eta, o);
+            e0[LEAN ? 0 : e][1] = at32(eta, o + 1);
+        }
+        row_fetch<double, EPC>(g, rt, src.p[0], X);
+    }
 #pragma unroll 1
     for (int i = 0; i < NQ; ++i) {
+        if (LEAN) row_fetch<double, EPC>(g, rt, src.p[i], X);
         row_join<double, EPC>(g, rt, X, rt.lds, tw, dx.f[i], tpx);
         // in flight across the transform: the next field's entries, and the factor
         // this field is consumed with (u_c for d_c delta and d_c beta, (grad h)_c for
         // d_c eta)
         const int c = i < 2 ? 0 : (i - 2) % D;
-        if (i + 1 < NQ) row_fetch<double, EPC>(g, rt, src.p[i + 1], X);
+        if (!LEAN && i + 1 < NQ) row_fetch<double, EPC>(g, rt, src.p[i + 1], X);
         const double* fac = i < 2 ? eta : (i <= 1 + 2 * D ? u : gh) + c * npts;
-        double fv[EPC][2];
+        double fv[LEAN ? 1 : EPC][2];
+        if (!LEAN) {
 #pragma unroll
-        for (int e = 0; e < EPC; ++e) {
-            bool ok;
-            const unsigned o = point(e, ok);
-            fv[e][0] = at32(fac, o);
-            fv[e][1] = at32(fac, o + 1);
+            for (int e = 0; e < EPC; ++e) {
+                bool ok;
+                const unsigned o = point(e, ok);
+                fv[LEAN ? 0 : e][0] = at32(fac, o);
+                fv[LEAN ? 0 : e][1] = at32(fac, o + 1);
+            }
         }
+        auto factor = [&](int e, int s, unsigned o) { return LEAN ? at32(fac, o) : fv[LEAN ? 0 : e][s]; };
         block_lds_barrier();
         cpx<double> z[1][EPC];
         row_inverse_lds<double, EPC, 1>(g, rt, twm, z);
         block_lds_barrier();
         // eta, opaque: its powers are formed where they are used, not held across the
         // loop over the fields
-        auto depth = [&](int e, int s) {
-            double v = e0[e][s];
+        auto depth = [&](int e, int s, unsigned o) {
+            if (LEAN) return at32(eta, o);
+            double v = e0[LEAN ? 0 : e][s];
             asm volatile("" : "+v"(v));
             return v;
         };
@@ -437,37 +451,39 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
         } else if (i == 1) {                // delta
             each([&](int e, int s, double q, unsigned, bool) {
                 A1[e][s] = q;
-                A2[e][s] = -q * q;
+                if (!LEAN) A2[LEAN ? 0 : e][s] = -q * q;
             });
         } else if (i <= 1 + D) {            // d_c delta: P += u_c d_c delta
-            each([&](int e, int s, double q, unsigned, bool) { A2[e][s] += fv[e][s] * q; });
+            if (!LEAN) each([&](int e, int s, double q, unsigned o, bool) { A2[LEAN ? 0 : e][s] += factor(e, s, o) * q; });
             if (i == 1 + D) {               // P complete: fold into S, T
-                each([&](int e, int s, double, unsigned o, bool) {
-                    const double et = depth(e, s);
+                each([&](int e, int s, double q, unsigned o, bool) {
+                    const double et = depth(e, s, o);
                     double bt = 0.0;
 #pragma unroll
                     for (int cc = 0; cc < D; ++cc) bt += at32(gh + cc * npts, o) * at32(u + cc * npts, o);
-                    const double e2 = et * et, mm = A0[e][s], d0 = A1[e][s], pp = A2[e][s];
+                    const double e2 = et * et, mm = A0[e][s], d0 = A1[e][s];
+                    const double pp = LEAN ? -d0 * d0 + factor(e, s, o) * q : A2[LEAN ? 0 : e][s];
                     A0[e][s] = e2 * et / 3.0 * pp + e2 * mm * d0 + et * mm * bt;   // S
                     A1[e][s] = e2 / 2.0 * pp + et * mm * d0 + mm * bt;            // T
                 });
             }
         } else if (i <= 1 + 2 * D) {        // d_c beta: Q += u_c d_c beta
-            each([&](int e, int s, double q, unsigned, bool) {
-                const double et = depth(e, s), t = fv[e][s] * q;
+            each([&](int e, int s, double q, unsigned o, bool) {
+                const double et = depth(e, s, o), t = factor(e, s, o) * q;
                 A0[e][s] += et * et / 2.0 * t;
                 A1[e][s] += et * t;
             });
             if (D == 2 && i == 1 + 2 * D) {   // S_x, S_y, while u is whole: U_t may be written over it
                 each([&](int e, int s, double, unsigned o, bool) {
-                    const double et = depth(e, s), u0 = at32(u, o), u1 = fv[e][s], S = A0[e][s];
+                    const double et = depth(e, s, o), u0 = at32(u, o), u1 = factor(e, s, o), S = A0[e][s];
                     A0[e][s] = S - et * u0 * u0;
-                    A2[e][s] = S - et * u1 * u1;
+                    A2[LEAN ? 0 : e][s] = S - et * u1 * u1;
                 });
             }
         } else {                            // d_c eta: U_t less the flux and grad S
             each([&](int e, int s, double q, unsigned o, bool ok) {
-                if (ok) at32(U_t + c * npts, o) = -e0[e][s] * (q - fv[e][s]) - fv[e][s] * A1[e][s];
+                const double et = LEAN ? at32(eta, o) : e0[LEAN ? 0 : e][s], hx = factor(e, s, o);
+                if (ok) at32(U_t + c * npts, o) = -et * (q - hx) - hx * A1[e][s];
             });
         }
     }
@@ -478,7 +494,8 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             const bool ok = rt.t + g.TPR * e < g.M && rt.valid;
-            z1[0][e] = !ok ? C<double>(0, 0) : c == 0 ? C<double>(A0[e][0], A0[e][1]) : C<double>(A2[e][0], A2[e][1]);
+            z1[0][e] = !ok ? C<double>(0, 0) : c == 0 ? C<double>(A0[e][0], A0[e][1])
+                                           : C<double>(A2[LEAN ? 0 : e][0], A2[LEAN ? 0 : e][1]);
         }
         cpx<double>* H1[1] = {c == 0 ? Sdst : Sydst};
         row_forward<double, EPC, 1>(g, rt, z1, H1, tw, twm, 1.0);

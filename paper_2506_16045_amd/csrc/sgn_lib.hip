@@ -2078,6 +2078,8 @@ sgn_status precond_apply(sgn_ctx* ctx, const Dims& d, double sig, double alp, co
 // ---------------------------------------------------------------------------
 // Right-hand side f(w, p)  (FP64)
 // ---------------------------------------------------------------------------
+sgn_status copy_d(sgn_ctx* ctx, double* dst, const double* src, size_t n);
+
 template <int D>
 sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double* gh, const double* u,
                     double* eta_t, double* U_t, void* ws) {
@@ -2202,10 +2204,14 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
         const RowLaunch RI = D == 1 ? RL : rhs_inv_launch(d);
         const int groups = D == 2 && RI.g.M <= 512 ? 8 : 1;
         const size_t ilds = row_lds_bytes<double>(RI.g, groups);
+        // the pass of the longest line reads its inputs again after it has stored eta_t: over
+        // one of them, eta_t goes through a spectrum's place that is free by now
+        const bool staged = D == 1 && (eta_t == eta || eta_t == gh || eta_t == u);
+        double* et = staged ? reinterpret_cast<double*>(HA + NS) : eta_t;
         auto launch = [&](auto k) -> sgn_status {
             HIPCHK(ctx, allow_lds(k, ilds));
             hipLaunchKernelGGL(k, dim3(RI.g.nblocks), dim3(RI.threads * groups), ilds, ctx->stream, RI.g, q, eta, u,
-                               gh, eta_t, U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0, dx, d.tpx);
+                               gh, et, U_t, HA, D == 2 ? HA + NS : nullptr, ctx->tw64, 1.0, dx, d.tpx);
             CHECK_LAUNCH(ctx);
             return SGN_OK;
         };
@@ -2220,6 +2226,7 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
             s = groups == 8 ? launch(k_rhs_rows_inv_f) : launch(k_rhs_rows_inv<D, 4, 512>);
         }
         if (s != SGN_OK) return s;
+        if (staged && (s = copy_d(ctx, eta_t, et, N)) != SGN_OK) return s;
     }
     // U_t += grad S - div(eta u (x) u), formed in the spectral domain from S and the
     // (negated) row-transformed flux fields in HB, into OA (free again)
@@ -2241,7 +2248,6 @@ sgn_status rhs_impl(sgn_ctx* ctx, const Dims& d, const double* eta, const double
 }
 
 
-sgn_status copy_d(sgn_ctx* ctx, double* dst, const double* src, size_t n);
 // A 1D right-hand side of up to BATCH_NMAX points by one workgroup in one launch.
 sgn_status rhs_1d_block(sgn_ctx* ctx, const Dims& d, const double* eta, const double* gh, const double* u,
                         double* eta_t, double* U_t, void* ws) {

@@ -1,7 +1,8 @@
 """The right-hand side written over its own inputs equals the one written elsewhere, bit
 for bit, where that has always been so: on 1D lines of up to 8192 points either output
 over any input (the short-line path and the one-workgroup engine beside it), on 2D grids
-U_t over u (each of the three forms of the inverse row pass)."""
+U_t over u (each of the three forms of the inverse row pass); and on the line of 16384
+points, whose own pass reads its inputs again after it has stored eta_t."""
 import numpy as np
 import pytest
 
@@ -47,6 +48,14 @@ def test_lines(ctx, n):
         for U_t in (None, "eta", "gh", "u"):
             if eta_t is None or eta_t != U_t:
                 _check(ctx, fields, eta_t, U_t)
+
+
+def test_longest_line(ctx):
+    fields = _fields(ctx, 16384)
+    for eta_t in (None, "eta", "gh", "u"):
+        _check(ctx, fields, eta_t, None)
+        if eta_t != "u":
+            _check(ctx, fields, eta_t, "u")
 
 
 @pytest.mark.parametrize("nx,ny", ((8, 8), (512, 16), (1024, 8), (2048, 4), (2048, 512), (4096, 4)))

@@ -79,3 +79,19 @@ def test_right_hand_side(ctx, nx, ny):
     assert np.linalg.norm(e_t.cpu().numpy() - e_r) <= 16 * g.d * EPS * s * (1.0 + k) * eta.max() * um
     top = eta.max() ** 3 / 3.0 * um ** 2 * (1.0 + k ** 3) + eta.max() ** 2 * (1.0 + k)
     assert np.linalg.norm(U_t.cpu().numpy() - U_r) <= 16 * g.d ** 2 * EPS * s * top
+
+
+# rows of 2048 and 4096 points on enough rows that a block holds two or four of them
+# (four at 2048 x 1024): the blocks of 512 and 1024 threads that the grids above do not reach
+TALL = [(2048, 512), (2048, 1024), (4096, 512)]
+
+
+@pytest.mark.parametrize("nx,ny", TALL, ids=[f"{nx}x{ny}" for nx, ny in TALL])
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_solves_with_several_long_rows_per_block(ctx, nx, ny, precision):
+    test_solves(ctx, nx, ny, precision)
+
+
+@pytest.mark.parametrize("nx,ny", TALL, ids=[f"{nx}x{ny}" for nx, ny in TALL])
+def test_right_hand_side_with_several_long_rows_per_block(ctx, nx, ny):
+    test_right_hand_side(ctx, nx, ny)

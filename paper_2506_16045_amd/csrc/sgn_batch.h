@@ -124,7 +124,7 @@ __device__ __forceinline__ void blk_allmax(double (&v)[NACC], double* red) {
 template <typename T, int NF>
 __device__ __forceinline__ void blk_rfft_fwd_n(cpx<T>* buf, int fstride, int M, const cpx<T>* __restrict__ tw_all) {
     __syncthreads();
-    lds_fft<T, 1, NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), false);
+    lds_fft<T, NF>(buf, fstride, M, threadIdx.x, tw_size(tw_all, M), false);
     const cpx<T>* tw2 = tw_size(tw_all, 2 * M);
     const T half = (T)0.5;
     for (int p = threadIdx.x; p <= M / 2; p += blockDim.x) {
@@ -174,7 +174,7 @@ __device__ __forceinline__ void blk_rfft_inv_n(cpx<T>* buf, int fstride, int M, 
         }
     }
     __syncthreads();
-    lds_fft<T, 1, NF>(buf, fstride, M, threadIdx.x, blockDim.x, tw_size(tw_all, M), true);
+    lds_fft<T, NF>(buf, fstride, M, threadIdx.x, tw_size(tw_all, M), true);
 }
 
 template <typename T>
@@ -266,11 +266,10 @@ __device__ __forceinline__ cpx<T> cvt(cpx<U> v) {
     return C<T>((T)v.re, (T)v.im);
 }
 
-// PCG of section 3.2 on G d = r0 in precision T from d = 0, with the Krylov
-// vectors d, r, p in the registers of the workgroup (mode k of the half
-// spectrum in thread k mod NT, slot k / NT) and the transforms in two LDS
-// buffers (lds and lds + M + 1: p and D p inverse-transformed in lockstep, a and
-// w forward-transformed in lockstep), so the loop touches global memory for the
+// PCG of section 3.2 on G d = r0 in precision T from d = 0, mode k of the Krylov vectors
+// d, r, p (at most SMALL_MMAX + 1 modes) in the registers of thread k and the transforms
+// in two LDS buffers (lds and lds + M + 1: p and D p inverse-transformed in lockstep, a
+// and w forward-transformed in lockstep), so the loop touches global memory for the
 // coefficient fields at most (REGCOEF: eta and h_x held in registers too).
 // r0 is read from r0h; on return xh += d (xh may hold a wider type).  Stops
 // when r.r <= tol2 * bbref or after max_iter iterations; returns the
@@ -278,45 +277,36 @@ __device__ __forceinline__ cpx<T> cvt(cpx<U> v) {
 template <typename T, bool REGCOEF, typename TX>
 __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h, T sig, T alp, double tol2,
                            double bbref, int max_iter, double& rr, cpx<T>* lds, double* red) {
-    constexpr int NT = 64;    // lines of at most SMALL_MMAX entries: one slot per thread
-    constexpr int KPT = SMALL_MMAX / NT + 1;
-    constexpr int JPT = 1;
-    constexpr int JC = REGCOEF ? JPT : 1;
-    const int M = A.M, N = A.N, t = threadIdx.x;
+    static_assert(SMALL_MMAX < 64, "a mode per thread of the smallest workgroup");
+    const int M = A.M, N = A.N;
     const int fs = M + 1;
     cpx<T>* la = lds;
     cpx<T>* lb = lds + fs;
     const T invN = (T)1 / (T)N;
     const double dinvN = 1.0 / (double)N;
-    // FP32 inner solves accumulate their correction in registers; the FP64 solve,
-    // whose registers are fuller, adds each step to xh directly
+    // FP32 inner solves accumulate their correction in a register, the FP64 solve adds
+    // each step to xh directly
     constexpr bool XREG = sizeof(T) == 4;
-    cpx<T> x[XREG ? KPT : 1], r[KPT], p[KPT];
-    T er[JC][2], hr[JC][2];
+    const int k = threadIdx.x;
+    const T kk = wavenumber<T>(k, N, A.tp);
+    cpx<T> x = C<T>(0, 0), r = C<T>(0, 0), p = C<T>(0, 0);
+    T er[2], hr[2];
     double acc[2] = {0.0, 0.0};
-#pragma unroll
-    for (int e = 0; e < KPT; ++e) {
-        const int k = t + NT * e;
-        if (XREG) x[XREG ? e : 0] = C<T>(0, 0);
-        p[e] = C<T>(0, 0);
-        r[e] = C<T>(0, 0);
-        if (k <= M) {
-            r[e] = cvt<T>(r0h[k]);
-            const cpx<T> z = batch_precond<T>(wavenumber<T>(k, N, A.tp), sig, alp, r[e]);
-            const double w = half_weight(k, N) * dinvN;
-            acc[0] += w * ((double)r[e].re * (double)z.re + (double)r[e].im * (double)z.im);
-            acc[1] += w * ((double)r[e].re * (double)r[e].re + (double)r[e].im * (double)r[e].im);
-        }
+    auto dots = [&]() {
+        const cpx<T> z = batch_precond<T>(kk, sig, alp, r);
+        const double w = half_weight(k, N) * dinvN;
+        acc[0] += w * ((double)r.re * (double)z.re + (double)r.im * (double)z.im);
+        acc[1] += w * ((double)r.re * (double)r.re + (double)r.im * (double)r.im);
+    };
+    if (k <= M) {
+        r = cvt<T>(r0h[k]);
+        dots();
     }
     if (REGCOEF) {
 #pragma unroll
-        for (int e = 0; e < JC; ++e) {
-            const int j = t + NT * e;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                er[e][s] = j < M ? A.eta[2 * j + s] : (T)0;
-                hr[e][s] = j < M ? A.hx[2 * j + s] : (T)0;
-            }
+        for (int s = 0; s < 2; ++s) {
+            er[s] = k < M ? A.eta[2 * k + s] : (T)0;
+            hr[s] = k < M ? A.hx[2 * k + s] : (T)0;
         }
     }
     blk_allsum<2>(acc, red);
@@ -326,64 +316,46 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
     int it = 0;
     const T third = (T)1 / (T)3, half = (T)0.5;
     while (!(rr <= tol2 * bbref) && it < max_iter && rr == rr) {
-        // FP64: the thread index, opaque to the compiler inside the loop, so that
-        // per-mode indices, wavenumbers and weights are recomputed each iteration
-        // instead of being hoisted into registers that the Krylov vectors need
-        int t = threadIdx.x;
-        if (!XREG) asm volatile("" : "+v"(t));
         const T beta = it == 0 ? (T)0 : (T)(rz / rho_prev);
         // p = z + beta p; p / N and i k p / N into the two buffers
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-            const int k = t + NT * e;
-            const T kk = wavenumber<T>(k, N, A.tp);
-            const cpx<T> z = batch_precond<T>(kk, sig, alp, r[e]);
-            p[e] = it == 0 ? z : z + beta * p[e];
-            if (k <= M) {
-                la[k] = invN * p[e];
-                lb[k] = invN * ik(kk, p[e]);
-            }
+        const cpx<T> z = batch_precond<T>(kk, sig, alp, r);
+        p = it == 0 ? z : z + beta * p;
+        if (k <= M) {
+            la[k] = invN * p;
+            lb[k] = invN * ik(kk, p);
         }
         blk_rfft_inv_n<T, 2>(lds, fs, M, A.tw);
         // pointwise: a into buffer a, w into buffer b; curvature p.Gp
-        double pqa[1] = {0.0};
-        constexpr int PU = REGCOEF ? JPT : 1;   // the FP64 loop reads eta, h_x from memory
-#pragma unroll PU
-        for (int e = 0; e < JPT; ++e) {
-            const int j = t + NT * e;
-            if (j < M) {
-                cpx<T> pv = la[j], dv = lb[j];
+        double pqa = 0.0;
+        if (k < M) {
+            cpx<T> pv = la[k], dv = lb[k];
 #pragma unroll
-                for (int s = 0; s < 2; ++s) {
-                    const T pp = s ? pv.im : pv.re;
-                    const T dl = s ? dv.im : dv.re;
-                    const T et = REGCOEF ? er[REGCOEF ? e : 0][s] : A.eta[2 * j + s];
-                    const T h = REGCOEF ? hr[REGCOEF ? e : 0][s] : A.hx[2 * j + s];
-                    const T bt = h * pp, e2 = et * et;
-                    const T w1 = third * e2 * et * dl + half * e2 * bt;
-                    const T w2 = half * e2 * dl + et * bt;
-                    const T a = et * pp + h * w2;
-                    pqa[0] += (double)et * (double)pp * (double)pp + (double)dl * (double)w1 + (double)bt * (double)w2;
-                    if (s) {
-                        pv.im = a;
-                        dv.im = w1;
-                    } else {
-                        pv.re = a;
-                        dv.re = w1;
-                    }
+            for (int s = 0; s < 2; ++s) {
+                const T pp = s ? pv.im : pv.re;
+                const T dl = s ? dv.im : dv.re;
+                const T et = REGCOEF ? er[s] : A.eta[2 * k + s];
+                const T h = REGCOEF ? hr[s] : A.hx[2 * k + s];
+                const T bt = h * pp, e2 = et * et;
+                const T w1 = third * e2 * et * dl + half * e2 * bt;
+                const T w2 = half * e2 * dl + et * bt;
+                const T a = et * pp + h * w2;
+                pqa += (double)et * (double)pp * (double)pp + (double)dl * (double)w1 + (double)bt * (double)w2;
+                if (s) {
+                    pv.im = a;
+                    dv.im = w1;
+                } else {
+                    pv.re = a;
+                    dv.re = w1;
                 }
-                la[j] = pv;
-                lb[j] = dv;
             }
+            la[k] = pv;
+            lb[k] = dv;
         }
         // p.Gp: wave sums now, the block sum (waves in order, as blk_allsum) after
         // the forward transform, whose barriers publish the wave partials
-        {
-            double x = pqa[0];
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-            if ((threadIdx.x & 63) == 0) red[RED_PQ + (threadIdx.x >> 6)] = x;
-        }
+        for (int off = 32; off > 0; off >>= 1) pqa += __shfl_xor(pqa, off, 64);
+        if ((threadIdx.x & 63) == 0) red[RED_PQ + (threadIdx.x >> 6)] = pqa;
         blk_rfft_fwd_n<T, 2>(lds, fs, M, A.tw);
         double pq = 0.0;
         for (unsigned w = 0; w < blockDim.x / 64; ++w) pq += red[RED_PQ + w];
@@ -391,22 +363,14 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
         const double rho = rz;
         const T alpha = (T)(rho / pq);
         acc[0] = acc[1] = 0.0;
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-            const int k = t + NT * e;
-            if (k <= M) {
-                const T kk = wavenumber<T>(k, N, A.tp);
-                const cpx<T> q = la[k] - ik(kk, lb[k]);
-                if (XREG)
-                    x[XREG ? e : 0] = x[XREG ? e : 0] + alpha * p[e];
-                else
-                    xh[k] = xh[k] + cvt<TX>(alpha * p[e]);
-                r[e] = r[e] - alpha * q;
-                const cpx<T> z = batch_precond<T>(kk, sig, alp, r[e]);
-                const double w = half_weight(k, N) * dinvN;
-                acc[0] += w * ((double)r[e].re * (double)z.re + (double)r[e].im * (double)z.im);
-                acc[1] += w * ((double)r[e].re * (double)r[e].re + (double)r[e].im * (double)r[e].im);
-            }
+        if (k <= M) {
+            const cpx<T> q = la[k] - ik(kk, lb[k]);
+            if (XREG)
+                x = x + alpha * p;
+            else
+                xh[k] = xh[k] + cvt<TX>(alpha * p);
+            r = r - alpha * q;
+            dots();
         }
         blk_allsum<2>(acc, red);
         rho_prev = rho;
@@ -414,13 +378,7 @@ __device__ int blk_pcg_reg(const BatchOp<T>& A, cpx<TX>* xh, const cpx<TX>* r0h,
         rr = acc[1];
         ++it;
     }
-    if (XREG) {
-#pragma unroll
-        for (int e = 0; e < KPT; ++e) {
-            const int k = t + NT * e;
-            if (k <= M) xh[k] = xh[k] + cvt<TX>(x[XREG ? e : 0]);
-        }
-    }
+    if (XREG && k <= M) xh[k] = xh[k] + cvt<TX>(x);
     __syncthreads();
     return it;
 }

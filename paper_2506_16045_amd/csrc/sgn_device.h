@@ -74,14 +74,13 @@ __device__ __forceinline__ const cpx<T>* tw_size(const cpx<T>* __restrict__ tw_a
 }
 
 // ---------------------------------------------------------------------------
-// The transform of the short 1D lines (sgn_batch.h): Stockham FFT of length M (power
-// of two) on NF buffers in LDS at buf + f * fstride, in lockstep by TPX cooperating
-// threads (thread index t): radix-8 (few fields) or radix-4 (many fields) passes while
-// they fit, then one radix-4 or radix-2 pass for the remaining factor (a pass of radix
-// R over span Ns reads
+// The transform of the short 1D lines (sgn_batch.h): Stockham FFT of length M (a power of
+// two, at most 32) on NF fields in LDS at buf + f * fstride, in lockstep, thread t one
+// butterfly of each pass: a radix-8 pass where it fits, then one radix-4 or radix-2
+// pass for the remaining factor (a pass of radix R over span Ns reads
 // x[j + r M/R], twiddles by W_{R Ns}^{k r} with k = j mod Ns, and writes the
 // R-point DFT to y[(j - k) R + k + q Ns]).  Every thread of the block must call
-// it (it contains block barriers); M <= EPC * TPX.  twm[m] = W_M^m.
+// it (it contains block barriers).  twm[m] = W_M^m.
 // Forward: exp(-i ...); inverse: exp(+i ...); unnormalised.
 // ---------------------------------------------------------------------------
 
@@ -128,81 +127,57 @@ __device__ __forceinline__ void dft_small(cpx<T> (&v)[R], bool inverse) {
     }
 }
 
-template <typename T, int R, int NB, int NF>
-__device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t, int TPX,
-                                         const cpx<T>* __restrict__ twm, bool inverse, int Ns, int sh) {
+template <typename T, int R, int NF>
+__device__ __forceinline__ void fft_pass(cpx<T>* buf, int fstride, int M, int t, const cpx<T>* __restrict__ twm,
+                                         bool inverse, int Ns, int sh) {
     const int MR = M / R;
-    cpx<T> v[NB][NF][R];
+    cpx<T> v[NF][R];
+    if (t < MR) {
+        const int k = t & (Ns - 1);
+        cpx<T> w[R];
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int j = t + i * TPX;
-        if (j < MR) {
-            const int k = j & (Ns - 1);
-            cpx<T> w[R];
+        for (int r = 1; r < R; ++r) {
+            w[r] = twm[(k * r) << sh];   // W_{R Ns}^{k r} = W_M^{k r M / (R Ns)}
+            if (inverse) w[r].im = -w[r].im;
+        }
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                w[r] = twm[(k * r) << sh];   // W_{R Ns}^{k r} = W_M^{k r M / (R Ns)}
-                if (inverse) w[r].im = -w[r].im;
-            }
+        for (int f = 0; f < NF; ++f) {
+            const cpx<T>* bf = buf + f * fstride;
+            v[f][0] = bf[t];
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                const cpx<T>* bf = buf + f * fstride;
-                v[i][f][0] = bf[j];
-#pragma unroll
-                for (int r = 1; r < R; ++r) {
-                    const int a = j + r * MR;
-                    v[i][f][r] = bf[a] * w[r];
-                }
-            }
+            for (int r = 1; r < R; ++r) v[f][r] = bf[t + r * MR] * w[r];
         }
     }
     __syncthreads();
+    if (t < MR) {
+        const int k = t & (Ns - 1), o = (t - k) * R + k;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int j = t + i * TPX;
-        if (j < MR) {
-            const int k = j & (Ns - 1);
-            const int o = (j - k) * R + k;
+        for (int f = 0; f < NF; ++f) {
+            dft_small<T, R>(v[f], inverse);
+            cpx<T>* bf = buf + f * fstride;
 #pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                dft_small<T, R>(v[i][f], inverse);
-                cpx<T>* bf = buf + f * fstride;
-#pragma unroll
-                for (int q = 0; q < R; ++q) {
-                    const int a = o + q * Ns;
-                    bf[a] = v[i][f][q];
-                }
-            }
+            for (int q = 0; q < R; ++q) bf[o + q * Ns] = v[f][q];
         }
     }
     __syncthreads();
 }
 
-template <typename T, int EPC, int NF>
-__device__ __forceinline__ void lds_fft(cpx<T>* buf, int fstride, int M, int t, int TPX,
-                                        const cpx<T>* __restrict__ twm, bool inverse) {
-    constexpr int NB8 = EPC / 8 > 0 ? EPC / 8 : 1;
-    constexpr int NB4 = EPC / 4 > 0 ? EPC / 4 : 1;
-    constexpr int NB2 = EPC / 2 > 0 ? EPC / 2 : 1;
-    // radix-8 passes hold 8 NF values per butterfly in registers: used while that
-    // stays within 16 FP64 complex words (more fields in lockstep use radix 4)
-    constexpr bool R8 = NF * (int)sizeof(T) <= 16;
+template <typename T, int NF>
+__device__ __forceinline__ void lds_fft(cpx<T>* buf, int fstride, int M, int t, const cpx<T>* __restrict__ twm,
+                                        bool inverse) {
     const int logM = ilog2(M);
-    int Ns = 1;
-    int logNs = 0;
-    if (R8) {
-        for (; Ns * 8 <= M; Ns <<= 3, logNs += 3)
-            fft_pass<T, 8, NB8, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 3));
-    } else {
-        for (; Ns * 16 <= M; Ns <<= 2, logNs += 2)
-            fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2));
+    int Ns = 1, logNs = 0;
+    if (M >= 8) {
+        fft_pass<T, 8, NF>(buf, fstride, M, t, twm, inverse, 1, logM - 3);
+        Ns = 8;
+        logNs = 3;
     }
     if (Ns * 4 <= M) {
-        fft_pass<T, 4, NB4, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 2));
+        fft_pass<T, 4, NF>(buf, fstride, M, t, twm, inverse, Ns, logM - (logNs + 2));
         Ns <<= 2;
         logNs += 2;
     }
-    if (Ns * 2 <= M) fft_pass<T, 2, NB2, NF>(buf, fstride, M, t, TPX, twm, inverse, Ns, logM - (logNs + 1));
+    if (Ns * 2 <= M) fft_pass<T, 2, NF>(buf, fstride, M, t, twm, inverse, Ns, logM - (logNs + 1));
 }
 
 // Block barrier that orders LDS only.  __syncthreads() fences all memory, which

@@ -31,17 +31,21 @@ def kernel_family(demangled: str, grid_size: int = 0, n: int = 0):
     ('pcg_r1', 'f32') or ('rhs_rows_inv', 'f64'), else None.  The right-hand side's
     two column launches share one kernel; they are told apart by their job count
     (grid_size work-items over 256-thread blocks of n/2 + 1 columns per job)."""
-    if re.search(r"k_rhs_rows_fwd<2,", demangled):
+    # (_f: the fields side by side; _w: wave-private rows of 1024 points)
+    if re.search(r"k_rhs_rows_fwd(<2,|_f\b)", demangled):
         return "rhs_rows_fwd", "f64"
-    if re.search(r"k_rhs_rows_inv<2,|k_rhs_rows_inv_w\b", demangled):
+    if re.search(r"k_rhs_rows_inv(<2,|_[wf]\b)", demangled):
         return "rhs_rows_inv", "f64"
     if re.search(r"k_cols_lin_jobs<double, 4, [34], 3>", demangled) and n:
         jobs = round(grid_size / (256 * (n // 2 + 1)))
         return ("rhs_cols", "f64") if jobs == 3 else ("rhs_flux", "f64") if jobs == 1 else None
-    m = re.search(r"k_pcg_(c1|r1|c2|init)w?<(double|float)(?:, (\d+))?(?:, (\d+))?(?:, (\d+|true|false))?", demangled)
+    m = re.search(r"k_pcg_long_(c1|rows|c2)<(double|float)", demangled)   # the line of 16384 points
+    if m:
+        return "pcg_" + m.group(1).replace("rows", "r1"), ("f64" if m.group(2) == "double" else "f32")
+    m = re.search(r"k_pcg_(c1|r1|c2|init)[wf]?<(double|float)(?:, (\d+))?(?:, (\d+))?(?:, (\d+|true|false))?", demangled)
     if not m:
         return None
-    fam, typ = m.group(1), m.group(2)   # k_pcg_r1w, k_pcg_c1w, k_pcg_c2w: the wave-private passes
+    fam, typ = m.group(1), m.group(2)   # k_pcg_r1w, k_pcg_c1w, k_pcg_c2w: the wave-private passes; k_pcg_r1f: by fields
     mode = m.group(5)
     if fam == "c1" and mode not in (None, "0"):
         return None           # initial-residual copy mode, not the loop pass
@@ -61,7 +65,7 @@ def kernel_stats(db_path: str):
     for name, durs in agg.items():
         # only the Krylov loop passes return early; other kernels' durations vary
         # with their arguments (field counts), not with convergence
-        loop = re.search(r"k_pcg_(c1|r1|c2)w?<", dem[name]) is not None
+        loop = re.search(r"k_pcg_(c1|r1|c2)[wf]?<|k_pcg_long_(c1|rows|c2)<|k_wall_c[12]<", dem[name]) is not None
         full, early = split_launches(durs) if loop else (durs, [])
         out.append({"name": dem[name], "calls": len(durs), "total_ns": sum(durs),
                     "avg_ns": sum(durs) / len(durs), "min_ns": min(durs), "max_ns": max(durs),

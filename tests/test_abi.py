@@ -165,3 +165,17 @@ def test_kernel_family_names_the_right_hand_side_launches():
     assert profiling.kernel_family(name, 3 * cols, 1024) == ("rhs_cols", "f64")
     assert profiling.kernel_family(name, cols, 1024) == ("rhs_flux", "f64")
     assert profiling.kernel_family("void sgn::k_pcg_r1w<float, 2>(int, ...)") == ("pcg_r1", "f32")
+
+
+def test_kernel_family_names_the_passes_by_fields_and_of_the_longest_line():
+    """The short-row forms of the passes (a group of threads per field) and the fused
+    passes of the line of 16384 points belong to the families they stand for."""
+    from paper_2506_16045_amd import profiling
+    for name, family in (("k_pcg_r1f<double, 2>", ("pcg_r1", "f64")), ("k_pcg_r1f<float, 2>", ("pcg_r1", "f32")),
+                         ("k_pcg_c1<double, 4, 2, 0, true>", ("pcg_c1", "f64")), ("k_pcg_c1<double, 4, 2, 1, false>", None),
+                         ("k_pcg_c2<float, 4, 2, 3, false, true>", ("pcg_c2", "f32")),
+                         ("k_pcg_long_c1<double>", ("pcg_c1", "f64")), ("k_pcg_long_rows<float>", ("pcg_r1", "f32")),
+                         ("k_pcg_long_c2<double>", ("pcg_c2", "f64"))):
+        assert profiling.kernel_family(f"void sgn::{name}(...)") == family, name
+    assert profiling.kernel_family("sgn::k_rhs_rows_fwd_f(sgn::RowGeom, ...)") == ("rhs_rows_fwd", "f64")
+    assert profiling.kernel_family("sgn::k_rhs_rows_inv_f(sgn::RowGeom, ...)") == ("rhs_rows_inv", "f64")

@@ -7,8 +7,7 @@
 // and x in FP64).  Per-system convergence: a workgroup moves to its next system as
 // soon as the current one is done.  Lines of 128 points and more run on the
 // register engine of sgn_line.h; the blk_ functions here take the shorter ones, whose
-// transforms (M <= 32, one entry per thread) that engine's eight entries per
-// thread do not divide into.
+// at most 33 modes are held one per thread of a wave.
 #pragma once
 
 #include <type_traits>

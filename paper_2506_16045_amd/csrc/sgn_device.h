@@ -329,7 +329,7 @@ __device__ __forceinline__ void reg_fft(cpx<T> (*v)[E], cpx<T>* buf, int fstride
 // Row geometry: a block holds R rows of TPR threads each; row r of the block is
 // grid row row0 + r.  Thread t of a row owns complex positions j = t + TPR*e
 // (e < EPC), i.e. real positions 2j and 2j+1.  LDS: NF fields x R rows of M+1
-// complex entries (field stride R (M+1)), then the twiddle table.
+// complex entries (field stride R (M+1)).
 // ---------------------------------------------------------------------------
 struct RowGeom {
     int nx, ny, M, TPR, R, nblocks;
@@ -373,7 +373,7 @@ __device__ __forceinline__ RowThread<T> row_thread(const RowGeom& g, cpx<T>* lds
     return row_thread_at<T>(g, lds, blockIdx.x, threadIdx.x);
 }
 
-// LDS entries a row kernel with NF fields needs before its twiddle table.
+// LDS entries a row kernel with NF fields needs.
 __host__ __device__ inline int row_lds_data(const RowGeom& g, int NF) { return NF * g.R * (g.M + 1); }
 
 // row_inverse in pieces, for passes that overlap a field's transposed loads with
@@ -572,8 +572,7 @@ __device__ __forceinline__ void row_forward_idle(const RowGeom& g) {
 // ---------------------------------------------------------------------------
 // Column geometry: a block holds Cb columns (kx) of TPC threads each; column c
 // is kx = blockIdx.x * Cb + c.  Thread t owns modes j = t + TPC*e (e < EPC,
-// j < ny).  LDS: NF fields x Cb columns of ny entries (field stride Cb ny), then
-// the twiddle table.
+// j < ny).  LDS: NF fields x Cb columns of ny entries (field stride Cb ny).
 // ---------------------------------------------------------------------------
 struct ColGeom {
     int nx, ny, nxh, TPC, Cb, nblocks;
@@ -709,9 +708,9 @@ __device__ __forceinline__ double wave_max(double v) {
 
 // ---------------------------------------------------------------------------
 // Deterministic reductions.  Each block reduces NACC doubles in a fixed tree
-// (wave shuffles, then waves in order) and writes them to partials[block];
-// the last block to finish sums the partials in block order, so the result
-// does not depend on scheduling.
+// (wave sums, then waves in order) and writes them to partials[block]; every block
+// of the next kernel sums the partials in the one order of partials_sum, so the
+// result does not depend on scheduling and is the same in all of them.
 // ---------------------------------------------------------------------------
 template <int NACC>
 __device__ __forceinline__ void block_wave_sums(double (&v)[NACC]) {
@@ -842,7 +841,7 @@ __device__ __forceinline__ void partials_sum(const double* __restrict__ partials
     }
 }
 
-// Maximum of the per-block partials by the whole last block (order independent);
+// Maximum of the per-block partials by one block (order independent);
 // the result is in thread 0.
 template <int NACC>
 __device__ __forceinline__ void final_max(const double* __restrict__ partials, unsigned nblocks,

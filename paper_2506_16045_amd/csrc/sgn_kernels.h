@@ -502,21 +502,11 @@ __global__ void __launch_bounds__(MAXT, MAXT <= 256 ? 2 : 1) k_rhs_rows_inv(RowG
     }
 }
 
-// Linear spectral operators on columns: out_o = sum_i c(code[o][i], k) in_i, with
-// y-FFT of the inputs and y-IFFT of the outputs.  Codes: 0 none, 1 identity,
-// 2 i kx, 3 i ky, 4 (i kx)^2, 5 (i kx)(i ky), 6 (i ky)^2; every value is also
-// multiplied by `scale`.
-constexpr int LIN_MAXO = 6;
-constexpr int LIN_MAXI = 5;
-struct LinCodes {
-    int code[LIN_MAXO][LIN_MAXI];
-    int no;
-};
-
-// The same on 2D grids with rows of up to 1024 points, the fields side by side (order
-// m, delta, grad delta, grad eta, grad beta): each of eight groups of R TPR threads
-// transforms a field into LDS, then every thread forms the right-hand side at one point
-// from the eight values there, and the first two groups transform S_x and S_y forward.
+// The inverse row pass of the right-hand side (see k_rhs_rows_inv) on 2D grids with rows
+// of up to 1024 points, the fields side by side (order m, delta, grad delta, grad eta,
+// grad beta): each of eight groups of R TPR threads transforms a field into LDS, then
+// every thread forms the right-hand side at one point from the eight values there, and
+// the first two groups transform S_x and S_y forward.
 // The eight fields one after another on the same threads, with the accumulated state of
 // eight points each, took 27 us at 256 x 128 and 32 at 512 x 512; here 8.2 and 15.
 // Longer rows (eight entries per thread, one row per block, two batches of four fields
@@ -594,6 +584,17 @@ __global__ void __launch_bounds__(1024) k_rhs_rows_inv_f(RowGeom g, PtrList<cons
         row_forward_idle<EPC>(g);
     }
 }
+
+// Linear spectral operators on columns: out_o = sum_i c(code[o][i], k) in_i, with
+// y-FFT of the inputs and y-IFFT of the outputs.  Codes: 0 none, 1 identity,
+// 2 i kx, 3 i ky, 4 (i kx)^2, 5 (i kx)(i ky), 6 (i ky)^2; every value is also
+// multiplied by `scale`.
+constexpr int LIN_MAXO = 6;
+constexpr int LIN_MAXI = 5;
+struct LinCodes {
+    int code[LIN_MAXO][LIN_MAXI];
+    int no;
+};
 
 template <typename T>
 __device__ __forceinline__ cpx<T> lin_coef(int code, T kx, T ky) {
@@ -1009,8 +1010,8 @@ __global__ void k_publish_flags(const SolveScal* __restrict__ sc, int* d, int se
     if (threadIdx.x == 0 && blockIdx.x == 0) publish_flags(sc, d, seq);
 }
 
-// Row pass R1 on rows of 256 threads and more: a block's fields one after another,
-// the next one's loads in flight meanwhile (three fields of LDS do not fit).
+// Row pass R1 on rows above 1024 points: a block's fields one after another, the next
+// one's loads in flight meanwhile (three fields of LDS do not fit).
 template <typename T, int EPC, int D, int MAXT>
 __global__ void __launch_bounds__(MAXT) k_pcg_r1(RowGeom g, const cpx<T>* __restrict__ tw,
                                                  SolveScal* __restrict__ sc, cpx<T>* H, size_t NS,
@@ -1548,11 +1549,14 @@ __device__ __forceinline__ cpx<T> wall_project(int c, cpx<T> a, cpx<T> b, int kx
 // projected onto the symmetric modes before it is used (rounding would otherwise
 // seed the other parity, which the iteration amplifies at low wavenumbers).
 // FEW (blocks of 128 threads, launches of at most one block of 256 per compute unit, where
-// only latency counts): two waves per SIMD instead of three, which ends the last spills (a kernel that uses
-// scratch memory takes 1 to 2 us longer), and the fields the new residual needs loaded
-// with the columns, in flight across the transform, where that fits the registers (all
-// but the FP64 update, which spills again: 9.1 -> 10.2 us at 256 x 128).  FP64 512 x 512:
-// residual 10.7 -> 9.2 us, initial residual 12.6 -> 10.7; FP32 update 5.6 -> 5.3.
+// only latency counts): two waves per SIMD instead of three, without the 28 to 52 bytes of
+// scratch that the FP64 forms for larger launches spill into (a kernel that uses scratch
+// takes 1 to 2 us longer), and the fields the new residual needs loaded with the columns,
+// in flight across the transform, where that fits the registers (all but the FP64 update,
+// which spills again: 9.1 -> 10.2 us at 256 x 128).  256 x 128: update 9.0 -> 7.6 us,
+// initial residual 10.0 -> 7.0; 512 x 512: FP64 residual 10.3 -> 9.2, initial residual
+// 12.6 -> 10.1, FP32 update 5.6 -> 4.9.  Larger launches keep three waves: at 1024 x 1024
+// two were slower (25 -> 27 us) with nothing spilled.
 template <typename T, int MODE, bool FEW>
 constexpr bool C2_PRE = FEW && (sizeof(T) == 4 || MODE != C2_UPDATE);
 template <typename T, int EPC, int D, int MODE, bool WALL = false, bool FEW = false>

@@ -296,8 +296,8 @@ ColLaunch col_launch(int nx, int ny, int epc = 4, int threads = 256) {
 }
 
 // Column launches on 2D grids: blocks of 128 threads where those of 256 would be at most
-// one per compute unit (256 x 128: Krylov passes 8.2 -> 6.9 and 9.4 -> 7.5 us, walls
-// 512 x 512 12.3 -> 11.4 and 13.0 -> 12.4).
+// one per compute unit (256 x 128: Krylov passes C1 7.6 -> 6.9 and C2 9.0 -> 7.6 us, walls
+// 512 x 512 12.3 -> 11.4 and 13.0 -> 12.6, FP32 512 x 512 5.5 -> 5.2 and 5.6 -> 4.9).
 template <typename T>
 ColLaunch few_cols(const Dims& d) {
     const ColLaunch L = col_launch<T>(d.nx, d.ny);

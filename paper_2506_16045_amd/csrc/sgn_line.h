@@ -6,9 +6,9 @@
 // latency: barriers, LDS round trips and dependent loads, not bytes or flops.
 // The layout removes what it can of each:
 //   - two fields at a time (p and Dp backwards, a and w forwards), one per half of
-//     the workgroup, E = 8 (16 for M = 4096) complex entries per thread, so a
-//     transform is two to four radix-8 (16) passes in registers with one LDS
-//     exchange between passes;
+//     the workgroup, E = 4 complex entries per thread up to M = 1024, 8 at 2048 and 16
+//     at 4096, so a transform is three to five radix-E passes in registers (the last
+//     one of what is left) with one LDS exchange between two of them;
 //   - the first pass reads and the last pass leaves the natural layout (thread t
 //     of G = M / E holds entries t + s G), so the passes around a transform need
 //     no LDS trip of their own beyond the real split's;
@@ -16,8 +16,8 @@
 //     M - k together, whose real split (section 6.1's transforms of real data) is
 //     one complex product for both; modes 0 and M, both real and of zero
 //     wavenumber, share one complex entry;
-//   - where a field fits one wave (M <= 512) its exchanges need no barrier, where
-//     the whole system does (M <= 256) nothing does; the barriers that remain order
+//   - where a field fits one wave (M <= 256) its exchanges need no barrier, where
+//     the whole system does (M <= 128) nothing does; the barriers that remain order
 //     LDS only, and the exchanges alternate between two buffers where LDS holds
 //     them, so each costs one barrier.
 // A system's geometry is a function of its size alone, and the sums run in a fixed

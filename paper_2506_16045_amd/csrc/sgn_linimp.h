@@ -1,16 +1,16 @@
 // One step of a linearly implicit scheme (Eq:IMEX_DAE) of a 1D state of 128 to 4096
-// points by one workgroup, after the step's right-hand side: the launches it stands for
-// (transform of U, three passes of G, the mode-wise update, the way back, the two
-// combinations and the copies of the level ring) each took 2 to 21 us for a line that
-// one compute unit holds (n = 4096: 72 us of a step's 98; here 38.5).
+// points by one workgroup, after the step's right-hand side: the thirteen launches it
+// stands for (transform of U, three passes of G, the mode-wise update, the way back, the
+// two combinations and the copies of the level ring) each took 2 to 21 us for a line
+// that one compute unit holds.
 #pragma once
 #include "sgn_device.h"
 
 namespace sgn {
 
-// Against the general path, us per step: 63 -> 18 at 128 points, 57 -> 22 at 512, 72 -> 43
-// at 2048, 91 -> 65 at 4096; at 8192, where the four vectors of a thread no longer fit
-// its registers, 132 -> 150, so that length keeps the general path.
+// Against the general path, us per step with its right-hand side: 62 -> 19 at 128 points,
+// 63 -> 23 at 512, 74 -> 43 at 2048, 93 -> 66 at 4096; at 8192, where the four vectors of
+// a thread no longer fit its registers, 133 -> 149, so that length keeps the general path.
 constexpr int LINIMP_NMIN = 128, LINIMP_NMAX = 4096;
 constexpr int LINIMP_TERMS = 6;
 struct LinimpLine {
